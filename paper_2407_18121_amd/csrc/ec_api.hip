@@ -31,7 +31,7 @@ int score_simt_dispatch(const void* q, const void* k, const void* v, void* out, 
                         float scale, hipStream_t stream);
 int score_mfma_dispatch(const void* q, const void* k, const void* v, void* out, float* lse,
                         float* head_imp, int B, int H, ScoreGeom geo, const int32_t* seq_len, int D,
-                        int dt, float scale, int forced_waves, hipStream_t stream);
+                        int dt, float scale, hipStream_t stream);
 int retention_step_launch(int32_t* n_seen_b, int32_t* cache_len_b, int32_t* evict_idx_b, int32_t* new_pos_b,
                           int32_t* pending_b, int B, int gamma_num, int gamma_den, int budget_mode, int fixed_len,
                           int trunc_mode, int recent, int n_tl, int protect_first, int flush_only, hipStream_t stream);
@@ -96,8 +96,10 @@ int score_pass(const void* q, const void* k, const void* v, void* out, float* ls
     float* head_imp = (G == H) ? score : ws_imp;
 
     int rc;
-    if (dt == EC_BF16)
-        rc = ec::score_mfma_dispatch(q, k, v, out, lse_buf, head_imp, B, H, geo, seq_len, D, dt, scale, 0, s);
+    // the matrix-core path moves 16 bytes at a time; rows that do not lie on 16-byte boundaries take the other one
+    const bool aligned = (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out) & 15) == 0;
+    if (dt == EC_BF16 && aligned)
+        rc = ec::score_mfma_dispatch(q, k, v, out, lse_buf, head_imp, B, H, geo, seq_len, D, dt, scale, s);
     else
         rc = ec::score_simt_dispatch(q, k, v, out, lse_buf, head_imp, B, H, geo, seq_len, D, dt, scale, s);
     if (rc != EC_OK) return rc;

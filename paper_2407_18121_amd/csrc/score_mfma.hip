@@ -3,25 +3,27 @@
 // prompt pass is P = 0.
 //
 // Two kernels, neither of which stores the T x T matrix:
-//   attn_fwd     : one workgroup = 128 or 256 queries (4 or 8 waves x 32), key tiles of 64 double-
-//                  buffered in LDS.  The score tile is computed TRANSPOSED, S^T = K.Q^T, with
-//                  v_mfma_f32_32x32x16_bf16: in the accumulator layout a lane then owns one query
-//                  (column) and 16 keys (rows), so the row max / row sum of the online softmax are
-//                  in-lane reductions plus one exchange between the two half-waves, the rescale
-//                  factor is a per-lane scalar, and the fp32 accumulators -- rounded to bf16 -- are
-//                  directly the B operand of O^T += V^T.P^T (the contraction index is permuted the
-//                  same way on both operands).  V tiles are staged as they lie in memory and transposed
-//                  by the LDS transpose read on their way to the registers, so no V^T copy is made.
-//                  Emits out (optional) and the row log-sum-exp.
-//   colsum       : one workgroup = 128 keys (4 waves x 32) whose K fragments stay in registers;
-//                  query tiles of 64 at or below the diagonal are streamed through LDS, S = Q.K^T
-//                  is recomputed un-transposed so that a lane owns one key (column): p =
-//                  exp(s - lse_row) is summed down the column in-lane.  One workgroup owns a column,
-//                  so there are no atomics and the result is deterministic.
+//   attn_fwd     : one workgroup = 128 queries (4 waves x 32) at a time, key tiles of 64 double-buffered in
+//                  LDS.  The score tile is computed TRANSPOSED, S^T = K.Q^T, with v_mfma_f32_32x32x16_bf16: in the
+//                  accumulator layout a lane then owns one query (column) and 16 keys (rows), so the row max / row
+//                  sum of the online softmax are in-lane reductions plus one exchange between the two half-waves,
+//                  the rescale factor is a per-lane scalar, and the fp32 accumulators -- rounded to bf16 -- are
+//                  directly the B operand of O^T += V^T.P^T (the contraction index is permuted the same way on both
+//                  operands).  V tiles are staged as they lie in memory and transposed by the LDS transpose read on
+//                  their way to the registers, so no V^T copy is made.  Emits out (optional) and the row log-sum-exp.
+//   colsum       : one workgroup = 128 or 256 keys (4 waves x 32 or 64) whose K fragments stay in registers; query
+//                  tiles at or below the diagonal are streamed through LDS, S^T = K.Q^T is recomputed and p =
+//                  exp(s - lse_row) is summed per key, over a lane's queries first and over the lanes at the end.
+//                  One workgroup owns a column, so there are no atomics and the result is deterministic.
+// Causal work is uneven: the last query tile sees every key, the first one only itself.  Where a launch has enough of
+// them, a workgroup takes two tiles of a head, the n-th from either end, so that all workgroups do the same work and
+// the start of the second tile travels while the first is written out.
 //
 // MFMA operand layout used throughout (wave64, lane l, half h = l / 32):
 //   A (32 x 16): lane holds A[l % 32][8h .. 8h+7]      B (16 x 32): lane holds B[8h .. 8h+7][l % 32]
 //   C (32 x 32): lane holds C[8g + 4h + t][l % 32] in register 4g + t, g,t in 0..3
+#include <type_traits>
+
 #include "ec_common.h"
 
 namespace ec {
@@ -29,577 +31,814 @@ namespace ec {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;  // 16-byte staging register (native vector: stays in VGPRs)
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
 
-constexpr int kMfmaThreads = 256;
 constexpr int kFwdBN = 64;   // keys per LDS tile
-constexpr int kSplitMaxWorkgroups = 256;  // launches of at most this many workgroups split one workgroup's loop over two wave groups
-constexpr int kColBM = 64;   // queries per LDS tile in colsum (128 measured slower: it halves the occupancy)
+constexpr int kSplitMaxWorkgroups = 256;  // launches of at most this many workgroups divide a workgroup's loop over two wave groups
+constexpr int kPairMinWorkgroups = 256;   // workgroups take two tiles each when at least this many are left
 
-// Workgroups are handed to the 8 XCDs round-robin by linear id, and each XCD has its own L2.  Work
-// items are therefore renumbered so that one XCD gets a CONTIGUOUS range of items: all tiles of a
-// head (which share its K and V) then sit behind the same L2 instead of being fetched eight times.
+// Workgroups are handed to the 8 XCDs round-robin by linear id, and each XCD has its own L2.  Work items are therefore
+// renumbered so that all tiles of a head (which share its K and V) sit behind the same L2 instead of being fetched
+// eight times.  Heads go to the XCDs in turn: a ragged batch, whose long sequences are neighbouring heads, then loads
+// them alike (B16 H40, 312..624 rows: the slowest XCD ended at 141 us, the fastest at 105, with contiguous ranges).  A
+// head count that eight does not divide is cut into equal contiguous ranges of items.
 constexpr int kXcds = 8;
 inline int xcd_grid(int total) { return (total + kXcds - 1) / kXcds * kXcds; }
-__device__ __forceinline__ int xcd_contiguous_item(int linear_id, int total)
+__device__ __forceinline__ int xcd_item(int linear_id, int per_head, int n_heads)
 {
-    const int per_xcd = (total + kXcds - 1) / kXcds;
-    if (linear_id / kXcds >= per_xcd) return total;
-    return (linear_id % kXcds) * per_xcd + linear_id / kXcds;  // may be >= total: caller exits
+    const int xcd = linear_id % kXcds, nth = linear_id / kXcds;
+    if (n_heads % kXcds == 0) return (nth / per_head * kXcds + xcd) * per_head + nth % per_head;
+    const int total = per_head * n_heads, per_xcd = (total + kXcds - 1) / kXcds;
+    return nth < per_xcd ? xcd * per_xcd + nth : total;  // may be >= total: caller exits
 }
 
 // Buffer descriptor over `bytes` bytes at p (raw: no stride, 32-bit data format).  Loads through it whose byte
 // offset is at or beyond `bytes` return zeros instead of touching memory.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const void* p, int bytes)
+__device__ __forceinline__ u32x4 tile_rsrc(const void* p, int bytes)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
-}
-// The whole offset travels in the vector operand: the bounds check of this hardware generation does not see
-// the scalar offset.
-__device__ __forceinline__ u32x4 buffer_load_16(__amdgpu_buffer_rsrc_t rsrc, int byte_offset)
-{
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, byte_offset, 0, 0));
+    const uint64_t at = (uint64_t)(uintptr_t)p;
+    u32x4 r;
+    r.x = __builtin_amdgcn_readfirstlane((uint32_t)at);
+    r.y = __builtin_amdgcn_readfirstlane((uint32_t)(at >> 32) & 0xffffu);
+    r.z = __builtin_amdgcn_readfirstlane((uint32_t)bytes);
+    r.w = 0x00020000u;
+    return r;
 }
 
+// ------------------------------------------------------------------ tiles moved straight from memory into LDS
+// A tile of ROWS rows of D bf16 values sits in LDS without padding (a lane of a direct load writes the 16 bytes
+// behind its neighbour's), so bank conflicts are avoided by permuting the 16-byte chunks of a row: chunk c of row r
+// is stored at place c ^ swizzle(r), which the loading lane arranges by fetching from the permuted address.
+template <int D> struct SwizzleRows {  // operand reads of 16 consecutive rows at one chunk number touch every bank once
+    static constexpr int kPeriod = 16;  // rows after which it repeats
+    static __device__ __forceinline__ int at(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
+};
+template <int D> struct SwizzleTr {  // four rows at the same 64 bytes (a transposed read's half) land in different banks
+    static constexpr int kPeriod = 4;
+    static __device__ __forceinline__ int at(int r) { return D == 128 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; }
+};
+
+typedef __attribute__((address_space(3))) void lds_void;
+__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(lds_void*)p; }
+// A value that the compiler has to take up anew: what is derived from it is computed here, not before the loop around.
+__device__ __forceinline__ int anew(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+// An LDS byte address that stays one register: the compiler would otherwise keep a copy per constant it is added to.
+__device__ __forceinline__ uint32_t one_register(uint32_t a)
+{
+    asm volatile("" : "+v"(a));
+    return a;
+}
+// One direct load: lane l writes its 16 (4) bytes at byte lds + 16 l (4 l).  Written in assembly because the compiler
+// would make every later LDS read wait for every load in flight (it cannot tell the tiles of one array apart); the loads
+// have no result register, and the waits below are the ones they need.  The five wait states are those between a vector
+// instruction that writes a scalar register (a restored spill) and a load that reads it.
+__device__ __forceinline__ void load_lds_16(u32x4 rsrc, uint32_t lds, int byte_offset)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :: "s"(lds), "v"(byte_offset), "s"(rsrc) : "memory");
+}
+__device__ __forceinline__ void load_lds_4(u32x4 rsrc, uint32_t lds, int byte_offset)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :: "s"(lds), "v"(byte_offset), "s"(rsrc) : "memory");
+}
+// the wave's loads into LDS have landed / its LDS reads have returned / the workgroup meets
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void meet()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+// All loads of this wave into LDS have landed and all its LDS reads have returned; then the workgroup meets.
+__device__ __forceinline__ void tile_barrier()
+{
+    wait_loads();
+    wait_lds();
+    meet();
+}
+
+// Moves ROWS rows starting at row0 of a matrix into LDS, WAVES waves sharing the work; issue(lds, row0, j), j in
+// 0..NI-1, is one load instruction of this wave, so that a kernel can spread them over its arithmetic.  The bounds check
+// of the descriptor covers rows beyond the matrix: nothing is read there, and the caller masks what they produce.
+template <int D, int ROWS, int WAVES, typename SWZ> struct TileToLds {
+    static constexpr int CH = D / 8;            // 16-byte chunks per row
+    static constexpr int RPI = kWave / CH;      // rows one wave moves per instruction
+    static constexpr int NI = ROWS / RPI / WAVES;
+    static constexpr int PERIOD = SWZ::kPeriod > RPI ? SWZ::kPeriod / RPI : 1;  // the lane's part of the address repeats
+    static constexpr int PARTS = NI < PERIOD ? NI : PERIOD;
+    static_assert(NI * RPI * WAVES == ROWS && (NI % PERIOD == 0 || PERIOD % NI == 0), "a wave's share within the period");
+    u32x4 rsrc;
+    int w0;                                     // first row of the wave's share (scalar)
+    int part[PARTS];
+    __device__ __forceinline__ TileToLds(u32x4 r, int wave, int lane) : rsrc(r), w0(wave * NI * RPI)
+    {
+#pragma unroll
+        for (int j = 0; j < PARTS; ++j) {
+            const int row = j * RPI + lane / CH;
+            part[j] = (row * CH + (lane % CH ^ SWZ::at(w0 + row))) * 16;
+        }
+    }
+    // lds: byte address of the tile (scalar)
+    __device__ __forceinline__ void issue(uint32_t lds, int row0, int j) const
+    {
+        load_lds_16(rsrc, lds + (w0 + j * RPI) * (D * 2), part[j % PARTS] + (row0 + w0 + j / PARTS * PARTS * RPI) * (D * 2));
+    }
+};
+
 // ------------------------------------------------------------------ forward
-// Double-buffered: the global loads of key tile i+1 are issued before tile i is consumed and land
-// in the other LDS buffer after it, so there is one barrier per tile and the HBM/L2 latency is
-// hidden behind the MFMA + softmax work of the current tile.
-// KSPLIT = 2 (short prompts that give the chip one workgroup per compute unit or less): the 8 waves form two
-// groups of 4 that share the workgroup's 128 queries and take alternate key tiles, each group staging its own
-// tiles; their (max, sum, O) are merged through LDS at the end.  The key loop of a workgroup, which is what
-// bounds such launches, is half as long, and every SIMD has two waves.
-template <int D, int WAVES, int KSPLIT>
-__global__ __launch_bounds__(WAVES * kWave, 2) void attn_fwd_mfma_kernel(
+// One workgroup = QW * 32 queries (one wave per 32); key tiles of 64, K and V double-buffered in LDS and moved there
+// without passing through registers.  Per tile a wave issues 16 matrix instructions for S^T = K.Q^T and 16 for
+// O^T += V^T.P^T (D = 128), and per 32 x 32 block 8 max, 16 scale-and-shift, 16 exponential, 16 add and 8 convert
+// instructions.  Bound: both pipes, so they have to run at the same time: the scores of tile i + 1 are multiplied while
+// tile i is turned into probabilities (phase A), and their row maximum is taken while tile i is multiplied with V
+// (phase B).  The issue order inside a phase is fixed by hand: some vector work behind every matrix instruction, LDS
+// operands four fragments ahead, the loads of later tiles in between.  Measured at B16 H32 T8192 D128: 9.2 ms before
+// (phases one after the other, tiles through registers, 256 queries per workgroup), 8.3 ms with this loop, 8.0 ms with
+// PAIR; B8 T2048: 400 -> 340 -> 290 us (the last 40 of them by the coalesced ways in and out).  The clock follows the
+// power: 19.2 M cycles at 2.05 GHz became 13.7 M at 1.7 GHz.  256 queries per workgroup took 8.8 ms; six or eight
+// fragments ahead changed nothing.
+// PAIR: the workgroup takes query tiles n - 1 - i and i of its head, one after the other.
+// KSPLIT = 2 (short prompts that give the chip one workgroup per compute unit or less): two groups of QW waves share
+// the workgroup's queries and take alternate key tiles, each group moving its own tiles; their (max, sum, O) are merged
+// through LDS at the end.  The key loop of a workgroup, which is what bounds such launches, is half as long.
+constexpr int kFwdAhead = 4;  // LDS fragments requested ahead of the matrix pipe
+template <int D, int QW, int KSPLIT, bool PAIR, bool OUT>
+__global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     uint16_t* __restrict__ out, float* __restrict__ lse, ScoreGeom geo, float scale_log2e, int n_qtiles,
     int n_heads, const int32_t* __restrict__ seq_len, int H)
 {
-    constexpr int GW = WAVES / KSPLIT;  // waves of one group: one per 32 queries
-    constexpr int THREADS = GW * kWave; // threads that stage one tile together
-    constexpr int BM = GW * 32;      // queries per workgroup
-    constexpr int KB = D / 16;       // contraction blocks of Q.K
-    constexpr int DB = D / 32;       // 32-row blocks of O^T
-    constexpr int KP = D + 8;        // K tile pitch in elements (272 B for D=128: conflict-free b128)
-    constexpr int KCH = kFwdBN * (D / 8) / THREADS;  // 16-byte chunks of the K tile per thread
-    constexpr int VP = D + 32;       // V tile pitch in elements (320 B for D=128: the transposed b64 reads measure conflict-free)
-    constexpr int VCH = kFwdBN * (D / 8) / THREADS;  // 16-byte chunks of the V tile per thread
-    __shared__ __align__(16) uint16_t ks_all[KSPLIT][2][kFwdBN * KP];
-    __shared__ __align__(16) uint16_t vs_all[KSPLIT][2][kFwdBN * VP];
+    constexpr int BM = QW * 32;   // queries per workgroup
+    constexpr int KB = D / 16;    // contraction blocks of Q.K
+    constexpr int DB = D / 32;    // 32-row blocks of O^T
+    constexpr int NA = 2 * KB;    // matrix instructions of phase A: (kb, 32-key block)
+    constexpr int NP = 4 * DB;    // of phase B: (16-key block, db)
+    constexpr int EV = 32 / NA;   // elements turned into probabilities per matrix instruction of phase A
+    constexpr int TILE = kFwdBN * D;
+    using KMove = TileToLds<D, kFwdBN, QW, SwizzleRows<D>>;
+    using VMove = TileToLds<D, kFwdBN, QW, SwizzleTr<D>>;
+    constexpr int NI = KMove::NI;
+    // per group: K of even tiles, K of odd tiles, V of even tiles, V of odd tiles
+    __shared__ __align__(16) uint16_t tiles[KSPLIT][4 * TILE];
+    __shared__ float stats[KSPLIT == 2 ? 2 * QW * kWave : 1];
 
     const int lane = threadIdx.x % kWave;
     const int wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int grp = wave_wg / GW;    // scalar: which key tiles (tile number mod KSPLIT)
-    const int wave = wave_wg % GW;   // scalar: which 32 queries; tile skips branch instead of masking
-    const int tid = threadIdx.x % THREADS;
-    uint16_t (*ks)[kFwdBN * KP] = ks_all[grp];
-    uint16_t (*vs)[kFwdBN * VP] = vs_all[grp];
+    const int grp = wave_wg / QW;   // scalar: which key tiles (tile number mod KSPLIT)
+    const int wave = wave_wg % QW;  // scalar: which 32 queries
     const int c32 = lane % 32, h = lane / 32;
-    // LDS row j of the K tile holds key swap23(j) (bits 2 and 3 of the row number exchanged), i.e. row
-    // i of a 32-key S^T block is key 16(i/16) + 8((i/4)%2) + 4((i/8)%2) + i%4.  In the accumulator
-    // layout (register 4g+t of half h = row 8g+4h+t) registers 8G..8G+7 of a lane then hold the 8
-    // CONSECUTIVE keys 16G + 8h .. +7: the P fragment of a P.V MFMA is a run of registers and its V^T
-    // operand a single 16-byte LDS read, while the K-tile reads stay linear and conflict-free.
-    const int item = xcd_contiguous_item(blockIdx.x, n_qtiles * n_heads);
-    if (item >= n_qtiles * n_heads) return;
-    const int bh = item / n_qtiles;
+    const int n_items = PAIR ? (n_qtiles + 1) / 2 : n_qtiles;  // per head
+    const int item = xcd_item(blockIdx.x, n_items, n_heads);
+    if (item >= n_items * n_heads) return;
+    const int bh = item / n_items;
     const int Tq = ragged_rows(seq_len, bh / H, geo.Tq), P = geo.P, L = P + Tq;
-    const int m0 = (n_qtiles - 1 - item % n_qtiles) * BM;  // longest rows first inside a head
-    if (m0 >= Tq) return;  // ragged batch: this sequence ends before the tile (whole workgroup)
-    const int mw = m0 + wave * 32;                          // first query of this wave
-    const int m = mw + c32;                            // this lane's query
+    const int own_tiles = (Tq + BM - 1) / BM;  // query tiles of this sequence
+    const int early = PAIR ? item % n_items : n_qtiles - 1 - item % n_items;
+    int qtile = PAIR ? own_tiles - 1 - early : early;  // the longer tile of a pair first
+    if (qtile < (PAIR ? early : 0) || qtile >= own_tiles) return;  // ragged batch: the sequence is shorter (whole workgroup)
     const uint16_t* qh = q + (size_t)bh * geo.q_rows * D;
-    const uint16_t* kh = k + (size_t)bh * geo.kv_rows * D;
-    const uint16_t* vh = v + (size_t)bh * geo.kv_rows * D;
-    const bool want_out = out != nullptr;
-    // V rows sit in LDS as they are in memory (key-major); the operand of O^T += V^T.P^T needs, per lane, 8
-    // keys of ONE feature.  ds_read_b64_tr_b16 does that transposition on the way out of LDS: in a group of
-    // 16 lanes, lane r points at 4 consecutive features of key r/4 (features 4(r%4).. of the group's 16),
-    // and lane j receives feature j of keys 0..3.  Two such reads (keys +0..3, +4..7) make one 8-key
-    // fragment.  Groups 0,1 (half h = 0) take keys 0..7 of a 16-key contraction block, groups 2,3 keys 8..15.
-    const int vt_lane = ((lane / 32) * 8 + (lane % 16) / 4) * VP + ((lane / 16) % 2) * 16 + (lane % 4) * 4;
-
-    bf16x8 qf[KB];
+    // tiles are fetched through descriptors that end at the sequence's last row: rows beyond it arrive as zeros
+    const KMove k_move(tile_rsrc(k + (size_t)bh * geo.kv_rows * D, L * D * 2), wave, lane);
+    const VMove v_move(tile_rsrc(v + (size_t)bh * geo.kv_rows * D, L * D * 2), wave, lane);
+    constexpr int K0 = 0, K1 = TILE, V0 = 2 * TILE, V1 = 3 * TILE;  // elements
+    const uint32_t mine_at = lds_address(tiles[grp]);
+    auto row_of = [&](int i) { return (i * KSPLIT + grp) * kFwdBN; };  // first key of the group's i-th tile
+    auto move_k = [&](int at, int i) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-        uint4 x = make_uint4(0, 0, 0, 0);
-        if (m < Tq) x = *reinterpret_cast<const uint4*>(qh + (size_t)m * D + kb * 16 + h * 8);
-        qf[kb] = __builtin_bit_cast(bf16x8, x);
+        for (int j = 0; j < NI; ++j) k_move.issue(mine_at + at * 2, row_of(i), j);
+    };
+    auto move_v = [&](int at, int i) __attribute__((always_inline)) {
+        if constexpr (OUT) {
+#pragma unroll
+            for (int j = 0; j < NI; ++j) v_move.issue(mine_at + at * 2, row_of(i), j);
+        }
+    };
+    // A wave's 32 query rows travel through the place of its own share of the V tiles (16 rows each), so that no other wave
+    // has to be waited for, and K of the first tile goes with them.
+    const uint32_t q_at = mine_at + V0 * 2 + wave * (16 * D * 2);
+    const TileToLds<D, 32, 1, SwizzleRows<D>> q_move(tile_rsrc(qh, Tq * D * 2), 0, lane);
+    auto first_loads = [&](int mw) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < q_move.NI; ++j)
+            q_move.issue(q_at + (j < q_move.NI / 2 ? 0 : (TILE - 16 * D) * 2), mw, j);
+        move_k(K0, 0);
+    };
+    first_loads(qtile * BM + wave * 32);
+
+    // A operand of S^T: row i of a 32-key block is key swap23(i) (bits 2 and 3 of i exchanged), i.e. key
+    // 16(i/16) + 8((i/4)%2) + 4((i/8)%2) + i%4.  In the accumulator layout (register 4g+t of half h = row 8g+4h+t)
+    // registers 8G..8G+7 of a lane then hold the 8 CONSECUTIVE keys 16G + 8h .. +7: the P fragment of a P.V matrix
+    // instruction is a run of registers.
+    bf16x8 qf[KB];  // B operand: this lane's query
+    const int krow = (c32 & ~12) | ((c32 & 4) << 1) | ((c32 & 8) >> 1);
+    uint32_t k_at[KB];  // byte address of this lane's 16 bytes of contraction block kb in tile K0
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+        k_at[kb] = one_register(mine_at + krow * (D * 2) + ((2 * kb + h) ^ SwizzleRows<D>::at(krow)) * 16);
+    auto k_frag = [&](int kt, int f) __attribute__((always_inline)) {  // f = 2 kb + 32-key block
+        return *(lds_bf16x8*)(uintptr_t)(k_at[f / 2] + (kt + f % 2 * 32 * D) * 2);
+    };
+    // V rows sit in LDS key-major; the operand of O^T += V^T.P^T needs, per lane, 8 keys of ONE feature.
+    // ds_read_b64_tr_b16 does that transposition on the way out of LDS: in a group of 16 lanes, lane r points at 4
+    // consecutive features of key r/4 (features 4(r%4).. of the group's 16), and lane j receives feature j of keys
+    // 0..3.  Two such reads (keys +0..3, +4..7) make one 8-key fragment.  Groups 0,1 (half h = 0) take keys 0..7 of a
+    // 16-key contraction block, groups 2,3 keys 8..15.
+    uint32_t v_at[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+        const int row = h * 8 + (lane % 16) / 4, chunk = db * 4 + (lane / 16) % 2 * 2 + lane % 4 / 2;
+        v_at[db] = one_register(mine_at + row * (D * 2) + (chunk ^ SwizzleTr<D>::at(row)) * 16 + lane % 2 * 8);
     }
-
-    f32x16 o[DB];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
-    // l_run: this half-wave's share of the row sum.  A group that does not start at key 0 can meet a tile in
-    // which a query sees no key at all; a finite floor for the running maximum keeps exp2(-inf - m) at zero
-    // there instead of exp2(-inf + inf).
-    float m_run = (KSPLIT == 1) ? -INFINITY : -1e30f, l_run = 0.f;
-
-    // K and V tiles are fetched through buffer descriptors that end at the sequence's last row: a 16-byte
-    // chunk beyond it comes back as zeros from the address unit itself (no compare, no branch, and 0 * padding
-    // stays 0 for V), and the per-thread offset is one add per tile.
-    const __amdgpu_buffer_rsrc_t k_rsrc = tile_rsrc(kh, L * D * 2);
-    const __amdgpu_buffer_rsrc_t v_rsrc = tile_rsrc(vh, L * D * 2);
-    u32x4 kreg[KCH], vreg[VCH];
-    auto fetch = [&](int n0) {
-        const int off = n0 * (D * 2) + tid * 16;  // chunk c = tid + i THREADS of the tile sits 16 c bytes into it
-#pragma unroll
-        for (int i = 0; i < KCH; ++i) kreg[i] = buffer_load_16(k_rsrc, off + i * THREADS * 16);
-        if (want_out) {
-#pragma unroll
-            for (int i = 0; i < VCH; ++i) vreg[i] = buffer_load_16(v_rsrc, off + i * THREADS * 16);
-        }
-    };
-    auto stage = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < KCH; ++i) {
-            const int c = tid + i * THREADS;
-            const int r = c / (D / 8), cc = c % (D / 8);
-            const int lr = (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1);  // swap23
-            *reinterpret_cast<u32x4*>(&ks[buf][lr * KP + cc * 8]) = kreg[i];
-        }
-        if (want_out) {
-#pragma unroll
-            for (int i = 0; i < VCH; ++i) {
-                const int c = tid + i * THREADS;
-                const int r = c / (D / 8), cc = c % (D / 8);
-                *reinterpret_cast<u32x4*>(&vs[buf][r * VP + cc * 8]) = vreg[i];
-            }
-        }
+    auto v_frag = [&](int vt, int g) __attribute__((always_inline)) {  // g = DB * (16-key block) + db
+        const uint32_t src = v_at[g % DB] + (vt + g / DB * 16 * D) * 2;
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(uintptr_t)src);
+        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(uintptr_t)(src + 4 * D * 2));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
 
-    const int n_end = min(L, P + m0 + BM);  // the workgroup's last query sees rows up to P + m0 + BM - 1
-    const int n_iter = ((n_end + kFwdBN - 1) / kFwdBN + KSPLIT - 1) / KSPLIT;  // same for both groups: one barrier each
-    fetch(grp * kFwdBN);
-    stage(0);
-    __syncthreads();
-    int buf = 0;
-    for (int it = 0; it < n_iter; ++it, buf ^= 1) {
-        const int n0 = (it * KSPLIT + grp) * kFwdBN;
-        const bool more = n0 + KSPLIT * kFwdBN < n_end;
-        if (more) fetch(n0 + KSPLIT * kFwdBN);
+    for (;;) {  // one query tile after the other
+        const int m0 = qtile * BM;
+        const int mw = m0 + wave * 32;  // first query of this wave
+        const int m = mw + c32;         // this lane's query
+        f32x16 o[DB];
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+        // m_run: running maximum of the scaled scores, base 2, of every tile whose scores have been computed (one tile
+        // ahead of o and l_run, which are already scaled to it).  A group that does not start at key 0 can meet a tile in
+        // which a query sees no key at all; a finite floor for the maximum keeps exp2(-inf - m) at zero there instead of
+        // exp2(-inf + inf).  l_run: this half-wave's share of the row sum.
+        float m_run = (KSPLIT == 1) ? -INFINITY : -1e30f, l_run = 0.f;
+        f32x16 sA[2], sB[2];
+        bf16x8 pf[4];
 
-        if (n0 < n_end && n0 <= P + mw + 31) {  // otherwise every key of the tile is in this wave's future
-            // S^T = K . Q^T : two 32-key blocks x this wave's 32 queries
-            f32x16 s[2];
-            {
-                bf16x8 ka[2][KB];  // every A fragment of the tile is requested before the first MFMA
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                    for (int nb = 0; nb < 2; ++nb)
-                        ka[nb][kb] = *reinterpret_cast<const bf16x8*>(
-                            &ks[buf][(nb * 32 + c32) * KP + kb * 16 + h * 8]);
+        auto mask = [&](f32x16 (&s)[2], int n0) __attribute__((always_inline)) {
+            if (n0 + kFwdBN - 1 > P + mw || n0 + kFwdBN > L) {  // tile with keys behind one of the wave's queries
+                const int last = min(P + m, L - 1) - n0 - h * 8;
 #pragma unroll
                 for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) s[nb][r] = 0.f;
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                    for (int nb = 0; nb < 2; ++nb)
-                        s[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[nb][kb], qf[kb], s[nb], 0, 0, 0);
-                // LDS reads run ahead of the matrix pipe: 4 in flight, then one read per MFMA
-                __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-                for (int i = 0; i < 2 * KB - 4; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                }
-                __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+                    for (int r = 0; r < 16; ++r)
+                        if (nb * 32 + (r / 8) * 16 + (r % 8) > last) s[nb][r] = -INFINITY;
             }
-            // causal mask (diagonal tiles only), row max on the raw products
-            if ((n0 + kFwdBN - 1 > P + mw) || (n0 + kFwdBN > L)) {
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int n = n0 + nb * 32 + (r / 8) * 16 + h * 8 + (r % 8);  // key of register r
-                        if (n > P + m || n >= L) s[nb][r] = -INFINITY;
-                    }
-            }
-            float mx = -INFINITY;
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[nb][r]);
-            {   // the other half-wave holds the other 32 keys of each query: exchange through the lane-swap
-                // instruction (a shuffle would go through LDS and its latency sits on the critical path)
-                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-                mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2e;
-            }
+        };
+        // the other half-wave holds the other 32 keys of each query: exchange through the lane-swap instruction (a shuffle
+        // would go through LDS and its latency sits on the critical path)
+        auto raise_max = [&](float mx) __attribute__((always_inline)) {
+            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+            mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2e;
             const float m_new = fmaxf(m_run, mx);  // finite: key 0 is visible to every query
-            const bool grew = m_new > m_run;
             const float corr = __builtin_amdgcn_exp2f(m_run - m_new);  // exp2(-inf) = 0 on the first tile
+            const bool grew = m_new > m_run;
             m_run = m_new;
-            float psum = 0.f;
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float p = __builtin_amdgcn_exp2f(fmaf(s[nb][r], scale_log2e, -m_new));
-                    s[nb][r] = p;
-                    psum += p;
-                }
-            l_run = l_run * corr + psum;
-
-            if (want_out) {
-                if (__any(grew)) {  // wave-uniform: the running max settles after a few tiles
-#pragma unroll
-                    for (int db = 0; db < DB; ++db)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) o[db][r] *= corr;
-                }
-                // O^T += V^T . P^T, 16 keys per MFMA: half h contracts keys 16 kk + 8h .. +7
-                bf16x8 va[4][DB];
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-                    for (int db = 0; db < DB; ++db) {
-                        const uint16_t* src = &vs[buf][vt_lane + (kk * 16) * VP + db * 32];
-                        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)src);
-                        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(src + 4 * VP));
-                        va[kk][db] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-                    }
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                    const int nb = kk / 2, r0 = (kk % 2) * 8;
-                    bf16x8 pf;
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) pf[t] = (__bf16)s[nb][r0 + t];
-#pragma unroll
-                    for (int db = 0; db < DB; ++db)
-                        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[kk][db], pf, o[db], 0, 0, 0);
-                }
-                __builtin_amdgcn_sched_group_barrier(0x100, 8, 1);
-#pragma unroll
-                for (int i = 0; i < 4 * DB - 4; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-                    __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
-                }
-                __builtin_amdgcn_sched_group_barrier(0x008, 4, 1);
-            }
-        }
-        if (more) stage(buf ^ 1);  // that buffer was last read before the previous barrier
-        __syncthreads();
-    }
-
-    if (KSPLIT == 2) {
-        // group 1 hands its state over through the K tile area (all tile reads ended at the last barrier);
-        // word j of thread t sits at j * THREADS + t: consecutive lanes, consecutive words
-        static_assert(KSPLIT == 1 || sizeof(ks_all) >= sizeof(float) * THREADS * (2 + DB * 16), "hand-over area");
-        float* xch = reinterpret_cast<float*>(&ks_all[0][0][0]);
-        if (grp == 1) {
-            xch[0 * THREADS + tid] = m_run;
-            xch[1 * THREADS + tid] = l_run;
-            if (want_out) {
+            l_run *= corr;
+            if (OUT && __any(grew)) {  // wave-uniform
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) xch[(2 + db * 16 + r) * THREADS + tid] = o[db][r];
+                    for (int r = 0; r < 16; ++r) o[db][r] *= corr;
+            }
+        };
+        auto pin = [&](bf16x8 (&p)[4]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                u32x4 w = __builtin_bit_cast(u32x4, p[kk]);
+                asm volatile("" : "+v"(w));
+                p[kk] = __builtin_bit_cast(bf16x8, w);
+            }
+        };
+        // Phase A: probabilities of the tile in s (into pf and the row sum) beside sn = K.Q^T of the next one; extra(f) is
+        // issued behind the f-th matrix instruction.
+        auto phase_a = [&](auto next, f32x16 (&s)[2], f32x16 (&sn)[2], int kt, auto&& extra) __attribute__((always_inline)) {
+            bf16x8 ka[NA];
+            if constexpr (next.value) {
+#pragma unroll
+                for (int f = 0; f < kFwdAhead; ++f) ka[f] = k_frag(kt, f);
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sn[nb][r] = 0.f;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            float x[EV], y[EV], ps[2] = {0.f, 0.f};
+#pragma unroll
+            for (int f = 0; f < NA + 2; ++f) {
+                if constexpr (next.value)
+                    if (f < NA) {
+                        sn[f % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[f], qf[f / 2], sn[f % 2], 0, 0, 0);
+                        if (f + kFwdAhead < NA) ka[f + kFwdAhead] = k_frag(kt, f + kFwdAhead);
+                    }
+                extra(f);
+                if (f >= 2) {  // third stage of the elements of two instructions ago: sum and round
+#pragma unroll
+                    for (int e = 0; e < EV; ++e) {
+                        const int el = (f - 2) * EV + e;
+                        ps[e % 2] += y[e];
+                        pf[el / 8][el % 8] = (__bf16)y[e];
+                    }
+                }
+                if (f >= 1 && f <= NA) {
+#pragma unroll
+                    for (int e = 0; e < EV; ++e) y[e] = __builtin_amdgcn_exp2f(x[e]);
+                }
+                if (f < NA) {
+#pragma unroll
+                    for (int e = 0; e < EV; ++e) {
+                        const int el = f * EV + e;
+                        x[e] = fmaf(s[el / 16][el % 16], scale_log2e, -m_run);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            l_run += ps[0] + ps[1];
+            asm volatile("" : "+v"(l_run));
+            pin(pf);  // sum and probabilities are formed here, beside the matrix instructions, not where they are used
+        };
+        // Phase B: O^T += V^T.P^T of the tile in pf beside the row maximum of the scores in sn.
+        auto phase_b = [&](auto next, f32x16 (&sn)[2], int vt) __attribute__((always_inline)) {
+            float mx[2] = {-INFINITY, -INFINITY};
+            bf16x8 va[NP];
+            if constexpr (OUT) {
+#pragma unroll
+                for (int g = 0; g < kFwdAhead; ++g) va[g] = v_frag(vt, g);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            constexpr int MV = 32 / NP;
+#pragma unroll
+            for (int g = 0; g < NP; ++g) {
+                if constexpr (OUT) {
+                    o[g % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[g], pf[g / DB], o[g % DB], 0, 0, 0);
+                    if (g + kFwdAhead < NP) va[g + kFwdAhead] = v_frag(vt, g + kFwdAhead);
+                }
+                if constexpr (next.value) {
+#pragma unroll
+                    for (int e = 0; e < MV; e += 2) {
+                        const int el = g * MV + e;
+                        mx[(e / 2 + g) % 2] = fmaxf(fmaxf(mx[(e / 2 + g) % 2], sn[el / 16][el % 16]), sn[el / 16][el % 16 + 1]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (next.value) raise_max(fmaxf(mx[0], mx[1]));
+        };
+
+        const int n_end = min(L, P + m0 + BM);  // the workgroup's last query sees rows up to P + m0 + BM - 1
+        const int n_iter = ((n_end + kFwdBN - 1) / kFwdBN + KSPLIT - 1) / KSPLIT;  // same for both groups: one barrier each
+        // tiles of this wave: the group's tiles with a key that one of its queries sees
+        const int seen = (mw < Tq) ? (min(P + mw + 32, n_end) + kFwdBN - 1) / kFwdBN : 0;
+        const int count = max(seen - grp + KSPLIT - 1, 0) / KSPLIT;
+
+        wait_loads();  // this wave's queries and its share of the first K tile
+        {
+            const int row = anew(c32);
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+                qf[kb] = *(lds_bf16x8*)(uintptr_t)(q_at + row / 16 * (TILE * 2) + row % 16 * (D * 2) +
+                                                   ((2 * kb + h) ^ SwizzleRows<D>::at(row)) * 16);
+        }
+        wait_lds();  // their place is free
+        move_v(V0, 0);
+        move_k(K1, 1);
+        meet();
+        if (count > 0) {  // scores of the first tile
+            bf16x8 ka[NA];
+#pragma unroll
+            for (int f = 0; f < NA; ++f) ka[f] = k_frag(K0, f);
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sA[nb][r] = 0.f;
+#pragma unroll
+            for (int f = 0; f < NA; ++f) sA[f % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[f], qf[f / 2], sA[f % 2], 0, 0, 0);
+            mask(sA, row_of(0));
+            float mx = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(fmaxf(mx, sA[0][r]), sA[1][r]);
+            raise_max(mx);
+        }
+        // One tile with a successor: K of tile i + 1 and V of tile i have landed; K of tile i + 2 goes where K of tile i was, V
+        // of tile i + 1 where V of tile i - 1 was, both read for the last time before the barrier.
+        auto body = [&](int i, f32x16 (&s)[2], f32x16 (&sn)[2], int k_old, int k_next, int v_cur, int v_next) __attribute__((always_inline)) {
+            tile_barrier();
+            const int k_row = (i + 2 < n_iter) ? row_of(i + 2) : L;  // L: nothing is fetched
+            const int v_row = row_of(i + 1);
+            phase_a(std::true_type{}, s, sn, k_next, [&](int f) __attribute__((always_inline)) {
+                constexpr int EVERY = NA / (2 * NI);
+                static_assert(EVERY >= 1, "a phase has room for its loads");
+                if (f < NA && f % EVERY == 0) {
+                    if (f / EVERY < NI)
+                        k_move.issue(mine_at + k_old * 2, k_row, f / EVERY);
+                    else if (OUT)
+                        v_move.issue(mine_at + v_next * 2, v_row, f / EVERY - NI);
+                }
+            });
+            mask(sn, row_of(i + 1));
+            phase_b(std::true_type{}, sn, v_cur);
+        };
+        int i = 0;
+        for (; i + 2 < count; i += 2) {
+            body(i, sA, sB, K0, K1, V0, V1);
+            body(i + 1, sB, sA, K1, K0, V1, V0);
+        }
+        const bool odd = i + 1 < count;
+        if (odd) {
+            body(i, sA, sB, K0, K1, V0, V1);
+            ++i;
+        }
+        // the wave's last tile, then nothing but its share of the loads that other waves still need
+        for (bool work = i < count; i < n_iter; ++i, work = false) {
+            tile_barrier();
+            const bool even = i % 2 == 0;
+            if (i + 2 < n_iter) move_k(even ? K0 : K1, i + 2);
+            if (i + 1 < n_iter) move_v(even ? V1 : V0, i + 1);
+            if (work) {
+                if (odd) {
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb) sA[nb] = sB[nb];
+                }
+                phase_a(std::false_type{}, sA, sB, K0, [](int) {});
+                phase_b(std::false_type{}, sB, even ? V0 : V1);
             }
         }
-        __syncthreads();
-        if (grp == 1) return;
-        const float m1 = xch[0 * THREADS + tid], l1 = xch[1 * THREADS + tid];
-        const float m_all = fmaxf(m_run, m1);  // group 0 has seen key 0: a real maximum
-        const float f0 = __builtin_amdgcn_exp2f(m_run - m_all), f1 = __builtin_amdgcn_exp2f(m1 - m_all);
-        l_run = l_run * f0 + l1 * f1;
-        m_run = m_all;
-        if (want_out) {
+
+        if (KSPLIT == 2) {
+            // group 1 hands its state over through group 0's tiles; word j of thread t sits at j * THREADS + t: consecutive
+            // lanes, consecutive words
+            constexpr int THREADS = QW * kWave;
+            static_assert(KSPLIT == 1 || !OUT || sizeof(tiles) >= sizeof(float) * THREADS * DB * 16, "hand-over area");
+            float* xch = reinterpret_cast<float*>(&tiles[0][0]);
+            const int tid = threadIdx.x % THREADS;
+            tile_barrier();
+            if (grp == 1) {
+                stats[tid] = m_run;
+                stats[THREADS + tid] = l_run;
+                if constexpr (OUT) {
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+                    for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    o[db][r] = o[db][r] * f0 + xch[(2 + db * 16 + r) * THREADS + tid] * f1;
-        }
-    }
-    const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
-    if (m < Tq) {
-        if (h == 0) lse[(size_t)bh * geo.q_rows + m] = (m_run + log2f(l_tot)) * kLn2;
-        if (want_out) {
-            const float inv = 1.f / l_tot;
-            uint16_t* orow = out + ((size_t)bh * geo.q_rows + m) * D;
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    bf16x4 y;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) y[t] = (__bf16)(o[db][g * 4 + t] * inv);
-                    *reinterpret_cast<bf16x4*>(orow + db * 32 + g * 8 + h * 4) = y;
+                        for (int r = 0; r < 16; ++r)
+                            xch[(db * 16 + r) * THREADS + tid] = o[db][r];
                 }
+            }
+            __syncthreads();
+            if (grp == 1) return;
+            const float m1 = stats[tid], l1 = stats[THREADS + tid];
+            const float m_all = fmaxf(m_run, m1);  // group 0 has seen key 0: a real maximum
+            const float f0 = __builtin_amdgcn_exp2f(m_run - m_all), f1 = __builtin_amdgcn_exp2f(m1 - m_all);
+            l_run = l_run * f0 + l1 * f1;
+            m_run = m_all;
+            if constexpr (OUT) {
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        o[db][r] = o[db][r] * f0 + xch[(db * 16 + r) * THREADS + tid] * f1;
+            }
         }
+        const int next_tile = PAIR ? own_tiles - 1 - qtile : qtile;
+        const bool more = PAIR && next_tile < qtile;
+        if (more) {  // what the second tile starts with travels while the first one is written out
+            tile_barrier();
+            first_loads(next_tile * BM + wave * 32);
+        }
+        const int el = anew(lane), ec = el % 32, eh = el / 32;  // lane, row and half of the way out
+        const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
+        if (mw + ec < Tq && eh == 0) lse[(size_t)bh * geo.q_rows + mw + ec] = (m_run + log2f(l_tot)) * kLn2;
+        if constexpr (OUT) {
+            // The accumulators hold 8-byte pieces of 32 rows per register pair.  Half a row at a time they are turned through
+            // this wave's share of tile K1 (every wave has read K for the last time), so that a store instruction writes
+            // whole 128-byte (D = 64: 64-byte) stretches.
+            constexpr int HC = D / 16;        // 16-byte chunks in half a row
+            constexpr int RPS = kWave / HC;   // rows per store instruction
+            const float inv = 1.f / l_tot;
+            const uint32_t stage = lds_address(tiles[KSPLIT - 1]) + K1 * 2 + wave * (16 * D * 2);
+            auto place = [&](int row, int chunk) { return row * (HC * 16) + (chunk ^ (D == 128 ? row & 7 : (row >> 2) & 3)) * 16; };
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+#pragma unroll
+                for (int d2 = 0; d2 < DB / 2; ++d2)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        bf16x4 y;
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) y[t] = (__bf16)(o[half * (DB / 2) + d2][g * 4 + t] * inv);
+                        *(lds_bf16x4*)(uintptr_t)(stage + place(ec, d2 * 4 + g) + eh * 8) = y;
+                    }
+#pragma unroll
+                for (int j = 0; j < 32 / RPS; ++j) {
+                    const int row = j * RPS + el / HC;
+                    const bf16x8 y = *(lds_bf16x8*)(uintptr_t)(stage + place(row, el % HC));
+                    if (mw + row < Tq)
+                        *reinterpret_cast<bf16x8*>(out + ((size_t)bh * geo.q_rows + mw + row) * D + half * (D / 2) + el % HC * 8) = y;
+                }
+            }
+        }
+        if (!more) return;
+        qtile = next_tile;
     }
 }
 
 // ------------------------------------------------------------------ column mass
-// One workgroup = 4 waves x NB blocks of 32 keys; the K fragments of a wave's keys stay in registers and every
-// Q fragment read from LDS feeds NB matrix instructions.  Work advances in steps of 32 queries.  The
-// exponentials of a step are issued between the matrix instructions of the NEXT step (the score block of a
-// step is kept "pending" for one step), so that the vector and transcendental work of one block runs while
-// the matrix pipe computes the following one.
-// QSPLIT = 2 (launches of one workgroup per compute unit or less): 8 waves in two groups of 4 that own the same
-// keys and take alternate query tiles, each group staging its own tiles; group 1's column sums are added to
-// group 0's through LDS at the end (always in that order).
-template <int D, int NB, bool PIPE, int MINW, int QSPLIT>
-__global__ __launch_bounds__(kMfmaThreads * QSPLIT, MINW) void colsum_mfma_kernel(
+// One workgroup owns KW * 32 * NB keys of a head; KW * QG waves.  A wave keeps the K fragments of its 32 * NB keys in
+// registers and takes every QG-th step of 32 queries; the Q rows of QT queries at a time are moved straight into
+// LDS (two tiles, one being read while the other lands).  S^T = K.Q^T, so a lane owns ONE query: its log-sum-exp is
+// a single value per step, and p = exp2(s c - lse) is added to the lane's own partial column sums, 16 per block of
+// 32 keys, which are reduced over the lanes once at the end.  No workgroup shares a column: deterministic.
+// Bound: vector issue and matrix pipe together.  Per 32 x 32 block 8 matrix instructions (256 clocks) stand against 16
+// scale-and-shift, 16 exponential (two issue slots each) and 16 add instructions (256 clocks): the exponentials of a
+// step are issued between the matrix instructions of the next one (its score block stays pending for one step).  Q
+// fragments are reloaded for the next step right after their last use, so no LDS latency is exposed.  Measured at
+// B16 H32 T8192 D128: 4.4 ms before (compiler's order, a lane per key), 4.35 ms in this order, 3.9 ms with PAIR.
+// PAIR: the workgroup takes key tiles i and n - 1 - i of its head, one after the other.
+// QG = 2 (launches of one workgroup per compute unit or less): twice the waves on the same keys.
+template <int D, int NB, int KW, int QG, int QT, bool PAIR>
+__global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const float* __restrict__ lse,
     float* __restrict__ head_imp, ScoreGeom geo, float scale_log2e, int n_ktiles, int n_heads,
     const int32_t* __restrict__ seq_len, int H)
 {
     constexpr int KB = D / 16;
-    constexpr int QP = D + 8;
-    constexpr int KEYS_W = 32 * NB;                   // keys per wave
-    constexpr int BN = (kMfmaThreads / kWave) * KEYS_W;  // keys per workgroup
-    __shared__ __align__(16) uint16_t qs_all[QSPLIT][2][kColBM * QP];
-    __shared__ __align__(16) float lse2_all[QSPLIT][2][kColBM];  // row log-sum-exp in base-2 units
-    __shared__ float col_xch[QSPLIT == 2 ? BN : 1];
+    constexpr int WAVES = KW * QG;
+    constexpr int KEYS_W = 32 * NB;     // keys per wave
+    constexpr int BN = KW * KEYS_W;     // keys per workgroup
+    constexpr int SPT = QT / 32 / QG;  // steps of one wave per tile
+    __shared__ __align__(16) uint16_t qs[2 * QT * D];  // two tiles
+    __shared__ __align__(16) float ls[2 * QT];
+    __shared__ __align__(16) float red[WAVES][4][KEYS_W / 2];  // [wave][half-wave, 16-lane row][16 sums per 32 keys]
 
-    const int tid = threadIdx.x % kMfmaThreads, lane = tid % kWave;  // tid: thread within its group
-    const int wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int grp = wave_wg / (kMfmaThreads / kWave);   // scalar: which query tiles (tile number mod QSPLIT)
-    const int wave = wave_wg % (kMfmaThreads / kWave);  // scalar: which keys; conditions on it branch, not mask
-    uint16_t (*qs)[kColBM * QP] = qs_all[grp];
-    float (*lse2)[kColBM] = lse2_all[grp];
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int qg = wave / KW, kw = wave % KW;
     const int c32 = lane % 32, h = lane / 32;
-    const int item = xcd_contiguous_item(blockIdx.x, n_ktiles * n_heads);
-    if (item >= n_ktiles * n_heads) return;
-    const int bh = item / n_ktiles;
+    const int n_items = PAIR ? (n_ktiles + 1) / 2 : n_ktiles;  // per head
+    const int item = xcd_item(blockIdx.x, n_items, n_heads);
+    if (item >= n_items * n_heads) return;
+    const int bh = item / n_items;
     const int Tq = ragged_rows(seq_len, bh / H, geo.Tq), P = geo.P, L = P + Tq;
-    const int n0 = (item % n_ktiles) * BN;  // low key tiles (most query tiles) first inside a head
-    if (n0 >= L) return;  // ragged batch: this sequence ends before the tile (whole workgroup)
-    const int nw = n0 + wave * KEYS_W;  // first key of this wave
+    const int own_tiles = (L + BN - 1) / BN;  // key tiles of this sequence
+    int ktile = item % n_items;               // low tiles have the most queries: first
+    if (ktile >= (PAIR ? (own_tiles + 1) / 2 : own_tiles)) return;  // ragged batch: the sequence is shorter (whole workgroup)
     const uint16_t* qh = q + (size_t)bh * geo.q_rows * D;
     const uint16_t* kh = k + (size_t)bh * geo.kv_rows * D;
-    const float* lh = lse + (size_t)bh * geo.q_rows;
+    const u32x4 q_rsrc = tile_rsrc(qh, Tq * D * 2);
+    const u32x4 l_rsrc = tile_rsrc(lse + (size_t)bh * geo.q_rows, Tq * 4);
 
-    bf16x8 kf[NB][KB];
+    for (;;) {  // one key tile after the other
+        const int n0 = ktile * BN;
+        const int nw = n0 + kw * KEYS_W;  // first key of this wave
+        const int m_begin = (max(n0 - P, 0) / QT) * QT;  // first tile with a query that sees key n0 (m sees n <= P + m)
+        const int n_tiles = (Tq - m_begin + QT - 1) / QT;
+        using Mover = TileToLds<D, QT, WAVES, SwizzleRows<D>>;
+        const Mover mover(q_rsrc, wave, lane);
+        const uint32_t qs_at = lds_address(qs), ls_at = lds_address(ls);
+        auto fetch_lse = [&](int buf, int t) __attribute__((always_inline)) {
+            if (wave < QT / kWave)
+                load_lds_4(l_rsrc, ls_at + (buf * QT + wave * kWave) * 4, (m_begin + t * QT + wave * kWave + lane) * 4);
+        };
+        auto fetch = [&](int buf, int t, int j) __attribute__((always_inline)) {
+            mover.issue(qs_at + buf * QT * D * 2, m_begin + t * QT, j);
+        };
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int n = nw + nb * 32 + c32;  // this lane's key in block nb
+        for (int t = 0; t < 2; ++t) {
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-            uint4 x = make_uint4(0, 0, 0, 0);
-            if (n < L) x = *reinterpret_cast<const uint4*>(kh + (size_t)n * D + kb * 16 + h * 8);
-            kf[nb][kb] = __builtin_bit_cast(bf16x8, x);
+            for (int j = 0; j < Mover::NI; ++j) fetch(t, t, j);
+            fetch_lse(t, t);
         }
-    }
 
-    constexpr int QCH = kColBM * (D / 8) / kMfmaThreads;  // 16-byte chunks of the Q tile per thread
-    u32x4 qreg[QCH];
-    float lreg = 0.f;
-    const __amdgpu_buffer_rsrc_t q_rsrc = tile_rsrc(qh, Tq * D * 2);  // queries beyond the sequence read as zeros
-    auto fetch = [&](int m0) {
-        const int off = m0 * (D * 2) + tid * 16;
-#pragma unroll
-        for (int i = 0; i < QCH; ++i) qreg[i] = buffer_load_16(q_rsrc, off + i * kMfmaThreads * 16);
-        // no arithmetic on the loaded value here: using it would wait for every load just issued
-        if (tid < kColBM) lreg = (m0 + tid < Tq) ? lh[m0 + tid] : INFINITY;
-    };
-    auto stage = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < QCH; ++i) {
-            const int c = tid + i * kMfmaThreads;
-            const int r = c / (D / 8), cc = c % (D / 8);
-            *reinterpret_cast<u32x4*>(&qs[buf][r * QP + cc * 8]) = qreg[i];
-        }
-        if (tid < kColBM) lse2[buf][tid] = lreg * kLog2e;
-    };
-
-    // PIPE: a step's score block stays "pending" for one step and its exponentials are issued between the
-    // matrix instructions of the next one.  Two register sets, A and B, take turns: the first step of a query
-    // tile computes into A while B is pending, the second into B while A is pending, so no block is ever
-    // copied.  B's initial values make its exponentials exact zeros (rows with lse = +inf carry no mass).
-    f32x16 sA[NB], sB[NB];
-    float lA[16], lB[16];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sA[nb][r] = sB[nb][r] = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) lA[r] = lB[r] = INFINITY;
-    int mq_pend = 0x3fffffff;  // first query of the step pending in B between tiles
-    float col[NB][2];  // two chains per key keep the adds off the exp latency
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) col[nb][0] = col[nb][1] = 0.f;
-
-    // exponentials of a block with the causal mask (steps that touch the diagonal, and the last one)
-    auto exp_masked = [&](const f32x16 (&sx)[NB], const float (&lx)[16], int mq) {
+        bf16x8 kf[NB][KB];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            const int n = nw + nb * 32 + c32;
+            const int n = min(nw + nb * 32 + anew(c32), L - 1);  // sums of keys beyond L are not stored
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(sx[nb][r], scale_log2e, -lx[r]));
-                const int mm = mq + (r / 4) * 8 + h * 4 + (r % 4);
-                col[nb][r & 1] += (P + mm >= n) ? p : 0.f;
-            }
+            for (int kb = 0; kb < KB; ++kb)
+                kf[nb][kb] = *reinterpret_cast<const bf16x8*>(kh + (size_t)n * D + kb * 16 + h * 8);
         }
-    };
-    auto exp_plain = [&](const f32x16 (&sx)[NB], const float (&lx)[16]) {
+
+        // A and B take turns: one is being computed while the other is pending
+        f32x16 sA[NB], sB[NB];
+        float lA = -INFINITY, lB = -INFINITY;  // minus the log-sum-exp of the lane's query, base 2; -inf: no mass
+        int mA = 0x3fffff00, mB = 0x3fffff00;  // first query of the step in A, B
+        f32x16 col[NB];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                col[nb][r & 1] += __builtin_amdgcn_exp2f(fmaf(sx[nb][r], scale_log2e, -lx[r]));
-    };
-    // S = Q.K^T of the 32 queries of step st into sn, their log-sum-exp into ln
-    auto load_q = [&](int buf, int st, bf16x8 (&qa)[KB], float (&ln)[16]) {
+            for (int r = 0; r < 16; ++r) sA[nb][r] = sB[nb][r] = col[nb][r] = 0.f;
+
+        // this lane's address inside a step: row c32, chunk 2 kb + h, swizzled
+        const int swz = SwizzleRows<D>::at(c32);
+        uint32_t q_at[KB];
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-            qa[kb] = *reinterpret_cast<const bf16x8*>(&qs[buf][(st * 32 + c32) * QP + kb * 16 + h * 8]);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const float4 l4 = *reinterpret_cast<const float4*>(&lse2[buf][st * 32 + g * 8 + h * 4]);
-            ln[g * 4 + 0] = l4.x;
-            ln[g * 4 + 1] = l4.y;
-            ln[g * 4 + 2] = l4.z;
-            ln[g * 4 + 3] = l4.w;
-        }
-    };
-    auto mfmas = [&](const bf16x8 (&qa)[KB], f32x16 (&sn)[NB]) {
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sn[nb][r] = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
+        for (int kb = 0; kb < KB; ++kb) q_at[kb] = one_register(qs_at + (qg * 32 + c32) * (D * 2) + ((2 * kb + h) ^ swz) * 16);
+        auto frag = [&](int u, int kb) __attribute__((always_inline)) {  // u: step of 32 queries inside the two tiles
+            return *(lds_bf16x8*)(uintptr_t)(q_at[kb] + u * 32 * D * 2);
+        };
+        // pairs that the mask takes out (keys behind the query, queries behind the end): score -inf, mass zero
+        auto mask = [&](f32x16 (&sp)[NB], int mp) __attribute__((always_inline)) {
+            const int last = (mp + c32 < Tq) ? P + mp + c32 - nw - h * 4 : -1;  // last key this lane's query sees
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
-                sn[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[kb], kf[nb][kb], sn[nb], 0, 0, 0);
-    };
-    // one pipelined step: sn, ln <- step st of the tile; the pending block (sp, lp, first query mqp) is retired
-    auto piped_step = [&](int buf, int st, f32x16 (&sn)[NB], float (&ln)[16], const f32x16 (&sp)[NB],
-                          const float (&lp)[16], int mqp) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (nb * 32 + (r / 4) * 8 + (r % 4) > last) sp[nb][r] = -INFINITY;
+        };
         bf16x8 qa[KB];
-        load_q(buf, st, qa, ln);
-        if (P + mqp < nw + KEYS_W - 1) {  // some (query, key) pair of the pending step is masked
-            exp_masked(sp, lp, mqp);
-            mfmas(qa, sn);
-        } else {
-            mfmas(qa, sn);
-            exp_plain(sp, lp);
-            // issue order: LDS reads run ahead, then per matrix instruction two elements' worth of vector
-            // work (scale-and-shift, exponential, add) of the pending block
-            __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+        bool loaded = false;  // qa, ln hold this wave's next step
+        float ln = 0.f;  // log-sum-exp of the step in qa
+        // One step: S^T of the step held in qa into sn while the pending block (sp, lp) is turned into mass; qa is
+        // refilled with step u_next of tile qs_next.
+        auto step = [&](f32x16 (&sn)[NB], float& l_n, int& m_n, int mq, f32x16 (&sp)[NB], float& lp, int mp,
+                        int u_next, auto&& extra) __attribute__((always_inline)) {
+            l_n = -ln * kLog2e;
+            m_n = mq;
+            ln = ls[(u_next + qg) * 32 + c32];
+            if (P + mp < nw + KEYS_W - 1 || mp + 32 > Tq) mask(sp, mp);  // some pair of the pending step is masked
 #pragma unroll
-            for (int i = 0; i < NB * KB; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
-                __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
-            }
-        }
-    };
-
-    const int m_begin = (max(n0 - P, 0) / kColBM) * kColBM;  // first query tile that sees key n0 (query m sees n <= P + m)
-    const int n_iter = ((Tq - m_begin + kColBM - 1) / kColBM + QSPLIT - 1) / QSPLIT;  // same for both groups
-    fetch(m_begin + grp * kColBM);  // a tile beyond the sequence reads as zero queries with lse = +inf: no mass
-    stage(0);
-    __syncthreads();
-    int buf = 0;
-    for (int it = 0; it < n_iter; ++it, buf ^= 1) {
-        const int m0 = m_begin + (it * QSPLIT + grp) * kColBM;
-        const bool more = m0 + QSPLIT * kColBM < Tq;
-        if (more) fetch(m0 + QSPLIT * kColBM);
-
-        if (PIPE) {
-            // a tile takes part as soon as one of its queries sees one of this wave's keys (wave-uniform); a
-            // step of it that sees none is masked away like the diagonal
-            if (P + m0 + kColBM - 1 >= nw) {
-                static_assert(kColBM == 64, "two steps per query tile");
-                piped_step(buf, 0, sA, lA, sB, lB, mq_pend);
-                piped_step(buf, 1, sB, lB, sA, lA, m0);
-                mq_pend = m0 + 32;
-            }
-        } else {
+            for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int st = 0; st < kColBM / 32; ++st) {
-                const int mq = m0 + st * 32;  // first query of this step
-                if (mq < Tq && P + mq + 31 >= nw) {  // else no query of the step sees any of this wave's keys (wave-uniform)
-                    // no pending block: this step's exponentials follow its own matrix instructions; other
-                    // waves of the SIMD fill the matrix pipe meanwhile
-                    bf16x8 qa[KB];
-                    load_q(buf, st, qa, lA);
-                    mfmas(qa, sA);
-                    if (P + mq < nw + KEYS_W - 1)  // some (query, key) pair of the step is masked
-                        exp_masked(sA, lA, mq);
-                    else
-                        exp_plain(sA, lA);
+                for (int r = 0; r < 16; ++r) sn[nb][r] = 0.f;
+            // Issue order, fixed by hand: per matrix instruction EV elements are scaled, the EV before them exponentiated and
+            // the EV before those added, so that no instruction waits for the one in front of it.
+            constexpr int EV = 16 / KB;
+            constexpr int NM = NB * KB;
+            float x[EV], y[EV];
+#pragma unroll
+            for (int i = 0; i < NM + 2; ++i) {
+                if (i < NM) {
+                    const int kb = i / NB, nb = i % NB;
+                    sn[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[nb][kb], qa[kb], sn[nb], 0, 0, 0);
+                    if (nb == NB - 1) qa[kb] = frag(u_next, kb);
+                    extra(i);
                 }
+                if (i >= 2) {
+#pragma unroll
+                    for (int e = 0; e < EV; ++e) {
+                        const int el = (i - 2) * EV + e;
+                        col[el / 16][el % 16] += y[e];
+                    }
+                }
+                if (i >= 1 && i <= NM) {
+#pragma unroll
+                    for (int e = 0; e < EV; ++e) y[e] = __builtin_amdgcn_exp2f(x[e]);
+                }
+                if (i < NM) {
+#pragma unroll
+                    for (int e = 0; e < EV; ++e) {
+                        const int el = i * EV + e;
+                        x[e] = fmaf(sp[el / 16][el % 16], scale_log2e, lp);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) asm volatile("" : "+v"(col[nb]));  // added here, beside the matrix instructions
+            lp = -INFINITY;  // retired
+        };
+
+        const int mq_first = nw - P - 31;  // the last query of a step has to see the wave's first key
+        static_assert(SPT % 2 == 0, "A and B alternate through a tile");
+        constexpr auto nothing = [](int) {};
+        auto tile = [&](int buf, int t) __attribute__((always_inline)) {
+            const int m0 = m_begin + t * QT + qg * 32;
+            const int u0 = buf * (QT / 32);  // steps are counted from the wave's first one
+#pragma unroll
+            for (int i = 0; i < SPT; ++i) {
+                const int u = u0 + i * QG, mq = m0 + i * QG * 32;
+                const bool last = i == SPT - 1;
+                const bool active = mq >= mq_first && mq < Tq;  // some query of the step sees a key of this wave (wave-uniform)
+                if (active && !loaded) {  // its first step: nothing has been loaded ahead
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb) qa[kb] = frag(u, kb);
+                    ln = ls[(u + qg) * 32 + c32];
+                    loaded = true;
+                }
+                if (last) {
+                    tile_barrier();  // the other tile has landed, and every wave has read this one for the last time
+                    fetch_lse(buf, t + 2);
+                }
+                if (!active) {
+                    if (last) {
+#pragma unroll
+                        for (int j = 0; j < Mover::NI; ++j) fetch(buf, t + 2, j);
+                    }
+                    continue;
+                }
+                if (i % 2 == 0)
+                    step(sA, lA, mA, mq, sB, lB, mB, u + QG, nothing);
+                else if (!last)
+                    step(sB, lB, mB, mq, sA, lA, mA, u + QG, nothing);
+                else  // the tile after the next one takes this one's place, its loads spread over the matrix instructions
+                    step(sB, lB, mB, mq, sA, lA, mA, (buf ^ 1) * (QT / 32), [&](int g) __attribute__((always_inline)) {
+                        constexpr int EVERY = NB * KB / Mover::NI;
+                        if (g % EVERY == 0) fetch(buf, t + 2, g / EVERY);
+                    });
+            }
+        };
+        tile_barrier();
+        for (int t = 0; t < n_tiles; t += 2) {
+            tile(0, t);
+            if (t + 1 < n_tiles) tile(1, t + 1);
         }
-        if (more) stage(buf ^ 1);
+
+        // at most one of the two is still pending, the other one adds zeros
+        auto retire = [&](f32x16 (&sp)[NB], float lp, int mp) __attribute__((always_inline)) {
+            mask(sp, mp);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) col[nb][r] += __builtin_amdgcn_exp2f(fmaf(sp[nb][r], scale_log2e, lp));
+        };
+        retire(sA, lA, mA);
+        retire(sB, lB, mB);
+        const int el = anew(lane);
+        // over the 16 lanes of a row by DPP, over the rows and the query groups through LDS, always in the same order
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                float4 y;
+                y.x = group_sum<16>(col[nb][4 * g]);
+                y.y = group_sum<16>(col[nb][4 * g + 1]);
+                y.z = group_sum<16>(col[nb][4 * g + 2]);
+                y.w = group_sum<16>(col[nb][4 * g + 3]);
+                if (el % 16 == 0) *reinterpret_cast<float4*>(&red[wave][el / 16][nb * 16 + 4 * g]) = y;
+            }
         __syncthreads();
-    }
-    if (PIPE) exp_masked(sB, lB, mq_pend);
-    float csum[NB];
+        const int key = anew(threadIdx.x);
+        if (key < BN && n0 + key < L) {
+            const int w = key / KEYS_W, j = key % 32, slot = (key % KEYS_W) / 32 * 16 + j / 8 * 4 + j % 4, hh = (j / 4) % 2;
+            float sum = 0.f;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        csum[nb] = col[nb][0] + col[nb][1];
-        csum[nb] += __shfl_xor(csum[nb], 32, kWave);
-    }
-    if (QSPLIT == 2) {
-        if (grp == 1 && h == 0) {
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) col_xch[wave * KEYS_W + nb * 32 + c32] = csum[nb];
+            for (int g = 0; g < QG; ++g) sum += red[g * KW + w][2 * hh][slot] + red[g * KW + w][2 * hh + 1][slot];
+            head_imp[(size_t)bh * geo.imp_rows + n0 + key] = sum;
         }
-        __syncthreads();
-        if (grp == 1) return;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) csum[nb] += col_xch[wave * KEYS_W + nb * 32 + c32];
-    }
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int n = nw + nb * 32 + c32;
-        if (h == 0 && n < L) head_imp[(size_t)bh * geo.imp_rows + n] = csum[nb];
+        const int next_tile = PAIR ? own_tiles - 1 - ktile : ktile;
+        if (!PAIR || next_tile <= ktile) return;
+        ktile = next_tile;
+        __syncthreads();  // the sums have been read
     }
 }
 
 template <int D>
 static int launch_mfma(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse,
                        float* head_imp, int B, int H, ScoreGeom geo, const int32_t* seq_len, float scale,
-                       int forced_waves, hipStream_t stream)
+                       hipStream_t stream)
 {
     const float sl = scale * kLog2e;
     const int Tq = geo.Tq, L = geo.L;
     const int BH = B * H;
-    // 8-wave workgroups (256 queries) halve the LDS staging per flop, which pays once the key loop is long
-    // (measured crossover between 2048 and 2304 keys); 4-wave ones balance shorter prompts better
-    int waves = forced_waves;
-    if (waves != 4 && waves != 8) waves = (L >= 2176 && (long long)BH * ((Tq + 255) / 256) >= 512) ? 8 : 4;
     const int qt128 = (Tq + 127) / 128;
-    if (waves == 8)
-        hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 8, 1>), dim3(xcd_grid(((Tq + 255) / 256) * BH)), dim3(512), 0,
-                           stream, q, k, v, out, lse, geo, sl, (Tq + 255) / 256, BH, seq_len, H);
-    else if (forced_waves == 0 && (long long)qt128 * BH <= kSplitMaxWorkgroups && L >= 4 * kFwdBN)
-        // a workgroup per compute unit or less: the launch lasts as long as its longest key loop
-        hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 8, 2>), dim3(xcd_grid(qt128 * BH)), dim3(512), 0, stream, q, k,
-                           v, out, lse, geo, sl, qt128, BH, seq_len, H);
+#define EC_FWD(KS_, PAIR_)                                                                                           \
+    do {                                                                                                             \
+        const dim3 grid(xcd_grid((PAIR_ ? (qt128 + 1) / 2 : qt128) * BH)), block(4 * KS_ * kWave);                    \
+        if (out != nullptr)                                                                                          \
+            hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 4, KS_, PAIR_, true>), grid, block, 0, stream, q, k, v, out,  \
+                               lse, geo, sl, qt128, BH, seq_len, H);                                                 \
+        else                                                                                                         \
+            hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 4, KS_, PAIR_, false>), grid, block, 0, stream, q, k, v, out, \
+                               lse, geo, sl, qt128, BH, seq_len, H);                                                 \
+    } while (0)
+    // Launch shapes of the forward pass, us (pairs / single tiles / two wave groups per tile), H 32, D 128:
+    //   B1 T512 18.2 / 13.7 / 14.7    B1 T1024 26.4 / 22.6 / 22.2   B1 T2048 46.5 / 60.1 / 61.8   B2 T1024 29.0 / 33.3 / 39.9
+    //   B4 T1024 47.0 / 63.4 / 75.9   B8 T1536 180 / 204 / 234      B2 T8192 1068 / 1112 / 1172   B16 H40 T256 35.9 / 33.2 / 49.1
+    //   H8 B1: T1024 25.3 / 20.3 / 19.7   T2048 39.3 / 34.6 / 32.8   T4096 70.0 / 65.4 / 61.7
+    // Pairs from one per compute unit on (three tiles or fewer have nothing to even out); below that two groups per tile
+    // once the key loop is long enough to pay for merging them.
+    if (qt128 >= 4 && (long long)((qt128 + 1) / 2) * BH >= kPairMinWorkgroups)
+        EC_FWD(1, true);
+    else if ((long long)qt128 * BH <= kSplitMaxWorkgroups && L >= 1024)
+        EC_FWD(2, false);
     else
-        hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 4, 1>), dim3(xcd_grid(qt128 * BH)), dim3(256), 0, stream, q, k,
-                           v, out, lse, geo, sl, qt128, BH, seq_len, H);
+        EC_FWD(1, false);
+#undef EC_FWD
     int rc = status_from_hip(hipGetLastError());
     if (rc != EC_OK) return rc;
-    // 64 keys per wave halve the LDS reads per matrix instruction; 32 keep twice as many workgroups for
-    // shapes that would otherwise leave compute units idle
     const int kt256 = (L + 255) / 256, kt128 = (L + 127) / 128;
-#define EC_COLSUM(NB_, PIPE_, MINW_, KT_, QS_)                                                                   \
-    hipLaunchKernelGGL((colsum_mfma_kernel<D, NB_, PIPE_, MINW_, QS_>), dim3(xcd_grid(KT_ * BH)),                \
-                       dim3(kMfmaThreads * QS_), 0, stream, q, k, lse, head_imp, geo, sl, KT_, BH, seq_len, H)
-    // measured (B4 H32 T8192 / B8 H32 T2048): 64 keys per wave with the pending-block pipeline 1165 / 223 us,
-    // 32 keys per wave without it at four waves per SIMD 1272 / 202 us
-    if ((long long)kt256 * BH >= 4096 || (L >= 6144 && (long long)kt256 * BH >= 1024))  // B2 H32 T8192: 1762 / 1802 us
-        EC_COLSUM(2, true, 2, kt256, 1);
-    else if ((long long)kt128 * BH <= kSplitMaxWorkgroups && Tq >= 4 * kColBM)
-        EC_COLSUM(1, false, 2, kt128, 2);  // the launch lasts as long as the first key tile's loop over the queries
+#define EC_COLSUM(NB_, QG_, QT_, PAIR_)                                                                              \
+    do {                                                                                                             \
+        const int kt = (L + 128 * NB_ - 1) / (128 * NB_);                                                            \
+        hipLaunchKernelGGL((colsum_mfma_kernel<D, NB_, 4, QG_, QT_, PAIR_>),                                         \
+                           dim3(xcd_grid((PAIR_ ? (kt + 1) / 2 : kt) * BH)), dim3(4 * QG_ * kWave), 0, stream, q, k, \
+                           lse, head_imp, geo, sl, kt, BH, seq_len, H);                                              \
+    } while (0)
+    // Launch shapes of the column pass, us (64 keys per wave in pairs / 32 keys per wave / 32 keys, two query groups):
+    //   H32 D128: B1 T512 22.7 / 11.3 / 9.0   B1 T1024 30.4 / 14.9 / 13.2   B2 T1024 31.9 / 22.3 / 25.8   B1 T2048 46.4 / 37.1 / 37.8
+    //   B2 T2048 53.8 / 54.5 / 66.2   B4 T1024 35.2 / 39.6 / 47.0   B8 T1536 107 / 111 / 156   B2 T8192 524 / 591 / 647
+    //   B16 H40 T512 63.5 / 50.0 / 82.5; a chunk of 1024 over 640 rows, B8: 117 / 99 (its first tiles are equally long: nothing to pair)
+    if (kt256 >= 4 && (long long)((kt256 + 1) / 2) * BH >= kPairMinWorkgroups && 2 * geo.P <= Tq)
+        EC_COLSUM(2, 1, 128, true);
+    else if ((long long)kt128 * BH <= kSplitMaxWorkgroups)
+        EC_COLSUM(1, 2, 128, false);
     else
-        EC_COLSUM(1, false, 4, kt128, 1);
+        EC_COLSUM(1, 1, 64, false);
 #undef EC_COLSUM
     return status_from_hip(hipGetLastError());
 }
@@ -607,15 +846,15 @@ static int launch_mfma(const uint16_t* q, const uint16_t* k, const uint16_t* v, 
 // Per-head importance into head_imp [B,H,L]; out may be NULL (then v is not read).
 int score_mfma_dispatch(const void* q, const void* k, const void* v, void* out, float* lse, float* head_imp,
                         int B, int H, ScoreGeom geo, const int32_t* seq_len, int D, int dt, float scale,
-                        int forced_waves, hipStream_t stream)
+                        hipStream_t stream)
 {
     if (dt != EC_BF16) return EC_EUNSUPPORTED;
     if (D == 128)
         return launch_mfma<128>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (uint16_t*)out, lse,
-                                head_imp, B, H, geo, seq_len, scale, forced_waves, stream);
+                                head_imp, B, H, geo, seq_len, scale, stream);
     if (D == 64)
         return launch_mfma<64>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (uint16_t*)out, lse,
-                               head_imp, B, H, geo, seq_len, scale, forced_waves, stream);
+                               head_imp, B, H, geo, seq_len, scale, stream);
     return EC_EUNSUPPORTED;
 }
 

@@ -92,6 +92,27 @@ def test_prefill_chain_ragged(dtype, D, H, Gmode, lens):
         assert (to_host(kc[b, :, nb:]) == 9.0).all() and (assign[b, :, n:] == -1).all() and (pos[b, :, nb:] == -5).all()
 
 
+@pytest.mark.parametrize("D", [128, 64])
+def test_prefill_score_ragged_paired_tiles(D):
+    """Batches whose launch gives every workgroup two tiles of a head: each sequence pairs its own tiles."""
+    H, lens = 32, [897, 640, 0, 128, 129, 256, 257, 1]
+    B, T = len(lens), max(lens)
+    cfg = syn.custom("t", H=H, D=D, B=B, T=T, dtype="bf16", cid=3900)
+    q, k, v = syn.prompt_qkv(cfg)
+    dq, dk, dv = (_nan_pad(x, lens, "bf16") for x in (q, k, v))
+    out = torch.full((B, H, T, D), 5.0, dtype=torch.bfloat16, device="cuda")
+    score = torch.full((B, H, T), 5.0, dtype=torch.float32, device="cuda")
+    ws = ec.new_workspace(ec.EC_FN_PREFILL_SCORE, B, H, T, D, ec.EC_BF16)
+    ec.ec_prefill_score_varlen(dq, dk, dv, out, None, score, _i32(lens), cfg.scale, ws)
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        if n:
+            r = oracle.prefill_score(q[b:b + 1, :, :n], k[b:b + 1, :, :n], v[b:b + 1, :, :n], cfg.scale, H)
+            assert_close(to_host(out[b:b + 1, :, :n]), r["out"], "bf16", f"out[{b}]")
+            assert_close(to_host(score[b:b + 1, :, :n]), r["score"], "bf16", f"score[{b}]")
+        assert (out[b, :, n:] == 5.0).all()  # rows beyond the sequence are left alone
+
+
 @pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f32", 64)])
 @pytest.mark.parametrize("H,G,cap,lens,victims", [
     (2, 1, 40, [5, 0, 39, 17], [-1, 0, 14, 17]),          # append, drop the only row, shift, drop the new row

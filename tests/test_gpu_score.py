@@ -80,6 +80,45 @@ def test_prefill_score_launch_shapes_of_short_prompts(D, B, H, T):
     np.testing.assert_allclose(score.sum(-1), T, rtol=1e-5)
 
 
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("B,H,T", [
+    (4, 32, 385),   # the shortest prompt whose query tiles are taken in pairs: four tiles, the last of one row
+    (2, 43, 640),   # five full tiles: the middle one has no partner; head count that the XCDs do not divide
+    (4, 32, 769),   # the shortest whose key tiles are: four tiles of 256, the last of one key
+    (8, 8, 1281),   # an odd number of either, ragged tails
+])
+def test_prefill_score_paired_tiles(D, B, H, T):
+    """bf16 launches with enough workgroups give each of them two tiles of a head."""
+    cfg = syn.custom("t", H=H, D=D, B=B, T=T, dtype="bf16", cid=4500 + T + H)
+    q, k, v = syn.prompt_qkv(cfg)
+    ref = oracle.prefill_score(q, k, v, cfg.scale, 1)
+    out, lse, score = run_gpu_score(q, k, v, "bf16", cfg.scale, 1)
+    assert_close(out, ref["out"], "bf16", "out")
+    assert_close(lse, ref["lse"], "bf16", "lse")
+    assert_close(score, ref["score"], "bf16", "score")
+    _, _, alone = run_gpu_score(q, k, v, "bf16", cfg.scale, 1, want_out=False)
+    np.testing.assert_array_equal(alone, score)  # the same scores when the attention output is not wanted
+
+
+def test_prefill_score_of_rows_off_the_16_byte_grid():
+    """Tensors that start at an odd element of their storage."""
+    cfg = syn.custom("t", H=2, D=64, B=1, T=200, dtype="bf16", cid=4900)
+    q, k, v = syn.prompt_qkv(cfg)
+    ref = oracle.prefill_score(q, k, v, cfg.scale, 2)
+    shifted = []
+    for x in (q, k, v, np.zeros_like(q)):
+        room = torch.zeros(x.size + 8, dtype=torch.bfloat16, device="cuda")
+        t = room[1:1 + x.size].view(x.shape)
+        t.copy_(to_dev(x, "bf16"))
+        shifted.append(t)
+    dq, dk, dv, out = shifted
+    score = torch.zeros((1, 2, 200), dtype=torch.float32, device="cuda")
+    ec.ec_prefill_score(dq, dk, dv, out, None, score, cfg.scale, ec.new_workspace(ec.EC_FN_PREFILL_SCORE, 1, 2, 200, 64, ec.EC_BF16))
+    torch.cuda.synchronize()
+    assert_close(to_host(out), ref["out"], "bf16", "out")
+    assert_close(to_host(score), ref["score"], "bf16", "score")
+
+
 @pytest.mark.parametrize("B,G,Tq,P", [(2, 3, 300, 0), (1, 1, 37, 120), (3, 2, 1, 64), (1, 4, 5000, 700)])
 def test_importance_mean_metric(B, G, Tq, P):
     """Table 3d's "Mean" metric: the sums divided by the number of queries that see each row."""
