@@ -8,7 +8,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libelastic_cache.so")
-SOURCES = ["ec_api.hip", "decode.hip", "merge.hip", "select.hip", "score_simt.hip", "score_mfma.hip"]
+SOURCES = ["ec_api.hip", "decode.hip", "merge.hip", "select.hip", "score_simt.hip", "score_mfma.hip",
+           "score_f32.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fno-gpu-rdc",

@@ -29,6 +29,8 @@ int select_dispatch(const float* score, int B, int G, int T, int n_anchor, int p
 int score_simt_dispatch(const void* q, const void* k, const void* v, void* out, float* lse,
                         float* head_imp, int B, int H, ScoreGeom geo, const int32_t* seq_len, int D, int dt,
                         float scale, hipStream_t stream);
+int score_f32_dispatch(const void* q, const void* k, const void* v, void* out, float* lse, bool lse_wanted,
+                       float* head_imp, int B, int H, ScoreGeom geo, const int32_t* seq_len, int D, float scale, hipStream_t stream);
 int score_mfma_dispatch(const void* q, const void* k, const void* v, void* out, float* lse,
                         float* head_imp, int B, int H, ScoreGeom geo, const int32_t* seq_len, int D,
                         int dt, float scale, hipStream_t stream);
@@ -96,10 +98,12 @@ int score_pass(const void* q, const void* k, const void* v, void* out, float* ls
     float* head_imp = (G == H) ? score : ws_imp;
 
     int rc;
-    // the matrix-core path moves 16 bytes at a time; rows that do not lie on 16-byte boundaries take the other one
+    // the matrix-core paths move 16 bytes at a time; rows that do not lie on 16-byte boundaries take the vector one
     const bool aligned = (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out) & 15) == 0;
     if (dt == EC_BF16 && aligned)
         rc = ec::score_mfma_dispatch(q, k, v, out, lse_buf, head_imp, B, H, geo, seq_len, D, dt, scale, s);
+    else if (aligned)
+        rc = ec::score_f32_dispatch(q, k, v, out, lse_buf, lse != nullptr, head_imp, B, H, geo, seq_len, D, scale, s);
     else
         rc = ec::score_simt_dispatch(q, k, v, out, lse_buf, head_imp, B, H, geo, seq_len, D, dt, scale, s);
     if (rc != EC_OK) return rc;

@@ -100,23 +100,44 @@ def test_prefill_score_paired_tiles(D, B, H, T):
     np.testing.assert_array_equal(alone, score)  # the same scores when the attention output is not wanted
 
 
-def test_prefill_score_of_rows_off_the_16_byte_grid():
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("B,H,T", [
+    (4, 64, 1), (4, 64, 15), (4, 64, 63),  # one wave per 16 queries, keys shared by nobody: a tile and less
+    (4, 64, 65), (8, 32, 130),             # tiles of 32 keys and of 64 queries with a remainder of one and of two
+    (1, 3, 16), (1, 3, 17), (1, 51, 257),  # four waves share the keys of 16 queries: block and tile edges
+    (1, 32, 200), (2, 13, 257),            # two waves share them: 128 and 130 workgroups' worth of 64 queries
+    (2, 52, 257), (4, 32, 129),            # either side of the widest launch that does
+])
+def test_prefill_score_fp32_launch_shapes(D, B, H, T):
+    cfg = syn.custom("t", H=H, D=D, B=B, T=T, dtype="f32", cid=4700 + T + H)
+    q, k, v = syn.prompt_qkv(cfg)
+    ref = oracle.prefill_score(q, k, v, cfg.scale, 1)
+    out, lse, score = run_gpu_score(q, k, v, "f32", cfg.scale, 1)
+    assert_close(out, ref["out"], "f32", "out")
+    assert_close(lse, ref["lse"], "f32", "lse")
+    assert_close(score, ref["score"], "f32", "score")
+    _, _, alone = run_gpu_score(q, k, v, "f32", cfg.scale, 1, want_out=False, want_lse=False)
+    assert_close(alone, ref["score"], "f32", "score without the other outputs")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_prefill_score_of_rows_off_the_16_byte_grid(dtype):
     """Tensors that start at an odd element of their storage."""
-    cfg = syn.custom("t", H=2, D=64, B=1, T=200, dtype="bf16", cid=4900)
+    cfg = syn.custom("t", H=2, D=64, B=1, T=200, dtype=dtype, cid=4900)
     q, k, v = syn.prompt_qkv(cfg)
     ref = oracle.prefill_score(q, k, v, cfg.scale, 2)
     shifted = []
     for x in (q, k, v, np.zeros_like(q)):
-        room = torch.zeros(x.size + 8, dtype=torch.bfloat16, device="cuda")
+        room = torch.zeros(x.size + 8, dtype=torch_dtype(dtype), device="cuda")
         t = room[1:1 + x.size].view(x.shape)
-        t.copy_(to_dev(x, "bf16"))
+        t.copy_(to_dev(x, dtype))
         shifted.append(t)
     dq, dk, dv, out = shifted
     score = torch.zeros((1, 2, 200), dtype=torch.float32, device="cuda")
-    ec.ec_prefill_score(dq, dk, dv, out, None, score, cfg.scale, ec.new_workspace(ec.EC_FN_PREFILL_SCORE, 1, 2, 200, 64, ec.EC_BF16))
+    ec.ec_prefill_score(dq, dk, dv, out, None, score, cfg.scale, ec.new_workspace(ec.EC_FN_PREFILL_SCORE, 1, 2, 200, 64, ec.dtype_code(dq)))
     torch.cuda.synchronize()
-    assert_close(to_host(out), ref["out"], "bf16", "out")
-    assert_close(to_host(score), ref["score"], "bf16", "score")
+    assert_close(to_host(out), ref["out"], dtype, "out")
+    assert_close(to_host(score), ref["score"], dtype, "score")
 
 
 @pytest.mark.parametrize("B,G,Tq,P", [(2, 3, 300, 0), (1, 1, 37, 120), (3, 2, 1, 64), (1, 4, 5000, 700)])
