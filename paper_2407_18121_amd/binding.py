@@ -115,21 +115,21 @@ def _ptr(t, name="tensor"):
 
 def _chk(t, name, dtype, shape, optional=False):
     """Pointer of a tensor after checking what the C ABI cannot: element type, shape, device, layout.
-    A wrong type or shape would make a kernel read or write out of bounds."""
+    A wrong type or shape would make a kernel read or write out of bounds.  A tensor that is only in the wrong place
+    or layout is handed on as _Checked: _call complains about it once every other argument has been looked at."""
     if t is None:
         if optional:
             return None
         raise ValueError(f"{name} is required")
     if t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
-    return _Checked(t, name)
+    return t.data_ptr() if t.is_cuda and t.is_contiguous() else _Checked(t, name)
 
 
 class _Checked:
-    """A tensor whose type and shape fit; its device and layout are checked when the pointer is taken, after
-    every argument of the call has passed the type and shape checks."""
+    """A tensor whose type and shape fit but not its device or layout."""
     __slots__ = ("t", "name")
 
     def __init__(self, t, name):
@@ -137,17 +137,21 @@ class _Checked:
 
 
 def _call(fn, *args):
-    """Call a library function; _Checked arguments become device pointers here, and the stream (passed as the
-    function that looks it up) is resolved last, once every tensor has been found in device memory."""
-    ptrs = [_ptr(a.t, a.name) if isinstance(a, _Checked) else a for a in args]
-    return fn(*[a() if callable(a) else a for a in ptrs])
+    """Call a library function.  ctypes turns down a _Checked argument (and a stream that could not be looked up)
+    before anything is called; the error is then the tensor's, and only after that the stream's.  The usual call
+    costs no pass over its arguments: a generated token of a 32-layer model makes 32 of them."""
+    try:
+        return fn(*args)
+    except ctypes.ArgumentError:
+        ptrs = [_ptr(a.t, a.name) if isinstance(a, _Checked) else a for a in args]
+        return fn(*[a() if callable(a) else a for a in ptrs])
 
 
 def _ws(ws):
     """(pointer, bytes) of an optional workspace tensor."""
     if ws is None:
         return None, 0
-    return _Checked(ws, "ws"), ws.numel() * ws.element_size()
+    return (ws.data_ptr() if ws.is_cuda and ws.is_contiguous() else _Checked(ws, "ws")), ws.nbytes
 
 
 def _groups(G, H, what):
@@ -156,8 +160,20 @@ def _groups(G, H, what):
     return G
 
 
-def _stream():
+def _late_stream():
     return torch.cuda.current_stream().cuda_stream
+
+
+# the current stream's handle without a Stream object around it, where this torch offers that
+_raw_stream, _device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+
+
+def _stream():
+    """Handle of the current stream; without a device, the function that says so (see _call)."""
+    try:
+        return _raw_stream(_device())
+    except Exception:
+        return _late_stream
 
 
 def ec_workspace_bytes(fn: int, B: int, H: int, T: int, D: int, dt: int) -> int:
@@ -183,7 +199,7 @@ def ec_prefill_score(q, k, v, out, lse, score, scale: float, ws, check=True) -> 
     rc = _call(load().ec_prefill_score, _chk(q, "q", dt, (B, H, T, D)), _chk(k, "k", dt, (B, H, T, D)),
                                  _chk(v, "v", dt, (B, H, T, D)), _chk(out, "out", dt, (B, H, T, D), True),
                                  _chk(lse, "lse", f32, (B, H, T), True), _chk(score, "score", f32, (B, G, T)),
-                                 B, H, G, T, D, dtype_code(q), scale, wp, wb, _stream)
+                                 B, H, G, T, D, dtype_code(q), scale, wp, wb, _stream())
     if check and rc != EC_OK:
         raise EcError("ec_prefill_score", rc)
     return rc
@@ -202,7 +218,7 @@ def ec_chunk_score(q, k, v, P: int, out, lse, score, scale: float, ws, check=Tru
                                _chk(v, "v", dt, (B, H, kv_rows, D)), _chk(out, "out", dt, (B, H, T_new, D), True),
                                _chk(lse, "lse", f32, (B, H, T_new), True),
                                _chk(score, "score", f32, (B, G, P + T_new)), B, H, G, T_new, P, kv_rows, D,
-                               dtype_code(q), scale, wp, wb, _stream)
+                               dtype_code(q), scale, wp, wb, _stream())
     if check and rc != EC_OK:
         raise EcError("ec_chunk_score", rc)
     return rc
@@ -215,7 +231,7 @@ def ec_select_anchors(score, n_anchor: int, protect_first: int, protect_last: in
     B, G, T = score.shape
     rc = _call(load().ec_select_anchors, _chk(score, "score", torch.float32, (B, G, T)), B, G, T, n_anchor, protect_first,
                                   protect_last, _chk(anchor_idx, "anchor_idx", torch.int32, (B, G, n_anchor)), None, 0,
-                                  _stream)
+                                  _stream())
     if check and rc != EC_OK:
         raise EcError("ec_select_anchors", rc)
     return rc
@@ -236,7 +252,7 @@ def ec_merge_compact(k, v, anchor_idx, k_cache, v_cache, counts=None, assign=Non
                                  _chk(v_cache, "v_cache", dt, (B, H, cap, D)), cap,
                                  _chk(counts, "counts", i32, (B, G, n_anchor), True),
                                  _chk(assign, "assign", i32, (B, G, T), True), _chk(pos, "pos", i32, (B, G, cap), True),
-                                 _stream)
+                                 _stream())
     if check and rc != EC_OK:
         raise EcError("ec_merge_compact", rc)
     return rc
@@ -259,7 +275,7 @@ def ec_remerge_compact(k, v, L: int, anchor_idx, k_cache, v_cache, weights=None,
                                    _chk(v_cache, "v_cache", dt, (B, H, cap, D)), cap,
                                    _chk(counts, "counts", i32, (B, G, n_anchor), True),
                                    _chk(assign, "assign", i32, (B, G, L), True),
-                                   _chk(pos, "pos", i32, (B, G, cap), True), _stream)
+                                   _chk(pos, "pos", i32, (B, G, cap), True), _stream())
     if check and rc != EC_OK:
         raise EcError("ec_remerge_compact", rc)
     return rc
@@ -296,7 +312,7 @@ def ec_decode_step(q, k_new, v_new, k_cache, v_cache, pos, cache_len: int, evict
     ptrs, po, (B, H, G, D, cap) = _decode_args(q, k_new, v_new, k_cache, v_cache, pos, out, G, "ec_decode_step")
     wp, wb = _ws(ws)
     rc = _call(load().ec_decode_step, *ptrs, B, H, G, D, cap, cache_len, evict_idx, new_pos, scale, dtype_code(k_cache), po,
-                               wp, wb, _stream)
+                               wp, wb, _stream())
     if check and rc != EC_OK:
         raise EcError("ec_decode_step", rc)
     return rc
@@ -309,7 +325,7 @@ def ec_decode_step_shaped(q, k_new, v_new, k_cache, v_cache, pos, cache_len: int
     ptrs, po, (B, H, G, D, cap) = _decode_args(q, k_new, v_new, k_cache, v_cache, pos, out, G, "ec_decode_step_shaped")
     wp, wb = _ws(ws)
     rc = _call(load().ec_decode_step_shaped, *ptrs, B, H, G, D, cap, cache_len, evict_idx, new_pos, scale,
-                                      dtype_code(k_cache), po, wp, wb, waves, unroll, splits, _stream)
+                                      dtype_code(k_cache), po, wp, wb, waves, unroll, splits, _stream())
     if check and rc != EC_OK:
         raise EcError("ec_decode_step_shaped", rc)
     return rc
@@ -324,7 +340,7 @@ def ec_decode_score_step(q, k_new, v_new, k_cache, v_cache, pos, freq, cache_len
                                                "ec_decode_score_step")
     wp, wb = _ws(ws)
     rc = _call(load().ec_decode_score_step, *ptrs, _chk(freq, "freq", torch.float32, (B, G, cap)), B, H, G, D, cap, cache_len,
-                                     new_pos, scale, dtype_code(k_cache), po, wp, wb, _stream)
+                                     new_pos, scale, dtype_code(k_cache), po, wp, wb, _stream())
     if check and rc != EC_OK:
         raise EcError("ec_decode_score_step", rc)
     return rc
@@ -338,7 +354,7 @@ def ec_decode_score_step_static(q, k_new, v_new, k_cache, v_cache, pos, freq, ca
     ptrs, po, (B, H, G, D, cap) = _decode_args(q, k_new, v_new, k_cache, v_cache, pos, out, freq.shape[1],
                                                "ec_decode_score_step_static")
     rc = _call(load().ec_decode_score_step_static, *ptrs, _chk(freq, "freq", torch.float32, (B, G, cap)), B, H, G, D,
-               cap, cache_len, new_pos, scale, dtype_code(k_cache), po, _stream)
+               cap, cache_len, new_pos, scale, dtype_code(k_cache), po, _stream())
     if check and rc != EC_OK:
         raise EcError("ec_decode_score_step_static", rc)
     return rc
@@ -355,7 +371,7 @@ def ec_evict_min(k_cache, v_cache, pos, freq, length: int, protect_first: int, p
     rc = _call(load().ec_evict_min, _chk(k_cache, "k_cache", dt, (B, H, cap, D)), _chk(v_cache, "v_cache", dt, (B, H, cap, D)),
                              _chk(pos, "pos", torch.int32, (B, G, cap), True),
                              _chk(freq, "freq", torch.float32, (B, G, cap)), B, H, G, D, cap, length, protect_first,
-                             protect_recent, dtype_code(k_cache), _chk(victim, "victim", torch.int32, (B, G)), _stream)
+                             protect_recent, dtype_code(k_cache), _chk(victim, "victim", torch.int32, (B, G)), _stream())
     if check and rc != EC_OK:
         raise EcError("ec_evict_min", rc)
     return rc
@@ -368,7 +384,7 @@ def _i32(t, name, n, optional=False):
         raise ValueError(f"{name} is required")
     if t.dtype != torch.int32 or t.numel() != n:
         raise ValueError(f"{name} must be an int32 tensor of {n} entries")
-    return _Checked(t, name)
+    return t.data_ptr() if t.is_cuda and t.is_contiguous() else _Checked(t, name)
 
 
 def ec_prefill_score_varlen(q, k, v, out, lse, score, seq_len, scale: float, ws, check=True) -> int:
@@ -383,7 +399,7 @@ def ec_prefill_score_varlen(q, k, v, out, lse, score, seq_len, scale: float, ws,
                                         _chk(v, "v", dt, (B, H, T, D)), _chk(out, "out", dt, (B, H, T, D), True),
                                         _chk(lse, "lse", f32, (B, H, T), True), _chk(score, "score", f32, (B, G, T)),
                                         _i32(seq_len, "seq_len", B), B, H, G, T, D, dtype_code(q), scale, wp, wb,
-                                        _stream)
+                                        _stream())
     if check and rc != EC_OK:
         raise EcError("ec_prefill_score_varlen", rc)
     return rc
@@ -399,7 +415,7 @@ def ec_select_anchors_varlen(score, seq_len, n_anchor_b, protect_first: int, pro
     rc = _call(load().ec_select_anchors_varlen, _chk(score, "score", torch.float32, (B, G, T)), _i32(seq_len, "seq_len", B),
                                          _i32(n_anchor_b, "n_anchor_b", B), B, G, T, n_max, protect_first,
                                          protect_last, _chk(anchor_idx, "anchor_idx", torch.int32, (B, G, n_max)),
-                                         None, 0, _stream)
+                                         None, 0, _stream())
     if check and rc != EC_OK:
         raise EcError("ec_select_anchors_varlen", rc)
     return rc
@@ -421,7 +437,7 @@ def ec_merge_compact_varlen(k, v, anchor_idx, seq_len, n_anchor_b, k_cache, v_ca
                                         _chk(v_cache, "v_cache", dt, (B, H, cap, D)), cap,
                                         _chk(counts, "counts", i32, (B, G, n_max), True),
                                         _chk(assign, "assign", i32, (B, G, T), True),
-                                        _chk(pos, "pos", i32, (B, G, cap), True), _stream)
+                                        _chk(pos, "pos", i32, (B, G, cap), True), _stream())
     if check and rc != EC_OK:
         raise EcError("ec_merge_compact_varlen", rc)
     return rc
@@ -434,7 +450,7 @@ def ec_decode_step_varlen(q, k_new, v_new, k_cache, v_cache, pos, cache_len_b, e
     wp, wb = _ws(ws)
     rc = _call(load().ec_decode_step_varlen, *ptrs, _i32(cache_len_b, "cache_len_b", B),
                                       _i32(evict_idx_b, "evict_idx_b", B, True), _i32(new_pos_b, "new_pos_b", B, True),
-                                      B, H, G, D, cap, scale, dtype_code(k_cache), po, wp, wb, _stream)
+                                      B, H, G, D, cap, scale, dtype_code(k_cache), po, wp, wb, _stream())
     if check and rc != EC_OK:
         raise EcError("ec_decode_step_varlen", rc)
     return rc
@@ -446,7 +462,7 @@ def ec_importance_mean(score, T_new: int, P: int = 0, check=True) -> int:
     if score.dim() != 3:
         raise ValueError("ec_importance_mean: score must be [B,G,P+T_new]")
     B, G, L = score.shape
-    rc = _call(load().ec_importance_mean, _chk(score, "score", torch.float32, (B, G, P + T_new)), B, G, T_new, P, _stream)
+    rc = _call(load().ec_importance_mean, _chk(score, "score", torch.float32, (B, G, P + T_new)), B, G, T_new, P, _stream())
     if check and rc != EC_OK:
         raise EcError("ec_importance_mean", rc)
     return rc
@@ -461,7 +477,7 @@ def ec_retention_step_varlen(n_seen_b, cache_len_b, evict_idx_b, new_pos_b, pend
     rc = _call(load().ec_retention_step_varlen, _i32(n_seen_b, "n_seen_b", B), _i32(cache_len_b, "cache_len_b", B),
                                          _i32(evict_idx_b, "evict_idx_b", B), _i32(new_pos_b, "new_pos_b", B),
                                          _i32(pending_b, "pending_b", B), B, gamma_num, gamma_den, budget_mode, fixed_len,
-                                         trunc_mode, recent, n_tl, protect_first, 1 if flush_only else 0, _stream)
+                                         trunc_mode, recent, n_tl, protect_first, 1 if flush_only else 0, _stream())
     if check and rc != EC_OK:
         raise EcError("ec_retention_step_varlen", rc)
     return rc
