@@ -686,115 +686,94 @@ int decode_score_dispatch(const void* q, const void* k_new, const void* v_new, v
     return EC_EUNSUPPORTED;
 }
 
-// Least-mass row of one score group: lowest index among equal fp32 values, rows [lo, hi] only.
-__device__ __forceinline__ int argmin_row(const float* __restrict__ f, int lo, int hi, int tid, int threads,
-                                          float* sh_v, int* sh_i)
+// ec_evict_min in two launches: one workgroup per score group finds the least-mass row and closes the gap in the group's
+// masses and positions, then two workgroups per (batch, head), one for K and one for V, move the rows behind it up by
+// one.  The first launch is a chain of latencies (load, reduction, load, store), the second moves 2 * row bytes * rows
+// behind the victim, half the cache for a victim anywhere.  Everything that moves is held in registers between one
+// barrier's two sides as far as the unroll reaches (512 rows of 256 bytes), so the usual case is one round of loads.
+// Measured at B8 H32 D128, 641 rows, bf16 (rows + bookkeeping): victims anywhere 59 + 4.8 us when every (batch, head)
+// looked for the victim itself and moved 64 rows a round, 40 + 5.2 us now; victims
+// 26 rows from the end 20 + 4.8 and 4.7 + 3.9 us.
+constexpr int kEvictMetaThreads = 1024;
+constexpr int kEvictMetaUnroll = 4;
+__global__ __launch_bounds__(kEvictMetaThreads) void evict_min_meta_kernel(float* freq, int32_t* pos,
+                                                                          int32_t* __restrict__ victim, int cap, int len,
+                                                                          int lo, int hi)
 {
-    float bv = INFINITY;
-    int bi = 0x7fffffff;
-    for (int j = lo + tid; j <= hi; j += threads) {  // ascending per thread: strict < keeps the first
-        const float v = f[j];
-        if (v < bv || bi == 0x7fffffff) {
-            bv = v;
-            bi = j;
-        }
+    constexpr int WAVES = kEvictMetaThreads / kWave;
+    __shared__ unsigned long long sh_best[WAVES];
+    const int bg = blockIdx.x, tid = threadIdx.x;
+    float* f = freq + (size_t)bg * cap;
+    int32_t* p = pos ? pos + (size_t)bg * cap : nullptr;
+    // (mass, index) as one integer whose order is the fp32 order, -0 equal to +0, the lower index first
+    unsigned long long best = ~0ull;
+    for (int j = lo + tid; j <= hi; j += kEvictMetaThreads) {
+        uint32_t u = __float_as_uint(f[j]);
+        if (u == 0x80000000u) u = 0u;
+        u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+        best = min(best, ((unsigned long long)u << 32) | (uint32_t)j);
     }
 #pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const float ov = __shfl_xor(bv, off, kWave);
-        const int oi = __shfl_xor(bi, off, kWave);
-        if (oi != 0x7fffffff && (bi == 0x7fffffff || ov < bv || (ov == bv && oi < bi))) {
-            bv = ov;
-            bi = oi;
-        }
-    }
-    const int wave = tid / kWave, lane = tid % kWave;
-    if (lane == 0) {
-        sh_v[wave] = bv;
-        sh_i[wave] = bi;
-    }
+    for (int off = 1; off < kWave; off <<= 1) best = min(best, __shfl_xor(best, off, kWave));
+    if (tid % kWave == 0) sh_best[tid / kWave] = best;
     __syncthreads();
-    bv = sh_v[0];
-    bi = sh_i[0];
-    for (int w = 1; w < threads / kWave; ++w) {
-        const float ov = sh_v[w];
-        const int oi = sh_i[w];
-        if (oi != 0x7fffffff && (bi == 0x7fffffff || ov < bv || (ov == bv && oi < bi))) {
-            bv = ov;
-            bi = oi;
+    best = sh_best[tid % WAVES];
+#pragma unroll
+    for (int off = 1; off < WAVES; off <<= 1) best = min(best, __shfl_xor(best, off, kWave));
+    const int vic = (int)(uint32_t)best;
+    if (tid == 0) victim[bg] = vic;
+
+    const int total = len - 1 - vic;
+    for (int c0 = 0; c0 < total; c0 += kEvictMetaThreads * kEvictMetaUnroll) {
+        float fv[kEvictMetaUnroll];
+        int32_t pv[kEvictMetaUnroll];
+#pragma unroll
+        for (int u = 0; u < kEvictMetaUnroll; ++u) {
+            const int c = c0 + u * kEvictMetaThreads + tid;
+            if (c < total) {
+                fv[u] = f[vic + 1 + c];
+                pv[u] = p ? p[vic + 1 + c] : 0;
+            }
         }
+        __syncthreads();  // read completely before any of it is overwritten
+#pragma unroll
+        for (int u = 0; u < kEvictMetaUnroll; ++u) {
+            const int c = c0 + u * kEvictMetaThreads + tid;
+            if (c < total) {
+                f[vic + c] = fv[u];
+                if (p) p[vic + c] = pv[u];
+            }
+        }
+        __syncthreads();  // and written before the next slab, which overlaps it by one element, is read
     }
-    return bi;
 }
 
-constexpr int kEvictThreads = 256;
-constexpr int kEvictUnroll = 4;
-
-// Every (b,h) workgroup finds its group's victim itself (freq is only read here) and moves its own K and V
-// rows up by one; the group's first head also publishes the index.
+constexpr int kEvictThreads = 512;
+constexpr int kEvictUnroll = 16;
 __global__ __launch_bounds__(kEvictThreads) void evict_min_rows_kernel(uint4* k_cache, uint4* v_cache,
-                                                                       const float* __restrict__ freq,
-                                                                       int32_t* __restrict__ victim, int H, int G,
-                                                                       int cap, int len, int lo, int hi, int lpr)
+                                                                       const int32_t* __restrict__ victim, int H, int G,
+                                                                       int cap, int len, int lpr)
 {
-    __shared__ float sh_v[kEvictThreads / kWave];
-    __shared__ int sh_i[kEvictThreads / kWave];
     const int bh = blockIdx.x, tid = threadIdx.x;
     const int b = bh / H, h = bh % H;
-    const size_t bg = (size_t)b * G + (G == 1 ? 0 : h);
-    const int vic = argmin_row(freq + bg * cap, lo, hi, tid, kEvictThreads, sh_v, sh_i);
-    if (tid == 0 && (G == H || h == 0)) victim[bg] = vic;
-
-    uint4* kc = k_cache + (size_t)bh * cap * lpr;
-    uint4* vc = v_cache + (size_t)bh * cap * lpr;
+    const int vic = victim[(size_t)b * G + (G == 1 ? 0 : h)];
+    uint4* dst = (blockIdx.y == 0 ? k_cache : v_cache) + ((size_t)bh * cap + vic) * lpr;
+    const uint4* src = dst + lpr;
     const int total = (len - 1 - vic) * lpr;  // 16-byte chunks that move, in ascending address order
     for (int c0 = 0; c0 < total; c0 += kEvictThreads * kEvictUnroll) {
-        uint4 kk[kEvictUnroll], vv[kEvictUnroll];
+        uint4 x[kEvictUnroll];
 #pragma unroll
         for (int u = 0; u < kEvictUnroll; ++u) {
             const int c = c0 + u * kEvictThreads + tid;
-            if (c < total) {
-                kk[u] = kc[(size_t)(vic + 1) * lpr + c];
-                vv[u] = vc[(size_t)(vic + 1) * lpr + c];
-            }
+            if (c < total) x[u] = src[c];
         }
         __syncthreads();  // the slab is read completely before any of it is overwritten
 #pragma unroll
         for (int u = 0; u < kEvictUnroll; ++u) {
             const int c = c0 + u * kEvictThreads + tid;
-            if (c < total) {
-                kc[(size_t)vic * lpr + c] = kk[u];
-                vc[(size_t)vic * lpr + c] = vv[u];
-            }
+            if (c < total) dst[c] = x[u];
         }
         __syncthreads();  // and written before the next slab, which overlaps it by one row, is read
-    }
-}
-
-// The group's positions and masses follow their rows.
-__global__ __launch_bounds__(kEvictThreads) void evict_min_meta_kernel(float* freq, int32_t* pos,
-                                                                       const int32_t* __restrict__ victim, int cap,
-                                                                       int len)
-{
-    const int bg = blockIdx.x, tid = threadIdx.x;
-    const int vic = victim[bg];
-    float* f = freq + (size_t)bg * cap;
-    int32_t* p = pos ? pos + (size_t)bg * cap : nullptr;
-    const int total = len - 1 - vic;
-    for (int c0 = 0; c0 < total; c0 += kEvictThreads) {
-        const int c = c0 + tid;
-        float fv = 0.f;
-        int32_t pv = 0;
-        if (c < total) {
-            fv = f[vic + 1 + c];
-            if (p) pv = p[vic + 1 + c];
-        }
-        __syncthreads();
-        if (c < total) {
-            f[vic + c] = fv;
-            if (p) p[vic + c] = pv;
-        }
-        __syncthreads();
     }
 }
 
@@ -802,11 +781,12 @@ int evict_min_dispatch(void* k_cache, void* v_cache, int32_t* pos, float* freq, 
                        int len, int protect_first, int protect_recent, int dt, int32_t* victim, hipStream_t stream)
 {
     const int lpr = D * (dt == EC_F32 ? 4 : 2) / 16;
-    hipLaunchKernelGGL(evict_min_rows_kernel, dim3(B * H), dim3(kEvictThreads), 0, stream, (uint4*)k_cache,
-                       (uint4*)v_cache, freq, victim, H, G, cap, len, protect_first, len - 1 - protect_recent, lpr);
+    hipLaunchKernelGGL(evict_min_meta_kernel, dim3(B * G), dim3(kEvictMetaThreads), 0, stream, freq, pos, victim, cap, len,
+                       protect_first, len - 1 - protect_recent);
     int rc = status_from_hip(hipGetLastError());
     if (rc != EC_OK) return rc;
-    hipLaunchKernelGGL(evict_min_meta_kernel, dim3(B * G), dim3(kEvictThreads), 0, stream, freq, pos, victim, cap, len);
+    hipLaunchKernelGGL(evict_min_rows_kernel, dim3(B * H, 2), dim3(kEvictThreads), 0, stream, (uint4*)k_cache,
+                       (uint4*)v_cache, victim, H, G, cap, len, lpr);
     return status_from_hip(hipGetLastError());
 }
 

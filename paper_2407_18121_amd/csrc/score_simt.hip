@@ -11,6 +11,8 @@
 //                      key column.  One workgroup owns a column, so there are no
 //                      atomics and the result is deterministic.
 // Then the head mean for the layer-wise score (G == 1).
+#include <type_traits>
+
 #include "ec_common.h"
 
 namespace ec {
@@ -244,16 +246,21 @@ __global__ __launch_bounds__(64) void head_mean_kernel(const float* __restrict__
     const int b = blockIdx.y;
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= T) return;
-    // loads are issued 8 at a time; the additions keep ascending head order
+    // A chain of load latencies: loads are issued 32 at a time, then 8 (B1 H32 T1024: 3.8 us with 8 at a time, 3.4 us); the
+    // additions keep ascending head order.
     float acc = 0.f;
     int h = 0;
-    for (; h + 8 <= H; h += 8) {
-        float x[8];
+    auto batch = [&](auto n_loads) __attribute__((always_inline)) {
+        constexpr int N = decltype(n_loads)::value;
+        float x[N];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = head_imp[((size_t)b * H + h + j) * T + n];
+        for (int j = 0; j < N; ++j) x[j] = head_imp[((size_t)b * H + h + j) * T + n];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc += x[j];
-    }
+        for (int j = 0; j < N; ++j) acc += x[j];
+        h += N;
+    };
+    while (h + 32 <= H) batch(std::integral_constant<int, 32>{});
+    while (h + 8 <= H) batch(std::integral_constant<int, 8>{});
     for (; h < H; ++h) acc += head_imp[((size_t)b * H + h) * T + n];
     score[(size_t)b * T + n] = acc / (float)H;
 }

@@ -93,6 +93,24 @@ def test_evict_min_bit_exact(dtype, D, B, H, Gmode, cap, length, pf, pr):
     np.testing.assert_array_equal(dfreq.cpu().numpy()[:, :, length:], freq[:, :, length:])
 
 
+@pytest.mark.parametrize("length", [64, 1025, 1026])      # one wave's worth of masses; either side of one workgroup's
+def test_evict_min_of_infinite_masses(length):
+    """Masses of +inf are ordinary values: the first candidate among equals, and finite ones before them."""
+    kc = torch.arange(length, dtype=torch.float32, device="cuda")[None, None, :, None].expand(1, 1, length, 64).contiguous()
+    for finite_at, expect in ((None, 3), (length - 2, length - 2)):
+        dkc, dvc = kc.clone(), -kc
+        freq = torch.full((1, 1, length), float("inf"), device="cuda")
+        if finite_at is not None:
+            freq[0, 0, finite_at] = 3e38
+        victim = torch.full((1, 1), -1, dtype=torch.int32, device="cuda")
+        ec.ec_evict_min(dkc, dvc, None, freq, length, 3, 1, victim)
+        torch.cuda.synchronize()
+        assert victim.item() == expect
+        left = torch.cat([kc[0, 0, :expect], kc[0, 0, expect + 1:]])
+        assert torch.equal(dkc[0, 0, :length - 1], left) and torch.equal(dvc[0, 0, :length - 1], -left)
+        assert torch.isinf(freq[0, 0, :length - 1]).all()
+
+
 def test_frequency_generation_against_the_oracle():
     """Forty generated tokens under the frequency policy at a fixed budget.  Each step the oracle's own
     counts (rounded to fp32) are what both sides choose the victim from."""
