@@ -15,12 +15,21 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 // head count that eight does not divide is cut into equal contiguous ranges of items.
 constexpr int kXcds = 8;
 inline int xcd_grid(int total) { return (total + kXcds - 1) / kXcds * kXcds; }
-__device__ __forceinline__ int xcd_item(int linear_id, int per_head, int n_heads)
+struct XcdItem {
+    int bh, tile;  // bh < 0: nothing to do
+};
+__device__ __forceinline__ XcdItem xcd_item(int linear_id, int per_head, int n_heads)
 {
     const int xcd = linear_id % kXcds, nth = linear_id / kXcds;
-    if (n_heads % kXcds == 0) return (nth / per_head * kXcds + xcd) * per_head + nth % per_head;
+    if (n_heads % kXcds == 0) {
+        const int head = nth / per_head;
+        return {head * kXcds + xcd, nth - head * per_head};
+    }
     const int total = per_head * n_heads, per_xcd = (total + kXcds - 1) / kXcds;
-    return nth < per_xcd ? xcd * per_xcd + nth : total;  // may be >= total: caller exits
+    const int item = xcd * per_xcd + nth;
+    if (nth >= per_xcd || item >= total) return {-1, 0};
+    const int bh = item / per_head;
+    return {bh, item - bh * per_head};
 }
 
 // Buffer descriptor over `bytes` bytes at p (raw: no stride, 32-bit data format).  Loads through it whose byte
