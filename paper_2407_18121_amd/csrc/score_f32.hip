@@ -10,8 +10,9 @@
 //                  no atomics, deterministic.
 // Bound: the matrix pipe at its fp32 rate (a sixteenth of the bf16 one; 149 TFLOP/s in a large product here); a block costs
 // 64 instructions of 32 clocks (D = 128) against some 30 vector instructions, so the phases simply follow each other and
-// the other wave of the SIMD fills the gaps.  Measured, before (vector ALU) -> after: B1 H32 T1024 D128 498 + 221 -> 112 + 53 us
-// (79 TFLOP/s over both passes; a workgroup loops over up to 32 tiles while the mean is 16), B1 H4 T256 D64 61 + 22 -> 7.7 + 4.3 us.
+// the other wave of the SIMD fills the gaps.  Measured, before (vector ALU) -> after: B1 H32 T1024 D128 498 + 221 -> 102 + 52 us
+// (84 TFLOP/s over both passes; a workgroup loops over up to 32 tiles while the mean is 16; 109 + 52 us with the waits for
+// the operands inside the loop), B1 H4 T256 D64 61 + 22 -> 7.7 + 4.3 us.
 // Error of out against 64 bits at T1024 6.3e-7 -> 2.8e-7, of the scores 1.3e-7 -> 0.7e-7.  Operands are read from LDS 16 bytes at a time, each read feeding four
 // instructions: both operands of a contraction enumerate it in the same permuted order.
 //
@@ -136,6 +137,11 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
     // keeps exp2(-inf - m) at zero there
     float m_run = KS == 1 ? -INFINITY : -1e30f, l_run = 0.f;  // l_run: this lane's share of the row sum
 
+    // The compiler learns here that the operand has arrived: the waits it would otherwise put before its uses inside the loop
+    // would be waits for the tile in flight.
+    wait_loads();
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(qf[kb]));
     for (int t = 0; t < n_tiles; ++t) {
         wait_loads();
         wait_lds();
@@ -307,6 +313,9 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void colsum_f32_kernel(
         for (int kb = 0; kb < KB; ++kb) kf[kb] = *reinterpret_cast<const f32x4*>(krow + kb * 16 + h * 4);
     }
     f32x4 col = f32x4{0.f, 0.f, 0.f, 0.f};  // keys nw + 4 h + r
+    wait_loads();  // as in the forward pass: no wait for the operand inside the loop
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(kf[kb]));
     for (int t = 0; t < n_tiles; ++t) {
         const int m0 = m_begin + t * TQ + qg * 16;  // the wave's blocks start 16 QG queries apart
         wait_loads();

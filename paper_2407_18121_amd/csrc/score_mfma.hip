@@ -456,7 +456,9 @@ __global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
 // scale-and-shift, 16 exponential (two issue slots each) and 16 add instructions (256 clocks): the exponentials of a
 // step are issued between the matrix instructions of the next one (its score block stays pending for one step).  Q
 // fragments are reloaded for the next step right after their last use, so no LDS latency is exposed.  Measured at
-// B16 H32 T8192 D128: 4.4 ms before (compiler's order, a lane per key), 4.35 ms in this order, 3.9 ms with PAIR.
+// B16 H32 T8192 D128: 4.4 ms before (compiler's order, a lane per key), 4.35 ms in this order, 4.1 ms with PAIR, 3.9 ms
+// without waits for memory inside the loop and with the second key tile's start under the end of the first; B8 T2048:
+// 200 -> 186 -> 160 us.
 // PAIR: the workgroup takes key tiles i and n - 1 - i of its head, one after the other.
 // QG = 2 (launches of one workgroup per compute unit or less): twice the waves on the same keys.
 template <int D, int NB, int KW, int QG, int QT, bool PAIR>
@@ -492,36 +494,57 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
     const u32x4 q_rsrc = tile_rsrc(qh, Tq * D * 2);
     const u32x4 l_rsrc = tile_rsrc(lse + (size_t)bh * geo.q_rows, Tq * 4);
 
+    // Single key tiles take their query tiles from the first one with a query that sees key n0 (m sees n <= P + m) upwards;
+    // pairs from the sequence's last one down, so that all workgroups of a head start at the same queries and the first
+    // two query tiles of the second key tile can travel before it begins.
+    const int m_last = (Tq - 1) / QT * QT;
+    auto first_seen = [&](int tile) __attribute__((always_inline)) { return max(tile * BN - P, 0) / QT * QT; };
+    constexpr int DIR = PAIR ? -1 : 1;
+    using Mover = TileToLds<D, QT, WAVES, SwizzleRows<D>>;
+    const uint32_t qs_at = lds_address(qs), ls_at = lds_address(ls);
+    auto fetch_lse = [&](int buf, int m) __attribute__((always_inline)) {
+        if (wave < QT / kWave)
+            load_lds_4(l_rsrc, ls_at + (buf * QT + wave * kWave) * 4, (m + wave * kWave + anew(lane)) * 4);
+    };
+    {
+        const Mover mover(q_rsrc, wave, anew(lane));
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int m = PAIR ? max(m_last - t * QT, 0) : first_seen(ktile) + t * QT;
+#pragma unroll
+            for (int j = 0; j < Mover::NI; ++j) mover.issue(qs_at + t * QT * D * 2, m, j);
+            fetch_lse(t, m);
+        }
+    }
+    bf16x8 kf[NB][KB];
+    auto load_keys = [&](int tile) __attribute__((always_inline)) {
+        const int lk = anew(lane);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int n = min(tile * BN + kw * KEYS_W + nb * 32 + lk % 32, L - 1);  // sums of keys beyond L are not stored
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+                kf[nb][kb] = *reinterpret_cast<const bf16x8*>(kh + (size_t)n * D + kb * 16 + lk / 32 * 8);
+        }
+    };
+    load_keys(ktile);
+
     for (;;) {  // one key tile after the other
         const int n0 = ktile * BN;
         const int nw = n0 + kw * KEYS_W;  // first key of this wave
-        const int m_begin = (max(n0 - P, 0) / QT) * QT;  // first tile with a query that sees key n0 (m sees n <= P + m)
-        const int n_tiles = (Tq - m_begin + QT - 1) / QT;
-        using Mover = TileToLds<D, QT, WAVES, SwizzleRows<D>>;
-        const Mover mover(q_rsrc, wave, lane);
-        const uint32_t qs_at = lds_address(qs), ls_at = lds_address(ls);
-        auto fetch_lse = [&](int buf, int t) __attribute__((always_inline)) {
-            if (wave < QT / kWave)
-                load_lds_4(l_rsrc, ls_at + (buf * QT + wave * kWave) * 4, (m_begin + t * QT + wave * kWave + lane) * 4);
+        const int m_begin = first_seen(ktile);
+        const int n_tiles = (m_last - m_begin) / QT + 1;
+        const int next_tile = PAIR ? own_tiles - 1 - ktile : ktile;
+        const bool more = PAIR && next_tile > ktile;
+        const int m_first = PAIR ? m_last : m_begin;
+        const Mover mover(q_rsrc, wave, anew(lane));
+        auto fetch = [&](int buf, int m, int j) __attribute__((always_inline)) { mover.issue(qs_at + buf * QT * D * 2, m, j); };
+        // What is fetched as tile t: behind the last tile of a pair's first half the first two of the second half, behind
+        // the very last rows behind the sequence, for which nothing is read.
+        auto first_query = [&](int buf, int t) __attribute__((always_inline)) {
+            if (!PAIR || t < n_tiles) return m_first + DIR * t * QT;
+            return more ? max(m_last - buf * QT, 0) : m_last + QT;
         };
-        auto fetch = [&](int buf, int t, int j) __attribute__((always_inline)) {
-            mover.issue(qs_at + buf * QT * D * 2, m_begin + t * QT, j);
-        };
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-#pragma unroll
-            for (int j = 0; j < Mover::NI; ++j) fetch(t, t, j);
-            fetch_lse(t, t);
-        }
-
-        bf16x8 kf[NB][KB];
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const int n = min(nw + nb * 32 + anew(c32), L - 1);  // sums of keys beyond L are not stored
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-                kf[nb][kb] = *reinterpret_cast<const bf16x8*>(kh + (size_t)n * D + kb * 16 + h * 8);
-        }
 
         // A and B take turns: one is being computed while the other is pending
         f32x16 sA[NB], sB[NB];
@@ -534,10 +557,10 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
             for (int r = 0; r < 16; ++r) sA[nb][r] = sB[nb][r] = col[nb][r] = 0.f;
 
         // this lane's address inside a step: row c32, chunk 2 kb + h, swizzled
-        const int swz = SwizzleRows<D>::at(c32);
+        const int lq = anew(lane), swz = SwizzleRows<D>::at(lq % 32);
         uint32_t q_at[KB];
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) q_at[kb] = one_register(qs_at + (qg * 32 + c32) * (D * 2) + ((2 * kb + h) ^ swz) * 16);
+        for (int kb = 0; kb < KB; ++kb) q_at[kb] = one_register(qs_at + (qg * 32 + lq % 32) * (D * 2) + ((2 * kb + lq / 32) ^ swz) * 16);
         auto frag = [&](int u, int kb) __attribute__((always_inline)) {  // u: step of 32 queries inside the two tiles
             return *(lds_bf16x8*)(uintptr_t)(q_at[kb] + u * 32 * D * 2);
         };
@@ -608,11 +631,11 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
         static_assert(SPT % 2 == 0, "A and B alternate through a tile");
         constexpr auto nothing = [](int) {};
         auto tile = [&](int buf, int t) __attribute__((always_inline)) {
-            const int m0 = m_begin + t * QT + qg * 32;
+            const int m0 = m_first + DIR * t * QT + qg * 32, m_refill = first_query(buf, t + 2);
             const int u0 = buf * (QT / 32);  // steps are counted from the wave's first one
 #pragma unroll
             for (int i = 0; i < SPT; ++i) {
-                const int u = u0 + i * QG, mq = m0 + i * QG * 32;
+                const int at = PAIR ? SPT - 1 - i : i, u = u0 + at * QG, mq = m0 + at * QG * 32;
                 const bool last = i == SPT - 1;
                 const bool active = mq >= mq_first && mq < Tq;  // some query of the step sees a key of this wave (wave-uniform)
                 if (active && !loaded) {  // its first step: nothing has been loaded ahead
@@ -623,32 +646,42 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
                 }
                 if (last) {
                     tile_barrier();  // the other tile has landed, and every wave has read this one for the last time
-                    fetch_lse(buf, t + 2);
+                    fetch_lse(buf, m_refill);
                 }
                 if (!active) {
                     if (last) {
 #pragma unroll
-                        for (int j = 0; j < Mover::NI; ++j) fetch(buf, t + 2, j);
+                        for (int j = 0; j < Mover::NI; ++j) fetch(buf, m_refill, j);
                     }
                     continue;
                 }
                 if (i % 2 == 0)
-                    step(sA, lA, mA, mq, sB, lB, mB, u + QG, nothing);
+                    step(sA, lA, mA, mq, sB, lB, mB, u + DIR * QG, nothing);
                 else if (!last)
-                    step(sB, lB, mB, mq, sA, lA, mA, u + QG, nothing);
+                    step(sB, lB, mB, mq, sA, lA, mA, u + DIR * QG, nothing);
                 else  // the tile after the next one takes this one's place, its loads spread over the matrix instructions
-                    step(sB, lB, mB, mq, sA, lA, mA, (buf ^ 1) * (QT / 32), [&](int g) __attribute__((always_inline)) {
+                    step(sB, lB, mB, mq, sA, lA, mA, (buf ^ 1) * (QT / 32) + (PAIR ? (SPT - 1) * QG : 0), [&](int g) __attribute__((always_inline)) {
                         constexpr int EVERY = NB * KB / Mover::NI;
-                        if (g % EVERY == 0) fetch(buf, t + 2, g / EVERY);
+                        if (g % EVERY == 0) fetch(buf, m_refill, g / EVERY);
                     });
             }
         };
         tile_barrier();
+        // The compiler learns here that the keys have arrived: the waits it would otherwise put before their uses inside the
+        // loop would be waits for the tiles in flight (4.13 -> 3.86 ms at T8192, 56 -> 53 us with 32 keys per wave).  The few
+        // steps of a two-group launch are 0.6 us slower without them (B1 T1024 13.5 / 14.1 us).
+        if constexpr (QG == 1) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(kf[nb][kb]));
+        }
         for (int t = 0; t < n_tiles; t += 2) {
             tile(0, t);
             if (t + 1 < n_tiles) tile(1, t + 1);
         }
 
+        if (more) load_keys(next_tile);  // travels while this tile's sums are brought together
         // at most one of the two is still pending
         auto retire = [&](f32x16 (&sp)[NB], float lp, int mp) __attribute__((always_inline)) {
             mask(sp, mp);
@@ -683,8 +716,7 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
             for (int g = 0; g < QG; ++g) sum += red[g * KW + w][2 * hh][slot] + red[g * KW + w][2 * hh + 1][slot];
             head_imp[(size_t)bh * geo.imp_rows + n0 + key] = sum;
         }
-        const int next_tile = PAIR ? own_tiles - 1 - ktile : ktile;
-        if (!PAIR || next_tile <= ktile) return;
+        if (!more) return;
         ktile = next_tile;
         __syncthreads();  // the sums have been read
     }
