@@ -14,7 +14,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fno-gpu-rdc",
     "-Wall", "-Wno-unused-function",
-    # packed fp32 instruction selection is switched off on the test machines
+    # packed fp32 instruction selection is switched off on this hardware
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 
