@@ -389,9 +389,10 @@ static int launch_f32(const float* q, const float* k, const float* v, float* out
             hipLaunchKernelGGL((attn_fwd_f32_kernel<D, QW_, KS_, false>), dim3(f32_grid(QT_, BH)), block, 0, stream,  \
                                q, k, v, out, lse, unit_out, geo, sl, QT_, BH, seq_len, H);                                      \
     } while (0)
-    // us for 64 / 32 / 16 queries per workgroup (one / two / four waves on the keys of 16 queries), H32 D128:
-    //   B1 T256 26.6 / 19.3 / 20.0   B1 T512 50.2 / 36.6 / 51.4   B1 T1024 112 / 116 / 172   B4 T256 33.7 / 37.2 / 68.0
-    //   H16 B1 T1024 94.5 / 65.4 / 85.8   H8 B1 T512 47.5 / - / 21.5
+    // us of the whole call for 64 / 32 / 16 queries per workgroup (one / two / four waves on the keys of 16 queries), H32
+    // D128, the column pass alike:
+    //   B1 T256 39.0 / 32.1 / 32.8   B1 T512 71.0 / 58.6 / 74.7   B1 T1024 153 / 160 / 209   B4 T256 51.0 / 55.2 / 87.7
+    //   B1 T2048 498 / 529 / 730   H16 B1 T1024 123 / 95 / 117   H8 B1 T512 64.2 / 49.5 / 38.4
     const long long wide = (long long)qt64 * BH;
     if (wide >= 512)
         EC_FWD_F32(4, 1, qt64);
@@ -403,7 +404,8 @@ static int launch_f32(const float* q, const float* k, const float* v, float* out
     int rc = status_from_hip(hipGetLastError());
     if (rc != EC_OK) return rc;
     const int kt32 = (geo.L + 31) / 32, kt16 = (geo.L + 15) / 16;
-    // 32 / 16 keys per workgroup: B1 T256 10.0 / 8.0   B1 T512 19.1 / 21.5   B1 T1024 52.6 / 64.8   B4 T256 18.2 / 25.3 (64 keys: 20.1)
+    // us of the whole call for 32 / 16 keys per workgroup, the forward pass alike: B1 T256 39.0 / 37.4   B1 T512 71.0 / 73.1
+    //   B1 T1024 153 / 157   B4 T256 51.0 / 59.0   H8 B1 T512 64.2 / 58.3   (64 keys, column pass alone at T1024: 62 against 53)
     if ((long long)kt32 * BH >= 512)
         hipLaunchKernelGGL((colsum_f32_kernel<D, 2, 2>), dim3(f32_grid(kt32, BH)), block, 0, stream, q, k, lse, unit_in,
                            head_imp, geo, sl, kt32, BH, seq_len, H);
