@@ -5,6 +5,7 @@
 #include <mutex>
 
 #include "ec_common.h"
+#include "score_route.h"
 
 namespace ec {
 int decode_dispatch(const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
@@ -98,14 +99,16 @@ int score_pass(const void* q, const void* k, const void* v, void* out, float* ls
     float* head_imp = (G == H) ? score : ws_imp;
 
     int rc;
-    // the matrix-core paths move 16 bytes at a time; rows that do not lie on 16-byte boundaries take the vector one
-    const bool aligned = (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out) & 15) == 0;
-    if (dt == EC_BF16 && aligned)
-        rc = ec::score_mfma_dispatch(q, k, v, out, lse_buf, head_imp, B, H, geo, seq_len, D, dt, scale, s);
-    else if (aligned)
-        rc = ec::score_f32_dispatch(q, k, v, out, lse_buf, lse != nullptr, head_imp, B, H, geo, seq_len, D, scale, s);
-    else
-        rc = ec::score_simt_dispatch(q, k, v, out, lse_buf, head_imp, B, H, geo, seq_len, D, dt, scale, s);
+    switch (ec::score_route(dt, D, geo.L, q, k, v, out)) {
+        case ec::ScoreRoute::kMfma:
+            rc = ec::score_mfma_dispatch(q, k, v, out, lse_buf, head_imp, B, H, geo, seq_len, D, dt, scale, s);
+            break;
+        case ec::ScoreRoute::kF32:
+            rc = ec::score_f32_dispatch(q, k, v, out, lse_buf, lse != nullptr, head_imp, B, H, geo, seq_len, D, scale, s);
+            break;
+        default:
+            rc = ec::score_simt_dispatch(q, k, v, out, lse_buf, head_imp, B, H, geo, seq_len, D, dt, scale, s);
+    }
     if (rc != EC_OK) return rc;
     if (G == 1) rc = ec::head_mean_launch(head_imp, score, B, H, geo.L, s);
     return rc;

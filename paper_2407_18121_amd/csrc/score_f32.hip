@@ -108,8 +108,8 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
     const int m0 = (n_qtiles - 1 - item.rank) * BM;
     if (m0 >= Tq) return;  // ragged batch: this sequence ends before the tile (whole workgroup)
     const int mw = m0 + qw * 16, m = mw + r16;  // first query of the wave, this lane's
-    const Mover k_move(tile_rsrc(k + (size_t)bh * geo.kv_rows * D, L * D * 4), wave, lane);
-    const Mover v_move(tile_rsrc(v + (size_t)bh * geo.kv_rows * D, L * D * 4), wave, lane);
+    const Mover k_move(tile_rsrc(k + (size_t)bh * geo.kv_rows * D, (uint32_t)L * (D * 4)), wave, lane);
+    const Mover v_move(tile_rsrc(v + (size_t)bh * geo.kv_rows * D, (uint32_t)L * (D * 4)), wave, lane);
     const uint32_t base = lds_address(tiles);
     auto fetch = [&](int t) __attribute__((always_inline)) {
         const uint32_t at = base + t % 2 * TILE;
@@ -292,7 +292,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void colsum_f32_kernel(
     const int n0 = item.rank * BN;  // low keys have the most queries
     if (n0 >= L) return;  // ragged batch: this sequence ends before the tile (whole workgroup)
     const int nw = n0 + kw * 16;
-    const Mover q_move(tile_rsrc(q + (size_t)bh * geo.q_rows * D, Tq * D * 4), wave, lane);
+    const Mover q_move(tile_rsrc(q + (size_t)bh * geo.q_rows * D, (uint32_t)Tq * (D * 4)), wave, lane);
     const float* lh = lse + (size_t)bh * geo.q_rows;
     const uint32_t base = lds_address(tiles);
     const int m_begin = max(n0 - P, 0) / TQ * TQ;  // first tile with a query that sees key n0

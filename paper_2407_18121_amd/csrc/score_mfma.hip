@@ -101,8 +101,8 @@ __global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
     if (qtile < (PAIR ? early : 0) || qtile >= own_tiles) return;  // ragged batch: the sequence is shorter (whole workgroup)
     const uint16_t* qh = q + (size_t)bh * geo.q_rows * D;
     // tiles are fetched through descriptors that end at the sequence's last row: rows beyond it arrive as zeros
-    const KMove k_move(tile_rsrc(k + (size_t)bh * geo.kv_rows * D, L * D * 2), wave, lane);
-    const VMove v_move(tile_rsrc(v + (size_t)bh * geo.kv_rows * D, L * D * 2), wave, lane);
+    const KMove k_move(tile_rsrc(k + (size_t)bh * geo.kv_rows * D, (uint32_t)L * (D * 2)), wave, lane);
+    const VMove v_move(tile_rsrc(v + (size_t)bh * geo.kv_rows * D, (uint32_t)L * (D * 2)), wave, lane);
     constexpr int K0 = 0, K1 = TILE, V0 = 2 * TILE, V1 = 3 * TILE;  // elements
     const uint32_t mine_at = lds_address(tiles[grp]);
     auto row_of = [&](int i) { return (i * KSPLIT + grp) * kFwdBN; };  // first key of the group's i-th tile
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
     // A wave's 32 query rows travel through the place of its own share of the V tiles (16 rows each), so that no other wave
     // has to be waited for, and K of the first tile goes with them.
     const uint32_t q_at = mine_at + V0 * 2 + wave * (16 * D * 2);
-    const TileToLds<D, 32, 1, SwizzleRows<D>> q_move(tile_rsrc(qh, Tq * D * 2), 0, lane);
+    const TileToLds<D, 32, 1, SwizzleRows<D>> q_move(tile_rsrc(qh, (uint32_t)Tq * (D * 2)), 0, lane);
     auto first_loads = [&](int mw) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < q_move.NI; ++j)
@@ -491,8 +491,8 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
     if (ktile >= (PAIR ? (own_tiles + 1) / 2 : own_tiles)) return;  // ragged batch: the sequence is shorter (whole workgroup)
     const uint16_t* qh = q + (size_t)bh * geo.q_rows * D;
     const uint16_t* kh = k + (size_t)bh * geo.kv_rows * D;
-    const u32x4 q_rsrc = tile_rsrc(qh, Tq * D * 2);
-    const u32x4 l_rsrc = tile_rsrc(lse + (size_t)bh * geo.q_rows, Tq * 4);
+    const u32x4 q_rsrc = tile_rsrc(qh, (uint32_t)Tq * (D * 2));
+    const u32x4 l_rsrc = tile_rsrc(lse + (size_t)bh * geo.q_rows, (uint32_t)Tq * 4);
 
     // Single key tiles take their query tiles from the first one with a query that sees key n0 (m sees n <= P + m) upwards;
     // pairs from the sequence's last one down, so that all workgroups of a head start at the same queries and the first

@@ -33,14 +33,15 @@ __device__ __forceinline__ XcdItem xcd_item(int linear_id, int per_head, int n_h
 }
 
 // Buffer descriptor over `bytes` bytes at p (raw: no stride, 32-bit data format).  Loads through it whose byte
-// offset is at or beyond `bytes` return zeros instead of touching memory.
-__device__ __forceinline__ u32x4 tile_rsrc(const void* p, int bytes)
+// offset is at or beyond `bytes` return zeros instead of touching memory.  Lengths and offsets are unsigned: a head may
+// be longer than 2 GiB (the host keeps the ones that 32 bits do not cover away).
+__device__ __forceinline__ u32x4 tile_rsrc(const void* p, uint32_t bytes)
 {
     const uint64_t at = (uint64_t)(uintptr_t)p;
     u32x4 r;
     r.x = __builtin_amdgcn_readfirstlane((uint32_t)at);
     r.y = __builtin_amdgcn_readfirstlane((uint32_t)(at >> 32) & 0xffffu);
-    r.z = __builtin_amdgcn_readfirstlane((uint32_t)bytes);
+    r.z = __builtin_amdgcn_readfirstlane(bytes);
     r.w = 0x00020000u;
     return r;
 }
@@ -67,12 +68,12 @@ __device__ __forceinline__ uint32_t one_register(uint32_t a)
 // would make every later LDS read wait for every load in flight (it cannot tell the tiles of one array apart); the loads
 // have no result register, and the waits below are the ones they need.  The five wait states are those between a vector
 // instruction that writes a scalar register (a restored spill) and a load that reads it.
-__device__ __forceinline__ void load_lds_16(u32x4 rsrc, uint32_t lds, int byte_offset)
+__device__ __forceinline__ void load_lds_16(u32x4 rsrc, uint32_t lds, uint32_t byte_offset)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                  :: "s"(lds), "v"(byte_offset), "s"(rsrc) : "memory");
 }
-__device__ __forceinline__ void load_lds_4(u32x4 rsrc, uint32_t lds, int byte_offset)
+__device__ __forceinline__ void load_lds_4(u32x4 rsrc, uint32_t lds, uint32_t byte_offset)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, 0 offen lds"
                  :: "s"(lds), "v"(byte_offset), "s"(rsrc) : "memory");
@@ -106,7 +107,7 @@ template <int D, int ROWS, int WAVES, typename SWZ> struct TileToLds {
     static_assert(NI * RPI * WAVES == ROWS && (NI % PERIOD == 0 || PERIOD % NI == 0), "a wave's share within the period");
     u32x4 rsrc;
     int w0;                                     // first row of the wave's share (scalar)
-    int part[PARTS];
+    uint32_t part[PARTS];
     __device__ __forceinline__ TileToLds(u32x4 r, int wave, int lane) : rsrc(r), w0(wave * NI * RPI)
     {
 #pragma unroll
@@ -118,7 +119,7 @@ template <int D, int ROWS, int WAVES, typename SWZ> struct TileToLds {
     // lds: byte address of the tile (scalar)
     __device__ __forceinline__ void issue(uint32_t lds, int row0, int j) const
     {
-        load_lds_16(rsrc, lds + (w0 + j * RPI) * (D * 2), part[j % PARTS] + (row0 + w0 + j / PARTS * PARTS * RPI) * (D * 2));
+        load_lds_16(rsrc, lds + (w0 + j * RPI) * (D * 2), part[j % PARTS] + (uint32_t)(row0 + w0 + j / PARTS * PARTS * RPI) * (D * 2));
     }
 };
 

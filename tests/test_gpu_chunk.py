@@ -287,3 +287,37 @@ def test_chunk_score_tile_boundary_sweep(dtype, D):
                 worst = max(worst, err)
                 assert err <= (2e-2 if dtype == "bf16" else 1e-4), (P, Tq, name, err)
     print(f"worst abs error over the sweep: {worst:.2e}")
+
+
+@pytest.mark.parametrize("dtype,D,L", [
+    ("f32", 128, 4_200_000),    # a head of 2 GiB: offsets beyond 31 bits
+    ("f32", 128, 8_389_000),    # of 4 GiB: beyond 32 bits
+    ("bf16", 64, 16_800_000),   # 2 GiB in bf16
+])
+def test_chunk_score_over_heads_of_gigabytes(dtype, D, L):
+    """Two queries over a cache of zero keys, each with one key that outweighs all others: row 5 and row L - 9.  In closed
+    form the key has weight w / (w + L') with w = e^30 against the L' other rows that the query sees."""
+    Tq = 2
+    scale, w = 1.0 / D, np.exp(30.0)
+    at = (5, L - 9)
+    q = torch.zeros((1, 1, Tq, D), dtype=torch_dtype(dtype), device="cuda")
+    k = torch.zeros((1, 1, L, D), dtype=torch_dtype(dtype), device="cuda")
+    v = torch.zeros_like(k)
+    for m, n in enumerate(at):
+        q[0, 0, m, 3 + m] = 30.0
+        k[0, 0, n, 3 + m] = D
+        v[0, 0, n] = torch.arange(1, D + 1, device="cuda") * (m + 1)   # at most 8 significant bits: exact in bf16
+    out = torch.zeros_like(q)
+    lse = torch.zeros((1, 1, Tq), dtype=torch.float32, device="cuda")
+    score = torch.zeros((1, 1, L), dtype=torch.float32, device="cuda")
+    ws = ec.new_workspace(ec.EC_FN_PREFILL_SCORE, 1, 1, L, D, ec.dtype_code(q))
+    ec.ec_chunk_score(q, k, v, L - Tq, out, lse, score, scale, ws)
+    torch.cuda.synchronize()
+    # the sums of up to 3.4e7 equal terms beside w = 1.1e13: the result is a rounding of one product
+    rel = 2.0 ** -8 if dtype == "bf16" else 1e-5
+    for m, n in enumerate(at):
+        weight = w / (w + (L - Tq + m))
+        np.testing.assert_allclose(to_host(out)[0, 0, m], to_host(v)[0, 0, n] * weight, rtol=rel)
+        np.testing.assert_allclose(lse[0, 0, m].item(), np.log(w + (L - Tq + m)), rtol=1e-6)
+        np.testing.assert_allclose(score[0, 0, n].item(), weight, rtol=1e-5)
+    assert score.sum().item() == pytest.approx(Tq, rel=1e-5)

@@ -1,0 +1,56 @@
+"""The rule that sends a scoring call to its kernels, compiled by itself: a head has to fit into the 32-bit byte offsets
+of the matrix-core kernels' buffer descriptors, whatever else is true of the call.  No kernels run."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2407_18121_amd import binding as ec
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2407_18121_amd", "csrc")
+MFMA, F32, SIMT = range(3)
+PROGRAM = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "score_route.h"
+int main(int argc, char** argv)
+{
+    for (int i = 1; i + 6 < argc; i += 7) {
+        const char* base = (const char*)(uintptr_t)(1 << 20);  // only the low bits of the addresses matter
+        const void* p[4];
+        for (int j = 0; j < 4; ++j) p[j] = base + atoi(argv[i + 3 + j]);
+        printf("%d\n", (int)ec::score_route(atoi(argv[i]), atoi(argv[i + 1]), atoll(argv[i + 2]), p[0], p[1], p[2], p[3]));
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def route(tmp_path_factory):
+    at = tmp_path_factory.mktemp("route")
+    source, binary = at / "route.cpp", at / "route"
+    source.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-I", CSRC, "-o", str(binary), str(source)], check=True)
+
+    def run(calls):
+        args = [str(x) for dt, D, rows, offsets in calls for x in (dt, D, rows, *offsets)]
+        return [int(x) for x in subprocess.run([str(binary), *args], check=True, capture_output=True, text=True).stdout.split()]
+    return run
+
+
+ON = (0, 0, 0, 0)
+
+
+@pytest.mark.parametrize("dt,D,matrix", [(ec.EC_F32, 128, F32), (ec.EC_F32, 64, F32), (ec.EC_BF16, 128, MFMA), (ec.EC_BF16, 64, MFMA)])
+def test_heads_beyond_the_descriptors_take_the_vector_kernels(route, dt, D, matrix):
+    row = D * (4 if dt == ec.EC_F32 else 2)
+    most = 2 ** 32 // row  # rows of 4 GiB
+    got = route([(dt, D, rows, ON) for rows in (1, 2 ** 31 // row, most - 1024, most - 1023, most, most + 1, 2 ** 30)])
+    assert got == [matrix] * 3 + [SIMT] * 4
+
+
+def test_rows_off_the_16_byte_grid(route):
+    for dt, matrix, element in ((ec.EC_F32, F32, 4), (ec.EC_BF16, MFMA, 2)):
+        assert route([(dt, 64, 500, ON), (dt, 64, 500, (16, 32, 48, 64))]) == [matrix] * 2
+        for i in range(4):
+            assert route([(dt, 64, 500, tuple(element if j == i else 0 for j in range(4)))]) == [SIMT]
