@@ -131,6 +131,9 @@ __device__ __forceinline__ int ragged_rows(const int32_t* __restrict__ seq_len, 
     return seq_len ? min(max(seq_len[b], 0), t_max) : t_max;
 }
 
+// What a running maximum starts from.  No finite score lies below it, so that it never hides one, and it is finite itself:
+// rows whose scores so far are all -inf get exp2(-inf - kLowest) = 0 where -inf - -inf would be NaN.
+constexpr float kLowest = -3.40282347e+38f;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 

@@ -133,9 +133,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
     f32x4 o[DB];  // O^T: register r of block db is feature 64 (db / 4) + 4 (4h + r) + db % 4
 #pragma unroll
     for (int db = 0; db < DB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // a wave that does not start at key 0 can meet a block of which a query sees nothing: a finite floor for the maximum
-    // keeps exp2(-inf - m) at zero there
-    float m_run = KS == 1 ? -INFINITY : -1e30f, l_run = 0.f;  // l_run: this lane's share of the row sum
+    float m_run = kLowest, l_run = 0.f;  // l_run: this lane's share of the row sum
 
     // The compiler learns here that the operand has arrived: the waits it would otherwise put before its uses inside the loop
     // would be waits for the tile in flight.
@@ -169,7 +167,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
             for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[b][r]);
         mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
         mx = fmaxf(mx, __shfl_xor(mx, 32, kWave)) * scale_log2e;
-        const float m_new = fmaxf(m_run, mx);  // finite: key 0 is visible to every query
+        const float m_new = fmaxf(m_run, mx);
         const float corr = exp2f(m_run - m_new);
         m_run = m_new;
         float psum = 0.f;
@@ -224,7 +222,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
         }
         __syncthreads();
         if (ks > 0) return;
-        float m_all = m_run;  // the first wave has seen key 0: a real maximum
+        float m_all = m_run;
 #pragma unroll
         for (int w = 1; w < KS; ++w) m_all = fmaxf(m_all, stats[(w * QW + qw) * 16 + r16]);
         const float f0 = exp2f(m_run - m_all);

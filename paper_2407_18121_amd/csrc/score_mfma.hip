@@ -170,9 +170,9 @@ __global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
             for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
         // m_run: running maximum of the scaled scores, base 2, of every tile whose scores have been computed (one tile
         // ahead of o and l_run, which are already scaled to it).  A group that does not start at key 0 can meet a tile in
-        // which a query sees no key at all; a finite floor for the maximum keeps exp2(-inf - m) at zero there instead of
-        // exp2(-inf + inf).  l_run: this half-wave's share of the row sum.
-        float m_run = (KSPLIT == 1) ? -INFINITY : -1e30f, l_run = 0.f;
+        // which a query sees no key at all, and any tile can hold nothing but scores of -inf.  l_run: this half-wave's share
+        // of the row sum.
+        float m_run = kLowest, l_run = 0.f;
         f32x16 sA[2], sB[2];
         bf16x8 pf[4];
 
@@ -191,8 +191,8 @@ __global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
         auto raise_max = [&](float mx) __attribute__((always_inline)) {
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
             mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2e;
-            const float m_new = fmaxf(m_run, mx);  // finite: key 0 is visible to every query
-            const float corr = __builtin_amdgcn_exp2f(m_run - m_new);  // exp2(-inf) = 0 on the first tile
+            const float m_new = fmaxf(m_run, mx);
+            const float corr = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 from kLowest to a score
             const bool grew = m_new > m_run;
             m_run = m_new;
             l_run *= corr;
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
             __syncthreads();
             if (grp == 1) return;
             const float m1 = stats[tid], l1 = stats[THREADS + tid];
-            const float m_all = fmaxf(m_run, m1);  // group 0 has seen key 0: a real maximum
+            const float m_all = fmaxf(m_run, m1);
             const float f0 = __builtin_amdgcn_exp2f(m_run - m_all), f1 = __builtin_amdgcn_exp2f(m1 - m_all);
             l_run = l_run * f0 + l1 * f1;
             m_run = m_all;

@@ -1,0 +1,51 @@
+"""Scoring calls whose scores are infinite, enormous or not numbers: every launch shape gives the softmax that remains.
+References: the same in 64 bits, where the products do not overflow."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2407_18121_amd import binding as ec
+from util import ATOL, assert_close, to_host, torch_dtype
+
+pytestmark = pytest.mark.gpu
+
+# (dtype, heads, rows) of every launch shape at D = 64
+SHAPES = [
+    ("f32", 2, 200), ("f32", 32, 200), ("f32", 128, 200),     # four, two, one wave(s) on the keys of 16 queries
+    ("bf16", 2, 200), ("bf16", 128, 200),                     # single tiles: one, two groups in the column pass
+    ("bf16", 2, 300), ("bf16", 2, 1100), ("bf16", 128, 900),  # either side of two groups per tile; pairs
+]
+
+
+def _inputs(H, T, seed):
+    g = torch.Generator().manual_seed(seed)
+    return [torch.randn((1, H, T, 64), generator=g) for _ in range(3)]
+
+
+def _score(q, k, v, dtype, scale):
+    q, k, v = (x.to(torch_dtype(dtype)).cuda() for x in (q, k, v))
+    B, H, T, D = q.shape
+    out, lse = torch.zeros_like(q), torch.zeros((B, H, T), device="cuda")
+    score = torch.zeros((B, H, T), device="cuda")
+    ec.ec_prefill_score(q, k, v, out, lse, score, scale, ec.new_workspace(ec.EC_FN_PREFILL_SCORE, B, H, T, D, ec.dtype_code(q)))
+    torch.cuda.synchronize()
+    return to_host(out), to_host(lse), to_host(score)
+
+
+def _reference(q, k, v, dtype, scale):
+    q, k, v = (x.to(torch_dtype(dtype)).double() for x in (q, k, v))
+    s = torch.matmul(q, k.transpose(-1, -2).contiguous()) * scale
+    s = s.masked_fill(torch.ones(s.shape[-2:], dtype=torch.bool).triu(1), -torch.inf)
+    a = torch.softmax(s, -1)
+    return torch.matmul(a, v).numpy(), torch.logsumexp(s, -1).numpy(), a.sum(-2).numpy()
+
+
+@pytest.mark.parametrize("dtype,H,T", SHAPES)
+def test_first_keys_at_minus_infinity(dtype, H, T):
+    """Most queries score the first 70 keys -inf: more than any kernel's first tile, which leaves them without a maximum."""
+    q, k, v = _inputs(H, T, 1)
+    q[..., 0] = k[..., 0] = 0.0
+    q[:, :, 70:, 0], k[:, :, :70, 0] = 1e30, -1e30
+    got, ref = _score(q, k, v, dtype, 0.125), _reference(q, k, v, dtype, 0.125)
+    for name, x, y in zip(("out", "lse", "score"), got, ref):
+        assert_close(x, y, dtype, name)
