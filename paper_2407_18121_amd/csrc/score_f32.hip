@@ -133,7 +133,9 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
     f32x4 o[DB];  // O^T: register r of block db is feature 64 (db / 4) + 4 (4h + r) + db % 4
 #pragma unroll
     for (int db = 0; db < DB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run = kLowest, l_run = 0.f;  // l_run: this lane's share of the row sum
+    // Maximum of the scores before scaling: the largest one's exponent is then exactly 0, however large the scores are,
+    // where a scaled maximum would leave the rounding of its product.  l_run: this lane's share of the row sum.
+    float m_run = kLowest, l_run = 0.f;
 
     // The compiler learns here that the operand has arrived: the waits it would otherwise put before its uses inside the loop
     // would be waits for the tile in flight.
@@ -166,16 +168,16 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
 #pragma unroll
             for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[b][r]);
         mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, kWave)) * scale_log2e;
+        mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
         const float m_new = fmaxf(m_run, mx);
-        const float corr = exp2f(m_run - m_new);
+        const float corr = exp2f((m_run - m_new) * scale_log2e);
         m_run = m_new;
         float psum = 0.f;
 #pragma unroll
         for (int b = 0; b < NBLK; ++b)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                s[b][r] = exp2f(fmaf(s[b][r], scale_log2e, -m_new));
+                s[b][r] = exp2f((s[b][r] - m_new) * scale_log2e);
                 psum += s[b][r];
             }
         l_run = fmaf(l_run, corr, psum);
@@ -225,13 +227,13 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
         float m_all = m_run;
 #pragma unroll
         for (int w = 1; w < KS; ++w) m_all = fmaxf(m_all, stats[(w * QW + qw) * 16 + r16]);
-        const float f0 = exp2f(m_run - m_all);
+        const float f0 = exp2f((m_run - m_all) * scale_log2e);
         l_run *= f0;
 #pragma unroll
         for (int db = 0; db < DB; ++db) o[db] *= f0;
 #pragma unroll
         for (int w = 1; w < KS; ++w) {
-            const float f = exp2f(stats[(w * QW + qw) * 16 + r16] - m_all);
+            const float f = exp2f((stats[(w * QW + qw) * 16 + r16] - m_all) * scale_log2e);
             l_run = fmaf(stats[(kF32Waves + w * QW + qw) * 16 + r16], f, l_run);
             if constexpr (OUT) {
 #pragma unroll
@@ -244,7 +246,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
         m_run = m_all;
     }
     if (m < Tq) {
-        if (h == 0) lse[(size_t)bh * geo.q_rows + m] = (m_run + log2f(l_run)) * lse_unit;
+        if (h == 0) lse[(size_t)bh * geo.q_rows + m] = fmaf(m_run, scale_log2e, log2f(l_run)) * lse_unit;
         if constexpr (OUT) {
             const float inv = 1.f / l_run;
             float* orow = out + ((size_t)bh * geo.q_rows + m) * D;

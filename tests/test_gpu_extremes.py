@@ -49,3 +49,19 @@ def test_first_keys_at_minus_infinity(dtype, H, T):
     got, ref = _score(q, k, v, dtype, 0.125), _reference(q, k, v, dtype, 0.125)
     for name, x, y in zip(("out", "lse", "score"), got, ref):
         assert_close(x, y, dtype, name)
+
+
+@pytest.mark.parametrize("magnitude", [-1e33, -1e12, 1e12, 1e33])
+@pytest.mark.parametrize("H,T", [(H, T) for dtype, H, T in SHAPES if dtype == "f32"])
+def test_enormous_fp32_scores(H, T, magnitude):
+    """Scores so far apart that one key takes it all.  (The column sums are not compared: they subtract a stored log-sum-exp
+    whose own rounding is many orders above one.)"""
+    q, k, v = _inputs(H, T, 2)
+    q[..., 0] = magnitude
+    g = torch.Generator().manual_seed(3)
+    rank = torch.stack([torch.randperm(T, generator=g) for _ in range(H)])[None]
+    k[..., 0] = 1.0 + rank / T
+    out, lse, _ = _score(q, k, v, "f32", 0.125)
+    ref_out, ref_lse, _ = _reference(q, k, v, "f32", 0.125)
+    assert_close(out, ref_out, "f32", "out")
+    np.testing.assert_allclose(lse, ref_lse, rtol=1e-6)  # a product, a sum and two scalings in 24 bits
