@@ -564,8 +564,17 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
         auto frag = [&](int u, int kb) __attribute__((always_inline)) {  // u: step of 32 queries inside the two tiles
             return *(lds_bf16x8*)(uintptr_t)(q_at[kb] + u * 32 * D * 2);
         };
-        // pairs that the mask takes out (keys behind the query, queries behind the end): score -inf, mass zero
-        auto mask = [&](f32x16 (&sp)[NB], int mp) __attribute__((always_inline)) {
+        // pairs that the mask takes out (keys behind the query, queries behind the end): score -inf, mass zero.  A
+        // log-sum-exp that would turn -inf into a number other than -inf (NaN, or that of a row of -inf) goes into the scores
+        // of the keys that the query sees, so that it does not reach the others.
+        auto mask = [&](f32x16 (&sp)[NB], float& lp, int mp) __attribute__((always_inline)) {
+            if (!(lp < INFINITY)) {
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sp[nb][r] += lp;
+                lp = 0.f;
+            }
             const int last = (mp + c32 < Tq) ? P + mp + c32 - nw - h * 4 : -1;  // last key this lane's query sees
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
@@ -583,7 +592,7 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
             l_n = -ln * kLog2e;
             m_n = mq;
             ln = ls[(u_next + qg) * 32 + c32];
-            if (P + mp < nw + KEYS_W - 1 || mp + 32 > Tq) mask(sp, mp);  // some pair of the pending step is masked
+            if (P + mp < nw + KEYS_W - 1 || mp + 32 > Tq) mask(sp, lp, mp);  // some pair of the pending step is masked
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -684,7 +693,7 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
         if (more) load_keys(next_tile);  // travels while this tile's sums are brought together
         // at most one of the two is still pending
         auto retire = [&](f32x16 (&sp)[NB], float lp, int mp) __attribute__((always_inline)) {
-            mask(sp, mp);
+            mask(sp, lp, mp);
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2407_18121_amd import binding as ec
-from util import ATOL, assert_close, to_host, torch_dtype
+from util import assert_close, to_host, torch_dtype
 
 pytestmark = pytest.mark.gpu
 
@@ -32,10 +32,10 @@ def _score(q, k, v, dtype, scale):
     return to_host(out), to_host(lse), to_host(score)
 
 
-def _reference(q, k, v, dtype, scale):
+def _reference(q, k, v, dtype, scale, P=0):
     q, k, v = (x.to(torch_dtype(dtype)).double() for x in (q, k, v))
     s = torch.matmul(q, k.transpose(-1, -2).contiguous()) * scale
-    s = s.masked_fill(torch.ones(s.shape[-2:], dtype=torch.bool).triu(1), -torch.inf)
+    s = s.masked_fill(torch.ones(s.shape[-2:], dtype=torch.bool).triu(1 + P), -torch.inf)
     a = torch.softmax(s, -1)
     return torch.matmul(a, v).numpy(), torch.logsumexp(s, -1).numpy(), a.sum(-2).numpy()
 
@@ -65,3 +65,26 @@ def test_enormous_fp32_scores(H, T, magnitude):
     ref_out, ref_lse, _ = _reference(q, k, v, "f32", 0.125)
     assert_close(out, ref_out, "f32", "out")
     np.testing.assert_allclose(lse, ref_lse, rtol=1e-6)  # a product, a sum and two scalings in 24 bits
+
+
+@pytest.mark.parametrize("dtype,H,T", SHAPES)
+@pytest.mark.parametrize("what", ["a query of NaN", "a query whose scores are all -inf"])
+def test_a_query_without_a_softmax_stays_among_the_keys_it_sees(dtype, H, T, what):
+    """Column sums of keys behind the query, and the output rows of all others, are what they are without it."""
+    q, k, v = _inputs(H, T, 4)
+    q[..., 0], k[..., 0] = 0.0, -1e30
+    where = sorted({37, 64, 101, 131, T - 30} & set(range(T)))   # inside, at the start of and late in a block of keys
+    ref_out, ref_lse, _ = _reference(q, k, v, dtype, 0.125)
+    for m in where:
+        bad = q.clone()
+        if what == "a query of NaN":
+            bad[:, :, m] = torch.nan
+        else:
+            bad[:, :, m, 0] = 1e30
+        out, lse, score = _score(bad, k, v, dtype, 0.125)
+        others = [i for i in range(T) if i != m]
+        assert_close(out[:, :, others], ref_out[:, :, others], dtype, "out")
+        assert_close(lse[:, :, others], ref_lse[:, :, others], dtype, "lse")
+        ref = _reference(q[:, :, m + 1:], k, v, dtype, 0.125, m + 1)[2]
+        assert_close(score[:, :, m + 1:], ref[:, :, m + 1:], dtype, "score")
+        assert np.isnan(score[:, :, :m + 1]).all() and np.isnan(out[:, :, m]).all()
