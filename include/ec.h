@@ -98,8 +98,9 @@ size_t ec_workspace_bytes(int fn, int B, int H, int T, int D, int dt);
  *   score  DEVICE [B,G,T] float, written
  *   ws     DEVICE scratch, ec_workspace_bytes(EC_FN_PREFILL_SCORE, B,H,T,D,dt)
  * bf16 inputs are multiplied on the matrix cores with fp32 accumulation; fp32
- * inputs use fp32 arithmetic throughout.  Results are deterministic.  Heads whose rows take 4 GiB and more
- * (T * D elements) run on the vector units, many times slower.
+ * inputs use fp32 arithmetic throughout.  Results are deterministic.  Tensors may start at any element; the
+ * fastest kernels need q, k and v (fp32: out as well) on 16-byte boundaries.  fp32 tensors off them, and heads
+ * whose rows take 4 GiB and more (T * D elements), run on the vector units, many times slower.
  */
 int ec_prefill_score(const void* q, const void* k, const void* v, void* out, float* lse,
                      float* score, int B, int H, int G, int T, int D, int dt, float scale,

@@ -34,7 +34,7 @@ int score_f32_dispatch(const void* q, const void* k, const void* v, void* out, f
                        float* head_imp, int B, int H, ScoreGeom geo, const int32_t* seq_len, int D, float scale, hipStream_t stream);
 int score_mfma_dispatch(const void* q, const void* k, const void* v, void* out, float* lse,
                         float* head_imp, int B, int H, ScoreGeom geo, const int32_t* seq_len, int D,
-                        int dt, float scale, hipStream_t stream);
+                        int dt, float scale, bool direct, hipStream_t stream);
 int retention_step_launch(int32_t* n_seen_b, int32_t* cache_len_b, int32_t* evict_idx_b, int32_t* new_pos_b,
                           int32_t* pending_b, int B, int gamma_num, int gamma_den, int budget_mode, int fixed_len,
                           int trunc_mode, int recent, int n_tl, int protect_first, int flush_only, hipStream_t stream);
@@ -99,9 +99,12 @@ int score_pass(const void* q, const void* k, const void* v, void* out, float* ls
     float* head_imp = (G == H) ? score : ws_imp;
 
     int rc;
-    switch (ec::score_route(dt, D, geo.L, q, k, v, out)) {
+    const ec::ScoreRoute route = ec::score_route(dt, D, geo.L, q, k, v, out);
+    switch (route) {
         case ec::ScoreRoute::kMfma:
-            rc = ec::score_mfma_dispatch(q, k, v, out, lse_buf, head_imp, B, H, geo, seq_len, D, dt, scale, s);
+        case ec::ScoreRoute::kMfmaOffGrid:
+            rc = ec::score_mfma_dispatch(q, k, v, out, lse_buf, head_imp, B, H, geo, seq_len, D, dt, scale,
+                                         route == ec::ScoreRoute::kMfma, s);
             break;
         case ec::ScoreRoute::kF32:
             rc = ec::score_f32_dispatch(q, k, v, out, lse_buf, lse != nullptr, head_imp, B, H, geo, seq_len, D, scale, s);

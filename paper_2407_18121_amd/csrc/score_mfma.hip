@@ -29,6 +29,7 @@
 namespace ec {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef bf16x8 __attribute__((aligned(2))) bf16x8_any;  // in memory: at any element
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
@@ -64,8 +65,9 @@ template <int D> struct SwizzleTr {  // four rows at the same 64 bytes (a transp
 // KSPLIT = 2 (short prompts that give the chip one workgroup per compute unit or less): two groups of QW waves share
 // the workgroup's queries and take alternate key tiles, each group moving its own tiles; their (max, sum, O) are merged
 // through LDS at the end.  The key loop of a workgroup, which is what bounds such launches, is half as long.
+// DIRECT = false: q, k or v does not start on a 16-byte boundary, and tiles pass through registers.
 constexpr int kFwdAhead = 4;  // LDS fragments requested ahead of the matrix pipe
-template <int D, int QW, int KSPLIT, bool PAIR, bool OUT>
+template <int D, int QW, int KSPLIT, bool PAIR, bool OUT, bool DIRECT>
 __global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     uint16_t* __restrict__ out, float* __restrict__ lse, ScoreGeom geo, float scale_log2e, int n_qtiles,
@@ -78,8 +80,8 @@ __global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
     constexpr int NP = 4 * DB;    // of phase B: (16-key block, db)
     constexpr int EV = 32 / NA;   // elements turned into probabilities per matrix instruction of phase A
     constexpr int TILE = kFwdBN * D;
-    using KMove = TileToLds<D, kFwdBN, QW, SwizzleRows<D>>;
-    using VMove = TileToLds<D, kFwdBN, QW, SwizzleTr<D>>;
+    using KMove = TileToLds<D, kFwdBN, QW, SwizzleRows<D>, DIRECT>;
+    using VMove = TileToLds<D, kFwdBN, QW, SwizzleTr<D>, DIRECT>;
     constexpr int NI = KMove::NI;
     // per group: K of even tiles, K of odd tiles, V of even tiles, V of odd tiles
     __shared__ __align__(16) uint16_t tiles[KSPLIT][4 * TILE];
@@ -119,7 +121,7 @@ __global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
     // A wave's 32 query rows travel through the place of its own share of the V tiles (16 rows each), so that no other wave
     // has to be waited for, and K of the first tile goes with them.
     const uint32_t q_at = mine_at + V0 * 2 + wave * (16 * D * 2);
-    const TileToLds<D, 32, 1, SwizzleRows<D>> q_move(tile_rsrc(qh, (uint32_t)Tq * (D * 2)), 0, lane);
+    const TileToLds<D, 32, 1, SwizzleRows<D>, DIRECT> q_move(tile_rsrc(qh, (uint32_t)Tq * (D * 2)), 0, lane);
     auto first_loads = [&](int mw) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < q_move.NI; ++j)
@@ -335,13 +337,19 @@ __global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
                 static_assert(EVERY >= 1, "a phase has room for its loads");
                 if (f < NA && f % EVERY == 0) {
                     if (f / EVERY < NI)
-                        k_move.issue(mine_at + k_old * 2, k_row, f / EVERY);
+                        k_move.begin(mine_at + k_old * 2, k_row, f / EVERY);
                     else if (OUT)
-                        v_move.issue(mine_at + v_next * 2, v_row, f / EVERY - NI);
+                        v_move.begin(mine_at + v_next * 2, v_row, f / EVERY - NI);
                 }
             });
+#pragma unroll
+            for (int j = 0; j < NI; ++j) k_move.finish(mine_at + k_old * 2, j);
             mask(sn, row_of(i + 1));
             phase_b(std::true_type{}, sn, v_cur);
+            if constexpr (OUT) {
+#pragma unroll
+                for (int j = 0; j < NI; ++j) v_move.finish(mine_at + v_next * 2, j);
+            }
         };
         int i = 0;
         for (; i + 2 < count; i += 2) {
@@ -437,7 +445,7 @@ __global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
                     const int row = j * RPS + el / HC;
                     const bf16x8 y = *(lds_bf16x8*)(uintptr_t)(stage + place(row, el % HC));
                     if (mw + row < Tq)
-                        *reinterpret_cast<bf16x8*>(out + ((size_t)bh * geo.q_rows + mw + row) * D + half * (D / 2) + el % HC * 8) = y;
+                        *reinterpret_cast<bf16x8_any*>(out + ((size_t)bh * geo.q_rows + mw + row) * D + half * (D / 2) + el % HC * 8) = y;
                 }
             }
         }
@@ -461,7 +469,7 @@ __global__ __launch_bounds__(QW * KSPLIT * kWave, 2) void attn_fwd_mfma_kernel(
 // 200 -> 186 -> 160 us.
 // PAIR: the workgroup takes key tiles i and n - 1 - i of its head, one after the other.
 // QG = 2 (launches of one workgroup per compute unit or less): twice the waves on the same keys.
-template <int D, int NB, int KW, int QG, int QT, bool PAIR>
+template <int D, int NB, int KW, int QG, int QT, bool PAIR, bool DIRECT>
 __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const float* __restrict__ lse,
     float* __restrict__ head_imp, ScoreGeom geo, float scale_log2e, int n_ktiles, int n_heads,
@@ -500,7 +508,7 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
     const int m_last = (Tq - 1) / QT * QT;
     auto first_seen = [&](int tile) __attribute__((always_inline)) { return max(tile * BN - P, 0) / QT * QT; };
     constexpr int DIR = PAIR ? -1 : 1;
-    using Mover = TileToLds<D, QT, WAVES, SwizzleRows<D>>;
+    using Mover = TileToLds<D, QT, WAVES, SwizzleRows<D>, DIRECT>;
     const uint32_t qs_at = lds_address(qs), ls_at = lds_address(ls);
     auto fetch_lse = [&](int buf, int m) __attribute__((always_inline)) {
         if (wave < QT / kWave)
@@ -524,7 +532,7 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
             const int n = min(tile * BN + kw * KEYS_W + nb * 32 + lk % 32, L - 1);  // sums of keys beyond L are not stored
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
-                kf[nb][kb] = *reinterpret_cast<const bf16x8*>(kh + (size_t)n * D + kb * 16 + lk / 32 * 8);
+                kf[nb][kb] = *reinterpret_cast<const bf16x8_any*>(kh + (size_t)n * D + kb * 16 + lk / 32 * 8);
         }
     };
     load_keys(ktile);
@@ -538,7 +546,6 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
         const bool more = PAIR && next_tile > ktile;
         const int m_first = PAIR ? m_last : m_begin;
         const Mover mover(q_rsrc, wave, anew(lane));
-        auto fetch = [&](int buf, int m, int j) __attribute__((always_inline)) { mover.issue(qs_at + buf * QT * D * 2, m, j); };
         // What is fetched as tile t: behind the last tile of a pair's first half the first two of the second half, behind
         // the very last rows behind the sequence, for which nothing is read.
         auto first_query = [&](int buf, int t) __attribute__((always_inline)) {
@@ -660,7 +667,7 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
                 if (!active) {
                     if (last) {
 #pragma unroll
-                        for (int j = 0; j < Mover::NI; ++j) fetch(buf, m_refill, j);
+                        for (int j = 0; j < Mover::NI; ++j) mover.issue(qs_at + buf * QT * D * 2, m_refill, j);
                     }
                     continue;
                 }
@@ -668,11 +675,14 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
                     step(sA, lA, mA, mq, sB, lB, mB, u + DIR * QG, nothing);
                 else if (!last)
                     step(sB, lB, mB, mq, sA, lA, mA, u + DIR * QG, nothing);
-                else  // the tile after the next one takes this one's place, its loads spread over the matrix instructions
+                else {  // the tile after the next one takes this one's place, its loads spread over the matrix instructions
                     step(sB, lB, mB, mq, sA, lA, mA, (buf ^ 1) * (QT / 32) + (PAIR ? (SPT - 1) * QG : 0), [&](int g) __attribute__((always_inline)) {
                         constexpr int EVERY = NB * KB / Mover::NI;
-                        if (g % EVERY == 0) fetch(buf, m_refill, g / EVERY);
+                        if (g % EVERY == 0) mover.begin(qs_at + buf * QT * D * 2, m_refill, g / EVERY);
                     });
+#pragma unroll
+                    for (int j = 0; j < Mover::NI; ++j) mover.finish(qs_at + buf * QT * D * 2, j);
+                }
             }
         };
         tile_barrier();
@@ -733,21 +743,21 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
 
 template <int D>
 static int launch_mfma(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse,
-                       float* head_imp, int B, int H, ScoreGeom geo, const int32_t* seq_len, float scale,
+                       float* head_imp, int B, int H, ScoreGeom geo, const int32_t* seq_len, float scale, bool direct,
                        hipStream_t stream)
 {
     const float sl = scale * kLog2e;
     const int Tq = geo.Tq, L = geo.L;
     const int BH = B * H;
     const int qt128 = (Tq + 127) / 128;
-#define EC_FWD(KS_, PAIR_)                                                                                           \
+#define EC_FWD(KS_, PAIR_, DIRECT_)                                                                                           \
     do {                                                                                                             \
         const dim3 grid(xcd_grid((PAIR_ ? (qt128 + 1) / 2 : qt128) * BH)), block(4 * KS_ * kWave);                    \
         if (out != nullptr)                                                                                          \
-            hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 4, KS_, PAIR_, true>), grid, block, 0, stream, q, k, v, out,  \
+            hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 4, KS_, PAIR_, true, DIRECT_>), grid, block, 0, stream, q, k, v, out,  \
                                lse, geo, sl, qt128, BH, seq_len, H);                                                 \
         else                                                                                                         \
-            hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 4, KS_, PAIR_, false>), grid, block, 0, stream, q, k, v, out, \
+            hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 4, KS_, PAIR_, false, DIRECT_>), grid, block, 0, stream, q, k, v, out, \
                                lse, geo, sl, qt128, BH, seq_len, H);                                                 \
     } while (0)
     // Launch shapes of the forward pass, us (pairs / single tiles / two wave groups per tile), H 32, D 128:
@@ -756,20 +766,25 @@ static int launch_mfma(const uint16_t* q, const uint16_t* k, const uint16_t* v, 
     //   H8 B1: T1024 25.3 / 20.3 / 19.7   T2048 39.3 / 34.6 / 32.8   T4096 70.0 / 65.4 / 61.7
     // Pairs from one per compute unit on (three tiles or fewer have nothing to even out); below that two groups per tile
     // once the key loop is long enough to pay for merging them.
-    if (qt128 >= 4 && (long long)((qt128 + 1) / 2) * BH >= kPairMinWorkgroups)
-        EC_FWD(1, true);
+    // Off the 16-byte grid one shape serves all sizes: the loads themselves, two requests for every 128 bytes, set the pace
+    // (whole call on / off the grid, B1 H32 T1024 D128 37 / 64 us, B8 T2048 503 / 831 us, B4 T8192 3.05 / 4.11 ms; in
+    // pairs the latter two take 814 us and 4.13 ms).
+    if (!direct)
+        EC_FWD(1, false, false);
+    else if (qt128 >= 4 && (long long)((qt128 + 1) / 2) * BH >= kPairMinWorkgroups)
+        EC_FWD(1, true, true);
     else if ((long long)qt128 * BH <= kSplitMaxWorkgroups && L >= 1024)
-        EC_FWD(2, false);
+        EC_FWD(2, false, true);
     else
-        EC_FWD(1, false);
+        EC_FWD(1, false, true);
 #undef EC_FWD
     int rc = status_from_hip(hipGetLastError());
     if (rc != EC_OK) return rc;
     const int kt256 = (L + 255) / 256, kt128 = (L + 127) / 128;
-#define EC_COLSUM(NB_, QG_, QT_, PAIR_)                                                                              \
+#define EC_COLSUM(NB_, QG_, QT_, PAIR_, DIRECT_)                                                                              \
     do {                                                                                                             \
         const int kt = (L + 128 * NB_ - 1) / (128 * NB_);                                                            \
-        hipLaunchKernelGGL((colsum_mfma_kernel<D, NB_, 4, QG_, QT_, PAIR_>),                                         \
+        hipLaunchKernelGGL((colsum_mfma_kernel<D, NB_, 4, QG_, QT_, PAIR_, DIRECT_>),                                         \
                            dim3(xcd_grid((PAIR_ ? (kt + 1) / 2 : kt) * BH)), dim3(4 * QG_ * kWave), 0, stream, q, k, \
                            lse, head_imp, geo, sl, kt, BH, seq_len, H);                                              \
     } while (0)
@@ -777,28 +792,31 @@ static int launch_mfma(const uint16_t* q, const uint16_t* k, const uint16_t* v, 
     //   H32 D128: B1 T512 22.7 / 11.3 / 9.0   B1 T1024 30.4 / 14.9 / 13.2   B2 T1024 31.9 / 22.3 / 25.8   B1 T2048 46.4 / 37.1 / 37.8
     //   B2 T2048 53.8 / 54.5 / 66.2   B4 T1024 35.2 / 39.6 / 47.0   B8 T1536 107 / 111 / 156   B2 T8192 524 / 591 / 647
     //   B16 H40 T512 63.5 / 50.0 / 82.5; a chunk of 1024 over 640 rows, B8: 117 / 99 (its first tiles are equally long: nothing to pair)
-    if (kt256 >= 4 && (long long)((kt256 + 1) / 2) * BH >= kPairMinWorkgroups && 2 * geo.P <= Tq)
-        EC_COLSUM(2, 1, 128, true);
+    if (!direct)
+        EC_COLSUM(1, 1, 64, false, false);
+    else if (kt256 >= 4 && (long long)((kt256 + 1) / 2) * BH >= kPairMinWorkgroups && 2 * geo.P <= Tq)
+        EC_COLSUM(2, 1, 128, true, true);
     else if ((long long)kt128 * BH <= kSplitMaxWorkgroups)
-        EC_COLSUM(1, 2, 128, false);
+        EC_COLSUM(1, 2, 128, false, true);
     else
-        EC_COLSUM(1, 1, 64, false);
+        EC_COLSUM(1, 1, 64, false, true);
 #undef EC_COLSUM
     return status_from_hip(hipGetLastError());
 }
 
-// Per-head importance into head_imp [B,H,L]; out may be NULL (then v is not read).
+// Per-head importance into head_imp [B,H,L]; out may be NULL (then v is not read).  direct: q, k and v start on 16-byte
+// boundaries.
 int score_mfma_dispatch(const void* q, const void* k, const void* v, void* out, float* lse, float* head_imp,
-                        int B, int H, ScoreGeom geo, const int32_t* seq_len, int D, int dt, float scale,
+                        int B, int H, ScoreGeom geo, const int32_t* seq_len, int D, int dt, float scale, bool direct,
                         hipStream_t stream)
 {
     if (dt != EC_BF16) return EC_EUNSUPPORTED;
     if (D == 128)
         return launch_mfma<128>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (uint16_t*)out, lse,
-                                head_imp, B, H, geo, seq_len, scale, stream);
+                                head_imp, B, H, geo, seq_len, scale, direct, stream);
     if (D == 64)
         return launch_mfma<64>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (uint16_t*)out, lse,
-                               head_imp, B, H, geo, seq_len, scale, stream);
+                               head_imp, B, H, geo, seq_len, scale, direct, stream);
     return EC_EUNSUPPORTED;
 }
 

@@ -7,7 +7,7 @@
 
 namespace ec {
 
-enum class ScoreRoute { kMfma = 0, kF32 = 1, kSimt = 2 };
+enum class ScoreRoute { kMfma = 0, kF32 = 1, kSimt = 2, kMfmaOffGrid = 3 };
 
 // The matrix-core kernels move tiles through buffer descriptors, whose length and byte offsets have 32 bits and cover one
 // head: all its rows and the ones that a prefetch asks for behind the last row (at most 384; the descriptor answers
@@ -19,9 +19,11 @@ inline ScoreRoute score_route(int dt, int D, long long rows, const void* q, cons
 {
     const long long row_bytes = (long long)D * (dt == EC_F32 ? 4 : 2);
     if ((rows + kRowsBehind) * row_bytes > kDescriptorBytes) return ScoreRoute::kSimt;
-    // the matrix-core kernels move 16 bytes at a time; rows that do not lie on 16-byte boundaries take the vector ones
-    if ((((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out) & 15) != 0) return ScoreRoute::kSimt;
-    return dt == EC_BF16 ? ScoreRoute::kMfma : ScoreRoute::kF32;
+    // Tiles go straight from memory into LDS, 16 bytes at a time.  Rows that do not lie on 16-byte boundaries pass through
+    // registers in bf16, and take the vector kernels in fp32.
+    const bool on_grid = (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v) & 15) == 0;
+    if (dt == EC_BF16) return on_grid ? ScoreRoute::kMfma : ScoreRoute::kMfmaOffGrid;
+    return on_grid && ((uintptr_t)out & 15) == 0 ? ScoreRoute::kF32 : ScoreRoute::kSimt;
 }
 
 }  // namespace ec

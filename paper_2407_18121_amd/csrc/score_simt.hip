@@ -1,7 +1,7 @@
 // ec_prefill_score / ec_chunk_score, vector-ALU path (fp32 arithmetic throughout).
 // Geometry (ScoreGeom): Tq queries over L = P + Tq key rows, query m sees rows n <= P + m.
 //
-// Used for tensors that do not start on a 16-byte boundary and for heads of 4 GiB and more, neither of which the
+// Used for heads of 4 GiB and more and for fp32 tensors that do not start on a 16-byte boundary, neither of which the
 // matrix-core paths (score_mfma.hip, score_f32.hip) take.  Two passes, neither of which stores the T x T matrix (Sec. 3.3,
 // Eq. 1 and I_n = sum_m A_mn):
 //   pass 1  attn_fwd : per 64-query tile, stream key tiles with an online softmax,

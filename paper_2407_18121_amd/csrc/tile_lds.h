@@ -7,6 +7,7 @@
 namespace ec {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;  // at any element of a 16-bit tensor
 
 // Workgroups are handed to the 8 XCDs round-robin by linear id, and each XCD has its own L2.  Work items are therefore
 // renumbered so that all tiles of a head (which share its K and V) sit behind the same L2 instead of being fetched
@@ -98,7 +99,11 @@ __device__ __forceinline__ void tile_barrier()
 // Moves ROWS rows (of D 16-bit words each) starting at row0 of a matrix into LDS, WAVES waves sharing the work; issue(lds, row0, j), j in
 // 0..NI-1, is one load instruction of this wave, so that a kernel can spread them over its arithmetic.  The bounds check
 // of the descriptor covers rows beyond the matrix: nothing is read there, and the caller masks what they produce.
-template <int D, int ROWS, int WAVES, typename SWZ> struct TileToLds {
+// A kernel that has arithmetic to put between the two halves of a move calls begin and later, in front of the barrier
+// behind which the tile is read, finish; issue is both at once.
+// DIRECT = false: for matrices that do not start on a 16-byte boundary, which loads straight into LDS need.  The rows
+// pass through registers then, in flight from begin to finish.
+template <int D, int ROWS, int WAVES, typename SWZ, bool DIRECT = true> struct TileToLds {
     static constexpr int CH = D / 8;            // 16-byte chunks per row
     static constexpr int RPI = kWave / CH;      // rows one wave moves per instruction
     static constexpr int NI = ROWS / RPI / WAVES;
@@ -108,6 +113,7 @@ template <int D, int ROWS, int WAVES, typename SWZ> struct TileToLds {
     u32x4 rsrc;
     int w0;                                     // first row of the wave's share (scalar)
     uint32_t part[PARTS];
+    mutable u32x4 held[DIRECT ? 1 : NI];
     __device__ __forceinline__ TileToLds(u32x4 r, int wave, int lane) : rsrc(r), w0(wave * NI * RPI)
     {
 #pragma unroll
@@ -117,9 +123,26 @@ template <int D, int ROWS, int WAVES, typename SWZ> struct TileToLds {
         }
     }
     // lds: byte address of the tile (scalar)
+    __device__ __forceinline__ void begin(uint32_t lds, int row0, int j) const
+    {
+        const uint32_t at = part[j % PARTS] + (uint32_t)(row0 + w0 + j / PARTS * PARTS * RPI) * (D * 2);
+        if constexpr (DIRECT) {
+            load_lds_16(rsrc, lds + (w0 + j * RPI) * (D * 2), at);
+        } else {
+            typedef __attribute__((address_space(1))) const u32x4_any global_u32x4;
+            held[j] = u32x4{0, 0, 0, 0};
+            if (at < rsrc.z) held[j] = *(global_u32x4*)(((uint64_t)rsrc.y << 32 | rsrc.x) + at);
+        }
+    }
+    __device__ __forceinline__ void finish(uint32_t lds, int j) const
+    {
+        typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+        if constexpr (!DIRECT) *(lds_u32x4*)(uintptr_t)(lds + (w0 + j * RPI) * (D * 2) + threadIdx.x % kWave * 16) = held[j];
+    }
     __device__ __forceinline__ void issue(uint32_t lds, int row0, int j) const
     {
-        load_lds_16(rsrc, lds + (w0 + j * RPI) * (D * 2), part[j % PARTS] + (uint32_t)(row0 + w0 + j / PARTS * PARTS * RPI) * (D * 2));
+        begin(lds, row0, j);
+        finish(lds, j);
     }
 };
 

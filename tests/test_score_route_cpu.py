@@ -8,7 +8,7 @@ import pytest
 from paper_2407_18121_amd import binding as ec
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2407_18121_amd", "csrc")
-MFMA, F32, SIMT = range(3)
+MFMA, F32, SIMT, MFMA_OFF_GRID = range(4)
 PROGRAM = r"""
 #include <stdio.h>
 #include <stdlib.h>
@@ -50,7 +50,9 @@ def test_heads_beyond_the_descriptors_take_the_vector_kernels(route, dt, D, matr
 
 
 def test_rows_off_the_16_byte_grid(route):
-    for dt, matrix, element in ((ec.EC_F32, F32, 4), (ec.EC_BF16, MFMA, 2)):
-        assert route([(dt, 64, 500, ON), (dt, 64, 500, (16, 32, 48, 64))]) == [matrix] * 2
-        for i in range(4):
-            assert route([(dt, 64, 500, tuple(element if j == i else 0 for j in range(4)))]) == [SIMT]
+    """bf16 stays on the matrix cores wherever its tensors start; out may start anywhere in either of its forms."""
+    for off in ((2, 0, 0, 0), (0, 2, 0, 0), (0, 0, 8, 0), (2, 4, 8, 6)):
+        assert route([(ec.EC_BF16, D, rows, off) for D in (64, 128) for rows in (1, 500, 100000)]) == [MFMA_OFF_GRID] * 6
+    assert route([(ec.EC_BF16, 64, 500, off) for off in (ON, (0, 0, 0, 2), (16, 32, 48, 64))]) == [MFMA] * 3
+    assert route([(ec.EC_F32, 64, 500, off) for off in (ON, (16, 32, 48, 64))]) == [F32] * 2
+    assert route([(ec.EC_F32, 64, 500, tuple(4 * (j == i) for j in range(4))) for i in range(4)]) == [SIMT] * 4
