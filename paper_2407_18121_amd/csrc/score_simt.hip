@@ -27,13 +27,16 @@ struct alignas(16) SimtSmem {
     float kt[kDC][kBN + 4];  // transposed K chunk: [d][col]
 };
 
+// Four elements, which may start at any element of a tensor: the types say so to the compiler.
+typedef float __attribute__((ext_vector_type(4), aligned(4))) f32x4_any;
+typedef uint32_t __attribute__((ext_vector_type(2), aligned(2))) u32x2_any;
 template <int DT> __device__ __forceinline__ void load4(const void* base, size_t elem_off, float* f)
 {
     if constexpr (DT == EC_F32) {
-        const float4 x = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(base) + elem_off);
+        const f32x4_any x = *reinterpret_cast<const f32x4_any*>(reinterpret_cast<const float*>(base) + elem_off);
         f[0] = x.x; f[1] = x.y; f[2] = x.z; f[3] = x.w;
     } else {
-        const uint2 x = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(base) + elem_off);
+        const u32x2_any x = *reinterpret_cast<const u32x2_any*>(reinterpret_cast<const uint16_t*>(base) + elem_off);
         f[0] = __uint_as_float(x.x << 16);
         f[1] = __uint_as_float(x.x & 0xffff0000u);
         f[2] = __uint_as_float(x.y << 16);
