@@ -705,11 +705,13 @@ __global__ __launch_bounds__(kEvictMetaThreads) void evict_min_meta_kernel(float
     const int bg = blockIdx.x, tid = threadIdx.x;
     float* f = freq + (size_t)bg * cap;
     int32_t* p = pos ? pos + (size_t)bg * cap : nullptr;
-    // (mass, index) as one integer whose order is the fp32 order, -0 equal to +0, the lower index first
+    // (mass, index) as one integer whose order is the fp32 order, -0 equal to +0, NaN of either sign behind +inf, the lower
+    // index first
     unsigned long long best = ~0ull;
     for (int j = lo + tid; j <= hi; j += kEvictMetaThreads) {
         uint32_t u = __float_as_uint(f[j]);
         if (u == 0x80000000u) u = 0u;
+        if ((u & 0x7fffffffu) > 0x7f800000u) u = 0x7fffffffu;
         u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
         best = min(best, ((unsigned long long)u << 32) | (uint32_t)j);
     }

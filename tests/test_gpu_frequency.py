@@ -111,6 +111,23 @@ def test_evict_min_of_infinite_masses(length):
         assert torch.isinf(freq[0, 0, :length - 1]).all()
 
 
+@pytest.mark.parametrize("bits", [0x7fc00000, 0xffc00000, 0xff800001])
+def test_evict_min_of_masses_that_are_not_numbers(bits):
+    """NaN of either sign never goes before a number."""
+    length, least = 700, 333
+    kc = torch.arange(length, dtype=torch.float32, device="cuda")[None, None, :, None].expand(1, 1, length, 64).contiguous()
+    mass = np.linspace(1.0, 2.0, length, dtype=np.float32)
+    mass[[5, 100, 301, 650]] = np.array([bits], np.uint32).view(np.float32)
+    for value in (0.5, np.inf):
+        mass[least] = value
+        if value == np.inf:   # +inf is the only number left
+            mass[np.arange(length) != least] = np.array([bits], np.uint32).view(np.float32)
+        freq, victim = torch.from_numpy(mass.copy()[None, None]).cuda(), torch.full((1, 1), -1, dtype=torch.int32, device="cuda")
+        ec.ec_evict_min(kc.clone(), -kc, None, freq, length, 3, 1, victim)
+        torch.cuda.synchronize()
+        assert victim.item() == least
+
+
 def test_frequency_generation_against_the_oracle():
     """Forty generated tokens under the frequency policy at a fixed budget.  Each step the oracle's own
     counts (rounded to fp32) are what both sides choose the victim from."""
