@@ -62,6 +62,25 @@ def test_chunk_score_parity(dtype, D, B, H, Tq, P, extra, Gmode):
     np.testing.assert_allclose(score.sum(-1), Tq, rtol=1e-5)   # every query row of A sums to one
 
 
+@pytest.mark.parametrize("dtype,D,B,H,Tq,P", [
+    # two groups per tile in the forward pass: 1024 rows and more, at most 256 workgroups; and a row less
+    ("bf16", 128, 1, 2, 700, 324), ("bf16", 128, 1, 2, 130, 1000), ("bf16", 64, 1, 2, 5, 1100), ("bf16", 64, 1, 2, 200, 823),
+    # pairs of query tiles: with too few key tiles to pair, with pairs of them (2 P <= Tq) and with a prefix one row too long
+    ("bf16", 64, 4, 32, 385, 57), ("bf16", 64, 4, 32, 700, 350), ("bf16", 128, 4, 32, 700, 350), ("bf16", 64, 4, 32, 700, 351),
+    # fp32: one wave per 16 queries, then two waves on the keys of 16; two and one key block(s) per workgroup
+    ("f32", 64, 4, 32, 257, 17), ("f32", 128, 4, 32, 257, 257), ("f32", 64, 16, 32, 1, 300),
+    ("f32", 64, 4, 32, 130, 17), ("f32", 128, 4, 32, 65, 257), ("f32", 128, 1, 40, 200, 33), ("f32", 64, 1, 128, 3, 90),
+])
+def test_chunk_score_launch_shapes(dtype, D, B, H, Tq, P):
+    """Every launch shape of either type with a prefix, whose shifted diagonal changes the tile range and the masks."""
+    q, k, v, scale = _chunk_inputs(B, H, Tq, P, D, dtype, 2500 + Tq + P)
+    ref = oracle.chunk_score(q, k, v, P, scale, 1)
+    out, lse, score = run_gpu_chunk(q, k, v, P, 2, dtype, scale, 1)
+    assert_close(out, ref["out"], dtype, "out")
+    assert_close(lse, ref["lse"], dtype, "lse")
+    assert_close(score, ref["score"], dtype, "score")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_chunk_score_without_prefix_is_prefill_score(dtype):
     B, H, T, D = 2, 2, 333, 64

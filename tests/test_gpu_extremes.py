@@ -12,8 +12,8 @@ pytestmark = pytest.mark.gpu
 # (dtype, heads, rows) of every launch shape at D = 64
 SHAPES = [
     ("f32", 2, 200), ("f32", 32, 200), ("f32", 128, 200),     # four, two, one wave(s) on the keys of 16 queries
-    ("bf16", 2, 200), ("bf16", 128, 200),                     # single tiles: one, two groups in the column pass
-    ("bf16", 2, 300), ("bf16", 2, 1100), ("bf16", 128, 900),  # either side of two groups per tile; pairs
+    ("bf16", 130, 200), ("bf16", 2, 200), ("bf16", 2, 300),   # single tiles; the same, two groups in the column pass
+    ("bf16", 2, 1100), ("bf16", 128, 900),                    # two groups in both passes; pairs in both
 ]
 
 

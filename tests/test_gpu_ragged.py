@@ -113,6 +113,32 @@ def test_prefill_score_ragged_paired_tiles(D):
         assert (out[b, :, n:] == 5.0).all()  # rows beyond the sequence are left alone
 
 
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("dtype,H,lens", [
+    ("bf16", 2, [1100, 0, 64, 1024]),   # two groups per tile
+    ("f32", 64, [129, 0, 1, 65]),       # one wave per 16 queries
+    ("f32", 32, [129, 0, 1, 65]),       # two waves on the keys of 16 queries
+])
+def test_prefill_score_ragged_launch_shapes(dtype, H, lens, D):
+    """The other launch shapes that small batches do not reach."""
+    B, T = len(lens), max(lens)
+    cfg = syn.custom("t", H=H, D=D, B=B, T=T, dtype=dtype, cid=3950)
+    q, k, v = syn.prompt_qkv(cfg)
+    dq, dk, dv = (_nan_pad(x, lens, dtype) for x in (q, k, v))
+    out = torch.full((B, H, T, D), 5.0, dtype=torch_dtype(dtype), device="cuda")
+    lse = torch.full((B, H, T), 5.0, dtype=torch.float32, device="cuda")
+    score = torch.full((B, H, T), 5.0, dtype=torch.float32, device="cuda")
+    ws = ec.new_workspace(ec.EC_FN_PREFILL_SCORE, B, H, T, D, ec.dtype_code(dq))
+    ec.ec_prefill_score_varlen(dq, dk, dv, out, lse, score, _i32(lens), cfg.scale, ws)
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        if n:
+            r = oracle.prefill_score(q[b:b + 1, :, :n], k[b:b + 1, :, :n], v[b:b + 1, :, :n], cfg.scale, H)
+            for name, x in (("out", out), ("lse", lse), ("score", score)):
+                assert_close(to_host(x[b:b + 1, :, :n]), r[name], dtype, f"{name}[{b}]")
+        assert (out[b, :, n:] == 5.0).all()
+
+
 @pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f32", 64)])
 @pytest.mark.parametrize("H,G,cap,lens,victims", [
     (2, 1, 40, [5, 0, 39, 17], [-1, 0, 14, 17]),          # append, drop the only row, shift, drop the new row

@@ -61,15 +61,17 @@ def test_tiny_config_full_layer():
 
 @pytest.mark.parametrize("D", [128, 64])
 @pytest.mark.parametrize("B,H,T", [
-    (1, 2, 255, ),    # one key tile short of the two-group launch shape
-    (1, 2, 256, ),    # its first length
-    (2, 16, 1024, ),  # 256 workgroups: the largest launch that takes it
+    (1, 2, 255, ),    # two groups in the column pass only: a row short of two tiles
+    (1, 2, 256, ),    # two whole tiles
+    (1, 2, 1023, ),   # one row short of the two-group forward pass
+    (1, 2, 1024, ),   # its first length
+    (2, 16, 1024, ),  # 256 workgroups: the largest launch that takes it in either pass (pairs in the forward pass: 128)
     (1, 33, 1024, ),  # 264 workgroups: the smallest that does not
     (1, 3, 1100, ),   # odd number of key and of query tiles, ragged tail
 ])
 def test_prefill_score_launch_shapes_of_short_prompts(D, B, H, T):
     """bf16 launches of at most 256 workgroups run two wave groups per workgroup (alternate key tiles in the
-    forward pass, alternate query tiles in the column pass); both sides of every threshold are checked."""
+    forward pass, from 1024 rows on; alternate steps of 32 queries in the column pass); both sides of either threshold."""
     cfg = syn.custom("t", H=H, D=D, B=B, T=T, dtype="bf16", cid=4000 + T + H)
     q, k, v = syn.prompt_qkv(cfg)
     ref = oracle.prefill_score(q, k, v, cfg.scale, 1)
@@ -85,7 +87,8 @@ def test_prefill_score_launch_shapes_of_short_prompts(D, B, H, T):
     (4, 32, 385),   # the shortest prompt whose query tiles are taken in pairs: four tiles, the last of one row
     (2, 43, 640),   # five full tiles: the middle one has no partner; head count that the XCDs do not divide
     (4, 32, 769),   # the shortest whose key tiles are: four tiles of 256, the last of one key
-    (8, 8, 1281),   # an odd number of either, ragged tails
+    (8, 8, 1281),   # eleven query tiles in pairs; the 192 pairs of key tiles are too few
+    (4, 32, 1100),  # five key tiles in pairs: the middle one has no partner
 ])
 def test_prefill_score_paired_tiles(D, B, H, T):
     """bf16 launches with enough workgroups give each of them two tiles of a head."""
@@ -102,11 +105,15 @@ def test_prefill_score_paired_tiles(D, B, H, T):
 
 @pytest.mark.parametrize("D", [128, 64])
 @pytest.mark.parametrize("B,H,T", [
-    (4, 64, 1), (4, 64, 15), (4, 64, 63),  # one wave per 16 queries, keys shared by nobody: a tile and less
+    # One wave per 16 queries, keys shared by nobody, from 512 workgroups' worth of 64 queries on:
+    (8, 64, 1), (8, 64, 15), (8, 64, 63),  # less than a tile
     (4, 64, 65), (8, 32, 130),             # tiles of 32 keys and of 64 queries with a remainder of one and of two
-    (1, 3, 16), (1, 3, 17), (1, 51, 257),  # four waves share the keys of 16 queries: block and tile edges
-    (1, 32, 200), (2, 13, 257),            # two waves share them: 128 and 130 workgroups' worth of 64 queries
-    (2, 52, 257), (4, 32, 129),            # either side of the widest launch that does
+    (2, 52, 257),                          # 520 workgroups
+    # two waves share the keys of 16 queries, from 128 on:
+    (4, 64, 1), (4, 64, 15), (4, 64, 63),  # less than a tile
+    (1, 128, 64), (1, 32, 200), (2, 13, 257), (1, 51, 257), (4, 32, 129),  # 128, 128, 130, 255 and 384
+    # four waves share them:
+    (1, 3, 16), (1, 3, 17), (1, 127, 64), (1, 25, 257),  # block and tile edges, 127 and 125
 ])
 def test_prefill_score_fp32_launch_shapes(D, B, H, T):
     cfg = syn.custom("t", H=H, D=D, B=B, T=T, dtype="f32", cid=4700 + T + H)
