@@ -10,11 +10,13 @@
 //                  no atomics, deterministic.
 // Bound: the matrix pipe at its fp32 rate (a sixteenth of the bf16 one; 149 TFLOP/s in a large product here); a block costs
 // 64 instructions of 32 clocks (D = 128) against some 30 vector instructions, so the phases simply follow each other and
-// the other wave of the SIMD fills the gaps.  Measured, before (vector ALU) -> after: B1 H32 T1024 D128 498 + 221 -> 102 + 52 us
-// (84 TFLOP/s over both passes; a workgroup loops over up to 32 tiles while the mean is 16; 109 + 52 us with the waits for
-// the operands inside the loop), B1 H4 T256 D64 61 + 22 -> 7.7 + 4.3 us.
-// Error of out against 64 bits at T1024 6.3e-7 -> 2.8e-7, of the scores 1.3e-7 -> 0.7e-7.  Operands are read from LDS 16 bytes at a time, each read feeding four
-// instructions: both operands of a contraction enumerate it in the same permuted order.
+// the other wave of the SIMD fills the gaps.  Measured, before (vector ALU) -> after: whole call at B1 H32 T1024 D128
+// 694 -> 143 us (90 TFLOP/s; a workgroup loops over up to 32 tiles while the mean is 16).  By the profiler, which times
+// every launch by itself and adds its start, the two passes take 498 + 221 -> 103 + 53 us there (109 + 52 us with the
+// waits for the operands inside the loop) and 61 + 22 -> 7.9 + 4.8 us at B1 H4 T256 D64.
+// Error of out against 64 bits at T1024 6.3e-7 -> 2.7e-7, of the scores 1.3e-7 -> 0.7e-7.
+// Operands are read from LDS 16 bytes at a time, each read feeding four instructions: both operands of a contraction
+// enumerate it in the same permuted order.
 //
 // Operand layout (wave64, lane l, quarter h = l / 16): A (16 x 4): lane holds A[l % 16][h];  B (4 x 16): B[h][l % 16];
 //   C (16 x 16): lane holds C[4h + r][l % 16] in register r.
@@ -54,8 +56,9 @@ inline int f32_grid(int n_tiles, int n_heads) { return (n_heads + kXcds - 1) / k
 
 // S^T = K.Q^T of NBLK blocks of 16 keys against the wave's 16 queries, in four chains per block: shorter sums, and no
 // instruction waits for the one before it.
-template <int D, int NBLK> __device__ __forceinline__ void score_blocks(const uint32_t (&at)[NBLK], const f32x4 (&qf)[D / 16], int swz, int h,
-                                                                       f32x4 (&s)[NBLK])
+template <int D, int NBLK>
+__device__ __forceinline__ void score_blocks(const uint32_t (&at)[NBLK], const f32x4 (&qf)[D / 16], int swz, int h,
+                                             f32x4 (&s)[NBLK])
 {
     f32x4 t[NBLK][4];
 #pragma unroll
@@ -269,12 +272,12 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
 template <int D, int KW, int QG>
 __global__ __launch_bounds__(kF32Waves * kWave, 2) void colsum_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ lse, float lse_unit,
-    float* __restrict__ head_imp, ScoreGeom geo, float scale_log2e, int n_ktiles, int n_heads, const int32_t* __restrict__ seq_len, int H)
+    float* __restrict__ head_imp, ScoreGeom geo, float scale_log2e, int n_ktiles, int n_heads,
+    const int32_t* __restrict__ seq_len, int H)
 {
     static_assert(KW * QG == kF32Waves, "four waves");
     constexpr int BN = KW * 16;
-        constexpr int NBLK = 1;                // query blocks of a tile per wave
-    constexpr int TQ = 16 * NBLK * QG;     // queries per tile
+    constexpr int TQ = 16 * QG;  // queries per tile
     constexpr int KB = D / 16;
     constexpr int TILE = TQ * D * 4;
     using Mover = TileToLds<2 * D, TQ, kF32Waves, Swizzle16>;
@@ -297,12 +300,11 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void colsum_f32_kernel(
     const uint32_t base = lds_address(tiles);
     const int m_begin = max(n0 - P, 0) / TQ * TQ;  // first tile with a query that sees key n0
     const int n_tiles = (Tq - m_begin + TQ - 1) / TQ;
-    float l2_next[NBLK];  // log-sum-exp of the lane's query in every block of the tile being fetched
+    float l2_next;  // log-sum-exp of the lane's query in the tile being fetched
     auto fetch = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < Mover::NI; ++j) q_move.issue(base + t % 2 * TILE, m_begin + t * TQ, j);
-#pragma unroll
-        for (int b = 0; b < NBLK; ++b) l2_next[b] = lh[min(m_begin + t * TQ + (b * QG + qg) * 16 + r16, Tq - 1)];
+        l2_next = lh[min(m_begin + t * TQ + qg * 16 + r16, Tq - 1)];
     };
     fetch(0);
 
@@ -317,42 +319,29 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void colsum_f32_kernel(
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(kf[kb]));
     for (int t = 0; t < n_tiles; ++t) {
-        const int m0 = m_begin + t * TQ + qg * 16;  // the wave's blocks start 16 QG queries apart
+        const int m0 = m_begin + t * TQ + qg * 16;  // first query of the wave's block
         wait_loads();
         wait_lds();
         meet();  // tile t has landed, tile t - 1 has been read
-        float l2[NBLK];
-#pragma unroll
-        for (int b = 0; b < NBLK; ++b) l2[b] = l2_next[b] * lse_unit;
+        const float l2 = l2_next * lse_unit;
         if (t + 1 < n_tiles) fetch(t + 1);
-        if (P + m0 + (NBLK - 1) * 16 * QG + 15 < nw) continue;  // no query of the tile sees a key of this wave
-        f32x4 s[NBLK][4];
+        if (P + m0 + 15 < nw) continue;  // no query of the tile sees a key of this wave
+        f32x4 s[4];
 #pragma unroll
-        for (int b = 0; b < NBLK; ++b)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s[b][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < 4; ++e) s[e] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
-            f32x4 a[NBLK];
+            const f32x4 a = lds_read(base + t % 2 * TILE + (qg * 16 + r16) * (D * 4) + ((4 * kb + h) ^ r16) * 16);
 #pragma unroll
-            for (int b = 0; b < NBLK; ++b)
-                a[b] = lds_read(base + t % 2 * TILE + ((b * QG + qg) * 16 + r16) * (D * 4) + ((4 * kb + h) ^ r16) * 16);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int b = 0; b < NBLK; ++b)
-                    s[b][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][e], a[b][e], s[b][e], 0, 0, 0);
+            for (int e = 0; e < 4; ++e) s[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][e], a[e], s[e], 0, 0, 0);
         }
+        const int m = m0 + r16;
+        const int last = m < Tq ? P + m - nw - 4 * h : -1;  // last of the lane's keys that its query sees
 #pragma unroll
-        for (int b = 0; b < NBLK; ++b) {
-            const int m = m0 + b * 16 * QG + r16;
-            const int last = m < Tq ? P + m - nw - 4 * h : -1;  // last of the lane's keys that its query sees
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float x = (s[b][0][r] + s[b][1][r]) + (s[b][2][r] + s[b][3][r]);
-                const float p = exp2f(fmaf(x, scale_log2e, -l2[b]));
-                col[r] += r <= last ? p : 0.f;
-            }
+        for (int r = 0; r < 4; ++r) {
+            const float x = (s[0][r] + s[1][r]) + (s[2][r] + s[3][r]);
+            const float p = exp2f(fmaf(x, scale_log2e, -l2));
+            col[r] += r <= last ? p : 0.f;
         }
     }
 #pragma unroll
@@ -391,8 +380,8 @@ static int launch_f32(const float* q, const float* k, const float* v, float* out
     } while (0)
     // us of the whole call for 64 / 32 / 16 queries per workgroup (one / two / four waves on the keys of 16 queries), H32
     // D128, the column pass alike:
-    //   B1 T256 39.0 / 32.1 / 32.8   B1 T512 71.0 / 58.6 / 74.7   B1 T1024 153 / 160 / 209   B4 T256 51.0 / 55.2 / 87.7
-    //   B1 T2048 498 / 529 / 730   H16 B1 T1024 123 / 95 / 117   H8 B1 T512 64.2 / 49.5 / 38.4
+    //   B1 T256 38.7 / 32.2 / 32.8   B1 T512 68.7 / 56.6 / 71.5   B1 T1024 143 / 151 / 208   B4 T256 50.3 / 54.1 / 85.7
+    //   B1 T2048 496 / 523 / 733   H16 B1 T1024 124 / 95 / 118   H8 B1 T512 64.8 / 49.7 / 38.2
     const long long wide = (long long)qt64 * BH;
     if (wide >= 512)
         EC_FWD_F32(4, 1, qt64);
@@ -404,8 +393,9 @@ static int launch_f32(const float* q, const float* k, const float* v, float* out
     int rc = status_from_hip(hipGetLastError());
     if (rc != EC_OK) return rc;
     const int kt32 = (geo.L + 31) / 32, kt16 = (geo.L + 15) / 16;
-    // us of the whole call for 32 / 16 keys per workgroup, the forward pass alike: B1 T256 39.0 / 37.4   B1 T512 71.0 / 73.1
-    //   B1 T1024 153 / 157   B4 T256 51.0 / 59.0   H8 B1 T512 64.2 / 58.3   (64 keys, column pass alone at T1024: 62 against 53)
+    // us of the whole call for 32 / 16 keys per workgroup, 64 queries per workgroup in the forward pass:
+    //   B1 T256 38.7 / 37.4   B1 T512 68.7 / 70.9   B1 T1024 143 / 155   B4 T256 50.3 / 58.9   H8 B1 T512 64.8 / 58.8
+    //   (64 keys, column pass alone at T1024: 62 against 53)
     if ((long long)kt32 * BH >= 512)
         hipLaunchKernelGGL((colsum_f32_kernel<D, 2, 2>), dim3(f32_grid(kt32, BH)), block, 0, stream, q, k, lse, unit_in,
                            head_imp, geo, sl, kt32, BH, seq_len, H);
@@ -417,14 +407,15 @@ static int launch_f32(const float* q, const float* k, const float* v, float* out
 
 // Per-head importance into head_imp [B,H,L]; out may be NULL (then v is not read).  lse is a scratch row unless lse_wanted.
 int score_f32_dispatch(const void* q, const void* k, const void* v, void* out, float* lse, bool lse_wanted,
-                       float* head_imp, int B, int H, ScoreGeom geo, const int32_t* seq_len, int D, float scale, hipStream_t stream)
+                       float* head_imp, int B, int H, ScoreGeom geo, const int32_t* seq_len, int D, float scale,
+                       hipStream_t stream)
 {
     if (D == 128)
-        return launch_f32<128>((const float*)q, (const float*)k, (const float*)v, (float*)out, lse, lse_wanted, head_imp, B, H, geo,
-                               seq_len, scale, stream);
+        return launch_f32<128>((const float*)q, (const float*)k, (const float*)v, (float*)out, lse, lse_wanted, head_imp,
+                               B, H, geo, seq_len, scale, stream);
     if (D == 64)
-        return launch_f32<64>((const float*)q, (const float*)k, (const float*)v, (float*)out, lse, lse_wanted, head_imp, B, H, geo,
-                              seq_len, scale, stream);
+        return launch_f32<64>((const float*)q, (const float*)k, (const float*)v, (float*)out, lse, lse_wanted, head_imp,
+                              B, H, geo, seq_len, scale, stream);
     return EC_EUNSUPPORTED;
 }
 
