@@ -689,11 +689,20 @@ int decode_score_dispatch(const void* q, const void* k_new, const void* v_new, v
 // ec_evict_min in two launches: one workgroup per score group finds the least-mass row and closes the gap in the group's
 // masses and positions, then two workgroups per (batch, head), one for K and one for V, move the rows behind it up by
 // one.  The first launch is a chain of latencies (load, reduction, load, store), the second moves 2 * row bytes * rows
-// behind the victim, half the cache for a victim anywhere.  Everything that moves is held in registers between one
-// barrier's two sides as far as the unroll reaches (512 rows of 256 bytes), so the usual case is one round of loads.
-// Measured at B8 H32 D128, 641 rows, bf16 (rows + bookkeeping): victims anywhere 59 + 4.8 us when every (batch, head)
-// looked for the victim itself and moved 64 rows a round, 40 + 5.2 us now; victims
-// 26 rows from the end 20 + 4.8 and 4.7 + 3.9 us.
+// behind the victim, half the cache for a victim anywhere.  What a round moves (256 rows of 256 bytes) is held in
+// registers between the two sides of a barrier, all its loads in flight at once: threads past the end read the last
+// element again instead of branching around the load, which would make every load wait for the one before it.
+// Measured at H32 D128, bf16, victims anywhere, whole call (four caches in turn): B8 640 rows 42.8 -> 21.2 us, B16 900 rows
+// 110 -> 58.5 us, B1 640 rows 13.2 -> 7.4 us from 512 rows a round, which went through scratch memory one by one.
+// Threads x loads 256 x 8 to 1024 x 8 differ by 5 %; more than 8 loads cost small caches up to 30 %.
+
+// All of x has arrived in registers: what follows neither waits for it nor runs before it.
+template <typename T, int N> __device__ __forceinline__ void arrived(T (&x)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));
+}
+
 constexpr int kEvictMetaThreads = 1024;
 constexpr int kEvictMetaUnroll = 4;
 __global__ __launch_bounds__(kEvictMetaThreads) void evict_min_meta_kernel(float* freq, int32_t* pos,
@@ -731,12 +740,12 @@ __global__ __launch_bounds__(kEvictMetaThreads) void evict_min_meta_kernel(float
         int32_t pv[kEvictMetaUnroll];
 #pragma unroll
         for (int u = 0; u < kEvictMetaUnroll; ++u) {
-            const int c = c0 + u * kEvictMetaThreads + tid;
-            if (c < total) {
-                fv[u] = f[vic + 1 + c];
-                pv[u] = p ? p[vic + 1 + c] : 0;
-            }
+            const int c = min(c0 + u * kEvictMetaThreads + tid, total - 1);
+            fv[u] = f[vic + 1 + c];
+            pv[u] = p ? p[vic + 1 + c] : 0;
         }
+        arrived(fv);
+        arrived(pv);
         __syncthreads();  // read completely before any of it is overwritten
 #pragma unroll
         for (int u = 0; u < kEvictMetaUnroll; ++u) {
@@ -751,24 +760,25 @@ __global__ __launch_bounds__(kEvictMetaThreads) void evict_min_meta_kernel(float
 }
 
 constexpr int kEvictThreads = 512;
-constexpr int kEvictUnroll = 16;
-__global__ __launch_bounds__(kEvictThreads) void evict_min_rows_kernel(uint4* k_cache, uint4* v_cache,
+constexpr int kEvictUnroll = 8;
+__global__ __launch_bounds__(kEvictThreads) void evict_min_rows_kernel(u32x4* k_cache, u32x4* v_cache,
                                                                        const int32_t* __restrict__ victim, int H, int G,
                                                                        int cap, int len, int lpr)
 {
     const int bh = blockIdx.x, tid = threadIdx.x;
     const int b = bh / H, h = bh % H;
     const int vic = victim[(size_t)b * G + (G == 1 ? 0 : h)];
-    uint4* dst = (blockIdx.y == 0 ? k_cache : v_cache) + ((size_t)bh * cap + vic) * lpr;
-    const uint4* src = dst + lpr;
+    u32x4* dst = (blockIdx.y == 0 ? k_cache : v_cache) + ((size_t)bh * cap + vic) * lpr;
+    const u32x4* src = dst + lpr;
     const int total = (len - 1 - vic) * lpr;  // 16-byte chunks that move, in ascending address order
     for (int c0 = 0; c0 < total; c0 += kEvictThreads * kEvictUnroll) {
-        uint4 x[kEvictUnroll];
+        u32x4 x[kEvictUnroll];
 #pragma unroll
         for (int u = 0; u < kEvictUnroll; ++u) {
-            const int c = c0 + u * kEvictThreads + tid;
-            if (c < total) x[u] = src[c];
+            const int c = min(c0 + u * kEvictThreads + tid, total - 1);
+            x[u] = src[c];
         }
+        arrived(x);
         __syncthreads();  // the slab is read completely before any of it is overwritten
 #pragma unroll
         for (int u = 0; u < kEvictUnroll; ++u) {
@@ -787,8 +797,8 @@ int evict_min_dispatch(void* k_cache, void* v_cache, int32_t* pos, float* freq, 
                        protect_first, len - 1 - protect_recent);
     int rc = status_from_hip(hipGetLastError());
     if (rc != EC_OK) return rc;
-    hipLaunchKernelGGL(evict_min_rows_kernel, dim3(B * H, 2), dim3(kEvictThreads), 0, stream, (uint4*)k_cache,
-                       (uint4*)v_cache, victim, H, G, cap, len, lpr);
+    hipLaunchKernelGGL(evict_min_rows_kernel, dim3(B * H, 2), dim3(kEvictThreads), 0, stream, (u32x4*)k_cache,
+                       (u32x4*)v_cache, victim, H, G, cap, len, lpr);
     return status_from_hip(hipGetLastError());
 }
 

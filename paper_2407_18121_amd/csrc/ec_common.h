@@ -11,6 +11,10 @@ namespace ec {
 
 constexpr int kWave = 64;
 
+// 16 bytes in registers.  Arrays of it stay there, where an array of uint4 (a class with a union inside) that is filled
+// under a condition goes to scratch memory.
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
 // Element access for the two storage types.  A "chunk" is the 16 bytes one lane
 // moves per vector load: 4 fp32 or 8 bf16 values.
 template <int DT> struct Elem;

@@ -6,7 +6,6 @@
 
 namespace ec {
 
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef u32x4 __attribute__((aligned(2))) u32x4_any;  // at any element of a 16-bit tensor
 
 // Workgroups are handed to the 8 XCDs round-robin by linear id, and each XCD has its own L2.  Work items are therefore

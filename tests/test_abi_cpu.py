@@ -168,6 +168,21 @@ def test_scale_must_be_finite_and_positive():
                                          0, 0, 0, None) == ec.EC_EINVAL
 
 
+def test_kernels_keep_their_values_in_registers():
+    """The kernels' own metadata in the library: no scratch memory in any kernel that a launch rule chooses for ordinary calls.
+    (Sixteen waves with six rows each are reachable through ec_decode_step_shaped only; the forward pass for tensors off
+    the 16-byte grid holds its tiles in registers as well.)"""
+    blob = open(ec.LIB_PATH, "rb").read()
+    scratch = {}
+    for m in re.finditer(rb"\xa5\.name(?:[\xa0-\xbf]|\xd9.|\xda..)(_ZN2ec\w+)\xbb\.private_segment_fixed_size(\xcd..|\xcc.|[\x00-\x7f])",
+                         blob, re.S):
+        value = m.group(2)
+        scratch[m.group(1).decode()] = int.from_bytes(value[1:], "big") if value[0] in (0xcc, 0xcd) else value[0]
+    assert len(scratch) > 100 and any("evict_min_rows" in n for n in scratch)
+    elsewhere = re.compile(r"decode_step_kernelILi\dELi\d+ELi16ELi6E|attn_fwd_mfma_kernelILi128ELi4ELi1ELb0ELb1ELb0E")
+    assert {n: x for n, x in scratch.items() if x and not elsewhere.search(n)} == {}
+
+
 def test_tune_tool_usage():
     """The timing tool prints its usage for an unknown table and refuses to run without a GPU."""
     import torch
