@@ -24,6 +24,7 @@
 //   C (32 x 32): lane holds C[8g + 4h + t][l % 32] in register 4g + t, g,t in 0..3
 #include <type_traits>
 
+#include "score_route.h"
 #include "tile_lds.h"
 
 namespace ec {
@@ -37,7 +38,6 @@ typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
 
 constexpr int kFwdBN = 64;   // keys per LDS tile
 constexpr int kSplitMaxWorkgroups = 256;  // launches of at most this many workgroups divide a workgroup's loop over two wave groups
-constexpr int kPairMinWorkgroups = 256;   // workgroups take two tiles each when at least this many are left
 
 // Chunk permutations of the LDS tiles (see TileToLds).
 template <int D> struct SwizzleRows {  // operand reads of 16 consecutive rows at one chunk number touch every bank once
@@ -750,28 +750,28 @@ static int launch_mfma(const uint16_t* q, const uint16_t* k, const uint16_t* v, 
     const int Tq = geo.Tq, L = geo.L;
     const int BH = B * H;
     const int qt128 = (Tq + 127) / 128;
-#define EC_FWD(KS_, PAIR_, DIRECT_)                                                                                           \
+#define EC_FWD(KS_, PAIR_, DIRECT_)                                                                                  \
     do {                                                                                                             \
         const dim3 grid(xcd_grid((PAIR_ ? (qt128 + 1) / 2 : qt128) * BH)), block(4 * KS_ * kWave);                    \
         if (out != nullptr)                                                                                          \
-            hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 4, KS_, PAIR_, true, DIRECT_>), grid, block, 0, stream, q, k, v, out,  \
-                               lse, geo, sl, qt128, BH, seq_len, H);                                                 \
+            hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 4, KS_, PAIR_, true, DIRECT_>), grid, block, 0, stream, q, k, \
+                               v, out, lse, geo, sl, qt128, BH, seq_len, H);                                         \
         else                                                                                                         \
-            hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 4, KS_, PAIR_, false, DIRECT_>), grid, block, 0, stream, q, k, v, out, \
-                               lse, geo, sl, qt128, BH, seq_len, H);                                                 \
+            hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, 4, KS_, PAIR_, false, DIRECT_>), grid, block, 0, stream, q,   \
+                               k, v, out, lse, geo, sl, qt128, BH, seq_len, H);                                      \
     } while (0)
     // Launch shapes of the forward pass, us (pairs / single tiles / two wave groups per tile), H 32, D 128:
     //   B1 T512 18.2 / 13.7 / 14.7    B1 T1024 26.4 / 22.6 / 22.2   B1 T2048 46.5 / 60.1 / 61.8   B2 T1024 29.0 / 33.3 / 39.9
     //   B4 T1024 47.0 / 63.4 / 75.9   B8 T1536 180 / 204 / 234      B2 T8192 1068 / 1112 / 1172   B16 H40 T256 35.9 / 33.2 / 49.1
     //   H8 B1: T1024 25.3 / 20.3 / 19.7   T2048 39.3 / 34.6 / 32.8   T4096 70.0 / 65.4 / 61.7
-    // Pairs from one per compute unit on (three tiles or fewer have nothing to even out); below that two groups per tile
-    // once the key loop is long enough to pay for merging them.
+    // Pairs by the rule of score_route.h; below it two groups per tile once the key loop is long enough to pay for merging
+    // them.
     // Off the 16-byte grid one shape serves all sizes: the loads themselves, two requests for every 128 bytes, set the pace
     // (whole call on / off the grid, B1 H32 T1024 D128 37 / 64 us, B8 T2048 503 / 831 us, B4 T8192 3.05 / 4.11 ms; in
     // pairs the latter two take 814 us and 4.13 ms).
     if (!direct)
         EC_FWD(1, false, false);
-    else if (qt128 >= 4 && (long long)((qt128 + 1) / 2) * BH >= kPairMinWorkgroups)
+    else if (pair_query_tiles(D, qt128, BH, Tq, geo.P))
         EC_FWD(1, true, true);
     else if ((long long)qt128 * BH <= kSplitMaxWorkgroups && L >= 1024)
         EC_FWD(2, false, true);
@@ -781,10 +781,10 @@ static int launch_mfma(const uint16_t* q, const uint16_t* k, const uint16_t* v, 
     int rc = status_from_hip(hipGetLastError());
     if (rc != EC_OK) return rc;
     const int kt256 = (L + 255) / 256, kt128 = (L + 127) / 128;
-#define EC_COLSUM(NB_, QG_, QT_, PAIR_, DIRECT_)                                                                              \
+#define EC_COLSUM(NB_, QG_, QT_, PAIR_, DIRECT_)                                                                     \
     do {                                                                                                             \
         const int kt = (L + 128 * NB_ - 1) / (128 * NB_);                                                            \
-        hipLaunchKernelGGL((colsum_mfma_kernel<D, NB_, 4, QG_, QT_, PAIR_, DIRECT_>),                                         \
+        hipLaunchKernelGGL((colsum_mfma_kernel<D, NB_, 4, QG_, QT_, PAIR_, DIRECT_>),                                \
                            dim3(xcd_grid((PAIR_ ? (kt + 1) / 2 : kt) * BH)), dim3(4 * QG_ * kWave), 0, stream, q, k, \
                            lse, head_imp, geo, sl, kt, BH, seq_len, H);                                              \
     } while (0)
@@ -794,7 +794,7 @@ static int launch_mfma(const uint16_t* q, const uint16_t* k, const uint16_t* v, 
     //   B16 H40 T512 63.5 / 50.0 / 82.5; a chunk of 1024 over 640 rows, B8: 117 / 99 (its first tiles are equally long: nothing to pair)
     if (!direct)
         EC_COLSUM(1, 1, 64, false, false);
-    else if (kt256 >= 4 && (long long)((kt256 + 1) / 2) * BH >= kPairMinWorkgroups && 2 * geo.P <= Tq)
+    else if (pair_key_tiles(D, kt256, BH, Tq, geo.P))
         EC_COLSUM(2, 1, 128, true, true);
     else if ((long long)kt128 * BH <= kSplitMaxWorkgroups)
         EC_COLSUM(1, 2, 128, false, true);

@@ -65,8 +65,9 @@ def test_chunk_score_parity(dtype, D, B, H, Tq, P, extra, Gmode):
 @pytest.mark.parametrize("dtype,D,B,H,Tq,P", [
     # two groups per tile in the forward pass: 1024 rows and more, at most 256 workgroups; and a row less
     ("bf16", 128, 1, 2, 700, 324), ("bf16", 128, 1, 2, 130, 1000), ("bf16", 64, 1, 2, 5, 1100), ("bf16", 64, 1, 2, 200, 823),
-    # pairs of query tiles: with too few key tiles to pair, with pairs of them (2 P <= Tq) and with a prefix one row too long
-    ("bf16", 64, 4, 32, 385, 57), ("bf16", 64, 4, 32, 700, 350), ("bf16", 128, 4, 32, 700, 350), ("bf16", 64, 4, 32, 700, 351),
+    # pairs of query tiles, with single key tiles; pairs of key tiles up to 2 P = Tq; pairs of both; neither
+    ("bf16", 128, 4, 32, 385, 57), ("bf16", 64, 8, 32, 385, 57), ("bf16", 64, 4, 32, 682, 341), ("bf16", 128, 4, 32, 682, 341),
+    ("bf16", 64, 4, 32, 682, 342), ("bf16", 64, 4, 32, 1024, 300), ("bf16", 128, 4, 32, 385, 386), ("bf16", 64, 8, 32, 385, 386),
     # fp32: one wave per 16 queries, then two waves on the keys of 16; two and one key block(s) per workgroup
     ("f32", 64, 4, 32, 257, 17), ("f32", 128, 4, 32, 257, 257), ("f32", 64, 16, 32, 1, 300),
     ("f32", 64, 4, 32, 130, 17), ("f32", 128, 4, 32, 65, 257), ("f32", 128, 1, 40, 200, 33), ("f32", 64, 1, 128, 3, 90),

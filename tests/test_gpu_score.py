@@ -84,11 +84,14 @@ def test_prefill_score_launch_shapes_of_short_prompts(D, B, H, T):
 
 @pytest.mark.parametrize("D", [128, 64])
 @pytest.mark.parametrize("B,H,T", [
-    (4, 32, 385),   # the shortest prompt whose query tiles are taken in pairs: four tiles, the last of one row
-    (2, 43, 640),   # five full tiles: the middle one has no partner; head count that the XCDs do not divide
+    (4, 32, 385),   # D 128: the shortest prompt whose query tiles are taken in pairs: four tiles, the last of one row
+    (8, 32, 385),   # the same in one full round: D 64 too
+    (2, 43, 640),   # D 128: five full tiles: the middle one has no partner; head count that the XCDs do not divide
+    (1, 44, 1409),  # twelve tiles, the last of one row, and a head count that they do not divide
     (4, 32, 769),   # the shortest whose key tiles are: four tiles of 256, the last of one key
     (8, 8, 1281),   # eleven query tiles in pairs; the 192 pairs of key tiles are too few
-    (4, 32, 1100),  # five key tiles in pairs: the middle one has no partner
+    (2, 32, 1600),  # seven key tiles in pairs: the middle one has no partner
+    (4, 32, 1100),  # neither: nine query tiles in more than a round, five key tiles
 ])
 def test_prefill_score_paired_tiles(D, B, H, T):
     """bf16 launches with enough workgroups give each of them two tiles of a head."""
