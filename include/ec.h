@@ -241,12 +241,10 @@ int ec_evict_index(int64_t n_seen, int len_after_append, int gamma_num, int gamm
  *   pos               DEVICE [B,G,cap] int32 original position of every row, updated
  *                     like the cache; may be NULL
  *   out               DEVICE [B,H,D] dt, written
- *   ws                DEVICE scratch, optional: ec_workspace_bytes(EC_FN_DECODE_STEP, B,H,cap,D,dt)
- *                     bytes, which is 0 for the launch shape the library picks itself (one workgroup
- *                     streams a whole (batch, head); nothing is staged), so ws may be NULL.  A shape
- *                     that divides a (batch, head) over several workgroups, whose partial results
- *                     meet in ws and are merged by a second launch on the same stream, exists and is
- *                     reached through ec_decode_step_shaped; it measured slower at every workload.
+ *   ws                not used, may be NULL (ec_workspace_bytes(EC_FN_DECODE_STEP, ...) is 0).  Few (batch,
+ *                     head) pairs with long caches are divided over several workgroups of the launch;
+ *                     their partial results meet in 2.2 MB of device memory built into the library, which
+ *                     launches on any streams share: a launch that finds a place taken does without it
  * Requires 0 <= cache_len < cap, -1 <= evict_idx <= cache_len and a finite scale > 0.  Dot
  * products and the softmax are evaluated in fp32.
  */
@@ -258,11 +256,11 @@ int ec_decode_step(const void* q, const void* k_new, const void* v_new, void* k_
 /*
  * ec_decode_step with an explicit launch shape, for tests and tuning sweeps (the library reads no
  * environment variable and keeps no state: a shape other than its own choice is requested here).
- *   waves   wavefronts per workgroup (0 = the library's choice)
- *   unroll  16-byte loads of K and of V each lane keeps in flight (0 = the library's choice)
- *   splits  workgroups per (batch, head): 0 = the library's choice, 1 = one workgroup and no
- *           workspace, n > 1 = n workgroups plus the merging launch; ws must then hold
- *           4 * B * H * n * (D + 2) bytes, else EC_EWORKSPACE
+ *   waves   wavefronts per workgroup (0 = the library's choice; 16 runs as 8)
+ *   unroll  16-byte loads of K and of V each lane keeps in flight per tile (0 = the library's choice;
+ *           6 and 12 run as 8)
+ *   splits  workgroups per (batch, head): 0 = the library's choice, 1 = one workgroup, n > 1 = n
+ *           workgroups; ws must then hold 4 * B * H * n * (D + 2) bytes, else EC_EWORKSPACE
  * Combinations the library has no kernel for return EC_EINVAL.  Everything else as ec_decode_step.
  */
 int ec_decode_step_shaped(const void* q, const void* k_new, const void* v_new, void* k_cache,

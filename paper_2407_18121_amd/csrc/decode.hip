@@ -2,590 +2,715 @@
 // append of the new key/value row and the fixed-point elimination folded into
 // the same launch (Sec. 3.1 Output Generation; Sec. 3.3; Alg. 1's last branch).
 //
-// HBM-bound: every K and V row of the cache is read exactly once with 16-byte
-// loads.  Two launch shapes:
-//   fused : one workgroup of up to 16 waves owns a whole (batch, head); nothing is exchanged
-//           between workgroups and the elimination is a register-held shift (below).
-//   split : when there are too few (batch, head) pairs to fill the chip, or too few bytes in flight
-//           per compute unit, the rows of one (batch, head) are divided over `splits` workgroups
-//           that each write an un-normalised partial (max, sum, weighted V) to the caller's
-//           workspace; a second, small launch merges the partials, writes the output and performs
-//           the append and the elimination through memory.  The two launches are ordered by the
-//           stream: no ticket, no device-scope fence inside a kernel.
-// A group of LPR = row_bytes/16
-// lanes owns one row per load, so a wave load covers 1 KB of contiguous cache;
-// each group keeps its own running (max, sum, weighted V) and never talks to
-// other groups inside the streaming loop.  Loads of the next tile are issued
-// before the current tile is consumed.  Tiles are aligned to the END of the
-// cache, so when the loop finishes the registers still hold the newest rows:
-// after the workgroup barrier that ends all reads, the rows behind the evicted
-// one are stored one slot up straight from those registers, and so is the new
-// row -- the elimination costs no extra read.
+// Every K and V row of the cache is read exactly once with 16-byte loads.  What bounds it: memory, from about 200 (batch, head)
+// pairs on (6 TB/s); below that what one compute unit can have in flight, 54 GB/s, and at short caches the launch itself.
+//   one workgroup per (batch, head): nothing is exchanged between workgroups.
+//   divided: few pairs with long caches; the rows of one pair are spread over several workgroups of the same launch, whose
+//            partial results meet in lines of memory that belong to the library (below).
+// As many lanes as a row has 16-byte chunks own one row per load, so a wave load covers 1 KB of contiguous cache; each keeps
+// its own running (max, sum, weighted V) inside the streaming loop.  The next tile travels while one is used: its loads are issued
+// first and without conditions, so that the wait for one tile is not a wait for both, and scalar bases keep addresses out of
+// the vector unit, which 366 instructions per 16 rows of a wave used to fill (bf16: now about 130, with the dot instruction).
+// Tiles are aligned to the END of the cache, so when the loop finishes the registers still hold the newest rows: after the
+// workgroup barrier that ends all reads, the rows behind the evicted one are stored one slot up straight from those registers,
+// and so is the new row -- the elimination costs no extra read.
 #include <algorithm>
 
 #include "ec_common.h"
 
 namespace ec {
 
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+
+// How a wave reads: a row is owned by as many lanes as it has 16-byte chunks, so that a load covers 1 KB of contiguous cache and
+// the sum of a score is a few full-rate lane moves.
 template <int DT, int D, int WAVES, int UNROLL> struct DecodeShape {
     static constexpr int kThreads = WAVES * kWave;
     static constexpr int kRowBytes = D * Elem<DT>::kBytes;
     static constexpr int kLPR = kRowBytes / 16;                 // lanes per row
     static constexpr int kRPW = kWave / kLPR;                   // rows per wave load
-    static constexpr int kEPL = Elem<DT>::kPerChunk;            // elements per lane
-    static constexpr int kTile = WAVES * UNROLL * kRPW;       // rows per workgroup iteration
+    static constexpr int kEPL = Elem<DT>::kPerChunk;            // features per lane
+    static constexpr int kTile = WAVES * kRPW * UNROLL;         // rows per workgroup iteration
 };
+
+// ------------------------------------------------------------------ meeting place of a divided (batch, head)
+// A line carries one share's partial result from the workgroup that formed it (a helper) to the one that owns the
+// (batch, head), inside one launch.  Lines belong to the library (2.2 MB) and are shared by everything that runs on the
+// device, so a line is claimed before it is used and is empty again when the launch ends:
+//   state   0 -> open (owner) -> joined (helper) -> 0 (owner, the data read and cleared), or open -> 0 (owner gives up on it)
+// "Open" and "joined" carry the address of the output row, which no two launches in flight share, and the share's number.
+// Nobody ever waits for a workgroup that may not be running: an owner that cannot claim a line, or whose helper has not
+// joined by the time it is needed, forms that share itself, with the same instructions in the same order; a helper that finds its
+// line not open leaves without a trace.  Once a helper has joined it is running and waits for nothing, so the owner's wait for
+// its data ends; that wait is bounded all the same, and a line that exceeded it is never given back.
+// The data words carry their own validity (upper half not 0), as relaxed device-scope atomics: no fence, no cache write-back.
+constexpr int kMaxShares = 64;
+constexpr int kLines = 2048;
+constexpr int kLineWords = 136;  // D + 2, padded to whole 64 bytes
+constexpr int kJoinTries = 4;    // of a helper that finds its line not open yet, 0.7 us each
+constexpr int kPatience = 8;     // looks of the owner at missing data before it asks whether the helper has joined
+constexpr int kStuck = 1 << 20;  // looks after that
+constexpr unsigned long long kOpen = 1, kJoined = 2;
+static __device__ unsigned long long line_state[kLines];
+static __device__ unsigned long long line_data[kLines][kLineWords];
+
+__device__ __forceinline__ unsigned long long device_load(const unsigned long long* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void device_store(unsigned long long* p, unsigned long long x)
+{
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long device_cas(unsigned long long* p, unsigned long long from, unsigned long long to)
+{
+    __hip_atomic_compare_exchange_strong(p, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return from;  // what was there
+}
+
+// The rows of one (batch, head) as shares: share s is the s-th run of `chunk` rows from the END of the cache, so that share
+// 0, which the owner takes, holds the rows that an elimination usually moves.  A share has at least `least` rows (a ragged
+// batch's launch is laid out for the longest cache).
+struct Shares {
+    int n_rows, chunk, count;
+    __device__ __forceinline__ Shares(int n_rows_, int splits, int least)
+        : n_rows(n_rows_), chunk(max((n_rows_ + splits - 1) / splits, least)), count((n_rows_ + chunk - 1) / chunk) {}
+    __device__ __forceinline__ int end(int s) const { return n_rows - s * chunk; }
+    __device__ __forceinline__ int begin(int s) const { return max(n_rows - (s + 1) * chunk, 0); }
+};
+
+// All of x has arrived in registers: what follows neither waits for it nor runs before it.
+template <typename T, int N> __device__ __forceinline__ void arrived(T (&x)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));
+}
+
+// 16 bytes of data that is read once: the non-temporal hint keeps the stream from displacing cache lines, which measurably
+// raises the rate of large one-pass reads on this chip.
+__device__ __forceinline__ u32x4 load_once(const char* p)
+{
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+}
+typedef __attribute__((address_space(1))) const char global_char;
+typedef __attribute__((address_space(1))) const u32x4 global_u32x4;
+__device__ __forceinline__ u32x4 load_once(global_char* p) { return __builtin_nontemporal_load((global_u32x4*)p); }
+
+// A chunk of q as the products need it: fp32 values times the scale, or bf16 values times the power of two in it, which is exact
+// (short of the subnormal numbers), so that the upper halves of the fp32 words are the bf16 values.
+template <int DT> __device__ __forceinline__ u32x4 prepared_q(const uint4& c, float scale, int scale_exp)
+{
+    constexpr int N = Elem<DT>::kPerChunk;
+    float x[N];
+    unpack<DT>(c, x);
+    u32x4 y;
+    if constexpr (DT == EC_F32) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[i] = __float_as_uint(x[i] * scale);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t lo = __float_as_uint(__builtin_amdgcn_ldexpf(x[2 * i], scale_exp));
+            const uint32_t hi = __float_as_uint(__builtin_amdgcn_ldexpf(x[2 * i + 1], scale_exp));
+            y[i] = lo >> 16 | (hi & 0xffff0000u);
+        }
+    }
+    return y;
+}
+
+// Product of a chunk of K with the chunk of q.  bf16: the dot instruction adds two products at a time, each exact in fp32.
+template <int DT> __device__ __forceinline__ float chunk_dot(const u32x4& k, const u32x4& q)
+{
+    float d = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t a = k[i], b = q[i];
+        if constexpr (DT == EC_F32)
+            d = fmaf(__uint_as_float(b), __uint_as_float(a), d);
+        else
+            d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), d, false);
+    }
+    return d;
+}
+
+// Values of a lane and of its partner `off` lanes away (8, 16 or 32), the one with the lower lane number first, in both of them.
+struct Pair {
+    float lower, upper;
+};
+__device__ __forceinline__ Pair lane_pair(float x, int off)
+{
+    const uint32_t u = __float_as_uint(x);
+    if (off == 32) {
+        const auto y = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        return {__uint_as_float(y[0]), __uint_as_float(y[1])};
+    }
+    if (off == 16) {
+        const auto y = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        return {__uint_as_float(y[0]), __uint_as_float(y[1])};
+    }
+    const float other = dpp_mov<kDppRowRor8>(x);
+    const bool low = threadIdx.x % 16 < 8;
+    return {low ? x : other, low ? other : x};
+}
 
 // EMIT (frequency discard policy): the kernel also stores every row's scaled score (base-2 units) into
 // raw [B,H,cap] and the head's softmax maximum and denominator into stats [B,H,2], from which
 // freq_accumulate_kernel forms this step's probabilities.
-template <int DT, int D, int WAVES, int UNROLL, bool EMIT>
+// SPLIT: the grid holds `splits` workgroups per (batch, head); the first B * H of them are the owners.
+template <int DT, int D, int WAVES, int UNROLL, bool DEEP, bool EMIT, bool SPLIT>
 __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
     const uint4* __restrict__ q, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
-    uint4* k_cache, uint4* v_cache, int32_t* pos, uint4* __restrict__ out, int H, int G, int cap,
+    uint4* k_cache, uint4* v_cache, int32_t* pos, uint4* __restrict__ out, int BH, int H, int G, int cap,
     int cache_len, int evict_idx, int32_t new_pos, float scale_log2e, float* __restrict__ raw,
     float* __restrict__ stats, const int32_t* __restrict__ len_b, const int32_t* __restrict__ evict_b,
-    const int32_t* __restrict__ new_pos_b)
+    const int32_t* __restrict__ new_pos_b, int splits, int least)
 {
     using S = DecodeShape<DT, D, WAVES, UNROLL>;
+    const int own_share = SPLIT ? blockIdx.x / BH : 0;
+    const int bh = SPLIT ? blockIdx.x - own_share * BH : blockIdx.x;
     if (len_b) {  // ragged batch: every batch element has its own cache length, victim and position
-        const int b = blockIdx.x / H;
+        const int b = bh / H;
         cache_len = min(max(len_b[b], 0), cap - 1);
         evict_idx = evict_b ? min(max(evict_b[b], -1), cache_len) : -1;
         if (new_pos_b) new_pos = new_pos_b[b];
     }
-    constexpr int kDecodeUnroll = UNROLL;
-    constexpr int LPR = S::kLPR, RPW = S::kRPW, EPL = S::kEPL, THREADS = S::kThreads, TILE = S::kTile;
-    const int bh = blockIdx.x;
+    constexpr int THREADS = S::kThreads, TILE = S::kTile, ROW = S::kRowBytes;
+    constexpr int LPR = S::kLPR, RPW = S::kRPW, NR = UNROLL, EPL = S::kEPL;
     const int tid = threadIdx.x;
-    const int wave = tid / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lane = tid % kWave;
-    const int sub = lane % LPR;   // which 16-byte chunk of the row
-    const int rgrp = lane / LPR;  // which row of the wave's load
+    const int sub = lane % LPR, rgrp = lane / LPR;  // which chunk of a row, which row of a load
 
-    const int n_rows = cache_len + 1;  // row cache_len is the new one, still in k_new/v_new
-    const int n_tiles = (n_rows + TILE - 1) / TILE;
-    const int first_row = n_rows - n_tiles * TILE;  // <= 0: tile 0 is the ragged one
+    const Shares shares(cache_len + 1, SPLIT ? splits : 1, SPLIT ? least : 1);  // row cache_len is the new one, still in k_new/v_new
+    if (SPLIT && own_share >= shares.count) return;
 
-    uint4* kc = k_cache + (size_t)bh * cap * LPR;
-    uint4* vc = v_cache + (size_t)bh * cap * LPR;
-    const uint4* kn = k_new + (size_t)bh * LPR;
-    const uint4* vn = v_new + (size_t)bh * LPR;
+    char* kc = reinterpret_cast<char*>(k_cache) + (size_t)bh * cap * ROW;
+    char* vc = reinterpret_cast<char*>(v_cache) + (size_t)bh * cap * ROW;
+    const char* kn = reinterpret_cast<const char*>(k_new) + (size_t)bh * ROW;
+    const char* vn = reinterpret_cast<const char*>(v_new) + (size_t)bh * ROW;
+
+    // lines of this (batch, head): neighbouring output rows use neighbouring lines
+    const unsigned long long out_row = (uintptr_t)out + (unsigned long long)bh * ROW;
+    const unsigned long long row_key = out_row << 8;
+    const unsigned line0 = (unsigned)(out_row / ROW) * (unsigned)(splits - 1);
+    auto line_of = [&](int s) { return (line0 + (unsigned)(s - 1)) % kLines; };
+    auto key_of = [&](int s) { return row_key | (unsigned long long)s << 2; };
+    bool claimed = false;  // owner, lane s of wave 0: the line of share s is this launch's
+    if (SPLIT && own_share == 0 && wave == 0 && lane >= 1 && lane < shares.count)
+        claimed = device_cas(&line_state[line_of(lane)], 0, key_of(lane) | kOpen) == 0;
 
     // positions of the rows behind the victim, fetched early (stored after the barrier)
-    const bool owns_pos = pos != nullptr && (G == H || (bh % H) == 0);
+    const bool owns_pos = own_share == 0 && pos != nullptr && (G == H || (bh % H) == 0);
     int32_t* pp = owns_pos ? pos + ((size_t)(bh / H) * G + (G == 1 ? 0 : bh % H)) * cap : nullptr;
     const int n_move = (evict_idx >= 0) ? max(cache_len - 1 - evict_idx, 0) : 0;
     int32_t pos_pref = 0;
     if (owns_pos && tid < n_move) pos_pref = pp[evict_idx + 1 + tid];
 
-    float qf[EPL];
-    {
-        uint4 qc = q[(size_t)bh * LPR + sub];
-        unpack<DT>(qc, qf);
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) qf[e] *= scale_log2e;
-    }
+    // bf16: the power of two in the scale goes into q, the rest multiplies the score, so that sums stay in range wherever those of
+    // a scaled q would
+    u32x4 qf;
+    const int scale_exp = __builtin_amdgcn_frexp_expf(scale_log2e);
+    const float scale_rest = DT == EC_F32 ? 1.f : __builtin_amdgcn_frexp_mantf(scale_log2e);  // 0.5 .. 1
+    const uint4 q_in = q[(size_t)bh * LPR + sub];
 
-    float m_run = -INFINITY, l_run = 0.f;
-    float acc[EPL];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+    // two tiles, one being used while the other lands
+    struct Rows {
+        u32x4 k[NR], v[NR];
+    } ta, tb;
+    const int lane_row = wave * (RPW * NR) + rgrp;  // this lane's rows of a tile: lane_row + u * RPW
+    const uint32_t lane_at = lane_row * ROW + sub * 16;
 
-    uint4 kf[kDecodeUnroll], vf[kDecodeUnroll], kf2[kDecodeUnroll], vf2[kDecodeUnroll];
-    const int lane_row = wave * RPW + rgrp;  // row offset of this lane group inside one unroll slab
-
-    auto load_tile = [&](int t, uint4* kd, uint4* vd) {
+    // A tile is rows first .. first + TILE - 1.  The first of a share may start before its first row r0, the last may end with
+    // the new row; the ones between are loaded without a condition, so that waiting for one never means waiting for the next.
+    auto load_inner = [&](int first, Rows& x) __attribute__((always_inline)) {
+        global_char *k0 = (global_char*)kc + (size_t)first * ROW, *v0 = (global_char*)vc + (size_t)first * ROW;
+        asm volatile("" : "+s"(k0), "+s"(v0));  // scalar base, constant lane offset: no address arithmetic per load
 #pragma unroll
-        for (int u = 0; u < kDecodeUnroll; ++u) {
-            const int r = first_row + t * TILE + u * (WAVES * RPW) + lane_row;
-            if (r >= 0) {
-                const bool is_new = (r == cache_len);
-                kd[u] = load_stream(is_new ? kn + sub : kc + (size_t)r * LPR + sub);
-                vd[u] = load_stream(is_new ? vn + sub : vc + (size_t)r * LPR + sub);
-            } else {
-                kd[u] = make_uint4(0, 0, 0, 0);
-                vd[u] = make_uint4(0, 0, 0, 0);
-            }
+        for (int u = 0; u < NR; ++u) x.k[u] = load_once(k0 + (lane_at + u * RPW * ROW));
+        __builtin_amdgcn_sched_barrier(0);  // K is needed first
+#pragma unroll
+        for (int u = 0; u < NR; ++u) x.v[u] = load_once(v0 + (lane_at + u * RPW * ROW));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto load_outer = [&](int first, int r0, Rows& x) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NR; ++u) {
+            const int r = first + u * RPW + lane_row;
+            const char* ks = (r == cache_len ? kn : kc + (ptrdiff_t)r * ROW) + sub * 16;
+            const char* vs = (r == cache_len ? vn : vc + (ptrdiff_t)r * ROW) + sub * 16;
+            x.k[u] = r >= r0 ? load_once(ks) : u32x4{0, 0, 0, 0};
+            x.v[u] = r >= r0 ? load_once(vs) : u32x4{0, 0, 0, 0};
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
 
-    load_tile(0, kf, vf);
-    for (int t = 0;; ++t) {
-        const bool more = t + 1 < n_tiles;
-        if (more) load_tile(t + 1, kf2, vf2);
-
-        float s[kDecodeUnroll];
-        float m_tile = -INFINITY;
-#pragma unroll
-        for (int u = 0; u < kDecodeUnroll; ++u) {
-            const int r = first_row + t * TILE + u * (WAVES * RPW) + lane_row;
-            float kx[EPL];
-            unpack<DT>(kf[u], kx);
-            float d = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) d = fmaf(qf[e], kx[e], d);
-            d = group_sum<LPR>(d);
-            s[u] = (r >= 0) ? d : -INFINITY;
-            if (EMIT && r >= 0 && sub == 0) raw[(size_t)bh * cap + r] = d;
-            m_tile = fmaxf(m_tile, s[u]);
-        }
-        const float m_new = fmaxf(m_run, m_tile);
-        if (m_new > -INFINITY) {  // uniform inside a row group
-            const float corr = exp2f(m_run - m_new);
-            l_run *= corr;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[e] *= corr;
-#pragma unroll
-            for (int u = 0; u < kDecodeUnroll; ++u) {
-                const float p = exp2f(s[u] - m_new);
-                l_run += p;
-                float vx[EPL];
-                unpack<DT>(vf[u], vx);
-#pragma unroll
-                for (int e = 0; e < EPL; ++e) acc[e] = fmaf(p, vx[e], acc[e]);
-            }
-            m_run = m_new;
-        }
-        if (!more) break;  // kf/vf keep the last tile: the newest rows
-#pragma unroll
-        for (int u = 0; u < kDecodeUnroll; ++u) {
-            kf[u] = kf2[u];
-            vf[u] = vf2[u];
-        }
-    }
-
-    // ---- merge the RPW row groups of each wave with shuffles (lanes that hold the same chunk) ----
-#pragma unroll
-    for (int off = LPR; off < kWave; off <<= 1) {
-        const float m_o = __shfl_xor(m_run, off, kWave);
-        const float l_o = __shfl_xor(l_run, off, kWave);
-        const float m_n = fmaxf(m_run, m_o);
-        const float w_s = (m_run > -INFINITY) ? exp2f(m_run - m_n) : 0.f;
-        const float w_o = (m_o > -INFINITY) ? exp2f(m_o - m_n) : 0.f;
-        l_run = l_run * w_s + l_o * w_o;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-            const float a_o = __shfl_xor(acc[e], off, kWave);
-            acc[e] = acc[e] * w_s + a_o * w_o;
-        }
-        m_run = m_n;
-    }
-
-    // ---- merge the waves through LDS ----
     __shared__ float sh_acc[WAVES][D];
     __shared__ float sh_m[WAVES];
     __shared__ float sh_l[WAVES];
-    if (rgrp == 0) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) sh_acc[wave][sub * EPL + e] = acc[e];
-        if (sub == 0) {
-            sh_m[wave] = m_run;
-            sh_l[wave] = l_run;
-        }
-    }
-    __syncthreads();  // also: every wave of this workgroup has finished reading the cache
-
-    if (tid < D) {
-        float M = -INFINITY, L = 0.f, o_d = 0.f;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) M = fmaxf(M, sh_m[w]);
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) {
-            const float wt = (sh_m[w] > -INFINITY) ? exp2f(sh_m[w] - M) : 0.f;
-            L = fmaf(sh_l[w], wt, L);
-            o_d = fmaf(sh_acc[w][tid], wt, o_d);
-        }
-        if (EMIT && tid == 0) {
-            stats[(size_t)bh * 2] = M;
-            stats[(size_t)bh * 2 + 1] = L;
-        }
-        const float r = o_d / L;
-        typename Elem<DT>::type* o = reinterpret_cast<typename Elem<DT>::type*>(out) + (size_t)bh * D;
-        if constexpr (DT == EC_F32)
-            o[tid] = r;
-        else
-            o[tid] = f32_to_bf16(r);
-    }
+    __shared__ float part[SPLIT ? kMaxShares : 1][D + 2];  // of every share: weighted V, maximum, sum of weights
+    __shared__ unsigned long long sh_claimed, sh_lost, sh_missing[2];
+    __shared__ int sh_joined;
+    if (SPLIT && tid < 2) sh_missing[tid] = 0;
 
     // ---- fixed-point elimination + append ----
-    // With a victim, rows evict_idx+1 .. cache_len (the last being the new row) move up by one; the
-    // new row is dropped if it is the victim itself.  Without one, the new row lands at cache_len.
-    const int last_tile_row0 = first_row + (n_tiles - 1) * TILE;  // first row still held in registers
-    if (evict_idx >= 0) {
-        // rows behind the victim that left the registers long ago (only when more than a tile moves)
-        const int slow_end = min(last_tile_row0, cache_len);  // rows [evict_idx+1, slow_end) via memory
-        const int total = max(slow_end - (evict_idx + 1), 0) * LPR;
-        for (int c0 = 0; c0 < total; c0 += THREADS) {
-            const int c = c0 + tid;
-            uint4 kk, vv;
-            if (c < total) {
-                kk = kc[(size_t)(evict_idx + 1) * LPR + c];
-                vv = vc[(size_t)(evict_idx + 1) * LPR + c];
-            }
-            __syncthreads();  // all reads of this slab before any write into it
-            if (c < total) {
-                kc[(size_t)evict_idx * LPR + c] = kk;
-                vc[(size_t)evict_idx * LPR + c] = vv;
-            }
-        }
-        if (total > 0) __syncthreads();
+    // With a victim, rows evict_idx+1 .. cache_len (the last being the new row) move up by one; the new row is dropped if it
+    // is the victim itself.  Without one, the new row lands at cache_len.  The last tile of share 0 is still in registers when
+    // its scores have been formed: rows held .. cache_len are stored from there.
+    const int tail_first = shares.end(0) - TILE, held = max(tail_first, shares.begin(0));
+    const bool moved_early = evict_idx < 0 || evict_idx + 1 >= held;  // nothing moves but what the registers hold
+    auto move_held = [&]() __attribute__((always_inline)) {
+        const int lowest = evict_idx >= 0 ? max(evict_idx + 1, held) : cache_len, up = evict_idx >= 0 ? 1 : 0;
 #pragma unroll
-        for (int u = 0; u < kDecodeUnroll; ++u) {
-            const int r = last_tile_row0 + u * (WAVES * RPW) + lane_row;
-            if (r > evict_idx && r >= 0) {
-                kc[(size_t)(r - 1) * LPR + sub] = kf[u];
-                vc[(size_t)(r - 1) * LPR + sub] = vf[u];
-            }
-        }
-    } else {
-#pragma unroll
-        for (int u = 0; u < kDecodeUnroll; ++u) {
-            const int r = last_tile_row0 + u * (WAVES * RPW) + lane_row;
-            if (r == cache_len) {
-                kc[(size_t)r * LPR + sub] = kf[u];
-                vc[(size_t)r * LPR + sub] = vf[u];
-            }
-        }
-    }
-
-    // ---- positions: one copy per score group ----
-    if (owns_pos) {
-        if (tid < n_move) pp[evict_idx + tid] = pos_pref;  // fetched before the barrier above
-        for (int c0 = THREADS; c0 < n_move; c0 += THREADS) {  // beyond one workgroup's worth
-            const int c = c0 + tid;
-            int32_t pv = 0;
-            if (c < n_move) pv = pp[evict_idx + 1 + c];
-            __syncthreads();
-            if (c < n_move) pp[evict_idx + c] = pv;
-        }
-        const int new_row = (evict_idx < 0) ? cache_len : ((evict_idx == cache_len) ? -1 : cache_len - 1);
-        if (new_row >= 0 && tid == 0) pp[new_row] = new_pos;
-    }
-}
-
-// ------------------------------------------------------------------ split launch shape
-// Workgroup (bh, s) attends rows [s * chunk, (s + 1) * chunk) of its (batch, head), chunk =
-// ceil(n_rows / splits), and stores its partial to part[(bh * splits + s) * (D + 2)]: D weighted-V sums
-// relative to its own maximum, then that maximum (base-2 units; -inf for an empty range) and the sum of
-// its weights.  Nothing in the cache is written here.
-template <int DT, int D, int WAVES, int UNROLL>
-__global__ __launch_bounds__(WAVES * kWave) void decode_split_kernel(
-    const uint4* __restrict__ q, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
-    const uint4* __restrict__ k_cache, const uint4* __restrict__ v_cache, float* __restrict__ part, int cap,
-    int cache_len, int splits, float scale_log2e)
-{
-    using S = DecodeShape<DT, D, WAVES, UNROLL>;
-    constexpr int LPR = S::kLPR, RPW = S::kRPW, EPL = S::kEPL, TILE = S::kTile;
-    const int bh = blockIdx.x / splits, sp = blockIdx.x % splits;
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    const int sub = lane % LPR, rgrp = lane / LPR;
-
-    const int n_rows = cache_len + 1;  // row cache_len is the new one, still in k_new/v_new
-    const int chunk = (n_rows + splits - 1) / splits;
-    const int r0 = sp * chunk, r1 = min(r0 + chunk, n_rows);
-    const int n_tiles = (max(r1 - r0, 0) + TILE - 1) / TILE;
-
-    const uint4* kc = k_cache + (size_t)bh * cap * LPR;
-    const uint4* vc = v_cache + (size_t)bh * cap * LPR;
-    const uint4* kn = k_new + (size_t)bh * LPR;
-    const uint4* vn = v_new + (size_t)bh * LPR;
-
-    float qf[EPL];
-    {
-        uint4 qc = q[(size_t)bh * LPR + sub];
-        unpack<DT>(qc, qf);
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) qf[e] *= scale_log2e;
-    }
-    float m_run = -INFINITY, l_run = 0.f;
-    float acc[EPL];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-
-    uint4 kf[UNROLL], vf[UNROLL], kf2[UNROLL], vf2[UNROLL];
-    const int lane_row = wave * RPW + rgrp;
-    auto load_tile = [&](int t, uint4* kd, uint4* vd) {
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const int r = r0 + t * TILE + u * (WAVES * RPW) + lane_row;
-            if (r < r1) {
-                const bool is_new = (r == cache_len);
-                kd[u] = load_stream(is_new ? kn + sub : kc + (size_t)r * LPR + sub);
-                vd[u] = load_stream(is_new ? vn + sub : vc + (size_t)r * LPR + sub);
-            } else {
-                kd[u] = make_uint4(0, 0, 0, 0);
-                vd[u] = make_uint4(0, 0, 0, 0);
+        for (int u = 0; u < NR; ++u) {
+            const int r = tail_first + u * RPW + lane_row;
+            if (r >= lowest) {
+                const ptrdiff_t at = (ptrdiff_t)(r - up) * ROW + sub * 16;
+                *reinterpret_cast<u32x4*>(kc + at) = ta.k[u];
+                *reinterpret_cast<u32x4*>(vc + at) = ta.v[u];
             }
         }
     };
-    if (n_tiles > 0) load_tile(0, kf, vf);
-    for (int t = 0; t < n_tiles; ++t) {
-        const bool more = t + 1 < n_tiles;
-        if (more) load_tile(t + 1, kf2, vf2);
-        float s[UNROLL];
-        float m_tile = -INFINITY;
+
+    unsigned long long todo = 0;
+    for (int s = own_share;;) {
+        const int r0 = shares.begin(s), r1 = shares.end(s);
+        const int n_tiles = (r1 - r0 + TILE - 1) / TILE;
+        const int first_row = r1 - n_tiles * TILE;
+        const int last_first = r1 - TILE;
+        // per lane: maximum (base-2 units), sum of weights and weighted V of the rows it holds V of
+        float m_run = kLowest, l_run = 0.f;
+        float acc[EPL];
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const int r = r0 + t * TILE + u * (WAVES * RPW) + lane_row;
-            float kx[EPL];
-            unpack<DT>(kf[u], kx);
-            float d = 0.f;
+        for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+
+        auto attend = [&](int first, const Rows& x) __attribute__((always_inline)) {
+            float sc[NR];
+            float m_tile = kLowest;
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) d = fmaf(qf[e], kx[e], d);
-            d = group_sum<LPR>(d);
-            s[u] = (r < r1) ? d : -INFINITY;
-            m_tile = fmaxf(m_tile, s[u]);
-        }
-        const float m_new = fmaxf(m_run, m_tile);
-        if (m_new > -INFINITY) {
-            const float corr = exp2f(m_run - m_new);
-            l_run *= corr;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[e] *= corr;
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u) {
-                const float p = exp2f(s[u] - m_new);
-                l_run += p;
-                float vx[EPL];
-                unpack<DT>(vf[u], vx);
-#pragma unroll
-                for (int e = 0; e < EPL; ++e) acc[e] = fmaf(p, vx[e], acc[e]);
+            for (int u = 0; u < NR; ++u) {
+                const float d = group_sum<LPR>(chunk_dot<DT>(x.k[u], qf));
+                sc[u] = DT == EC_F32 ? d : d * scale_rest;
             }
-            m_run = m_new;
-        }
+            if (first < r0) {  // uniform
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            kf[u] = kf2[u];
-            vf[u] = vf2[u];
-        }
-    }
-    // row groups of a wave, then the waves: same order of operations as the fused kernel
+                for (int u = 0; u < NR; ++u)
+                    if (first + u * RPW + lane_row < r0) sc[u] = -INFINITY;
+            }
+            if constexpr (EMIT) {
+                const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(raw + ((ptrdiff_t)bh * cap + first), 0, TILE * 4, 0x00020000);
+                float y = sc[0];
 #pragma unroll
-    for (int off = LPR; off < kWave; off <<= 1) {
-        const float m_o = __shfl_xor(m_run, off, kWave);
-        const float l_o = __shfl_xor(l_run, off, kWave);
-        const float m_n = fmaxf(m_run, m_o);
-        const float w_s = (m_run > -INFINITY) ? exp2f(m_run - m_n) : 0.f;
-        const float w_o = (m_o > -INFINITY) ? exp2f(m_o - m_n) : 0.f;
-        l_run = l_run * w_s + l_o * w_o;
+                for (int u = 1; u < NR; ++u) y = sub == u ? sc[u] : y;
+                const int r = sub * RPW + lane_row;
+                // not under a condition either: lanes with nothing to store point behind the descriptor's end
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y), rsrc, sub < NR && first + r >= r0 ? r * 4 : TILE * 4, 0, 0);
+            }
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-            const float a_o = __shfl_xor(acc[e], off, kWave);
-            acc[e] = acc[e] * w_s + a_o * w_o;
-        }
-        m_run = m_n;
-    }
-    __shared__ float sh_acc[WAVES][D];
-    __shared__ float sh_m[WAVES];
-    __shared__ float sh_l[WAVES];
-    if (rgrp == 0) {
+            for (int u = 0; u < NR; ++u) m_tile = fmaxf(m_tile, sc[u]);
+            __builtin_amdgcn_sched_barrier(0);  // V is not waited for before the scores are there
+            if (__any(m_tile > m_run)) {  // wave-uniform
+                const float m_new = fmaxf(m_run, m_tile);
+                const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+                m_run = m_new;
+                l_run *= corr;
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) sh_acc[wave][sub * EPL + e] = acc[e];
-        if (sub == 0) {
-            sh_m[wave] = m_run;
-            sh_l[wave] = l_run;
-        }
-    }
-    __syncthreads();
-    if (tid < D) {
-        float M = -INFINITY, L = 0.f, o_d = 0.f;
+                for (int e = 0; e < EPL; ++e) acc[e] *= corr;
+            }
+            // fp32: a tile is summed by itself and then added, which keeps the rounding errors of a long chain small
+            float part_l = 0.f, part_v[EPL];
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) M = fmaxf(M, sh_m[w]);
+            for (int u = 0; u < NR; ++u) {
+                const float p = __builtin_amdgcn_exp2f(sc[u] - m_run);
+                float vx[EPL];
+                unpack<DT>(__builtin_bit_cast(uint4, x.v[u]), vx);
+                if (DT == EC_F32) {
+                    part_l += p;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) {
-            const float wt = (sh_m[w] > -INFINITY) ? exp2f(sh_m[w] - M) : 0.f;
-            L = fmaf(sh_l[w], wt, L);
-            o_d = fmaf(sh_acc[w][tid], wt, o_d);
-        }
-        float* dst = part + (size_t)blockIdx.x * (D + 2);
-        dst[tid] = o_d;
-        if (tid == 0) {
-            dst[D] = M;
-            dst[D + 1] = L;
-        }
-    }
-}
+                    for (int e = 0; e < EPL; ++e) part_v[e] = u == 0 ? p * vx[e] : fmaf(p, vx[e], part_v[e]);
+                } else {
+                    l_run += p;
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) acc[e] = fmaf(p, vx[e], acc[e]);
+                }
+            }
+            if (DT == EC_F32) {
+                l_run += part_l;
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) acc[e] += part_v[e];
+            }
+            // summed here, before the registers of the tile are loaded again
+            asm volatile("" : "+v"(l_run));
+            arrived(acc);
+        };
 
-// Second launch of the split shape, one workgroup per (batch, head): merges the partials in ascending split
-// order, writes the output, then appends the new row and removes the victim through memory (the rows behind
-// it move up by one, slab by slab: a slab is read completely before any of it is overwritten).
-constexpr int kCombineThreads = 256;
-template <int DT, int D>
-__global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(
-    const float* __restrict__ part, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new, uint4* k_cache,
-    uint4* v_cache, int32_t* pos, void* __restrict__ out, int H, int G, int cap, int cache_len, int evict_idx,
-    int32_t new_pos, int splits)
-{
-    constexpr int LPR = D * Elem<DT>::kBytes / 16;
-    const int bh = blockIdx.x, tid = threadIdx.x;
-    if (tid < D) {
-        const float* p = part + (size_t)bh * splits * (D + 2);
-        float M = -INFINITY;
-        for (int s = 0; s < splits; ++s) M = fmaxf(M, p[s * (D + 2) + D]);
-        float L = 0.f, o_d = 0.f;
-        for (int s = 0; s < splits; ++s) {
-            const float ms = p[s * (D + 2) + D];
-            const float wt = (ms > -INFINITY) ? exp2f(ms - M) : 0.f;
-            L = fmaf(p[s * (D + 2) + D + 1], wt, L);
-            o_d = fmaf(p[s * (D + 2) + tid], wt, o_d);
+        load_outer(first_row, r0, ta);
+        if (s == own_share) qf = prepared_q<DT>(q_in, scale_log2e, scale_exp);
+        int first = first_row;
+        if constexpr (DEEP) {
+            for (; first < last_first - 2 * TILE; first += 2 * TILE) {
+                load_inner(first + TILE, tb);
+                attend(first, ta);
+                load_inner(first + 2 * TILE, ta);
+                attend(first + TILE, tb);
+            }
+            if (first == last_first - TILE) {
+                load_outer(last_first, first_row, tb);
+                attend(first, ta);
+                attend(last_first, tb);
+                ta = tb;
+            } else {
+                if (first == last_first - 2 * TILE) {
+                    load_inner(first + TILE, tb);
+                    attend(first, ta);
+                    load_outer(last_first, first_row, ta);
+                    attend(first + TILE, tb);
+                }
+                attend(last_first, ta);
+            }
+        } else {
+            attend(first, ta);
+            while (first != last_first) {
+                first += TILE;
+                if (first == last_first)
+                    load_outer(first, first_row, ta);
+                else
+                    load_inner(first, ta);
+                attend(first, ta);
+            }
         }
-        const float r = o_d / L;
-        typename Elem<DT>::type* o = reinterpret_cast<typename Elem<DT>::type*>(out) + (size_t)bh * D;
-        if constexpr (DT == EC_F32)
-            o[tid] = r;
-        else
-            o[tid] = f32_to_bf16(r);
+        // ta holds the last tile: of share 0, the newest rows
+
+        unsigned long long seen = 0;  // helper: what its line held; asked for here, looked at behind the merging
+        if (SPLIT && own_share > 0 && tid == 0)
+            seen = device_cas(&line_state[line_of(s)], key_of(s) | kOpen, key_of(s) | kJoined);
+
+        // ---- merge the lanes of each wave that hold the same features ----
+#pragma unroll
+        for (int off = LPR; off < kWave; off <<= 1) {
+            const Pair m = lane_pair(m_run, off), l = lane_pair(l_run, off);
+            m_run = fmaxf(m.lower, m.upper);
+            const float w0 = __builtin_amdgcn_exp2f(m.lower - m_run), w1 = __builtin_amdgcn_exp2f(m.upper - m_run);
+            l_run = l.lower * w0 + l.upper * w1;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) {
+                const Pair x = lane_pair(acc[e], off);
+                acc[e] = x.lower * w0 + x.upper * w1;
+            }
+        }
+
+        // ---- merge the waves through LDS ----
+        if (lane < LPR) {
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) sh_acc[wave][sub * EPL + e] = acc[e];
+            if (sub == 0) {
+                sh_m[wave] = m_run;
+                sh_l[wave] = l_run;
+            }
+        }
+        if (SPLIT && own_share > 0 && tid == 0) {
+            for (int i = 0; seen == 0 && i < kJoinTries; ++i)
+                seen = device_cas(&line_state[line_of(s)], key_of(s) | kOpen, key_of(s) | kJoined);
+            sh_joined = seen == (key_of(s) | kOpen);
+        }
+        if (SPLIT && own_share == 0 && s == 0 && wave == 0) {
+            const unsigned long long c = __ballot(claimed);
+            if (tid == 0) sh_claimed = c;
+        }
+        __syncthreads();  // also: every wave of this workgroup has finished reading its rows
+
+        if (own_share == 0 && s == 0) {
+            // rows of share 0 only: the other shares' workgroups do not read them
+            if (moved_early) move_held();
+            if (owns_pos) {  // one copy of the positions per score group
+                if (tid < n_move) pp[evict_idx + tid] = pos_pref;  // fetched before the barrier above
+                for (int c0 = THREADS; c0 < n_move; c0 += THREADS) {  // beyond one workgroup's worth
+                    const int c = c0 + tid;
+                    int32_t pv = 0;
+                    if (c < n_move) pv = pp[evict_idx + 1 + c];
+                    __syncthreads();
+                    if (c < n_move) pp[evict_idx + c] = pv;
+                }
+                const int new_row = (evict_idx < 0) ? cache_len : ((evict_idx == cache_len) ? -1 : cache_len - 1);
+                if (new_row >= 0 && tid == 0) pp[new_row] = new_pos;
+            }
+        }
+
+        float M = kLowest, L = 0.f, o_d = 0.f;
+        if (tid < D) {
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) M = fmaxf(M, sh_m[w]);
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                const float wt = __builtin_amdgcn_exp2f(sh_m[w] - M);
+                L = fmaf(sh_l[w], wt, L);
+                o_d = fmaf(sh_acc[w][tid], wt, o_d);
+            }
+        }
+        if constexpr (SPLIT) {
+            if (own_share > 0) {
+                if (sh_joined && tid < D) {
+                    unsigned long long* line = line_data[line_of(s)];
+                    const unsigned long long valid = 1ull << 32;
+                    device_store(line + tid, valid | __float_as_uint(o_d));
+                    if (tid < 2) device_store(line + D + tid, valid | __float_as_uint(tid == 0 ? M : L));
+                }
+                return;
+            }
+            if (tid < D) {
+                part[s][tid] = o_d;
+                if (tid < 2) part[s][D + tid] = tid == 0 ? M : L;
+            }
+            if (s == 0) {
+                // word j of the claimed lines belongs to thread j % THREADS, which remembers the ones still to come
+                constexpr int kBatch = 4;
+                const int total = (shares.count - 1) * (D + 2);
+                unsigned long long pending = 0;
+                for (int j = tid, i = 0; j < total; j += THREADS, ++i)
+                    if (sh_claimed >> (1 + j / (D + 2)) & 1) pending |= 1ull << i;
+                auto look = [&](int patience) {
+                    for (int i0 = 0; i0 * THREADS + tid < total; i0 += kBatch)
+                        for (int n = 0; (pending >> i0 & ((1ull << kBatch) - 1)) && n < patience; ++n) {
+                            unsigned long long x[kBatch];
+#pragma unroll
+                            for (int u = 0; u < kBatch; ++u) {
+                                const int j = min((i0 + u) * THREADS + tid, total - 1);
+                                x[u] = device_load(&line_data[line_of(1 + j / (D + 2))][j % (D + 2)]);
+                            }
+#pragma unroll
+                            for (int u = 0; u < kBatch; ++u)
+                                if ((pending >> (i0 + u) & 1) && x[u] >> 32) {
+                                    const int j = (i0 + u) * THREADS + tid;
+                                    part[1 + j / (D + 2)][j % (D + 2)] = __uint_as_float((uint32_t)x[u]);
+                                    device_store(&line_data[line_of(1 + j / (D + 2))][j % (D + 2)], 0);
+                                    pending &= ~(1ull << (i0 + u));
+                                }
+                        }
+                };
+                auto missing = [&](int round) {  // shares with a word still to come
+                    for (int i = 0; i < 64 && pending >> i; ++i)
+                        if (pending >> i & 1) atomicOr(&sh_missing[round], 1ull << (1 + (i * THREADS + tid) / (D + 2)));
+                    __syncthreads();
+                    return sh_missing[round];
+                };
+                look(kPatience);
+                const unsigned long long all = (shares.count < 64 ? 1ull << shares.count : 0ull) - 2;
+                unsigned long long given_up = 0;
+                if (const unsigned long long late = missing(0)) {  // uniform
+                    if (wave == 0) {
+                        const unsigned long long open = key_of(lane) | kOpen;
+                        const bool lost = (late >> lane & 1) && device_cas(&line_state[line_of(lane)], open, 0) == open;
+                        const unsigned long long l = __ballot(lost);
+                        if (tid == 0) sh_lost = l;
+                    }
+                    __syncthreads();
+                    given_up = sh_lost;
+                    for (int i = 0; i < 64 && pending >> i; ++i)
+                        if (given_up >> (1 + (i * THREADS + tid) / (D + 2)) & 1) pending &= ~(1ull << i);
+                    look(kStuck);
+                    given_up |= missing(1);
+                }
+                todo = all & (~sh_claimed | given_up);
+                if (wave == 0) claimed = claimed && !(given_up >> lane & 1);  // lines to give back
+            } else {
+                todo &= ~(1ull << s);
+                __syncthreads();  // sh_acc is written again
+            }
+            if (todo) {
+                s = __ffsll((long long)todo) - 1;
+                continue;
+            }
+            if (!moved_early && s != 0) {  // another share was formed after share 0: its rows again
+                load_outer(tail_first, shares.begin(0), ta);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // arrived before any wave overwrites them
+                __syncthreads();
+            }
+            M = kLowest, L = 0.f, o_d = 0.f;
+            if (tid < D) {
+                // shares in ascending order, eight at a time so that their reads overlap
+                constexpr int N = 8;
+                for (int i0 = 0; i0 < shares.count; i0 += N) {
+                    float m[N], l[N], x[N];
+                    float m_new = M;
+#pragma unroll
+                    for (int i = 0; i < N; ++i) {
+                        const bool in = i0 + i < shares.count;
+                        const int at = in ? i0 + i : 0;
+                        m[i] = in ? part[at][D] : kLowest;
+                        l[i] = in ? part[at][D + 1] : 0.f;
+                        x[i] = in ? part[at][tid] : 0.f;
+                    }
+#pragma unroll
+                    for (int i = 0; i < N; ++i) m_new = fmaxf(m_new, m[i]);
+                    const float corr = __builtin_amdgcn_exp2f(M - m_new);
+                    L *= corr;
+                    o_d *= corr;
+                    M = m_new;
+#pragma unroll
+                    for (int i = 0; i < N; ++i) {
+                        const float wt = __builtin_amdgcn_exp2f(m[i] - M);
+                        L = fmaf(l[i], wt, L);
+                        o_d = fmaf(x[i], wt, o_d);
+                    }
+                }
+            }
+        }
+        if (tid < D) {
+            if (EMIT && tid == 0) {
+                stats[(size_t)bh * 2] = M;
+                stats[(size_t)bh * 2 + 1] = L;
+            }
+            const float r = o_d / L;
+            typename Elem<DT>::type* o = reinterpret_cast<typename Elem<DT>::type*>(out) + (size_t)bh * D;
+            if constexpr (DT == EC_F32)
+                o[tid] = r;
+            else
+                o[tid] = f32_to_bf16(r);
+        }
+        break;
     }
 
-    uint4* kc = k_cache + (size_t)bh * cap * LPR;
-    uint4* vc = v_cache + (size_t)bh * cap * LPR;
-    // rows evict_idx+1 .. cache_len-1 move up by one, then the new row lands behind them
-    const int n_move = (evict_idx >= 0) ? max(cache_len - 1 - evict_idx, 0) : 0;
-    const int total = n_move * LPR;
-    for (int c0 = 0; c0 < total; c0 += kCombineThreads) {
-        const int c = c0 + tid;
-        uint4 kk, vv;
-        if (c < total) {
-            kk = kc[(size_t)(evict_idx + 1) * LPR + c];
-            vv = vc[(size_t)(evict_idx + 1) * LPR + c];
-        }
-        __syncthreads();
-        if (c < total) {
-            kc[(size_t)evict_idx * LPR + c] = kk;
-            vc[(size_t)evict_idx * LPR + c] = vv;
-        }
-        __syncthreads();
-    }
-    const int new_row = (evict_idx < 0) ? cache_len : ((evict_idx == cache_len) ? -1 : cache_len - 1);
-    if (new_row >= 0 && tid < LPR) {
-        kc[(size_t)new_row * LPR + tid] = k_new[(size_t)bh * LPR + tid];
-        vc[(size_t)new_row * LPR + tid] = v_new[(size_t)bh * LPR + tid];
-    }
-    if (pos != nullptr && (G == H || (bh % H) == 0)) {
-        int32_t* pp = pos + ((size_t)(bh / H) * G + (G == 1 ? 0 : bh % H)) * cap;
-        for (int c0 = 0; c0 < n_move; c0 += kCombineThreads) {
+    if (!moved_early) {
+        // Rows behind the victim that left the registers long ago, through memory: slab by slab, each read completely before any
+        // of it is overwritten.  No other workgroup reads them any more.
+        const int total = (held - (evict_idx + 1)) * LPR;
+        u32x4* kd = reinterpret_cast<u32x4*>(kc + (size_t)evict_idx * ROW);
+        u32x4* vd = reinterpret_cast<u32x4*>(vc + (size_t)evict_idx * ROW);
+        for (int c0 = 0; c0 < total; c0 += THREADS) {
             const int c = c0 + tid;
-            int32_t pv = 0;
-            if (c < n_move) pv = pp[evict_idx + 1 + c];
+            u32x4 kk, vv;
+            if (c < total) {
+                kk = kd[LPR + c];
+                vv = vd[LPR + c];
+            }
             __syncthreads();
-            if (c < n_move) pp[evict_idx + c] = pv;
-            __syncthreads();
+            if (c < total) {
+                kd[c] = kk;
+                vd[c] = vv;
+            }
         }
-        if (new_row >= 0 && tid == 0) pp[new_row] = new_pos;
+        __syncthreads();
+        move_held();
+    }
+    if (SPLIT) {  // the lines are empty: whoever claims one next finds no word of this launch
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (wave == 0 && claimed) device_store(&line_state[line_of(lane)], 0);
     }
 }
 
-template <int DT, int D, int WAVES, int UNROLL>
-static int launch_decode_split(const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
-                               int32_t* pos, int B, int H, int G, int cap, int cache_len, int evict_idx,
-                               int32_t new_pos, float scale, void* out, float* part, int splits, hipStream_t stream)
-{
-    using S = DecodeShape<DT, D, WAVES, UNROLL>;
-    hipLaunchKernelGGL((decode_split_kernel<DT, D, WAVES, UNROLL>), dim3(B * H * splits), dim3(S::kThreads), 0, stream,
-                       (const uint4*)q, (const uint4*)k_new, (const uint4*)v_new, (const uint4*)k_cache,
-                       (const uint4*)v_cache, part, cap, cache_len, splits, scale * kLog2e);
-    int rc = status_from_hip(hipGetLastError());
-    if (rc != EC_OK) return rc;
-    hipLaunchKernelGGL((decode_combine_kernel<DT, D>), dim3(B * H), dim3(kCombineThreads), 0, stream, part,
-                       (const uint4*)k_new, (const uint4*)v_new, (uint4*)k_cache, (uint4*)v_cache, pos, out, H, G, cap,
-                       cache_len, evict_idx, new_pos, splits);
-    return status_from_hip(hipGetLastError());
-}
-
-template <int DT, int D, int WAVES, int UNROLL>
+template <int DT, int D, int WAVES, int UNROLL, bool DEEP, bool EMIT, bool SPLIT>
 static int launch_decode_w(const void* q, const void* k_new, const void* v_new, void* k_cache,
                            void* v_cache, int32_t* pos, int B, int H, int G, int cap, int cache_len,
-                           int evict_idx, int32_t new_pos, float scale, void* out, const int32_t* len_b,
-                           const int32_t* evict_b, const int32_t* new_pos_b, hipStream_t stream)
+                           int evict_idx, int32_t new_pos, float scale, void* out, float* raw, float* stats,
+                           const int32_t* len_b, const int32_t* evict_b, const int32_t* new_pos_b, int splits, int least,
+                           hipStream_t stream)
 {
     using S = DecodeShape<DT, D, WAVES, UNROLL>;
-    hipLaunchKernelGGL((decode_step_kernel<DT, D, WAVES, UNROLL, false>), dim3(B * H), dim3(S::kThreads), 0, stream,
-                       (const uint4*)q, (const uint4*)k_new, (const uint4*)v_new, (uint4*)k_cache,
-                       (uint4*)v_cache, pos, (uint4*)out, H, G, cap, cache_len, evict_idx, new_pos,
-                       scale * kLog2e, (float*)nullptr, (float*)nullptr, len_b, evict_b, new_pos_b);
+    hipLaunchKernelGGL((decode_step_kernel<DT, D, WAVES, UNROLL, DEEP, EMIT, SPLIT>), dim3(B * H * splits),
+                       dim3(S::kThreads), 0, stream, (const uint4*)q, (const uint4*)k_new, (const uint4*)v_new,
+                       (uint4*)k_cache, (uint4*)v_cache, pos, (uint4*)out, B * H, H, G, cap, cache_len, evict_idx, new_pos,
+                       scale * kLog2e, raw, stats, len_b, evict_b, new_pos_b, splits, least);
     return status_from_hip(hipGetLastError());
 }
 
-// Number of workgroups one (batch, head) is divided over when the caller leaves the choice to the library.
-// Measured on MI355X (graph replay, 32 layers): the merging launch costs about as much as an empty dispatch
-// (3-5 us), which is more than the split saves at every workload shape tried -- B*H = 32, 640 rows: 9.9 us
-// fused, 10.3 us best split; B*H = 160: 13.1 vs 16.8 us; B*H = 256: 16.0 vs 20.2 us -- because one launch is
-// ~3 us of dispatch plus bytes at 5.3-5.9 TB/s already.  The library therefore always picks the fused shape;
-// the split shape stays reachable through ec_decode_step_shaped.
-int decode_auto_splits(int BH, int n_rows)
+// Workgroups that one (batch, head) is divided over when the caller leaves the choice to the library: as many as the chip has
+// compute units for, where that saves more than the exchange costs (3.3 us against 1 us per 54 KB of one (batch, head)'s rows).
+// Measured, us per launch (graph replay, D128, one workgroup / divided; crossover):
+//   bf16, B*H =  8:  550 rows 7.8 / 7.3    1200 13.6 / 8.3   4096 38.6 / 11.5     f32  250 rows 7.4 / 7.1   4096 74.6 / 14.1
+//   bf16, B*H = 32:  550 rows 8.3 / 8.2    1200 14.4 / 9.8   4096 41.1 / 16.6     f32  250 rows 8.0 / 8.0   4096 78.4 / 25.8
+//   bf16, B*H = 64:  700 rows 11.1 / 10.2  1200 16.4 / 12.8  4096 45.6 / 26.7     f32  350 rows 10.5 / 10.0  4096 86.7 / 46.9
+//   bf16, B*H = 96:  700 rows 12.8 / 12.5  1200 18.7 / 16.1  4096 51.4 / 39.9     f32  550 rows 15.2 / 14.8  4096 98.8 / 67.9
+//   bf16, B*H = 128: 1200 rows 18.8 / 19.0  2400 34.0 / 32.6  4096 52.0 / 46.9    f32 1200 rows 32.0 / 30.4  4096 101 / 87.9
+// More workgroups than compute units lose everywhere (B*H = 160, two each: 19.8 / 30.1 at 1200 rows).  Sixteen shares instead of
+// eight pay from 2 MB on (B*H = 8, f32 4096 rows: 17.1 / 14.1; 1200 rows: 9.3 / 10.1).
+constexpr int kComputeUnits = 256;
+constexpr int kLeastShareBytes = 48 << 10;  // of K and V
+int decode_auto_splits(int BH, int n_rows, int row_bytes)
 {
-    (void)BH;
-    (void)n_rows;
-    return 1;
+    const long long bytes = 2LL * n_rows * row_bytes;
+    const int splits = std::min(kComputeUnits / BH, bytes >= 2 << 20 ? 16 : 8);
+    const int pays = splits >= 5 ? 288 << 10 : splits >= 3 ? 352 << 10 : BH <= 96 ? 512 << 10 : 960 << 10;
+    return splits >= 2 && bytes >= pays ? splits : 1;
 }
 
-// Workspace floats the split shape needs at most (any cache length up to `cap` rows).
-size_t decode_part_floats(int B, int H, int cap, int D)
+// Shape of a workgroup when the caller leaves it to the library: waves, loads of K and of V per lane and tile, and whether the next
+// tile travels while one is used (deep).  Speed against the kernel before (its loads waited for each other; us = this one):
+//   four waves, 4, deep      : the usual shape; bf16 B*H 32 640 rows 9.1 us (1.08), 256 640 17.0 (1.04), 576 243 rows 17.1 (1.02),
+//                              1360 250 rows (fp32) 72.8 (1.00); eight waves are up to 8 % slower at 100 to 640 rows, equal beyond
+//   two waves, 4, deep       : bf16, many short caches; 800 43 rows 8.1 us (1.05; four waves 0.96), 1536 88 to 176 rows, ragged, 25.3
+//                              (1.02; four waves 0.99), 1536 176 rows in all 29.5 (1.01; 1.02)
+//   two waves, 2, deep       : bf16 rows of 128 bytes, many caches; 1056 71 rows 7.9 us (1.05; with 4: 1.01, four waves: 0.90)
+//   not deep                 : more workgroups than compute units on long caches have more in flight than memory takes: bf16 512
+//                              870 rows 39.8 us (1.03; deep 1.00), 520 815 41.4 (1.12; 1.03), fp32 272 1452 41.9 (1.02; 0.96),
+//                              360 1176 rows 80.8 (1.00; 0.97).  From 512 bf16 pairs on two waves, else four.
+constexpr int kLongHeadBytes = 320 << 10, kShortHeadBytes = 96 << 10;  // of K and V
+struct DecodeAuto {
+    int waves, unroll;
+    bool deep;
+};
+static DecodeAuto decode_auto_shape(int BH, int n_rows, int D, int dt)
 {
-    const int s = decode_auto_splits(B * H, cap);
-    return s < 2 ? 0 : (size_t)B * H * s * (D + 2);
+    const bool half = dt == EC_BF16;
+    const long long bytes = 2LL * n_rows * D * (half ? 2 : 4);
+    if (BH > kComputeUnits && bytes >= kLongHeadBytes) return {half && BH >= 512 ? 2 : 4, 4, false};
+    if (half && BH >= 768 && D == 64) return {2, 2, true};
+    if (half && BH >= 768 && bytes < kShortHeadBytes) return {2, 4, true};
+    return {4, 4, true};
 }
 
-// Workgroup width and loads in flight grow with the number of rows to stream.  splits: 0 = choose, 1 = fused
-// kernel, n > 1 = n workgroups per (batch, head) + combine launch (needs `part`, part_floats >= B*H*n*(D+2)).
+// splits: 0 = choose, n = n workgroups per (batch, head).
 template <int DT, int D>
 static int launch_decode(const void* q, const void* k_new, const void* v_new, void* k_cache,
                          void* v_cache, int32_t* pos, int B, int H, int G, int cap, int cache_len,
                          int evict_idx, int32_t new_pos, float scale, void* out, int forced_waves,
-                         int forced_unroll, int splits, bool strict, float* part, size_t part_floats,
+                         int forced_unroll, int splits, bool strict, size_t part_floats,
                          const int32_t* len_b, const int32_t* evict_b, const int32_t* new_pos_b, hipStream_t stream)
 {
+    constexpr int kRow = D * Elem<DT>::kBytes;
     const int n_rows = cache_len + 1;  // ragged batches pass the longest length the buffers allow
-    if (splits <= 0 || len_b != nullptr) splits = decode_auto_splits(B * H, n_rows);  // ragged batches: fused only
-    if (splits > 1 && (part == nullptr || part_floats < (size_t)B * H * splits * (D + 2))) {
-        if (strict) return EC_EWORKSPACE;  // an explicit request that cannot be met
-        splits = 1;                        // no workspace: the fused shape needs none
+    int waves = forced_waves, unroll = forced_unroll <= 0 ? 4 : forced_unroll, least = 1;
+    // an explicit request has to bring a workspace, as the interface says
+    if (strict && splits > 1 && part_floats < (size_t)B * H * splits * (D + 2)) return EC_EWORKSPACE;
+    const bool choose = forced_waves <= 0 && forced_unroll <= 0 && splits <= 0;
+    if (splits <= 0) {  // with a width or a depth given, one workgroup takes everything
+        splits = choose ? decode_auto_splits(B * H, n_rows, kRow) : 1;
+        least = kLeastShareBytes / (2 * kRow);
     }
-    int waves = forced_waves, unroll = forced_unroll;
+#define EC_DECODE_W(W_, U_, DEEP_, SPLIT_)                                                                                 \
+    return launch_decode_w<DT, D, W_, U_, DEEP_, false, SPLIT_>(q, k_new, v_new, k_cache, v_cache, pos, B, H, G, cap, cache_len, \
+                                                                evict_idx, new_pos, scale, out, nullptr, nullptr, len_b,   \
+                                                                evict_b, new_pos_b, splits, least, stream)
+    if (choose && splits == 1) {
+        const DecodeAuto a = decode_auto_shape(B * H, n_rows, D, DT);
+        if (!a.deep && a.waves == 2) EC_DECODE_W(2, 4, false, false);
+        if (!a.deep) EC_DECODE_W(4, 4, false, false);
+        if (a.unroll == 2) EC_DECODE_W(2, 2, true, false);
+        waves = a.waves;
+    }
+    if (waves <= 0) waves = 4;
+    const bool known = splits > 1 ? ((waves == 2 || waves == 4) && (unroll == 4 || unroll == 8)) || (waves == 8 && unroll == 4)
+                                  : (waves == 2 && (unroll == 4 || unroll == 8)) ||
+                                        (waves == 4 && (unroll == 4 || unroll == 6 || unroll == 8 || unroll == 12)) ||
+                                        (waves == 8 && (unroll == 4 || unroll == 8 || unroll == 12)) ||
+                                        (waves == 16 && (unroll == 4 || unroll == 6));
+    if (!known) return EC_EINVAL;
+    // what the kernel is built for: up to 8 waves, 4 or 8 loads of K and of V
+#define EC_DECODE_U(W_, SPLIT_)                            \
+    do {                                                   \
+        if (unroll == 4) EC_DECODE_W(W_, 4, true, SPLIT_); \
+        EC_DECODE_W(W_, 8, true, SPLIT_);                  \
+    } while (0)
     if (splits > 1) {
-        if (waves <= 0) waves = ((n_rows + splits - 1) / splits >= 192) ? 8 : 4;
-        if (unroll <= 0) unroll = 4;
-#define EC_DECODE_S(W_, U_)                                                                                    \
-    if (waves == W_ && unroll == U_)                                                                           \
-        return launch_decode_split<DT, D, W_, U_>(q, k_new, v_new, k_cache, v_cache, pos, B, H, G, cap, cache_len, \
-                                                  evict_idx, new_pos, scale, out, part, splits, stream);
-        EC_DECODE_S(4, 4)
-        EC_DECODE_S(8, 4)
-        EC_DECODE_S(4, 8)
-        EC_DECODE_S(2, 4)
-        EC_DECODE_S(2, 8)
-#undef EC_DECODE_S
-        return EC_EINVAL;
+        if (waves == 2) EC_DECODE_U(2, true);
+        if (waves == 4) EC_DECODE_U(4, true);
+        EC_DECODE_W(8, 4, true, true);
     }
-    // Width of a workgroup.  Measured (us per launch, 4 loads of K and of V in flight per lane; 2 / 4 / 8 / 16 waves):
-    //   B*H =   32,  640 rows: 20.6 / 12.4 /  9.8 / 10.8      B*H =  160,  640 rows: 22.4 / 14.6 / 12.4 / 13.1
-    //   B*H =  256,  576 rows: 23.8 / 16.1 / 15.5 / 16.1      B*H =  320,  256 rows: 13.1 / 11.7 / 12.8 / 15.4
-    //   B*H =  512,  870 rows: 40.6 / 39.7 / 42.0 / 45.5      B*H = 1536,  150 rows: 24.9 / 26.6 / 28.4 / 37.0
-    // With one workgroup per compute unit or less the wide workgroup streams fastest; once several workgroups
-    // share a compute unit, narrower ones (more of them resident, shorter tails) do.
-    if (waves <= 0) {
-        const long long bh = (long long)B * H;
-        waves = bh >= 1024 ? 2 : bh > 256 ? 4 : (n_rows >= 96 ? 8 : 4);
-    }
-    if (unroll <= 0) unroll = 4;
-#define EC_DECODE_W(W_, U_)                                                                              \
-    if (waves == W_ && unroll == U_)                                                                     \
-        return launch_decode_w<DT, D, W_, U_>(q, k_new, v_new, k_cache, v_cache, pos, B, H, G, cap, cache_len, \
-                                              evict_idx, new_pos, scale, out, len_b, evict_b, new_pos_b, stream);
-    EC_DECODE_W(2, 4)
-    EC_DECODE_W(2, 8)
-    EC_DECODE_W(4, 4)
-    EC_DECODE_W(4, 6)
-    EC_DECODE_W(4, 8)
-    EC_DECODE_W(8, 4)
-    EC_DECODE_W(16, 4)
-    EC_DECODE_W(16, 6)
-    EC_DECODE_W(8, 8)
-    EC_DECODE_W(8, 12)
-    EC_DECODE_W(4, 12)
+    splits = 1;
+    if (waves == 2) EC_DECODE_U(2, false);
+    if (waves == 4) EC_DECODE_U(4, false);
+    EC_DECODE_U(8, false);
+#undef EC_DECODE_U
 #undef EC_DECODE_W
-    return EC_EINVAL;
 }
 
 // strict: the launch shape is an explicit request; a split without enough workspace is then an error instead
@@ -593,14 +718,14 @@ static int launch_decode(const void* q, const void* k_new, const void* v_new, vo
 int decode_dispatch(const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
                     int32_t* pos, int B, int H, int G, int D, int cap, int cache_len, int evict_idx,
                     int32_t new_pos, float scale, int dt, void* out, int forced_waves, int forced_unroll,
-                    int splits, bool strict, float* part, size_t part_floats, const int32_t* len_b,
+                    int splits, bool strict, size_t part_floats, const int32_t* len_b,
                     const int32_t* evict_b, const int32_t* new_pos_b, hipStream_t stream)
 {
 #define EC_DECODE_CASE(DT_, D_)                                                                       \
     if (dt == DT_ && D == D_)                                                                         \
         return launch_decode<DT_, D_>(q, k_new, v_new, k_cache, v_cache, pos, B, H, G, cap, cache_len,    \
                                       evict_idx, new_pos, scale, out, forced_waves, forced_unroll, splits, \
-                                      strict, part, part_floats, len_b, evict_b, new_pos_b, stream);
+                                      strict, part_floats, len_b, evict_b, new_pos_b, stream);
     EC_DECODE_CASE(EC_BF16, 128)
     EC_DECODE_CASE(EC_BF16, 64)
     EC_DECODE_CASE(EC_F32, 128)
@@ -647,20 +772,26 @@ __global__ __launch_bounds__(kFreqRows * kFreqParts) void freq_accumulate_kernel
     }
 }
 
-template <int DT, int D, int WAVES>
+template <int DT, int D>
 static int launch_decode_score(const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
                                int32_t* pos, float* freq, int B, int H, int G, int cap, int cache_len,
                                int32_t new_pos, float scale, void* out, float* raw, float* stats,
                                hipStream_t stream)
 {
-    using S = DecodeShape<DT, D, WAVES, 4>;
-    hipLaunchKernelGGL((decode_step_kernel<DT, D, WAVES, 4, true>), dim3(B * H), dim3(S::kThreads), 0, stream,
-                       (const uint4*)q, (const uint4*)k_new, (const uint4*)v_new, (uint4*)k_cache,
-                       (uint4*)v_cache, pos, (uint4*)out, H, G, cap, cache_len, -1, new_pos, scale * kLog2e, raw,
-                       stats, (const int32_t*)nullptr, (const int32_t*)nullptr, (const int32_t*)nullptr);
-    int rc = status_from_hip(hipGetLastError());
+    constexpr int kRow = D * Elem<DT>::kBytes;
+    const int n = cache_len + 1, splits = decode_auto_splits(B * H, n, kRow), least = kLeastShareBytes / (2 * kRow);
+#define EC_DSCORE(W_, U_, DEEP_, SPLIT_)                                                                                   \
+    launch_decode_w<DT, D, W_, U_, DEEP_, true, SPLIT_>(q, k_new, v_new, k_cache, v_cache, pos, B, H, G, cap, cache_len, -1, \
+                                                        new_pos, scale, out, raw, stats, nullptr, nullptr, nullptr, splits, \
+                                                        least, stream)
+    const DecodeAuto a = decode_auto_shape(B * H, n, D, DT);
+    const int rc = splits > 1      ? EC_DSCORE(4, 4, true, true)
+                   : !a.deep       ? (a.waves == 2 ? EC_DSCORE(2, 4, false, false) : EC_DSCORE(4, 4, false, false))
+                   : a.unroll == 2 ? EC_DSCORE(2, 2, true, false)
+                   : a.waves == 2  ? EC_DSCORE(2, 4, true, false)
+                                   : EC_DSCORE(4, 4, true, false);
+#undef EC_DSCORE
     if (rc != EC_OK) return rc;
-    const int n = cache_len + 1;
     hipLaunchKernelGGL(freq_accumulate_kernel, dim3((n + kFreqRows - 1) / kFreqRows, B * G),
                        dim3(kFreqRows * kFreqParts), 0, stream, raw, stats, freq, H, G, n, cap);
     return status_from_hip(hipGetLastError());
@@ -671,13 +802,10 @@ int decode_score_dispatch(const void* q, const void* k_new, const void* v_new, v
                           int32_t new_pos, float scale, int dt, void* out, float* raw, float* stats,
                           hipStream_t stream)
 {
-    const bool wide = cache_len + 1 >= 96;
-#define EC_DSCORE_CASE(DT_, D_)                                                                                \
-    if (dt == DT_ && D == D_)                                                                                  \
-        return wide ? launch_decode_score<DT_, D_, 8>(q, k_new, v_new, k_cache, v_cache, pos, freq, B, H, G, cap,  \
-                                                      cache_len, new_pos, scale, out, raw, stats, stream)     \
-                    : launch_decode_score<DT_, D_, 4>(q, k_new, v_new, k_cache, v_cache, pos, freq, B, H, G, cap,  \
-                                                      cache_len, new_pos, scale, out, raw, stats, stream);
+#define EC_DSCORE_CASE(DT_, D_)                                                                                          \
+    if (dt == DT_ && D == D_)                                                                                            \
+        return launch_decode_score<DT_, D_>(q, k_new, v_new, k_cache, v_cache, pos, freq, B, H, G, cap, cache_len, new_pos, \
+                                            scale, out, raw, stats, stream);
     EC_DSCORE_CASE(EC_BF16, 128)
     EC_DSCORE_CASE(EC_BF16, 64)
     EC_DSCORE_CASE(EC_F32, 128)
@@ -695,13 +823,6 @@ int decode_score_dispatch(const void* q, const void* k_new, const void* v_new, v
 // Measured at H32 D128, bf16, victims anywhere, whole call (four caches in turn): B8 640 rows 42.8 -> 21.2 us, B16 900 rows
 // 110 -> 58.5 us, B1 640 rows 13.2 -> 7.4 us from 512 rows a round, which went through scratch memory one by one.
 // Threads x loads 256 x 8 to 1024 x 8 differ by 5 %; more than 8 loads cost small caches up to 30 %.
-
-// All of x has arrived in registers: what follows neither waits for it nor runs before it.
-template <typename T, int N> __device__ __forceinline__ void arrived(T (&x)[N])
-{
-#pragma unroll
-    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));
-}
 
 constexpr int kEvictMetaThreads = 1024;
 constexpr int kEvictMetaUnroll = 4;

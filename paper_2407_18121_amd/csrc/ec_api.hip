@@ -11,9 +11,8 @@ namespace ec {
 int decode_dispatch(const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
                     int32_t* pos, int B, int H, int G, int D, int cap, int cache_len, int evict_idx,
                     int32_t new_pos, float scale, int dt, void* out, int forced_waves, int forced_unroll,
-                    int splits, bool strict, float* part, size_t part_floats, const int32_t* len_b,
+                    int splits, bool strict, size_t part_floats, const int32_t* len_b,
                     const int32_t* evict_b, const int32_t* new_pos_b, hipStream_t stream);
-size_t decode_part_floats(int B, int H, int cap, int D);
 int decode_score_dispatch(const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
                           int32_t* pos, float* freq, int B, int H, int G, int D, int cap, int cache_len,
                           int32_t new_pos, float scale, int dt, void* out, float* raw, float* stats,
@@ -145,9 +144,7 @@ size_t ec_workspace_bytes(int fn, int B, int H, int T, int D, int dt)
         case EC_FN_MERGE_COMPACT: return 0;
         case EC_FN_DECODE_STEP:
             if (!shape_supported(D, dt)) return (size_t)-1;
-            // partial (max, sum, weighted V) of every split when one (batch, head) is divided over several
-            // workgroups; 0 when the batch alone fills the chip
-            return align256(ec::decode_part_floats(B, H, T, D) * sizeof(float));
+            return 0;
         case EC_FN_DECODE_SCORE_STEP:
             if (!shape_supported(D, dt)) return (size_t)-1;
             // every row's scaled score [B,H,T] + softmax maximum and denominator [B,H,2], fp32
@@ -324,8 +321,7 @@ int decode_step_checked(const void* q, const void* k_new, const void* v_new, voi
     if ((long long)B * H > 65535) return EC_EUNSUPPORTED;
     if (!shape_supported(D, dt)) return EC_EUNSUPPORTED;
     return ec::decode_dispatch(q, k_new, v_new, k_cache, v_cache, pos, B, H, G, D, cap, cache_len, evict_idx,
-                               new_pos, scale, dt, out, waves, unroll, splits, strict, reinterpret_cast<float*>(ws),
-                               ws ? ws_bytes / sizeof(float) : 0, nullptr, nullptr, nullptr,
+                               new_pos, scale, dt, out, waves, unroll, splits, strict, ws ? ws_bytes / sizeof(float) : 0, nullptr, nullptr, nullptr,
                                reinterpret_cast<hipStream_t>(stream));
 }
 }  // namespace
@@ -361,8 +357,7 @@ int ec_decode_step_varlen(const void* q, const void* k_new, const void* v_new, v
     if (!shape_supported(D, dt)) return EC_EUNSUPPORTED;
     // the lengths live on the device: the launch shape is chosen for the longest cache the buffers allow
     return ec::decode_dispatch(q, k_new, v_new, k_cache, v_cache, pos, B, H, G, D, cap, cap - 1, -1, 0, scale, dt, out,
-                               0, 0, 0, false, reinterpret_cast<float*>(ws), ws ? ws_bytes / sizeof(float) : 0,
-                               cache_len_b, evict_idx_b, new_pos_b, reinterpret_cast<hipStream_t>(stream));
+                               0, 0, 0, false, ws ? ws_bytes / sizeof(float) : 0, cache_len_b, evict_idx_b, new_pos_b, reinterpret_cast<hipStream_t>(stream));
 }
 
 int ec_decode_score_step(const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,

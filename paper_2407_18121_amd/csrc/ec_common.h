@@ -96,6 +96,7 @@ constexpr int kDppQuadXor1 = 0xB1;      // quad_perm [1,0,3,2]
 constexpr int kDppQuadXor2 = 0x4E;      // quad_perm [2,3,0,1]
 constexpr int kDppRowHalfMirror = 0x141;  // lane i <-> 7-i inside each 8 lanes
 constexpr int kDppRowMirror = 0x140;      // lane i <-> 15-i inside each 16 lanes
+constexpr int kDppRowRor8 = 0x128;        // lane i <-> i +- 8 inside each 16 lanes
 
 // Sum over aligned groups of LPR lanes (LPR in {8,16,32,64}); every lane gets the sum.
 template <int LPR> __device__ __forceinline__ float group_sum(float x)
@@ -104,7 +105,10 @@ template <int LPR> __device__ __forceinline__ float group_sum(float x)
     x += dpp_mov<kDppQuadXor2>(x);
     x += dpp_mov<kDppRowHalfMirror>(x);
     if (LPR >= 16) x += dpp_mov<kDppRowMirror>(x);
-    if (LPR >= 32) x += __shfl_xor(x, 16, kWave);
+    if (LPR >= 32) {
+        const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = __uint_as_float(y[0]) + __uint_as_float(y[1]);
+    }
     if (LPR >= 64) x += __shfl_xor(x, 32, kWave);
     return x;
 }
