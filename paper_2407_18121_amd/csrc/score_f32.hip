@@ -8,18 +8,22 @@
 //   colsum_f32   : the K operands of 16 keys stay in registers, queries stream through LDS, p = exp(s - lse_row) is
 //                  summed per key over a lane's queries and over the lanes at the end.  One workgroup owns a column:
 //                  no atomics, deterministic.
-// Bound: the matrix pipe at its fp32 rate (a sixteenth of the bf16 one; 149 TFLOP/s in a large product here); a block costs
-// 64 instructions of 32 clocks (D = 128) against some 30 vector instructions, so the phases simply follow each other and
-// the other wave of the SIMD fills the gaps.  Measured, before (vector ALU) -> after: whole call at B1 H32 T1024 D128
-// 694 -> 143 us (90 TFLOP/s; a workgroup loops over up to 32 tiles while the mean is 16).  By the profiler, which times
-// every launch by itself and adds its start, the two passes take 498 + 221 -> 103 + 53 us there (109 + 52 us with the
-// waits for the operands inside the loop) and 61 + 22 -> 7.9 + 4.8 us at B1 H4 T256 D64.
-// Error of out against 64 bits at T1024 6.3e-7 -> 2.7e-7, of the scores 1.3e-7 -> 0.7e-7.
+// Bound: the matrix pipe at its fp32 rate (a sixteenth of the bf16 one; 149 TFLOP/s in a large product here).  A tile of 32
+// keys costs a wave 128 instructions of 32 clocks (D = 128); while two waves share a SIMD the vector work fills the gaps, but the
+// longest workgroups end alone, and there everything between the matrix instructions adds up: 6.9 thousand clocks a tile
+// with the compiler's order, of which 4.1 matrix time.  Operands requested ahead at constant addresses, loads among the matrix
+// instructions and the bare exponential instruction took that down.  Measured (graph replay), vector ALU -> matrix
+// instructions -> now: whole call at B1 H32 T1024 D128 694 -> 148 -> 129 us (100 TFLOP/s; a workgroup loops over up to 32 tiles
+// while the mean is 16), T2048 496 -> 450, T512 58.5 -> 51.7, H8 T1024 81 -> 69.5, B1 H32 T1024 D64 88 -> 74.5.
+// Eight waves on 64 queries, two on the keys of each 16: 168 us at T1024 (81 at D64), all of them in step.
+// Error of out against 64 bits at T1024 6.3e-7 (vector ALU) -> 2.8e-7, of the scores 1.3e-7 -> 1.1e-7, no change by the order.
 // Operands are read from LDS 16 bytes at a time, each read feeding four instructions: both operands of a contraction
 // enumerate it in the same permuted order.
 //
 // Operand layout (wave64, lane l, quarter h = l / 16): A (16 x 4): lane holds A[l % 16][h];  B (4 x 16): B[h][l % 16];
 //   C (16 x 16): lane holds C[4h + r][l % 16] in register r.
+#include <type_traits>
+
 #include "tile_lds.h"
 
 namespace ec {
@@ -54,30 +58,19 @@ __device__ __forceinline__ F32Item f32_item(int linear_id, int n_tiles, int n_he
 }
 inline int f32_grid(int n_tiles, int n_heads) { return (n_heads + kXcds - 1) / kXcds * n_tiles * kXcds; }
 
-// S^T = K.Q^T of NBLK blocks of 16 keys against the wave's 16 queries, in four chains per block: shorter sums, and no
-// instruction waits for the one before it.
-template <int D, int NBLK>
-__device__ __forceinline__ void score_blocks(const uint32_t (&at)[NBLK], const f32x4 (&qf)[D / 16], int swz, int h,
-                                             f32x4 (&s)[NBLK])
+// A wave that has the SIMD to itself, as the longest workgroup of a launch does at the end, pays for every vector instruction
+// and every wait between its matrix instructions (a 16x16x4 takes 32 clocks, two additions behind it make that 44).  So operands
+// are requested kAhead reads before the four matrix instructions that use them, at addresses that differ by constants, the next
+// tile's loads are issued in between, and the order is fixed by hand.
+constexpr int kAhead = 4;
+
+// Maximum over the four quarters of the wave.
+__device__ __forceinline__ float quarters_max(float x)
 {
-    f32x4 t[NBLK][4];
-#pragma unroll
-    for (int b = 0; b < NBLK; ++b)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) t[b][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kb = 0; kb < D / 16; ++kb) {
-        f32x4 a[NBLK];
-#pragma unroll
-        for (int b = 0; b < NBLK; ++b) a[b] = lds_read(at[b] + ((4 * kb + h) ^ swz) * 16);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int b = 0; b < NBLK; ++b)
-                t[b][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b][e], qf[kb][e], t[b][e], 0, 0, 0);
-    }
-#pragma unroll
-    for (int b = 0; b < NBLK; ++b) s[b] = (t[b][0] + t[b][1]) + (t[b][2] + t[b][3]);
+    const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(y[0]), __uint_as_float(y[1]));
+    const auto z = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(z[0]), __uint_as_float(z[1]));
 }
 
 // ------------------------------------------------------------------ forward
@@ -114,18 +107,20 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
     const Mover k_move(tile_rsrc(k + (size_t)bh * geo.kv_rows * D, (uint32_t)L * (D * 4)), wave, lane);
     const Mover v_move(tile_rsrc(v + (size_t)bh * geo.kv_rows * D, (uint32_t)L * (D * 4)), wave, lane);
     const uint32_t base = lds_address(tiles);
-    auto fetch = [&](int t) __attribute__((always_inline)) {
+    constexpr int LOADS = OUT ? 2 * Mover::NI : Mover::NI;  // of a wave per tile
+    auto fetch = [&](int t, int from, int to) __attribute__((always_inline)) {
         const uint32_t at = base + t % 2 * TILE;
 #pragma unroll
-        for (int j = 0; j < Mover::NI; ++j) k_move.issue(at, t * TN, j);
-        if constexpr (OUT) {
-#pragma unroll
-            for (int j = 0; j < Mover::NI; ++j) v_move.issue(at + 2 * TILE, t * TN, j);
+        for (int j = from; j < to; ++j) {
+            if (j < Mover::NI)
+                k_move.issue(at, t * TN, j);
+            else
+                v_move.issue(at + 2 * TILE, t * TN, j - Mover::NI);
         }
     };
     const int n_end = min(L, P + m0 + BM);
     const int n_tiles = (n_end + TN - 1) / TN;
-    fetch(0);
+    fetch(0, 0, LOADS);
 
     f32x4 qf[KB];  // B operand: element e of block kb is feature 16 kb + 4 h + e of this lane's query
     {
@@ -145,19 +140,55 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
     wait_loads();
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(qf[kb]));
-    for (int t = 0; t < n_tiles; ++t) {
+    // Byte addresses of this lane's operands in the even tiles.  K: contraction block kb of key r16 of the wave's first block.
+    // V: 4 features (of every 64) of key 4h + j there.
+    constexpr int VC = D / 64;
+    uint32_t k_at[KB], v_at[4];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) k_at[kb] = one_register(base + (ks * 16 + r16) * (D * 4) + ((4 * kb + h) ^ r16) * 16);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        v_at[j] = one_register(base + 2 * TILE + (ks * 16 + 4 * h + j) * (D * 4) + (r16 ^ (4 * h + j)) * 16);
+
+    auto body = [&](int t, auto odd) __attribute__((always_inline)) {
+        constexpr int PAR = odd.value ? TILE : 0;
+        constexpr int NF = KB * NBLK, NV = NBLK * 4 * VC;  // operands of S^T: (block kb, key block); of O^T: (key block, j, 64 features)
+        constexpr bool SPREAD = NF >= 16;  // loads between the matrix instructions: B8 T300 H32 D128 127 -> 121 us; D64 76.4 -> 78.5
         wait_loads();
         wait_lds();
         meet();  // tile t has landed, tile t - 1 has been read
-        if (t + 1 < n_tiles) fetch(t + 1);
+        const bool more = t + 1 < n_tiles;
         const int n0 = t * TN + ks * 16;  // the wave's blocks start 16 KS keys apart
-        if (n0 > P + mw + 15) continue;   // every key is in the future of the wave's queries
-        const uint32_t at = base + t % 2 * TILE;
-        uint32_t rows[NBLK];
+        const bool idle = n0 > P + mw + 15;  // every key is in the future of the wave's queries
+        if (more && (!SPREAD || idle)) fetch(t + 1, 0, LOADS);
+        if (idle) return;
+        auto operand_k = [&](int f) __attribute__((always_inline)) { return lds_read(k_at[f / NBLK] + (PAR + f % NBLK * KS * 16 * D * 4)); };
+        auto operand_v = [&](int g) __attribute__((always_inline)) {
+            return lds_read(v_at[g / VC % 4] + (PAR + g / VC / 4 * KS * 16 * D * 4 + g % VC * 256));
+        };
+        // S^T in four chains per block: shorter sums, and no instruction waits for the one before it
+        f32x4 c[NBLK][4], ka[NF], va[NV], s[NBLK];
 #pragma unroll
-        for (int b = 0; b < NBLK; ++b) rows[b] = at + ((b * KS + ks) * 16 + r16) * (D * 4);
-        f32x4 s[NBLK];
-        score_blocks<D, NBLK>(rows, qf, r16, h, s);
+        for (int f = 0; f < kAhead; ++f) ka[f] = operand_k(f);
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) c[b][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                c[f % NBLK][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(ka[f][e], qf[f / NBLK][e], c[f % NBLK][e], 0, 0, 0);
+            if (f + kAhead < NF)
+                ka[f + kAhead] = operand_k(f + kAhead);
+            else if (OUT)
+                va[f + kAhead - NF] = operand_v(f + kAhead - NF);  // on their way during the softmax
+            if (SPREAD && more) fetch(t + 1, f * LOADS / NF, (f + 1) * LOADS / NF);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b) s[b] = (c[b][0] + c[b][1]) + (c[b][2] + c[b][3]);
         if (n0 + (NBLK - 1) * 16 * KS + 15 > P + mw) {
 #pragma unroll
             for (int b = 0; b < NBLK; ++b)
@@ -170,17 +201,16 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
         for (int b = 0; b < NBLK; ++b)
 #pragma unroll
             for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[b][r]);
-        mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+        mx = quarters_max(mx);
         const float m_new = fmaxf(m_run, mx);
-        const float corr = exp2f((m_run - m_new) * scale_log2e);
+        const float corr = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
         m_run = m_new;
         float psum = 0.f;
 #pragma unroll
         for (int b = 0; b < NBLK; ++b)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                s[b][r] = exp2f((s[b][r] - m_new) * scale_log2e);
+                s[b][r] = __builtin_amdgcn_exp2f((s[b][r] - m_new) * scale_log2e);
                 psum += s[b][r];
             }
         l_run = fmaf(l_run, corr, psum);
@@ -189,24 +219,24 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
             f32x4 ot[DB];
 #pragma unroll
             for (int db = 0; db < DB; ++db) ot[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int b = 0; b < NBLK; ++b)
+            for (int g = 0; g < NV; ++g) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int row = (b * KS + ks) * 16 + 4 * h + j;
-                    f32x4 a[D / 64];
-#pragma unroll
-                    for (int c = 0; c < D / 64; ++c)
-                        a[c] = lds_read(at + 2 * TILE + row * (D * 4) + ((c * 16 + r16) ^ (row & 15)) * 16);
-#pragma unroll
-                    for (int db = 0; db < DB; ++db)
-                        ot[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[db / 4][db % 4], s[b][j], ot[db], 0, 0, 0);
-                }
+                for (int e = 0; e < 4; ++e)
+                    ot[g % VC * 4 + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(va[g][e], s[g / VC / 4][g / VC % 4], ot[g % VC * 4 + e], 0, 0, 0);
+                if (g + kAhead < NV) va[g + kAhead] = operand_v(g + kAhead);
+                __builtin_amdgcn_sched_barrier(0);
+            }
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) o[db][r] = fmaf(o[db][r], corr, ot[db][r]);
         }
+    };
+    for (int t = 0; t < n_tiles; t += 2) {
+        body(t, std::false_type{});
+        if (t + 1 < n_tiles) body(t + 1, std::true_type{});
     }
 
     l_run += __shfl_xor(l_run, 16, kWave);
@@ -318,31 +348,53 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void colsum_f32_kernel(
     wait_loads();  // as in the forward pass: no wait for the operand inside the loop
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(kf[kb]));
-    for (int t = 0; t < n_tiles; ++t) {
+    uint32_t q_at[KB];  // byte address of this lane's operand of contraction block kb in the even tiles
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) q_at[kb] = one_register(base + (qg * 16 + r16) * (D * 4) + ((4 * kb + h) ^ r16) * 16);
+    auto body = [&](int t, auto odd) __attribute__((always_inline)) {
+        constexpr int PAR = odd.value ? TILE : 0;
         const int m0 = m_begin + t * TQ + qg * 16;  // first query of the wave's block
         wait_loads();
         wait_lds();
         meet();  // tile t has landed, tile t - 1 has been read
         const float l2 = l2_next * lse_unit;
         if (t + 1 < n_tiles) fetch(t + 1);
-        if (P + m0 + 15 < nw) continue;  // no query of the tile sees a key of this wave
-        f32x4 s[4];
+        if (P + m0 + 15 < nw) return;  // no query of the tile sees a key of this wave
+        f32x4 s[4], a[KB];
+#pragma unroll
+        for (int kb = 0; kb < kAhead; ++kb) a[kb] = lds_read(q_at[kb] + PAR);
 #pragma unroll
         for (int e = 0; e < 4; ++e) s[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
-            const f32x4 a = lds_read(base + t % 2 * TILE + (qg * 16 + r16) * (D * 4) + ((4 * kb + h) ^ r16) * 16);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][e], a[e], s[e], 0, 0, 0);
+            for (int e = 0; e < 4; ++e) s[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][e], a[kb][e], s[e], 0, 0, 0);
+            if (kb + kAhead < KB) a[kb + kAhead] = lds_read(q_at[kb + kAhead] + PAR);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        const int m = m0 + r16;
-        const int last = m < Tq ? P + m - nw - 4 * h : -1;  // last of the lane's keys that its query sees
+        f32x4 p;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float x = (s[0][r] + s[1][r]) + (s[2][r] + s[3][r]);
-            const float p = exp2f(fmaf(x, scale_log2e, -l2));
-            col[r] += r <= last ? p : 0.f;
+        for (int r = 0; r < 4; ++r) p[r] = fmaf((s[0][r] + s[1][r]) + (s[2][r] + s[3][r]), scale_log2e, -l2);
+        // the exponential instruction gives zero where the result is subnormal; exp2f, which is five times as long, does not
+        if (__any(fminf(fminf(p[0], p[1]), fminf(p[2], p[3])) < -126.f)) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p[r] = exp2f(p[r]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(p[r]);
         }
+        if (m0 + 16 > Tq || P + m0 < nw + 15) {  // uniform: a query behind the last one, or a key behind its query
+            const int m = m0 + r16;
+            const int last = m < Tq ? P + m - nw - 4 * h : -1;  // last of the lane's keys that its query sees
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p[r] = r <= last ? p[r] : 0.f;
+        }
+        col += p;
+    };
+    for (int t = 0; t < n_tiles; t += 2) {
+        body(t, std::false_type{});
+        if (t + 1 < n_tiles) body(t + 1, std::true_type{});
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -380,8 +432,8 @@ static int launch_f32(const float* q, const float* k, const float* v, float* out
     } while (0)
     // us of the whole call for 64 / 32 / 16 queries per workgroup (one / two / four waves on the keys of 16 queries), H32
     // D128, the column pass alike:
-    //   B1 T256 38.7 / 32.2 / 32.8   B1 T512 68.7 / 56.6 / 71.5   B1 T1024 143 / 151 / 208   B4 T256 50.3 / 54.1 / 85.7
-    //   B1 T2048 496 / 523 / 733   H16 B1 T1024 124 / 95 / 118   H8 B1 T512 64.8 / 49.7 / 38.2
+    //   B1 T256 34.0 / 28.2 / 29.8   B1 T512 61.0 / 52.2 / 67.0   B1 T1024 130 / 143 / 186   B4 T256 47.2 / 52.9 / 80.4
+    //   B1 T2048 451 / 476 / 642   H16 B1 T1024 105 / 82.6 / 104   H8 B1 T512 50.2 / 38.3 / 29.2
     const long long wide = (long long)qt64 * BH;
     if (wide >= 512)
         EC_FWD_F32(4, 1, qt64);
@@ -393,9 +445,8 @@ static int launch_f32(const float* q, const float* k, const float* v, float* out
     int rc = status_from_hip(hipGetLastError());
     if (rc != EC_OK) return rc;
     const int kt32 = (geo.L + 31) / 32, kt16 = (geo.L + 15) / 16;
-    // us of the whole call for 32 / 16 keys per workgroup, 64 queries per workgroup in the forward pass:
-    //   B1 T256 38.7 / 37.4   B1 T512 68.7 / 70.9   B1 T1024 143 / 155   B4 T256 50.3 / 58.9   H8 B1 T512 64.8 / 58.8
-    //   (64 keys, column pass alone at T1024: 62 against 53)
+    // us of the whole call for 32 / 16 keys per workgroup:
+    //   B1 T256 29.2 / 28.5   B1 T512 51.9 / 55.5   B1 T1024 131 / 144   B4 T256 47.7 / 57.2   H8 B1 T512 34.0 / 29.1
     if ((long long)kt32 * BH >= 512)
         hipLaunchKernelGGL((colsum_f32_kernel<D, 2, 2>), dim3(f32_grid(kt32, BH)), block, 0, stream, q, k, lse, unit_in,
                            head_imp, geo, sl, kt32, BH, seq_len, H);
