@@ -1,33 +1,70 @@
 // ec_merge_compact / ec_remerge_compact: bucket division (Sec. 3.3, Eq. 2), cache merging
 // (Eq. 3) and compaction (Alg. 1's gather) in one pass over K and V.
 //
-// HBM-bound: every prompt K/V row is read once, every cache row written once.
-// Buckets are contiguous position ranges, so the rows of bucket j are one
-// contiguous slab of memory.  A group of LPR = row_bytes/16 lanes owns bucket j:
-// it derives the bucket's bounds from the three neighbouring anchors, streams the
-// slab with 16-byte loads in ascending position, accumulates in fp32, divides by
-// the count once and stores the row.  Neighbouring groups own neighbouring
-// buckets, so a wave reads one contiguous stretch of the prompt.  Importance scores
-// put most anchors next to each other and leave a few buckets of hundreds of rows:
-// those are summed by all lane groups of the workgroup together.
+// Every prompt K/V row is read once, every cache row written once: HBM-bound where the launch fills the chip, bound by the
+// longest chain of loads that wait for each other where it does not.  Buckets are contiguous position ranges, so the rows of
+// bucket j are one contiguous slab of memory.  A group of LPR = row_bytes/16 lanes streams rows with 16-byte loads,
+// accumulates in fp32, divides by the count once and stores the row.
+// Importance scores put most anchors next to each other and leave buckets of tens to thousands of rows between the others, so
+//   - a workgroup's buckets are runs of a wave's width (1 KB of single rows) from all over the head: with one stretch of the
+//     head each, a few workgroups had all the long buckets.  Runs of 1 / 2 / 4 / 8 / 16 buckets, bf16 D128: B1 H32 T1024
+//     half the rows kept 12.0 / 11.8 / 11.7 / 12.3 / 15.4 us, B8 T1664 54 % kept 98.7 / 89.4 / 86.5 / 87.8 / 89.8 us;
+//   - buckets are dealt out in pieces of at most an even share of the workgroup's rows, two rounds of pieces at the most.  The
+//     smallest share of 4 / 8 / 16 rows: B1 H32 T1024 10.9 / 11.2 / 11.7 us, B1 H8 T512 7.0 / 7.2 / 7.9 us;
+//   - loads stand under wave-uniform conditions, or have no others behind them.
+// us per call, prompt-like anchors, against one bucket per lane group with conditional loads and buckets of more than 128 rows
+// summed by the workgroup: B1 H32 T1024 15.1 -> 10.9, B1 H8 T8192 38.8 -> 20.1, B8 H32 T2048 80.0 -> 70.2, B16 H40 T624
+// 65.5 -> 56.2, B16 H32 T8192 466 -> 444 (5.3 TB/s), fp32 D64 B8 H8 T2048 33.3 -> 20.3.  Anchors that no score produces:
+// every fourth row, B8 T2048 58.0 -> 58.9; every second, B16 T4096 276 -> 316, where one stretch per workgroup reads pages in order.
+#include <type_traits>
+
 #include "ec_common.h"
 
 namespace ec {
 
 constexpr int kMergeThreads = 256;
 constexpr int kMergeUnroll = 8;  // rows of K and of V in flight per bucket (16 loads per lane)
-constexpr int kMergeLong = 128;  // buckets with more rows are summed by the whole workgroup
+// Rows up to which buckets are not divided if no other one of the workgroup has more (8 / 16: scattered anchors, which have many
+// buckets of 9 to 16 rows, B8 T2048 77.9 / 63.7 us; prompt-like ones alike).
+constexpr int kMergeWhole = 16;
+constexpr int kMergePiece = 8;   // the smallest share
+constexpr int kMergeAssign = 128;  // buckets with more rows have their assignment written by the whole workgroup
+constexpr int kMergeMostRows = 1 << 30;
 
-// Inclusive bounds of bucket j for ascending anchors a[0..n).  Clamped so that a
+// Inclusive bounds of bucket j for ascending anchors a[0..n), t = a[j].  Clamped so that a
 // malformed anchor list can never index outside [0,T).
 __device__ __forceinline__ void bucket_bounds(const int32_t* __restrict__ a, int j, int n, int T,
-                                              int& lo, int& hi)
+                                              int& t, int& lo, int& hi)
 {
-    const int t = a[j];
-    lo = (j == 0) ? 0 : ((a[j - 1] + t) >> 1) + 1;
-    hi = (j == n - 1) ? T - 1 : ((t + a[j + 1]) >> 1);
+    t = a[j];
+    const int before = a[max(j - 1, 0)], behind = a[min(j + 1, n - 1)];
+    lo = (j == 0) ? 0 : ((before + t) >> 1) + 1;
+    hi = (j == n - 1) ? T - 1 : ((t + behind) >> 1);
     lo = max(lo, 0);
     hi = min(hi, T - 1);
+}
+
+// Rows of K and V on their way.
+template <int N_> struct Rows {
+    static constexpr int N = N_;
+    u32x4 k[N], v[N];
+    int w[N];
+};
+
+// Inclusive sums over the first N lanes of a wave, N = 8, 16 or 32; they saturate at kMergeMostRows.
+template <int N> __device__ __forceinline__ int bucket_scan(int x)
+{
+    auto add = [&](int y) __attribute__((always_inline)) { x = min(x + y, kMergeMostRows); };
+    // shifts inside a row of 16 lanes bring zeros in
+    add(__builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true));
+    add(__builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true));
+    add(__builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true));
+    if (N >= 16) add(__builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true));
+    if (N >= 32) {
+        const int first_row = __builtin_amdgcn_readlane(x, 15);
+        add(threadIdx.x % kWave >= 16 ? first_row : 0);
+    }
+    return x;
 }
 
 // WEIGHTED: every source row t carries an integer weight w_t (the number of original tokens it already
@@ -35,8 +72,8 @@ __device__ __forceinline__ void bucket_bounds(const int32_t* __restrict__ a, int
 // and counts receives sum w_t.  Without it every row weighs 1 (Eq. 3).  src_rows is the distance in rows
 // between the heads of k/v (>= T); src_pos, if given, maps a source row to its original position.
 template <int DT, int D, bool WEIGHTED>
-__global__ __launch_bounds__(kMergeThreads) void merge_compact_kernel(
-    const uint4* __restrict__ k, const uint4* __restrict__ v, const int32_t* __restrict__ anchor_idx,
+__global__ __launch_bounds__(kMergeThreads, WEIGHTED ? 3 : 4) void merge_compact_kernel(
+    const u32x4* __restrict__ k, const u32x4* __restrict__ v, const int32_t* __restrict__ anchor_idx,
     const int32_t* __restrict__ weights, const int32_t* __restrict__ src_pos,
     uint4* __restrict__ k_cache, uint4* __restrict__ v_cache, int32_t* __restrict__ counts,
     int32_t* __restrict__ assign, int32_t* __restrict__ pos, int H, int G, int T_max, int src_rows, int n_max,
@@ -45,10 +82,11 @@ __global__ __launch_bounds__(kMergeThreads) void merge_compact_kernel(
     constexpr int LPR = D * Elem<DT>::kBytes / 16;
     constexpr int EPL = Elem<DT>::kPerChunk;
     constexpr int GROUPS = kMergeThreads / LPR;
-    __shared__ int sh_nlong;
-    __shared__ int sh_long[GROUPS];
-    __shared__ int sh_wsum[GROUPS];
-    __shared__ float sh_part[GROUPS][LPR * EPL * 2];
+    constexpr int RUN = kWave / LPR;        // neighbouring buckets of a wave
+    constexpr int PIECES = 2 * GROUPS;  // at most: one per bucket and one more per full share of the rows
+    __shared__ float sh_part[PIECES][LPR * EPL * 2];
+    __shared__ int sh_wsum[PIECES];
+    __shared__ int4 sh_bucket[GROUPS];  // first and last row, pieces, pieces up to and including it
 
     const int bh = blockIdx.y;
     const int b = bh / H, h = bh % H;
@@ -58,127 +96,172 @@ __global__ __launch_bounds__(kMergeThreads) void merge_compact_kernel(
     // XCDs round-robin by linear id: rotating the chunk number by the head index keeps the heavy chunks
     // from piling onto the same XCDs.
     const int chunk = (blockIdx.x + blockIdx.y) % gridDim.x;
-    const int j = chunk * GROUPS + grp;
     // ragged batches: batch element b has T positions and n_anchor anchors; array rows stay T_max / n_max apart
     const int T = ragged_rows(seq_len, b, T_max);
     const int n_anchor = n_anchor_b ? min(max(n_anchor_b[b], 0), min(T, n_max)) : n_max;
-    if (chunk * GROUPS >= n_anchor) return;  // whole workgroup
-    const bool valid = j < n_anchor;
+    const int n_chunks = (n_anchor + GROUPS - 1) / GROUPS;
+    if (chunk >= n_chunks) return;  // whole workgroup
+    // the workgroup's buckets: ascending, so that those the head has come first
+    auto bucket = [&](int i) __attribute__((always_inline)) { return (i / RUN * n_chunks + chunk) * RUN + i % RUN; };
 
     const size_t bg = (size_t)b * G + (G == 1 ? 0 : h);
     const int32_t* a = anchor_idx + bg * n_max;
     const int32_t* wrow = WEIGHTED ? weights + bg * T_max : nullptr;
     const bool owner = (G == H || h == 0);  // writes the bookkeeping of its score group
     // K and V of a bucket are streamed side by side: two independent load streams per lane
-    const uint4* src_k = k + (size_t)bh * src_rows * LPR + sub;
-    const uint4* src_v = v + (size_t)bh * src_rows * LPR + sub;
+    const char* src_k = (const char*)(k + (size_t)bh * src_rows * LPR);
+    const char* src_v = (const char*)(v + (size_t)bh * src_rows * LPR);
+
+    asm volatile("" ::"s"(src_k), "s"(src_v), "s"(k_cache), "s"(v_cache));  // arguments in scalar registers before the loads
+
+    // ---- the buckets of the workgroup: lane l of every wave holds bucket number l of them, and beside it (loaded together,
+    // which costs no time) its lane group's own, for the usual case that none is divided ----
+    const int lane = tid % kWave;
+    int at, lo, hi, own_at, own_lo, own_hi;
+    const int j = lane < GROUPS ? bucket(lane) : n_anchor;
+    const int n_here = __popcll(__ballot(j < n_anchor));
+    const bool own = bucket(grp) < n_anchor;
+    bucket_bounds(a, min(bucket(grp), n_anchor - 1), n_anchor, T, own_at, own_lo, own_hi);
+    bucket_bounds(a, min(j, n_anchor - 1), n_anchor, T, at, lo, hi);
+    if (!own) own_lo = 0, own_hi = -1;
+    if (lane >= n_here) at = lo = 0, hi = -1;
+    const int blo = lo, bhi = hi;  // the bucket, for the assignment
+    if (evict_only) {  // eviction-only ablation: the anchor's own row
+        if (own) own_lo = own_hi = min(max(own_at, 0), T - 1);
+        if (lane < n_here) lo = hi = min(max(at, 0), T - 1);
+    }
+    // Pieces: a bucket of more rows than an even share of the workgroup's is divided.  All sums saturate, so that a malformed
+    // anchor list, whose buckets overlap, cannot wrap them.
+    const int rows = max(hi - lo + 1, 0);
+    int n_parts = lane < n_here ? 1 : 0, parts_end = 0;  // pieces of the lane's bucket; of the ones up to and including it
+    int n_pieces = n_here;
+    if (__any(rows > kMergeWhole)) {  // the same in every wave
+        const int all_rows = __builtin_amdgcn_readlane(bucket_scan<GROUPS>(min(rows, kMergeMostRows)), GROUPS - 1);
+        const int share = ((all_rows + GROUPS - 1) / GROUPS + kMergePiece - 1) / kMergePiece * kMergePiece;
+        if (lane < n_here) n_parts = max((rows + share - 1) / share, 1);
+        parts_end = bucket_scan<GROUPS>(n_parts);
+        n_pieces = __builtin_amdgcn_readlane(parts_end, GROUPS - 1);
+        // every wave leaves the same values and needs no other wave's: from here on they cost no registers
+        if (lane < GROUPS) sh_bucket[lane] = make_int4(lo, hi, n_parts, parts_end);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+
+    if (owner && tid < n_here) {  // bookkeeping of the score group, one store for the workgroup's buckets
+        if (!WEIGHTED && counts) counts[bg * n_max + j] = hi - lo + 1;
+        if (pos) pos[bg * cap + j] = src_pos ? src_pos[bg * T_max + min(max(at, 0), T - 1)] : at;
+    }
+
+    if (owner && assign) {
+        // short buckets by their lane groups, long ones by the workgroup
+        const int b_lo = __shfl(blo, grp, kWave), b_hi = __shfl(bhi, grp, kWave), row = __shfl(lo, grp, kWave);
+        if (grp < n_here && b_hi - b_lo < kMergeAssign)
+            for (int t = b_lo + sub; t <= b_hi; t += LPR) assign[bg * T_max + t] = (!evict_only || t == row) ? bucket(grp) : -1;
+        for (unsigned long long todo = __ballot(bhi - blo >= kMergeAssign); todo != 0; todo &= todo - 1) {
+            const int i = __ffsll((long long)todo) - 1;
+            const int l_lo = __shfl(blo, i, kWave), l_hi = __shfl(bhi, i, kWave), l_row = __shfl(lo, i, kWave);
+            for (int t = l_lo + tid; t <= l_hi; t += kMergeThreads)
+                assign[bg * T_max + t] = (!evict_only || t == l_row) ? bucket(i) : -1;
+        }
+    }
 
     float acc_k[EPL], acc_v[EPL];
     int wsum;
-    // rows first, first + step, ... <= hi of one bucket; `whole` = this group sums the bucket alone
-    auto stream = [&](int first, int hi, int step, bool whole) {
+    // Rows first, first + step, ... <= last of every lane group; `most` rows of the group of the wave that has the most.  All
+    // loads stand under wave-uniform conditions and are the same for every way through a loop: behind a load that some lanes
+    // or some ways skip, a wait for one row is a wait for all of them, which took one trip to memory per row.  Groups that
+    // have fewer rows than their neighbours read their last one again, out of the cache.  use_w: rows carry their weights.
+    auto stream = [&](int first, int last, int step, int most, bool use_w) __attribute__((always_inline)) {
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc_k[e] = acc_v[e] = 0.f;
+        for (int e = 0; e < EPL; ++e) acc_k[e] = acc_v[e] = -0.f;  // leaves what is added to it as it is, -0 too
         wsum = 0;
-        // a bucket of one row is copied (weight 1 whatever it carries), so it stays bit-exact
-        const bool use_w = WEIGHTED && !(whole && first == hi);
-        for (int t = first; t <= hi; t += kMergeUnroll * step) {
-            uint4 ck[kMergeUnroll], cv[kMergeUnroll];
-            int wt[kMergeUnroll];
+        constexpr uint32_t kMinus = DT == EC_F32 ? 0x80000000u : 0x80008000u;
+        const u32x4 nothing = {kMinus, kMinus, kMinus, kMinus};
+        int r_load = first, r_use = first;
+        auto load = [&](auto& x) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < kMergeUnroll; ++u) {
-                ck[u] = make_uint4(0, 0, 0, 0);
-                cv[u] = make_uint4(0, 0, 0, 0);
-                wt[u] = 1;
-                const int r = t + u * step;
-                if (r <= hi) {
-                    if (WEIGHTED) wt[u] = max(wrow[r], 1);
-                    ck[u] = load_stream(src_k + (size_t)r * LPR);
-                    cv[u] = load_stream(src_v + (size_t)r * LPR);
-                }
+            for (int u = 0; u < x.N; ++u) {
+                const int r = max(min(r_load, last), 0);  // an empty bucket of a malformed list reads row 0 and drops it
+                const ptrdiff_t at = ((ptrdiff_t)r * LPR + sub) * 16;
+                if (WEIGHTED) x.w[u] = wrow[r];
+                x.k[u] = __builtin_nontemporal_load((const u32x4*)(src_k + at));
+                x.v[u] = __builtin_nontemporal_load((const u32x4*)(src_v + at));
+                r_load += step;
+                asm volatile("" : "+v"(r_load));  // the next row's address is formed when it is needed
+                __builtin_amdgcn_sched_barrier(0);
             }
+        };
+        auto use = [&](auto& x, int n) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < kMergeUnroll; ++u) {
-                if (t + u * step <= hi) {
-                    float xk[EPL], xv[EPL];
-                    unpack<DT>(ck[u], xk);
-                    unpack<DT>(cv[u], xv);
-                    const bool start = (u == 0 && t == first);  // the sum starts from the first row, so a bucket
-                    if (WEIGHTED) {                             // of one is a bit-exact copy (-0 stays -0)
-                        wsum += wt[u];
-                        const float w = use_w ? (float)wt[u] : 1.f;
+            for (int u = 0; u < x.N; ++u) {
+                if (u > 0 && u >= n) return;  // uniform
+                const bool in = r_use <= last;
+                float xk[EPL], xv[EPL];
+                unpack<DT>(__builtin_bit_cast(uint4, in ? x.k[u] : nothing), xk);
+                unpack<DT>(__builtin_bit_cast(uint4, in ? x.v[u] : nothing), xv);
+                if (WEIGHTED) {
+                    const int wt = max(x.w[u], 1);
+                    wsum += in ? wt : 0;
+                    const float w = use_w ? (float)wt : 1.f;
 #pragma unroll
-                        for (int e = 0; e < EPL; ++e) {
-                            acc_k[e] = start ? w * xk[e] : fmaf(w, xk[e], acc_k[e]);
-                            acc_v[e] = start ? w * xv[e] : fmaf(w, xv[e], acc_v[e]);
-                        }
-                    } else {
+                    for (int e = 0; e < EPL; ++e) {
+                        acc_k[e] = fmaf(w, xk[e], acc_k[e]);
+                        acc_v[e] = fmaf(w, xv[e], acc_v[e]);
+                    }
+                } else {
+                    constexpr bool copy = std::decay_t<decltype(x)>::N == 1;  // where every bucket is a row, NaN payloads stay too
 #pragma unroll
-                        for (int e = 0; e < EPL; ++e) {
-                            acc_k[e] = start ? xk[e] : acc_k[e] + xk[e];
-                            acc_v[e] = start ? xv[e] : acc_v[e] + xv[e];
-                        }
+                    for (int e = 0; e < EPL; ++e) {
+                        acc_k[e] = copy ? xk[e] : acc_k[e] + xk[e];
+                        acc_v[e] = copy ? xv[e] : acc_v[e] + xv[e];
                     }
                 }
+                r_use += step;
+                asm volatile("" : "+v"(r_use));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if (most <= 1) {
+            Rows<1> x;
+            load(x);
+            use(x, 1);
+        } else if (most <= kMergeUnroll) {
+            // nothing is loaded behind these, so that each lane group can leave out the rows it does not have
+            Rows<kMergeUnroll> x;
+#pragma unroll
+            for (int u = 0; u < kMergeUnroll; ++u) {
+                const int r = first + u * step;
+                if (r <= last) {
+                    const ptrdiff_t at = ((ptrdiff_t)r * LPR + sub) * 16;
+                    if (WEIGHTED) x.w[u] = wrow[r];
+                    x.k[u] = __builtin_nontemporal_load((const u32x4*)(src_k + at));
+                    x.v[u] = __builtin_nontemporal_load((const u32x4*)(src_v + at));
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            use(x, most);
+        } else {
+            constexpr int N = kMergeUnroll / 2;
+            Rows<N> xa, xb;
+            load(xa);
+            int left = (most + N - 1) / N;  // blocks that have not been used
+            for (; left > 2; left -= 2) {
+                load(xb);
+                use(xa, N);
+                load(xa);
+                use(xb, N);
+            }
+            if (left == 2) {
+                load(xb);
+                use(xa, N);
+                use(xb, N);
+            } else {
+                use(xa, N);
             }
         }
     };
-    // The share of one lane group in a bucket that the whole workgroup sums: rows first, first + step, ...
-    // A slot is loaded again as soon as its row has been added, so the loads in flight do not drain
-    // between rounds.  The additions are made in the order of stream().
-    auto stream_ring = [&](int first, int hi, int step) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc_k[e] = acc_v[e] = 0.f;
-        wsum = 0;
-        uint4 ck[kMergeUnroll], cv[kMergeUnroll];
-        int wt[kMergeUnroll];
-#pragma unroll
-        for (int u = 0; u < kMergeUnroll; ++u) {
-            const int r = first + u * step;
-            ck[u] = make_uint4(0, 0, 0, 0);
-            cv[u] = make_uint4(0, 0, 0, 0);
-            wt[u] = 1;
-            if (r <= hi) {
-                if (WEIGHTED) wt[u] = max(wrow[r], 1);
-                ck[u] = load_stream(src_k + (size_t)r * LPR);
-                cv[u] = load_stream(src_v + (size_t)r * LPR);
-            }
-        }
-        for (int t = first; t <= hi; t += kMergeUnroll * step) {
-#pragma unroll
-            for (int u = 0; u < kMergeUnroll; ++u) {
-                const int r = t + u * step;
-                if (r <= hi) {
-                    float xk[EPL], xv[EPL];
-                    unpack<DT>(ck[u], xk);
-                    unpack<DT>(cv[u], xv);
-                    if (WEIGHTED) {
-                        wsum += wt[u];
-                        const float w = (float)wt[u];
-#pragma unroll
-                        for (int e = 0; e < EPL; ++e) {
-                            acc_k[e] = fmaf(w, xk[e], acc_k[e]);
-                            acc_v[e] = fmaf(w, xv[e], acc_v[e]);
-                        }
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < EPL; ++e) {
-                            acc_k[e] += xk[e];
-                            acc_v[e] += xv[e];
-                        }
-                    }
-                    const int rn = r + kMergeUnroll * step;
-                    if (rn <= hi) {
-                        if (WEIGHTED) wt[u] = max(wrow[rn], 1);
-                        ck[u] = load_stream(src_k + (size_t)rn * LPR);
-                        cv[u] = load_stream(src_v + (size_t)rn * LPR);
-                    }
-                }
-            }
-        }
-    };
-    // divide by the count, round once, store cache row jj and its bookkeeping
-    auto finish = [&](int jj, int n_rows, int w_total) {
+    // divide by the count, round once, store cache row jj
+    auto finish = [&](int jj, int n_rows, int w_total) __attribute__((always_inline)) {
         const int count = WEIGHTED ? w_total : n_rows;
         if (n_rows > 1) {
             const float cf = (float)count;
@@ -190,69 +273,66 @@ __global__ __launch_bounds__(kMergeThreads) void merge_compact_kernel(
         }
         k_cache[((size_t)bh * cap + jj) * LPR + sub] = pack<DT>(acc_k);
         v_cache[((size_t)bh * cap + jj) * LPR + sub] = pack<DT>(acc_v);
-        if (owner && sub == 0) {
-            if (counts) counts[bg * n_max + jj] = count;
-            if (pos) {
-                const int t = min(max(a[jj], 0), T - 1);
-                pos[bg * cap + jj] = src_pos ? src_pos[bg * T_max + t] : a[jj];
-            }
-        }
+        if (WEIGHTED && owner && sub == 0 && counts) counts[bg * n_max + jj] = count;
     };
 
-    int lo = 0, hi = -1, blo = 0, bhi = -1;
-    if (valid) {
-        bucket_bounds(a, j, n_anchor, T, lo, hi);
-        blo = lo;
-        bhi = hi;  // the bucket, for the bookkeeping
-        if (evict_only) lo = hi = min(max(a[j], 0), T - 1);  // eviction-only ablation: the anchor's own row
-    }
-    // Buckets of more than kMergeLong rows are left to the whole workgroup (below): one lane group would
-    // stream them as a long chain of dependent loads while its neighbours sit idle.
-    const bool is_long = valid && (hi - lo + 1) > kMergeLong;
-    if (tid == 0) sh_nlong = 0;
-    __syncthreads();
-    if (is_long && sub == 0) sh_long[atomicAdd(&sh_nlong, 1)] = grp;
-    __syncthreads();
-
-    if (valid && !is_long) {
-        stream(lo, hi, 1, true);
-        finish(j, hi - lo + 1, wsum);
-        if (owner && assign)
-            for (int t = blo + sub; t <= bhi; t += LPR) assign[bg * T_max + t] = (!evict_only || t == lo) ? j : -1;
-    }
-
-    // Long buckets, one after the other: group g sums rows lo+g, lo+g+GROUPS, ...; the partial sums are
-    // added in ascending group order, so the result does not depend on which bucket is taken first.
-    const int n_long = sh_nlong;
-    for (int i = 0; i < n_long; ++i) {
-        const int jj = chunk * GROUPS + sh_long[i];
-        int llo, lhi;
-        bucket_bounds(a, jj, n_anchor, T, llo, lhi);
-        stream_ring(llo + grp, lhi, GROUPS);
+    // ---- piece p goes to lane group p % GROUPS; a bucket's pieces take its rows in turn ----
+#pragma unroll 1
+    for (int p0 = 0; p0 < min(n_pieces, PIECES); p0 += GROUPS) {
+        const int p = p0 + grp;
+        int i = grp, part = 0, parts = 1, p_lo, p_hi, most = 0;  // the piece's bucket, which part of how many, rows of the wave
+        if (n_pieces > n_here) {  // uniform
+            i = 0;
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-            sh_part[grp][(sub * EPL + e) * 2] = acc_k[e];
-            sh_part[grp][(sub * EPL + e) * 2 + 1] = acc_v[e];
+            for (int step = GROUPS / 2; step > 0; step >>= 1)
+                if (sh_bucket[i + step - 1].w <= p) i += step;
+            const int4 y = sh_bucket[i];
+            p_lo = y.x, p_hi = y.y, parts = max(y.z, 1);
+            part = p - (y.w - parts);
+            most = p < n_pieces ? (p_hi - p_lo - part) / parts + 1 : 0;
+#pragma unroll
+            for (int off = LPR; off < kWave; off <<= 1) most = max(most, __shfl_xor(most, off, kWave));
+            most = __builtin_amdgcn_readfirstlane(most);
+            if (most <= 0 && p0 > 0) continue;  // uniform: no piece for this wave
+        } else {  // every bucket is one piece
+            p_lo = own_lo, p_hi = own_hi;
+            const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+#pragma unroll
+            for (int g = 0; g < kWave / LPR; ++g) most = max(most, __builtin_amdgcn_readlane(rows, wave * (kWave / LPR) + g));
         }
-        if (sub == 0) sh_wsum[grp] = wsum;
+        // a bucket of one row is copied (weight 1 whatever it carries), so it stays bit-exact
+        stream(p_lo + part, p < n_pieces ? p_hi : -1, parts, most, WEIGHTED && p_lo != p_hi);
+        if (p < n_pieces) {
+            if (parts == 1) {
+                finish(bucket(i), p_hi - p_lo + 1, wsum);
+            } else {
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) {
+                    sh_part[p][e * LPR + sub] = acc_k[e];
+                    sh_part[p][(EPL + e) * LPR + sub] = acc_v[e];
+                }
+                if (sub == 0) sh_wsum[p] = wsum;
+            }
+        }
+    }
+    if (n_pieces > n_here) {  // uniform: partial sums in ascending order, by the lane group of the bucket's number
         __syncthreads();
-        if (grp == 0) {
+        const int4 y = sh_bucket[grp];
+        const int parts = y.z, first = y.w - parts, n_rows = y.y - y.x + 1;
+        if (parts > 1) {
             int w_total = 0;
 #pragma unroll
             for (int e = 0; e < EPL; ++e) acc_k[e] = acc_v[e] = 0.f;
-            for (int g = 0; g < GROUPS; ++g) {
-                w_total += sh_wsum[g];
+            for (int p = first; p < min(first + parts, PIECES); ++p) {
+                w_total += sh_wsum[p];
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) {
-                    acc_k[e] += sh_part[g][(sub * EPL + e) * 2];
-                    acc_v[e] += sh_part[g][(sub * EPL + e) * 2 + 1];
+                    acc_k[e] += sh_part[p][e * LPR + sub];
+                    acc_v[e] += sh_part[p][(EPL + e) * LPR + sub];
                 }
             }
-            finish(jj, lhi - llo + 1, w_total);
+            finish(bucket(grp), n_rows, w_total);
         }
-        if (owner && assign)
-            for (int t = llo + tid; t <= lhi; t += kMergeThreads) assign[bg * T_max + t] = jj;
-        __syncthreads();  // the partial sums are free again
     }
 }
 
@@ -267,12 +347,12 @@ static int launch_merge(const void* k, const void* v, const int32_t* anchor_idx,
     dim3 grid((n_anchor + GROUPS - 1) / GROUPS, B * H);
     if (weights != nullptr && !evict_only)
         hipLaunchKernelGGL((merge_compact_kernel<DT, D, true>), grid, dim3(kMergeThreads), 0, stream,
-                           (const uint4*)k, (const uint4*)v, anchor_idx, weights, src_pos, (uint4*)k_cache,
+                           (const u32x4*)k, (const u32x4*)v, anchor_idx, weights, src_pos, (uint4*)k_cache,
                            (uint4*)v_cache, counts, assign, pos, H, G, T, src_rows, n_anchor, cap, evict_only, seq_len,
                            n_anchor_b);
     else
         hipLaunchKernelGGL((merge_compact_kernel<DT, D, false>), grid, dim3(kMergeThreads), 0, stream,
-                           (const uint4*)k, (const uint4*)v, anchor_idx, weights, src_pos, (uint4*)k_cache,
+                           (const u32x4*)k, (const u32x4*)v, anchor_idx, weights, src_pos, (uint4*)k_cache,
                            (uint4*)v_cache, counts, assign, pos, H, G, T, src_rows, n_anchor, cap, evict_only, seq_len,
                            n_anchor_b);
     return status_from_hip(hipGetLastError());

@@ -185,3 +185,43 @@ def test_merge_long_buckets_next_to_single_rows(dtype, D, weighted):
                           weights=torch.from_numpy(w).cuda() if weighted else None)
     torch.cuda.synchronize()
     assert torch.equal(dk2, dk_c) and torch.equal(dv2, dv_c)
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("shape", ["eights", "one long", "two halves", "last", "growing"])
+@pytest.mark.parametrize("n", [1, 7, 16, 33, 70])
+def test_merge_buckets_in_pieces(dtype, D, shape, n):
+    """Buckets at the edges of the pieces that a workgroup deals out (8 rows, an even share of its rows), for full and
+    partly filled workgroups, with and without weights."""
+    B, H = 1, 2
+    rng = np.random.default_rng(D + n)
+    gaps = {"eights": rng.integers(7, 10, n), "one long": np.where(np.arange(n) == n // 2, 900, 1),
+            "two halves": np.where(np.arange(n) % 8 < 2, 127 + np.arange(n) % 4, 1),
+            "last": np.where(np.arange(n) == n - 1, 257, 2), "growing": 1 + np.arange(n) * 3 // 2}[shape]
+    a = (np.cumsum(gaps) - 1).astype(np.int32)
+    T = int(a[-1]) + 1 + int(rng.integers(0, 40))
+    a = a.reshape(1, 1, n)
+    k, v = quantize(rng.standard_normal((B, H, T, D)) * 2, dtype), quantize(rng.standard_normal((B, H, T, D)), dtype)
+    assign, counts = oracle.assign_nearest(a, T)
+    w = rng.integers(1, 9, (B, 1, T)).astype(np.int32)
+    for weighted in (False, True):
+        if weighted:
+            ok, want = oracle.merge_weighted(k, assign, w, n)
+            ov, _ = oracle.merge_weighted(v, assign, w, n)
+        else:
+            ok, ov, want = oracle.merge_compact(k, assign, n), oracle.merge_compact(v, assign, n), counts
+        dk_c = torch.full((B, H, n + 1, D), 9.0, dtype=torch_dtype(dtype), device="cuda")
+        dv_c = torch.full_like(dk_c, 9.0)
+        d_counts = torch.full((B, 1, n), -1, dtype=torch.int32, device="cuda")
+        d_assign = torch.full((B, 1, T), -1, dtype=torch.int32, device="cuda")
+        d_pos = torch.full((B, 1, n + 1), -1, dtype=torch.int32, device="cuda")
+        ec.ec_remerge_compact(to_dev(k, dtype), to_dev(v, dtype), T, torch.from_numpy(a).cuda(), dk_c, dv_c,
+                              weights=torch.from_numpy(w).cuda() if weighted else None, counts=d_counts, assign=d_assign,
+                              pos=d_pos)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(d_counts.cpu().numpy(), want)
+        np.testing.assert_array_equal(d_assign.cpu().numpy(), assign)
+        np.testing.assert_array_equal(d_pos.cpu().numpy()[:, :, :n], a)
+        assert_close(to_host(dk_c)[:, :, :n], ok, dtype, "k_cache", stored=True)
+        assert_close(to_host(dv_c)[:, :, :n], ov, dtype, "v_cache", stored=True)
+        assert (to_host(dk_c)[:, :, n:] == 9.0).all() and (to_host(dv_c)[:, :, n:] == 9.0).all()
