@@ -257,7 +257,9 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
     // is the victim itself.  Without one, the new row lands at cache_len.  The last tile of share 0 is still in registers when
     // its scores have been formed: rows held .. cache_len are stored from there.
     const int tail_first = shares.end(0) - TILE, held = max(tail_first, shares.begin(0));
-    const bool moved_early = evict_idx < 0 || evict_idx + 1 >= held;  // nothing moves but what the registers hold
+    // Nothing moves but what the registers hold, and all of it to rows of share 0: the row before them belongs to a share that a
+    // helper may still be reading or that has yet to be formed.
+    const bool moved_early = evict_idx < 0 || (evict_idx >= shares.begin(0) && evict_idx + 1 >= held);
     auto move_held = [&]() __attribute__((always_inline)) {
         const int lowest = evict_idx >= 0 ? max(evict_idx + 1, held) : cache_len, up = evict_idx >= 0 ? 1 : 0;
 #pragma unroll
@@ -419,8 +421,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
         __syncthreads();  // also: every wave of this workgroup has finished reading its rows
 
         if (own_share == 0 && s == 0) {
-            // rows of share 0 only: the other shares' workgroups do not read them
-            if (moved_early) move_held();
+            if (moved_early) move_held();  // to rows of share 0 only: the other shares' workgroups do not read them
             if (owns_pos) {  // one copy of the positions per score group
                 if (tid < n_move) pp[evict_idx + tid] = pos_pref;  // fetched before the barrier above
                 for (int c0 = THREADS; c0 < n_move; c0 += THREADS) {  // beyond one workgroup's worth

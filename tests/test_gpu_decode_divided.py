@@ -79,6 +79,19 @@ def test_lines_that_are_taken(dtype):
         assert all(torch.equal(a, b) for a, b in zip(g, want))
 
 
+# the victim is the last row of share 1 while the rows behind it, share 0, all fit into the owner's registers; in the first line
+# there are more shares than lines, so that owners form share 1 themselves, after share 0
+@pytest.mark.parametrize("dtype,D,B,H,rows,waves,splits", [
+    ("bf16", 64, 16, 24, 200, 2, 64), ("f32", 64, 16, 24, 200, 2, 64), ("bf16", 128, 1, 8, 640, 8, 8), ("bf16", 128, 1, 4, 640, 8, 16),
+    ("f32", 128, 1, 8, 399, 4, 16), ("bf16", 64, 2, 3, 700, 4, 16), ("bf16", 128, 2, 4, 390, 4, 16)])
+def test_victim_is_the_last_row_of_the_next_share(dtype, D, B, H, rows, waves, splits):
+    share = -(-(rows + 1) // splits)
+    first = rows + 1 - share                          # of share 0
+    for victim in (first - 1, first, first - 2):
+        _case(dtype, D, B, H, 1, rows + 2, rows, victim, seed=rows + victim, shape=(waves, 4, splits))
+    _case(dtype, D, B, H, 1, rows + 2, rows, first - 1, seed=rows, shape=(waves, 4, 1))
+
+
 @pytest.mark.parametrize("dtype,D", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
 def test_long_caches_of_large_batches(dtype, D):
     """The shape with one tile in flight does the same sums in the same order as the deep one of its width."""
