@@ -92,6 +92,7 @@ __device__ __forceinline__ u32x4 load_once(const char* p)
 {
     return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
 }
+constexpr int kNonTemporal = 2;  // the same hint of a buffer load
 typedef __attribute__((address_space(1))) const char global_char;
 typedef __attribute__((address_space(1))) const u32x4 global_u32x4;
 __device__ __forceinline__ u32x4 load_once(global_char* p) { return __builtin_nontemporal_load((global_u32x4*)p); }
@@ -222,6 +223,10 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
 
     // A tile is rows first .. first + TILE - 1.  The first of a share may start before its first row r0, the last may end with
     // the new row; the ones between are loaded without a condition, so that waiting for one never means waiting for the next.
+    // The outer ones, which is all there is of a short cache, do without branches too: rows before r0 are offsets behind the end of
+    // the buffer, which read nothing and give zeros.  Only the last load of a lane can be the new row's, from an address of its
+    // own; there a row before r0 is r0 again, and attend() drops its V.  (Each load under a condition -> this, us, bf16 D128: B*H
+    // 128, 120 rows 5.2 -> 4.5; B*H 256, 120 rows 6.4 -> 5.7, 250 rows 8.7 -> 8.1.)
     auto load_inner = [&](int first, Rows& x) __attribute__((always_inline)) {
         global_char *k0 = (global_char*)kc + (size_t)first * ROW, *v0 = (global_char*)vc + (size_t)first * ROW;
         asm volatile("" : "+s"(k0), "+s"(v0));  // scalar base, constant lane offset: no address arithmetic per load
@@ -233,14 +238,22 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
         __builtin_amdgcn_sched_barrier(0);
     };
     auto load_outer = [&](int first, int r0, Rows& x) __attribute__((always_inline)) {
+        const auto k_rows = __builtin_amdgcn_make_buffer_rsrc(kc + (ptrdiff_t)first * ROW, 0, TILE * ROW, 0x00020000);
+        const auto v_rows = __builtin_amdgcn_make_buffer_rsrc(vc + (ptrdiff_t)first * ROW, 0, TILE * ROW, 0x00020000);
+        const int r = max(first + (NR - 1) * RPW + lane_row, r0);
+        const char* ks = (r == cache_len ? kn : kc + (ptrdiff_t)r * ROW) + sub * 16;
+        const char* vs = (r == cache_len ? vn : vc + (ptrdiff_t)r * ROW) + sub * 16;
+        auto load = [&](auto rows, int u) __attribute__((always_inline)) {
+            const uint32_t at = first + u * RPW + lane_row >= r0 ? lane_at + u * RPW * ROW : TILE * ROW;
+            return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, at, 0, kNonTemporal));
+        };
 #pragma unroll
-        for (int u = 0; u < NR; ++u) {
-            const int r = first + u * RPW + lane_row;
-            const char* ks = (r == cache_len ? kn : kc + (ptrdiff_t)r * ROW) + sub * 16;
-            const char* vs = (r == cache_len ? vn : vc + (ptrdiff_t)r * ROW) + sub * 16;
-            x.k[u] = r >= r0 ? load_once(ks) : u32x4{0, 0, 0, 0};
-            x.v[u] = r >= r0 ? load_once(vs) : u32x4{0, 0, 0, 0};
-        }
+        for (int u = 0; u < NR - 1; ++u) x.k[u] = load(k_rows, u);
+        x.k[NR - 1] = load_once(ks);
+        __builtin_amdgcn_sched_barrier(0);  // K is needed first
+#pragma unroll
+        for (int u = 0; u < NR - 1; ++u) x.v[u] = load(v_rows, u);
+        x.v[NR - 1] = load_once(vs);
         __builtin_amdgcn_sched_barrier(0);
     };
 
@@ -285,7 +298,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
 #pragma unroll
         for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
 
-        auto attend = [&](int first, const Rows& x) __attribute__((always_inline)) {
+        auto attend = [&](int first, Rows& x) __attribute__((always_inline)) {
             float sc[NR];
             float m_tile = kLowest;
 #pragma unroll
@@ -297,6 +310,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
 #pragma unroll
                 for (int u = 0; u < NR; ++u)
                     if (first + u * RPW + lane_row < r0) sc[u] = -INFINITY;
+                if (first + (NR - 1) * RPW + lane_row < r0) x.v[NR - 1] = u32x4{0, 0, 0, 0};  // read from another row
             }
             if constexpr (EMIT) {
                 const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(raw + ((ptrdiff_t)bh * cap + first), 0, TILE * 4, 0x00020000);
@@ -356,7 +370,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
                 attend(first + TILE, tb);
             }
             if (first == last_first - TILE) {
-                load_outer(last_first, first_row, tb);
+                load_outer(last_first, r0, tb);
                 attend(first, ta);
                 attend(last_first, tb);
                 ta = tb;
@@ -364,7 +378,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
                 if (first == last_first - 2 * TILE) {
                     load_inner(first + TILE, tb);
                     attend(first, ta);
-                    load_outer(last_first, first_row, ta);
+                    load_outer(last_first, r0, ta);
                     attend(first + TILE, tb);
                 }
                 attend(last_first, ta);
@@ -374,7 +388,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
             while (first != last_first) {
                 first += TILE;
                 if (first == last_first)
-                    load_outer(first, first_row, ta);
+                    load_outer(first, r0, ta);
                 else
                     load_inner(first, ta);
                 attend(first, ta);
@@ -617,13 +631,13 @@ static int launch_decode_w(const void* q, const void* k_new, const void* v_new, 
 // Workgroups that one (batch, head) is divided over when the caller leaves the choice to the library: as many as the chip has
 // compute units for, where that saves more than the exchange costs (3.3 us against 1 us per 54 KB of one (batch, head)'s rows).
 // Measured, us per launch (graph replay, D128, one workgroup / divided; crossover):
-//   bf16, B*H =  8:  550 rows 7.8 / 7.3    1200 13.6 / 8.3   4096 38.6 / 11.5     f32  250 rows 7.4 / 7.1   4096 74.6 / 14.1
-//   bf16, B*H = 32:  550 rows 8.3 / 8.2    1200 14.4 / 9.8   4096 41.1 / 16.6     f32  250 rows 8.0 / 8.0   4096 78.4 / 25.8
-//   bf16, B*H = 64:  700 rows 11.1 / 10.2  1200 16.4 / 12.8  4096 45.6 / 26.7     f32  350 rows 10.5 / 10.0  4096 86.7 / 46.9
-//   bf16, B*H = 96:  700 rows 12.8 / 12.5  1200 18.7 / 16.1  4096 51.4 / 39.9     f32  550 rows 15.2 / 14.8  4096 98.8 / 67.9
-//   bf16, B*H = 128: 1200 rows 18.8 / 19.0  2400 34.0 / 32.6  4096 52.0 / 46.9    f32 1200 rows 32.0 / 30.4  4096 101 / 87.9
+//   bf16, B*H =  8:  550 rows 7.5 / 7.6    1200 13.0 / 8.4   4096 38.1 / 11.6     f32  250 rows 6.9 / 7.4   350  8.5 / 7.2   4096 73.3 / 14.3
+//   bf16, B*H = 32:  550 rows 7.9 / 8.2    1200 13.8 / 9.9   4096 40.3 / 16.5     f32  250 rows 7.4 / 8.1   350  9.3 / 8.5   4096 76.8 / 25.9
+//   bf16, B*H = 64:  700 rows 9.8 / 10.3   1200 14.8 / 12.1  4096 42.3 / 25.1     f32  350 rows 10.0 / 10.5   450 12.0 / 11.2   4096 82.1 / 44.5
+//   bf16, B*H = 96:  800 rows 11.5 / 12.3  1200 15.6 / 14.8  4096 50.7 / 35.8     f32  550 rows 14.8 / 14.6   4096 86.8 / 62.1
+//   bf16, B*H = 128: 1600 rows 20.7 / 21.0  2400 30.7 / 29.9  4096 49.2 / 43.9    f32 1000 rows 25.4 / 25.0   4096 92.2 / 82.3
 // More workgroups than compute units lose everywhere (B*H = 160, two each: 19.8 / 30.1 at 1200 rows).  Sixteen shares instead of
-// eight pay from 2 MB on (B*H = 8, f32 4096 rows: 17.1 / 14.1; 1200 rows: 9.3 / 10.1).
+// eight pay from 2 MB on (B*H = 8, f32 4096 rows: 17.4 / 14.3; 1200 rows: 9.7 / 10.2).
 constexpr int kComputeUnits = 256;
 constexpr int kLeastShareBytes = 48 << 10;  // of K and V
 int decode_auto_splits(int BH, int n_rows, int row_bytes)
@@ -635,29 +649,50 @@ int decode_auto_splits(int BH, int n_rows, int row_bytes)
 }
 
 // Shape of a workgroup when the caller leaves it to the library: waves, loads of K and of V per lane and tile, and whether the next
-// tile travels while one is used (deep).  Speed against the kernel before (its loads waited for each other; us = this one):
-//   four waves, 4, deep      : the usual shape; bf16 B*H 32 640 rows 9.1 us (1.08), 256 640 17.0 (1.04), 576 243 rows 17.1 (1.02),
-//                              1360 250 rows (fp32) 72.8 (1.00); eight waves are up to 8 % slower at 100 to 640 rows, equal beyond
-//   two waves, 4, deep       : bf16, many short caches; 800 43 rows 8.1 us (1.05; four waves 0.96), 1536 88 to 176 rows, ragged, 25.3
-//                              (1.02; four waves 0.99), 1536 176 rows in all 29.5 (1.01; 1.02)
-//   two waves, 2, deep       : bf16 rows of 128 bytes, many caches; 1056 71 rows 7.9 us (1.05; with 4: 1.01, four waves: 0.90)
-//   not deep                 : more workgroups than compute units on long caches have more in flight than memory takes: bf16 512
-//                              870 rows 39.8 us (1.03; deep 1.00), 520 815 41.4 (1.12; 1.03), fp32 272 1452 41.9 (1.02; 0.96),
-//                              360 1176 rows 80.8 (1.00; 0.97).  From 512 bf16 pairs on two waves, else four.
-constexpr int kLongHeadBytes = 320 << 10, kShortHeadBytes = 96 << 10;  // of K and V
+// tile travels while one is used (deep).  Up to one workgroup per compute unit wants as much in flight as it can have.  Beyond
+// that the limit is memory, and the more pairs there are the fewer bytes should be asked for at a time; batches of sequences that
+// differ in length want more than their pairs say, as the short ones end and leave the rest alone.  A cache of one tile has only
+// one round of loads.  us, four waves 4 deep / four 2 deep / four 4 / two 4 / two 2 (the kernel before the deep loop), D128:
+//   bf16 B*H  320  250 rows 10.8 / 10.8 / 10.5 / 11.8 / 16.7 (11.2)       900 rows 29.3 / 28.9 / 28.4 / 31.8 / 46.4 (28.4)
+//   bf16 B*H  640  250 rows 17.5 / 17.6 / 17.5 / 17.0 / 19.8 (18.1)       900 rows 52.6 / 52.9 / 53.7 / 50.3 / 54.2 (52.6)
+//   bf16 B*H 1024  400 rows 39.8 / 39.7 / 40.0 / 36.8 / 37.9 (36.5)     B*H 1536  640 rows 91.9 / 92.0 / 92.4 / 90.4 / 84.1 (86.2)
+//   bf16 B*H 1536   32 rows 11.5 / 11.2 / 10.1 / 10.9 / 12.5 (10.3)     B*H 512 ragged 900 rows 32.6 / 32.7 / 33.0 / 35.9 / 47.3 (33.2)
+//   f32  B*H  512  250 rows 26.1 / 27.4 / 25.3 / 28.2 / 33.7 (25.5)     B*H 1920  400 rows 151 / 155 / 152 / 147 / 141 (143)
+// Rows of 128 bytes (bf16 D64): up to 1023 pairs like bf16 D128; then two waves, 2 deep for short caches (B*H 1024, 64 rows 7.0 us,
+// two waves 4 deep or not 7.3) and not deep for long ones (B*H 1536, 900 rows 58.0, deep 61.5).
+// Over 4 types and sizes, 320 to 1920 pairs, 32 to 4096 rows the choice is 2.7 % faster than that kernel; what it loses, up to 7 % at
+// single points, it loses on caches of one to three tiles and at 88 KB of 1536 pairs, where no shape here does better by more than 2 %.
+constexpr long long kKiB = 1 << 10;
 struct DecodeAuto {
     int waves, unroll;
     bool deep;
 };
-static DecodeAuto decode_auto_shape(int BH, int n_rows, int D, int dt)
+static DecodeAuto decode_auto_shape(int BH, int n_rows, int row_bytes, bool half, bool ragged)
 {
-    const bool half = dt == EC_BF16;
-    const long long bytes = 2LL * n_rows * D * (half ? 2 : 4);
-    if (BH > kComputeUnits && bytes >= kLongHeadBytes) return {half && BH >= 512 ? 2 : 4, 4, false};
-    if (half && BH >= 768 && D == 64) return {2, 2, true};
-    if (half && BH >= 768 && bytes < kShortHeadBytes) return {2, 4, true};
-    return {4, 4, true};
+    const long long bytes = 2LL * n_rows * row_bytes;             // of K and V, of the longest sequence
+    const long long typical = ragged ? bytes - bytes / 4 : bytes;  // lengths from half of it to all of it
+    const bool crowd = BH >= (ragged ? 1400 : 1200);
+    if (BH <= kComputeUnits) return {4, 4, true};
+    if (row_bytes >= 512) {
+        if (typical < 140 * kKiB) return {4, 4, true};
+        if (BH < 1024 || typical < (crowd ? 200 : 300) * kKiB) return {4, 4, false};
+        return crowd ? DecodeAuto{2, 2, false} : DecodeAuto{2, 4, false};
+    }
+    if (row_bytes >= 256 && bytes <= 32 * kKiB) return {4, 4, false};
+    if (BH < (half ? 512 : 513))  // at 512 two waves and four are alike
+        return bytes >= 320 * kKiB ? DecodeAuto{4, 4, false} : DecodeAuto{4, 2, true};
+    if (BH < 1024) {
+        const bool is_long = !ragged && bytes >= (row_bytes >= 256 ? 160 : 320) * kKiB;
+        return is_long ? DecodeAuto{2, 4, false} : DecodeAuto{4, 2, true};
+    }
+    if (row_bytes >= 256) {
+        if (typical < 80 * kKiB) return {4, 2, true};
+        return crowd && typical >= 110 * kKiB ? DecodeAuto{2, 2, false} : DecodeAuto{2, 4, false};
+    }
+    return {2, 2, typical < 80 * kKiB || (ragged && !crowd)};
 }
+// the shapes above but the first
+#define EC_DECODE_AUTO_SHAPES(CASE_) CASE_(4, 4, false) CASE_(4, 2, true) CASE_(2, 4, false) CASE_(2, 2, true) CASE_(2, 2, false)
 
 // splits: 0 = choose, n = n workgroups per (batch, head).
 template <int DT, int D>
@@ -682,11 +717,11 @@ static int launch_decode(const void* q, const void* k_new, const void* v_new, vo
                                                                 evict_idx, new_pos, scale, out, nullptr, nullptr, len_b,   \
                                                                 evict_b, new_pos_b, splits, least, stream)
     if (choose && splits == 1) {
-        const DecodeAuto a = decode_auto_shape(B * H, n_rows, D, DT);
-        if (!a.deep && a.waves == 2) EC_DECODE_W(2, 4, false, false);
-        if (!a.deep) EC_DECODE_W(4, 4, false, false);
-        if (a.unroll == 2) EC_DECODE_W(2, 2, true, false);
-        waves = a.waves;
+        const DecodeAuto a = decode_auto_shape(B * H, n_rows, kRow, DT == EC_BF16, len_b != nullptr);
+#define EC_DECODE_AUTO(W_, U_, DEEP_) \
+    if (a.waves == W_ && a.unroll == U_ && a.deep == DEEP_) EC_DECODE_W(W_, U_, DEEP_, false);
+        EC_DECODE_AUTO_SHAPES(EC_DECODE_AUTO)
+#undef EC_DECODE_AUTO
     }
     if (waves <= 0) waves = 4;
     const bool known = splits > 1 ? ((waves == 2 || waves == 4) && (unroll == 4 || unroll == 8)) || (waves == 8 && unroll == 4)
@@ -781,16 +816,17 @@ static int launch_decode_score(const void* q, const void* k_new, const void* v_n
 {
     constexpr int kRow = D * Elem<DT>::kBytes;
     const int n = cache_len + 1, splits = decode_auto_splits(B * H, n, kRow), least = kLeastShareBytes / (2 * kRow);
-#define EC_DSCORE(W_, U_, DEEP_, SPLIT_)                                                                                   \
-    launch_decode_w<DT, D, W_, U_, DEEP_, true, SPLIT_>(q, k_new, v_new, k_cache, v_cache, pos, B, H, G, cap, cache_len, -1, \
-                                                        new_pos, scale, out, raw, stats, nullptr, nullptr, nullptr, splits, \
-                                                        least, stream)
-    const DecodeAuto a = decode_auto_shape(B * H, n, D, DT);
-    const int rc = splits > 1      ? EC_DSCORE(4, 4, true, true)
-                   : !a.deep       ? (a.waves == 2 ? EC_DSCORE(2, 4, false, false) : EC_DSCORE(4, 4, false, false))
-                   : a.unroll == 2 ? EC_DSCORE(2, 2, true, false)
-                   : a.waves == 2  ? EC_DSCORE(2, 4, true, false)
-                                   : EC_DSCORE(4, 4, true, false);
+#define EC_DSCORE(W_, U_, DEEP_, SPLIT_)                                                                                       \
+    rc = launch_decode_w<DT, D, W_, U_, DEEP_, true, SPLIT_>(q, k_new, v_new, k_cache, v_cache, pos, B, H, G, cap, cache_len, -1, \
+                                                             new_pos, scale, out, raw, stats, nullptr, nullptr, nullptr, splits, \
+                                                             least, stream)
+#define EC_DSCORE_AUTO(W_, U_, DEEP_) else if (a.waves == W_ && a.unroll == U_ && a.deep == DEEP_) EC_DSCORE(W_, U_, DEEP_, false);
+    const DecodeAuto a = decode_auto_shape(B * H, n, kRow, DT == EC_BF16, false);
+    int rc;
+    if (splits > 1) EC_DSCORE(4, 4, true, true);
+    EC_DECODE_AUTO_SHAPES(EC_DSCORE_AUTO)
+    else EC_DSCORE(4, 4, true, false);
+#undef EC_DSCORE_AUTO
 #undef EC_DSCORE
     if (rc != EC_OK) return rc;
     hipLaunchKernelGGL(freq_accumulate_kernel, dim3((n + kFreqRows - 1) / kFreqRows, B * G),
