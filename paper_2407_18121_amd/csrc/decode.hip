@@ -97,24 +97,40 @@ typedef __attribute__((address_space(1))) const char global_char;
 typedef __attribute__((address_space(1))) const u32x4 global_u32x4;
 __device__ __forceinline__ u32x4 load_once(global_char* p) { return __builtin_nontemporal_load((global_u32x4*)p); }
 
-// A chunk of q as the products need it: fp32 values times the scale, or bf16 values times the power of two in it, which is exact
-// (short of the subnormal numbers), so that the upper halves of the fp32 words are the bf16 values.
-template <int DT> __device__ __forceinline__ u32x4 prepared_q(const uint4& c, float scale, int scale_exp)
+// A chunk of q as the products need it, and what their sum is multiplied by to be a score in base-2 units.  fp32: q times the
+// scale.  bf16: q times 2^n with n such that the rest of the scale is 1 .. 2, so that the upper halves of the fp32 words are bf16
+// values and no sum leaves the range that the score itself stays in; where that would push an element below bf16's range
+// (2^-123 and less at usual scales), the whole row stays as it is.
+struct PreparedQ {
+    u32x4 chunk;
+    float rest;
+};
+template <int DT> __device__ __forceinline__ PreparedQ prepared_q(const uint4& c, float scale)
 {
     constexpr int N = Elem<DT>::kPerChunk;
     float x[N];
     unpack<DT>(c, x);
-    u32x4 y;
+    PreparedQ y;
     if constexpr (DT == EC_F32) {
+        y.rest = 1.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) y[i] = __float_as_uint(x[i] * scale);
+        for (int i = 0; i < 4; ++i) y.chunk[i] = __float_as_uint(x[i] * scale);
     } else {
+        const int n = __builtin_amdgcn_frexp_expf(scale) - 1;
+        bool exact = true;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const uint32_t lo = __float_as_uint(__builtin_amdgcn_ldexpf(x[2 * i], scale_exp));
-            const uint32_t hi = __float_as_uint(__builtin_amdgcn_ldexpf(x[2 * i + 1], scale_exp));
-            y[i] = lo >> 16 | (hi & 0xffff0000u);
+            uint32_t word[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                word[e] = __float_as_uint(__builtin_amdgcn_ldexpf(x[2 * i + e], n)) & 0xffff0000u;
+                exact = exact && __builtin_amdgcn_ldexpf(__uint_as_float(word[e]), -n) == x[2 * i + e];
+            }
+            y.chunk[i] = word[0] >> 16 | word[1];
         }
+        const bool all_exact = __all(exact);  // the same in every wave: each holds the whole row
+        y.rest = all_exact ? 2.f * __builtin_amdgcn_frexp_mantf(scale) : scale;
+        if (!all_exact) y.chunk = u32x4{c.x, c.y, c.z, c.w};
     }
     return y;
 }
@@ -207,11 +223,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
     int32_t pos_pref = 0;
     if (owns_pos && tid < n_move) pos_pref = pp[evict_idx + 1 + tid];
 
-    // bf16: the power of two in the scale goes into q, the rest multiplies the score, so that sums stay in range wherever those of
-    // a scaled q would
-    u32x4 qf;
-    const int scale_exp = __builtin_amdgcn_frexp_expf(scale_log2e);
-    const float scale_rest = DT == EC_F32 ? 1.f : __builtin_amdgcn_frexp_mantf(scale_log2e);  // 0.5 .. 1
+    PreparedQ qp;
     const uint4 q_in = q[(size_t)bh * LPR + sub];
 
     // two tiles, one being used while the other lands
@@ -303,8 +315,8 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
             float m_tile = kLowest;
 #pragma unroll
             for (int u = 0; u < NR; ++u) {
-                const float d = group_sum<LPR>(chunk_dot<DT>(x.k[u], qf));
-                sc[u] = DT == EC_F32 ? d : d * scale_rest;
+                const float d = group_sum<LPR>(chunk_dot<DT>(x.k[u], qp.chunk));
+                sc[u] = DT == EC_F32 ? d : d * qp.rest;
             }
             if (first < r0) {  // uniform
 #pragma unroll
@@ -360,7 +372,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
         };
 
         load_outer(first_row, r0, ta);
-        if (s == own_share) qf = prepared_q<DT>(q_in, scale_log2e, scale_exp);
+        if (s == own_share) qp = prepared_q<DT>(q_in, scale_log2e);
         int first = first_row;
         if constexpr (DEEP) {
             for (; first < last_first - 2 * TILE; first += 2 * TILE) {

@@ -1,5 +1,5 @@
-"""Generation steps in every launch shape that the library chooses by itself, through the ordinary calls, against the same step
-in 64 bits (softmax, append and removal written out in torch)."""
+"""Generation steps in every launch shape that the library chooses by itself, through the ordinary calls, and at the ends of the
+numbers' range, against the same step in 64 bits (softmax, append and removal written out in torch)."""
 import pytest
 import torch
 
@@ -117,3 +117,40 @@ def test_tensors_that_start_at_any_element(dtype, D, B, H, n):
     ec.ec_decode_step(q, kn, vn, kc, vc, None, n, n - 25, 5, D ** -0.5, got, None, G=1)
     _close(got, out, dtype)
     assert torch.equal(kc[:, :, :n], k) and torch.equal(vc[:, :, :n], v)
+
+
+RANGES = {  # exponents of keys and of queries, scale
+    "keys below the normal range": (-130, 123, 1.0),
+    "queries below the normal range": (125, -130, 0.0884),
+    "queries that scaling takes below it": (124, -124, 0.0884),
+    "large queries": (-128, 127, 1.0),
+    "large keys": (127, -128, 1.0),
+}
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("n", [40, 1300])
+@pytest.mark.parametrize("what", RANGES)
+def test_queries_and_keys_at_the_ends_of_the_range(dtype, D, n, what):
+    """The scores are of size one; neither their products nor their sums leave the range that q * scale stays in."""
+    at_k, at_q, scale = RANGES[what]
+    q, kn, vn, kc, vc = _inputs(dtype, D, 2, 8, n + 1, n)
+    scaled = lambda x, e: (x.double().clamp(-1.3, 1.3) * 2.0 ** e).to(x.dtype)
+    q, kn, kc = scaled(q, at_q), scaled(kn, at_k), scaled(kc, at_k)
+    out, *_ = _expect(q, kn, vn, kc, vc, n, -1, scale)
+    got = torch.zeros_like(q)
+    ec.ec_decode_step(q, kn, vn, kc, vc, None, n, -1, 5, scale, got, None, G=1)
+    _close(got, out, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_scores_near_the_largest_number(dtype):
+    """Scores of 2.7e38 in base-2 units: the unscaled half of one would still fit, twice one would not."""
+    n, D = 40, 64
+    q, kn, vn, kc, vc = _inputs(dtype, D, 1, 4, n + 1, 1)
+    q[..., 0], kc[..., 0], kn[..., 0] = 2.0 ** 126, 1.0, 1.0
+    kc[:, :, 7:9, 0] = 2.203125
+    out, *_ = _expect(q, kn, vn, kc, vc, n, -1, 1.0)
+    got = torch.zeros_like(q)
+    ec.ec_decode_step(q, kn, vn, kc, vc, None, n, -1, 5, 1.0, got, None, G=1)
+    _close(got, out, dtype)
