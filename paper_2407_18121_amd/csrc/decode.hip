@@ -15,6 +15,7 @@
 // workgroup barrier that ends all reads, the rows behind the evicted one are stored one slot up straight from those registers,
 // and so is the new row -- the elimination costs no extra read.
 #include <algorithm>
+#include <cmath>
 
 #include "ec_common.h"
 
@@ -97,42 +98,56 @@ typedef __attribute__((address_space(1))) const char global_char;
 typedef __attribute__((address_space(1))) const u32x4 global_u32x4;
 __device__ __forceinline__ u32x4 load_once(global_char* p) { return __builtin_nontemporal_load((global_u32x4*)p); }
 
-// A chunk of q as the products need it, and what their sum is multiplied by to be a score in base-2 units.  fp32: q times the
-// scale.  bf16: q times 2^n with n such that the rest of the scale is 1 .. 2, so that the upper halves of the fp32 words are bf16
-// values and no sum leaves the range that the score itself stays in; where that would push an element below bf16's range
-// (2^-123 and less at usual scales), the whole row stays as it is.
+// The scale in base-2 units, log2(e) * scale, as a factor of q and one of the sums of products.  fp32: q takes all of it.  bf16: q
+// takes the power of two that leaves 1 .. 2, so that no sum leaves the range that the score itself stays in.
+struct ScoreScale {
+    float of_q, of_sum;
+};
+static ScoreScale score_scale(float scale, int dt)
+{
+    const float log2 = scale * kLog2e;
+    if (dt == EC_F32) return {log2, 1.f};
+    int n;
+    const float rest = std::frexp(log2, &n);  // 0.5 .. 1
+    return {std::ldexp(1.f, n - 1), 2.f * rest};
+}
+
+// A chunk of q as the products need it.  A bf16 chunk with an element that its power of two would push below bf16's range (2^-123 and
+// less at usual scales) stays as it is.  The first scores wait for this, so that the usual case is short.
 struct PreparedQ {
     u32x4 chunk;
-    float rest;
+    float of_sum;
 };
-template <int DT> __device__ __forceinline__ PreparedQ prepared_q(const uint4& c, float scale)
+template <int DT> __device__ __forceinline__ PreparedQ prepared_q(const uint4& c, ScoreScale scale)
 {
     constexpr int N = Elem<DT>::kPerChunk;
-    float x[N];
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    float x[N], y[N], smallest = INFINITY;
     unpack<DT>(c, x);
-    PreparedQ y;
-    if constexpr (DT == EC_F32) {
-        y.rest = 1.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) y.chunk[i] = __float_as_uint(x[i] * scale);
-    } else {
-        const int n = __builtin_amdgcn_frexp_expf(scale) - 1;
+    for (int i = 0; i < N; ++i) {
+        y[i] = x[i] * scale.of_q;
+        smallest = fminf(smallest, fabsf(y[i]));
+    }
+    PreparedQ p;
+    p.of_sum = scale.of_sum;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if constexpr (DT == EC_F32)
+            p.chunk[i] = __float_as_uint(y[i]);
+        else
+            p.chunk[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{y[2 * i], y[2 * i + 1]}), bf16x2));
+    }
+    if (DT == EC_BF16 && __builtin_expect(smallest < 0x1p-126f, 0)) {
         bool exact = true;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            uint32_t word[2];
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                word[e] = __float_as_uint(__builtin_amdgcn_ldexpf(x[2 * i + e], n)) & 0xffff0000u;
-                exact = exact && __builtin_amdgcn_ldexpf(__uint_as_float(word[e]), -n) == x[2 * i + e];
-            }
-            y.chunk[i] = word[0] >> 16 | word[1];
+        for (int i = 0; i < N; ++i) exact = exact && (x[i] == 0.f || fabsf(y[i]) >= 0x1p-126f);
+        if (!exact) {
+            p.chunk = u32x4{c.x, c.y, c.z, c.w};
+            p.of_sum *= scale.of_q;
         }
-        const bool all_exact = __all(exact);  // the same in every wave: each holds the whole row
-        y.rest = all_exact ? 2.f * __builtin_amdgcn_frexp_mantf(scale) : scale;
-        if (!all_exact) y.chunk = u32x4{c.x, c.y, c.z, c.w};
     }
-    return y;
+    return p;
 }
 
 // Product of a chunk of K with the chunk of q.  bf16: the dot instruction adds two products at a time, each exact in fp32.
@@ -148,6 +163,22 @@ template <int DT> __device__ __forceinline__ float chunk_dot(const u32x4& k, con
             d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), d, false);
     }
     return d;
+}
+
+// x[i] <- 2^x[i].  The exponential instruction gives zero where the result is subnormal; exp2f, which is six times as long, does not,
+// and is taken only where there is one (-149.. < x < -126; what lies below is zero either way, lanes without rows included).
+template <int N> __device__ __forceinline__ void exp2_all(float (&x)[N])
+{
+    bool subnormal = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) subnormal = subnormal | (fabsf(x[i] + 138.5f) < 12.5f);
+    if (__builtin_expect(__any(subnormal), 0)) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) x[i] = exp2f(x[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) x[i] = __builtin_amdgcn_exp2f(x[i]);
+    }
 }
 
 // Values of a lane and of its partner `off` lanes away (8, 16 or 32), the one with the lower lane number first, in both of them.
@@ -178,7 +209,7 @@ template <int DT, int D, int WAVES, int UNROLL, bool DEEP, bool EMIT, bool SPLIT
 __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
     const uint4* __restrict__ q, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
     uint4* k_cache, uint4* v_cache, int32_t* pos, uint4* __restrict__ out, int BH, int H, int G, int cap,
-    int cache_len, int evict_idx, int32_t new_pos, float scale_log2e, float* __restrict__ raw,
+    int cache_len, int evict_idx, int32_t new_pos, ScoreScale scale, float* __restrict__ raw,
     float* __restrict__ stats, const int32_t* __restrict__ len_b, const int32_t* __restrict__ evict_b,
     const int32_t* __restrict__ new_pos_b, int splits, int least)
 {
@@ -249,6 +280,24 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
         for (int u = 0; u < NR; ++u) x.v[u] = load_once(v0 + (lane_at + u * RPW * ROW));
         __builtin_amdgcn_sched_barrier(0);
     };
+    // An inner tile or the last one, by the same instructions: a branch between two kinds of loads makes the waits behind it waits
+    // for everything.
+    auto load_any = [&](int first, Rows& x) __attribute__((always_inline)) {
+        global_char *k0 = (global_char*)kc + (ptrdiff_t)first * ROW, *v0 = (global_char*)vc + (ptrdiff_t)first * ROW;
+        asm volatile("" : "+s"(k0), "+s"(v0));
+        const bool is_new = first + (NR - 1) * RPW + lane_row == cache_len;
+        const uint32_t at = lane_at + (NR - 1) * RPW * ROW;
+        global_char* ks = is_new ? (global_char*)kn + sub * 16 : k0 + at;
+        global_char* vs = is_new ? (global_char*)vn + sub * 16 : v0 + at;
+#pragma unroll
+        for (int u = 0; u < NR - 1; ++u) x.k[u] = load_once(k0 + (lane_at + u * RPW * ROW));
+        x.k[NR - 1] = load_once(ks);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < NR - 1; ++u) x.v[u] = load_once(v0 + (lane_at + u * RPW * ROW));
+        x.v[NR - 1] = load_once(vs);
+        __builtin_amdgcn_sched_barrier(0);
+    };
     auto load_outer = [&](int first, int r0, Rows& x) __attribute__((always_inline)) {
         const auto k_rows = __builtin_amdgcn_make_buffer_rsrc(kc + (ptrdiff_t)first * ROW, 0, TILE * ROW, 0x00020000);
         const auto v_rows = __builtin_amdgcn_make_buffer_rsrc(vc + (ptrdiff_t)first * ROW, 0, TILE * ROW, 0x00020000);
@@ -312,11 +361,12 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
 
         auto attend = [&](int first, Rows& x) __attribute__((always_inline)) {
             float sc[NR];
-            float m_tile = kLowest;
+            float m_tile = kLowest, least_score = INFINITY;
 #pragma unroll
             for (int u = 0; u < NR; ++u) {
-                const float d = group_sum<LPR>(chunk_dot<DT>(x.k[u], qp.chunk));
-                sc[u] = DT == EC_F32 ? d : d * qp.rest;
+                const float d = chunk_dot<DT>(x.k[u], qp.chunk);
+                sc[u] = group_sum<LPR>(DT == EC_F32 ? d : d * qp.of_sum);
+                least_score = fminf(least_score, sc[u]);
             }
             if (first < r0) {  // uniform
 #pragma unroll
@@ -338,17 +388,25 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
             __builtin_amdgcn_sched_barrier(0);  // V is not waited for before the scores are there
             if (__any(m_tile > m_run)) {  // wave-uniform
                 const float m_new = fmaxf(m_run, m_tile);
-                const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+                const float corr = exp2f(m_run - m_new);
                 m_run = m_new;
                 l_run *= corr;
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) acc[e] *= corr;
             }
+            float weight[NR];  // as exp2_all(), with a shorter question
+            if (__builtin_expect(__any(least_score - m_run < -126.f), 0)) {  // wave-uniform
+#pragma unroll
+                for (int u = 0; u < NR; ++u) weight[u] = exp2f(sc[u] - m_run);
+            } else {
+#pragma unroll
+                for (int u = 0; u < NR; ++u) weight[u] = __builtin_amdgcn_exp2f(sc[u] - m_run);
+            }
             // fp32: a tile is summed by itself and then added, which keeps the rounding errors of a long chain small
             float part_l = 0.f, part_v[EPL];
 #pragma unroll
             for (int u = 0; u < NR; ++u) {
-                const float p = __builtin_amdgcn_exp2f(sc[u] - m_run);
+                const float p = weight[u];
                 float vx[EPL];
                 unpack<DT>(__builtin_bit_cast(uint4, x.v[u]), vx);
                 if (DT == EC_F32) {
@@ -372,39 +430,30 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
         };
 
         load_outer(first_row, r0, ta);
-        if (s == own_share) qp = prepared_q<DT>(q_in, scale_log2e);
+        if (s == own_share) qp = prepared_q<DT>(q_in, scale);
         int first = first_row;
         if constexpr (DEEP) {
-            for (; first < last_first - 2 * TILE; first += 2 * TILE) {
+            for (; first < last_first - TILE; first += 2 * TILE) {
                 load_inner(first + TILE, tb);
                 attend(first, ta);
-                load_inner(first + 2 * TILE, ta);
+                load_any(first + 2 * TILE, ta);
                 attend(first + TILE, tb);
             }
-            if (first == last_first - TILE) {
-                load_outer(last_first, r0, tb);
+            if (first != last_first) {
+                load_any(last_first, tb);
                 attend(first, ta);
                 attend(last_first, tb);
                 ta = tb;
             } else {
-                if (first == last_first - 2 * TILE) {
-                    load_inner(first + TILE, tb);
-                    attend(first, ta);
-                    load_outer(last_first, r0, ta);
-                    attend(first + TILE, tb);
-                }
                 attend(last_first, ta);
             }
         } else {
-            attend(first, ta);
             while (first != last_first) {
-                first += TILE;
-                if (first == last_first)
-                    load_outer(first, r0, ta);
-                else
-                    load_inner(first, ta);
                 attend(first, ta);
+                first += TILE;
+                load_any(first, ta);
             }
+            attend(last_first, ta);
         }
         // ta holds the last tile: of share 0, the newest rows
 
@@ -412,17 +461,28 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
         if (SPLIT && own_share > 0 && tid == 0)
             seen = device_cas(&line_state[line_of(s)], key_of(s) | kOpen, key_of(s) | kJoined);
 
-        // ---- merge the lanes of each wave that hold the same features ----
+        // ---- merge the lanes of each wave that hold the same features: the maximum first, then plain sums ----
+        {
+            float m_wave = m_run;
 #pragma unroll
-        for (int off = LPR; off < kWave; off <<= 1) {
-            const Pair m = lane_pair(m_run, off), l = lane_pair(l_run, off);
-            m_run = fmaxf(m.lower, m.upper);
-            const float w0 = __builtin_amdgcn_exp2f(m.lower - m_run), w1 = __builtin_amdgcn_exp2f(m.upper - m_run);
-            l_run = l.lower * w0 + l.upper * w1;
+            for (int off = LPR; off < kWave; off <<= 1) {
+                const Pair m = lane_pair(m_wave, off);
+                m_wave = fmaxf(m.lower, m.upper);
+            }
+            const float corr = exp2f(m_run - m_wave);
+            m_run = m_wave;
+            l_run *= corr;
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) {
-                const Pair x = lane_pair(acc[e], off);
-                acc[e] = x.lower * w0 + x.upper * w1;
+            for (int e = 0; e < EPL; ++e) acc[e] *= corr;
+#pragma unroll
+            for (int off = LPR; off < kWave; off <<= 1) {
+                const Pair l = lane_pair(l_run, off);
+                l_run = l.lower + l.upper;
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) {
+                    const Pair x = lane_pair(acc[e], off);
+                    acc[e] = x.lower + x.upper;
+                }
             }
         }
 
@@ -464,13 +524,19 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
 
         float M = kLowest, L = 0.f, o_d = 0.f;
         if (tid < D) {
+            float wt[WAVES], l[WAVES], x[WAVES];  // read together
 #pragma unroll
-            for (int w = 0; w < WAVES; ++w) M = fmaxf(M, sh_m[w]);
+            for (int w = 0; w < WAVES; ++w) wt[w] = sh_m[w], l[w] = sh_l[w], x[w] = sh_acc[w][tid];
+            arrived(wt), arrived(l), arrived(x);
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) M = fmaxf(M, wt[w]);
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) wt[w] -= M;
+            exp2_all(wt);
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) {
-                const float wt = __builtin_amdgcn_exp2f(sh_m[w] - M);
-                L = fmaf(sh_l[w], wt, L);
-                o_d = fmaf(sh_acc[w][tid], wt, o_d);
+                L = fmaf(l[w], wt[w], L);
+                o_d = fmaf(x[w], wt[w], o_d);
             }
         }
         if constexpr (SPLIT) {
@@ -566,17 +632,21 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
                         l[i] = in ? part[at][D + 1] : 0.f;
                         x[i] = in ? part[at][tid] : 0.f;
                     }
+                    arrived(m), arrived(l), arrived(x);
 #pragma unroll
                     for (int i = 0; i < N; ++i) m_new = fmaxf(m_new, m[i]);
-                    const float corr = __builtin_amdgcn_exp2f(M - m_new);
-                    L *= corr;
-                    o_d *= corr;
+                    float wt[N + 1];
+#pragma unroll
+                    for (int i = 0; i < N; ++i) wt[i] = m[i] - m_new;
+                    wt[N] = M - m_new;
+                    exp2_all(wt);
                     M = m_new;
+                    L *= wt[N];
+                    o_d *= wt[N];
 #pragma unroll
                     for (int i = 0; i < N; ++i) {
-                        const float wt = __builtin_amdgcn_exp2f(m[i] - M);
-                        L = fmaf(l[i], wt, L);
-                        o_d = fmaf(x[i], wt, o_d);
+                        L = fmaf(l[i], wt[i], L);
+                        o_d = fmaf(x[i], wt[i], o_d);
                     }
                 }
             }
@@ -636,7 +706,7 @@ static int launch_decode_w(const void* q, const void* k_new, const void* v_new, 
     hipLaunchKernelGGL((decode_step_kernel<DT, D, WAVES, UNROLL, DEEP, EMIT, SPLIT>), dim3(B * H * splits),
                        dim3(S::kThreads), 0, stream, (const uint4*)q, (const uint4*)k_new, (const uint4*)v_new,
                        (uint4*)k_cache, (uint4*)v_cache, pos, (uint4*)out, B * H, H, G, cap, cache_len, evict_idx, new_pos,
-                       scale * kLog2e, raw, stats, len_b, evict_b, new_pos_b, splits, least);
+                       score_scale(scale, DT), raw, stats, len_b, evict_b, new_pos_b, splits, least);
     return status_from_hip(hipGetLastError());
 }
 
@@ -665,15 +735,16 @@ int decode_auto_splits(int BH, int n_rows, int row_bytes)
 // that the limit is memory, and the more pairs there are the fewer bytes should be asked for at a time; batches of sequences that
 // differ in length want more than their pairs say, as the short ones end and leave the rest alone.  A cache of one tile has only
 // one round of loads.  us, four waves 4 deep / four 2 deep / four 4 / two 4 / two 2 (the kernel before the deep loop), D128:
-//   bf16 B*H  320  250 rows 10.8 / 10.8 / 10.5 / 11.8 / 16.7 (11.2)       900 rows 29.3 / 28.9 / 28.4 / 31.8 / 46.4 (28.4)
-//   bf16 B*H  640  250 rows 17.5 / 17.6 / 17.5 / 17.0 / 19.8 (18.1)       900 rows 52.6 / 52.9 / 53.7 / 50.3 / 54.2 (52.6)
-//   bf16 B*H 1024  400 rows 39.8 / 39.7 / 40.0 / 36.8 / 37.9 (36.5)     B*H 1536  640 rows 91.9 / 92.0 / 92.4 / 90.4 / 84.1 (86.2)
-//   bf16 B*H 1536   32 rows 11.5 / 11.2 / 10.1 / 10.9 / 12.5 (10.3)     B*H 512 ragged 900 rows 32.6 / 32.7 / 33.0 / 35.9 / 47.3 (33.2)
-//   f32  B*H  512  250 rows 26.1 / 27.4 / 25.3 / 28.2 / 33.7 (25.5)     B*H 1920  400 rows 151 / 155 / 152 / 147 / 141 (143)
-// Rows of 128 bytes (bf16 D64): up to 1023 pairs like bf16 D128; then two waves, 2 deep for short caches (B*H 1024, 64 rows 7.0 us,
-// two waves 4 deep or not 7.3) and not deep for long ones (B*H 1536, 900 rows 58.0, deep 61.5).
-// Over 4 types and sizes, 320 to 1920 pairs, 32 to 4096 rows the choice is 2.7 % faster than that kernel; what it loses, up to 7 % at
-// single points, it loses on caches of one to three tiles and at 88 KB of 1536 pairs, where no shape here does better by more than 2 %.
+//   bf16 B*H  320  250 rows 10.8 / 10.8 / 10.6 / 11.8 / 17.2 (11.3)       900 rows 29.3 / 28.7 / 28.2 / 32.0 / 47.7 (28.4)
+//   bf16 B*H  640  250 rows 17.7 / 17.7 / 17.7 / 17.2 / 20.0 (18.2)       900 rows 52.8 / 52.8 / 53.5 / 50.2 / 55.0 (52.6)
+//   bf16 B*H 1024  400 rows 39.9 / 39.6 / 39.7 / 36.8 / 37.9 (36.8)     B*H 1536  640 rows 91.8 / 92.0 / 92.0 / 90.6 / 83.6 (85.8)
+//   bf16 B*H 1536   32 rows 10.9 / 10.5 / 10.2 / 10.9 / 12.6 (10.3)     B*H 512 ragged 900 rows 32.6 / 32.5 / 32.8 / 35.8 / 48.6 (33.1)
+//   f32  B*H  512  250 rows 25.8 / 27.3 / 24.9 / 28.2 / 34.2 (25.2)     B*H 1920  400 rows 151 / 155 / 150 / 147 / 141 (142)
+// Rows of 128 bytes (bf16 D64): up to 1023 pairs like bf16 D128; then two waves, 2 deep for short caches (B*H 1024, 64 rows 6.7 us,
+// four waves 2 deep 6.8) and not deep for long ones (B*H 1536, 900 rows 57.9, deep 61.5).
+// Over both types and sizes, 320 to 1920 pairs, 32 to 4096 rows the choice is 2 % faster than that kernel; what it loses, 3 to 7 % at
+// single points and 10 % for 1920 ragged caches of up to 33 rows, it loses on caches of one to three tiles and at 88 KB of 1536
+// pairs, where no shape here does better by more than 2 %.
 constexpr long long kKiB = 1 << 10;
 struct DecodeAuto {
     int waves, unroll;

@@ -29,7 +29,9 @@ def _inputs(dtype, D, B, H, cap, seed, shift=0):
 def _expect(q, kn, vn, kc, vc, n, victim, scale):
     """(out, cache rows afterwards, softmax) of [B,H] pairs with n cached rows."""
     k, v = (torch.cat([c[:, :, :n], x[:, :, None]], 2) for c, x in ((kc, kn), (vc, vn)))
-    p = torch.softmax((k.double() * q.double()[:, :, None]).sum(-1) * scale, -1)
+    s = (k.double() * q.double()[:, :, None]).sum(-1) * scale
+    p = (s - s.amax(-1, keepdim=True)).exp()  # torch.softmax on the device gives zero for what is subnormal in fp32
+    p = p / p.sum(-1, keepdim=True)
     out = (p[..., None] * v.double()).sum(2)
     if victim >= 0:
         k, v = (torch.cat([x[:, :, :victim], x[:, :, victim + 1:]], 2) for x in (k, v))
@@ -154,3 +156,24 @@ def test_scores_near_the_largest_number(dtype):
     got = torch.zeros_like(q)
     ec.ec_decode_step(q, kn, vn, kc, vc, None, n, -1, 5, 1.0, got, None, G=1)
     _close(got, out, dtype)
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("where", ["beside the largest", "behind it", "before it", "in another share"])
+def test_weights_below_the_normal_range(dtype, D, where):
+    """The row of the largest score has no V; all the others weigh 2^-127 to 2^-131 and have V rows of 1e34 and more."""
+    H, n = 8, 1300 if where == "in another share" else 300
+    q, kn, vn, kc, vc = _inputs(dtype, D, 1, H, n + 1, n)
+    at = {"beside the largest": 150, "behind it": 0, "before it": n - 1, "in another share": n // 2}[where]
+    for x in (q, kn, kc):
+        x.zero_()
+    low = lambda x: -88.5 - 2 * torch.rand(x.shape[:-1], device="cuda")
+    q[..., 0], kn[..., 0], kc[..., 0] = 1.0, low(kn), low(kc)
+    for x in (vn, vc):
+        x.copy_(1e34 * (1 + x.double().abs().clamp(max=2)))
+    kc[:, :, at], vc[:, :, at] = 0, 0
+    out, *_ = _expect(q, kn, vn, kc, vc, n, -1, 1.0)
+    got = torch.zeros_like(q)
+    ec.ec_decode_step(q, kn, vn, kc, vc, None, n, -1, 5, 1.0, got, None, G=1)
+    # scores of up to 131 in base-2 units, three roundings of 2^-24 each, are exponents: 131 * 3 * 2^-24 * ln 2 < 2^-15
+    torch.testing.assert_close(got.double(), out, rtol=2 ** -8 + 2 ** -15 if dtype == "bf16" else 2 ** -15, atol=0)
