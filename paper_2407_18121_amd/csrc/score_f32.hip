@@ -189,6 +189,11 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
         }
 #pragma unroll
         for (int b = 0; b < NBLK; ++b) s[b] = (c[b][0] + c[b][1]) + (c[b][2] + c[b][3]);
+        float mn = INFINITY;
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mn = fminf(mn, s[b][r]);
         if (n0 + (NBLK - 1) * 16 * KS + 15 > P + mw) {
 #pragma unroll
             for (int b = 0; b < NBLK; ++b)
@@ -203,16 +208,29 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
             for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[b][r]);
         mx = quarters_max(mx);
         const float m_new = fmaxf(m_run, mx);
-        const float corr = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
+        const float corr = exp2f((m_run - m_new) * scale_log2e);
         m_run = m_new;
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s[b][r] = (s[b][r] - m_new) * scale_log2e;
+        // the exponential instruction gives zero where the result is subnormal; exp2f, which is six times as long, does not
+        if (__builtin_expect(__any((mn - m_new) * scale_log2e < -126.f), 0)) {
+#pragma unroll
+            for (int b = 0; b < NBLK; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s[b][r] = exp2f(s[b][r]);
+        } else {
+#pragma unroll
+            for (int b = 0; b < NBLK; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s[b][r] = __builtin_amdgcn_exp2f(s[b][r]);
+        }
         float psum = 0.f;
 #pragma unroll
         for (int b = 0; b < NBLK; ++b)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                s[b][r] = __builtin_amdgcn_exp2f((s[b][r] - m_new) * scale_log2e);
-                psum += s[b][r];
-            }
+            for (int r = 0; r < 4; ++r) psum += s[b][r];
         l_run = fmaf(l_run, corr, psum);
         if constexpr (OUT) {
             // a tile is summed by itself and then added: the rounding errors of a long chain stay small
@@ -376,7 +394,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void colsum_f32_kernel(
         f32x4 p;
 #pragma unroll
         for (int r = 0; r < 4; ++r) p[r] = fmaf((s[0][r] + s[1][r]) + (s[2][r] + s[3][r]), scale_log2e, -l2);
-        // the exponential instruction gives zero where the result is subnormal; exp2f, which is five times as long, does not
+        // as in the forward pass
         if (__any(fminf(fminf(p[0], p[1]), fminf(p[2], p[3])) < -126.f)) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) p[r] = exp2f(p[r]);
