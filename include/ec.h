@@ -244,7 +244,9 @@ int ec_evict_index(int64_t n_seen, int len_after_append, int gamma_num, int gamm
  *   ws                not used, may be NULL (ec_workspace_bytes(EC_FN_DECODE_STEP, ...) is 0).  Few (batch,
  *                     head) pairs with long caches are divided over several workgroups of the launch;
  *                     their partial results meet in 2.2 MB of device memory built into the library, which
- *                     launches on any streams share: a launch that finds a place taken does without it
+ *                     launches on any streams share: a launch that finds a place taken does without it (launches
+ *                     in flight are told apart by their caches, which they write; `out` may be shared by launches
+ *                     whose output nobody reads)
  * Requires 0 <= cache_len < cap, -1 <= evict_idx <= cache_len and a finite scale > 0.  Dot
  * products and the softmax are evaluated in fp32.
  */

@@ -39,7 +39,8 @@ template <int DT, int D, int WAVES, int UNROLL> struct DecodeShape {
 // (batch, head), inside one launch.  Lines belong to the library (2.2 MB) and are shared by everything that runs on the
 // device, so a line is claimed before it is used and is empty again when the launch ends:
 //   state   0 -> open (owner) -> joined (helper) -> 0 (owner, the data read and cleared), or open -> 0 (owner gives up on it)
-// "Open" and "joined" carry the address of the output row, which no two launches in flight share, and the share's number.
+// "Open" and "joined" carry the address of the head's rows in the K cache, which a launch in flight has to itself, since it writes
+// them (an output row may be a throw-away that several share), and the share's number.
 // Nobody ever waits for a workgroup that may not be running: an owner that cannot claim a line, or whose helper has not
 // joined by the time it is needed, forms that share itself, with the same instructions in the same order; a helper that finds its
 // line not open leaves without a trace.  Once a helper has joined it is running and waits for nothing, so the owner's wait for
@@ -238,9 +239,8 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
     const char* vn = reinterpret_cast<const char*>(v_new) + (size_t)bh * ROW;
 
     // lines of this (batch, head): neighbouring output rows use neighbouring lines
-    const unsigned long long out_row = (uintptr_t)out + (unsigned long long)bh * ROW;
-    const unsigned long long row_key = out_row << 8;
-    const unsigned line0 = (unsigned)(out_row / ROW) * (unsigned)(splits - 1);
+    const unsigned long long row_key = (unsigned long long)(uintptr_t)kc << 8;
+    const unsigned line0 = (unsigned)(((uintptr_t)out + (unsigned long long)bh * ROW) / ROW) * (unsigned)(splits - 1);
     auto line_of = [&](int s) { return (line0 + (unsigned)(s - 1)) % kLines; };
     auto key_of = [&](int s) { return row_key | (unsigned long long)s << 2; };
     bool claimed = false;  // owner, lane s of wave 0: the line of share s is this launch's

@@ -148,3 +148,31 @@ def test_frequency_step_divided(dtype, D, rows):
     for x, y in zip(*res):
         # the divided sums in another order: fp32 rounding, then one of bf16
         torch.testing.assert_close(y, x.expand_as(y).contiguous(), rtol=2 ** -7 if x.dtype == torch.bfloat16 else 1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("dtype,D,rows", [("bf16", 128, 700), ("f32", 64, 1200)])
+def test_launches_that_share_a_throw_away_output(dtype, D, rows):
+    """Divided frequency steps of four streams over caches of their own, all with one output that nobody reads: the masses are
+    those of each launch alone."""
+    H, streams = 8, [torch.cuda.Stream() for _ in range(4)]
+    t = lambda *s: torch.randn(*s, device="cuda").to(DT[dtype])
+    out = torch.zeros(1, H, D, device="cuda", dtype=DT[dtype])
+
+    def step(inputs, out):
+        q, kn, vn, kc, vc = inputs
+        freq = torch.zeros(1, H, rows + 1, device="cuda")
+        ws = ec.new_workspace(ec.EC_FN_DECODE_SCORE_STEP, 1, H, rows + 1, D, ec.dtype_code(kc))
+        ec.ec_decode_score_step(q, kn, vn, kc.clone(), vc.clone(), None, freq, rows, 3, D ** -0.5, out, ws)
+        return freq, ws
+    torch.manual_seed(4)
+    cases = [(t(1, H, D), t(1, H, D), t(1, H, D), t(1, H, rows + 1, D), t(1, H, rows + 1, D)) for _ in streams]
+    want = [step(c, torch.zeros_like(out))[0] for c in cases]
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(8):
+        for i, stream in enumerate(streams):
+            with torch.cuda.stream(stream):
+                got.append((i, step(cases[i], out)))
+    torch.cuda.synchronize()
+    for i, (freq, _) in got:
+        assert torch.equal(freq, want[i])
