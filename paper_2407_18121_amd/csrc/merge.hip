@@ -16,8 +16,6 @@
 // summed by the workgroup: B1 H32 T1024 15.1 -> 10.9, B1 H8 T8192 38.8 -> 20.1, B8 H32 T2048 80.0 -> 70.2, B16 H40 T624
 // 65.5 -> 56.2, B16 H32 T8192 466 -> 444 (5.3 TB/s), fp32 D64 B8 H8 T2048 33.3 -> 20.3.  Anchors that no score produces:
 // every fourth row, B8 T2048 58.0 -> 58.9; every second, B16 T4096 276 -> 316, where one stretch per workgroup reads pages in order.
-#include <type_traits>
-
 #include "ec_common.h"
 
 namespace ec {
@@ -167,6 +165,7 @@ __global__ __launch_bounds__(kMergeThreads, WEIGHTED ? 3 : 4) void merge_compact
 
     float acc_k[EPL], acc_v[EPL];
     int wsum;
+    u32x4 row_k, row_v;  // of a bucket of one row, as they were read: the sum of a signalling NaN and nothing is a quiet one
     // Rows first, first + step, ... <= last of every lane group; `most` rows of the group of the wave that has the most.  All
     // loads stand under wave-uniform conditions and are the same for every way through a loop: behind a load that some lanes
     // or some ways skip, a wait for one row is a wait for all of them, which took one trip to memory per row.  Groups that
@@ -209,11 +208,10 @@ __global__ __launch_bounds__(kMergeThreads, WEIGHTED ? 3 : 4) void merge_compact
                         acc_v[e] = fmaf(w, xv[e], acc_v[e]);
                     }
                 } else {
-                    constexpr bool copy = std::decay_t<decltype(x)>::N == 1;  // where every bucket is a row, NaN payloads stay too
 #pragma unroll
                     for (int e = 0; e < EPL; ++e) {
-                        acc_k[e] = copy ? xk[e] : acc_k[e] + xk[e];
-                        acc_v[e] = copy ? xv[e] : acc_v[e] + xv[e];
+                        acc_k[e] += xk[e];
+                        acc_v[e] += xv[e];
                     }
                 }
                 r_use += step;
@@ -225,6 +223,7 @@ __global__ __launch_bounds__(kMergeThreads, WEIGHTED ? 3 : 4) void merge_compact
             Rows<1> x;
             load(x);
             use(x, 1);
+            row_k = x.k[0], row_v = x.v[0];
         } else if (most <= kMergeUnroll) {
             // nothing is loaded behind these, so that each lane group can leave out the rows it does not have
             Rows<kMergeUnroll> x;
@@ -240,6 +239,7 @@ __global__ __launch_bounds__(kMergeThreads, WEIGHTED ? 3 : 4) void merge_compact
             }
             __builtin_amdgcn_sched_barrier(0);
             use(x, most);
+            row_k = x.k[0], row_v = x.v[0];
         } else {
             constexpr int N = kMergeUnroll / 2;
             Rows<N> xa, xb;
@@ -255,8 +255,10 @@ __global__ __launch_bounds__(kMergeThreads, WEIGHTED ? 3 : 4) void merge_compact
                 load(xb);
                 use(xa, N);
                 use(xb, N);
+                row_k = xb.k[N - 1], row_v = xb.v[N - 1];  // a bucket of one row has it in every slot
             } else {
                 use(xa, N);
+                row_k = xa.k[N - 1], row_v = xa.v[N - 1];
             }
         }
     };
@@ -270,6 +272,9 @@ __global__ __launch_bounds__(kMergeThreads, WEIGHTED ? 3 : 4) void merge_compact
                 acc_k[e] = acc_k[e] / cf;
                 acc_v[e] = acc_v[e] / cf;
             }
+        } else if (n_rows == 1) {
+            unpack<DT>(__builtin_bit_cast(uint4, row_k), acc_k);
+            unpack<DT>(__builtin_bit_cast(uint4, row_v), acc_v);
         }
         k_cache[((size_t)bh * cap + jj) * LPR + sub] = pack<DT>(acc_k);
         v_cache[((size_t)bh * cap + jj) * LPR + sub] = pack<DT>(acc_v);

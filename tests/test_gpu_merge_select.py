@@ -100,6 +100,32 @@ def test_merge_identity_is_a_bit_exact_copy(dtype, D):
     assert torch.equal(dv.view(torch.int16 if dtype == 'bf16' else torch.int32), dv_c.view(torch.int16 if dtype == 'bf16' else torch.int32))
 
 
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+def test_merge_signalling_nans_of_single_rows_stay(D, weighted):
+    """A bucket of one row is a copy also beside buckets of two rows, of nine and of hundreds, in the same wave."""
+    H, T = 2, 700
+    bits = np.random.default_rng(D).integers(-2**31, 2**31, (2, 1, H, T, D)).astype(np.int32)
+    bits[..., ::3] = 0x7f800001 + np.arange(T, dtype=np.int32)[:, None]       # signalling NaNs, every one its own
+    bits[..., 1::3] = -0x007ffff0 + np.arange(T, dtype=np.int32)[:, None]     # 0xff800010 ...
+    a = np.concatenate([np.arange(200), np.arange(201, 300, 2), np.arange(300, 340), np.arange(345, 470, 9),
+                        [471, 472, 473, 690, 691, 692]]).astype(np.int32).reshape(1, 1, -1)
+    n = a.shape[-1]
+    assign, counts = oracle.assign_nearest(a, T)
+    single = np.flatnonzero(counts[0, 0] == 1)
+    assert len(single) > 200 and {2, 9} <= set(counts[0, 0]) and counts.max() > 100
+    k, v = (torch.from_numpy(x).cuda().view(torch.float32) for x in bits)
+    kc, vc = (torch.zeros((1, H, n, D), device="cuda") for _ in range(2))
+    if weighted:
+        w = torch.full((1, 1, T), 3, dtype=torch.int32, device="cuda")
+        ec.ec_remerge_compact(k, v, T, torch.from_numpy(a).cuda(), kc, vc, w)
+    else:
+        ec.ec_merge_compact(k, v, torch.from_numpy(a).cuda(), kc, vc)
+    torch.cuda.synchronize()
+    for got, src in ((kc, bits[0]), (vc, bits[1])):
+        np.testing.assert_array_equal(got.view(torch.int32).cpu().numpy()[:, :, single], src[:, :, a[0, 0, single]])
+
+
 def test_merge_optional_outputs_may_be_null_and_batches_are_independent():
     B, H, T, D, n, dtype = 3, 2, 200, 128, 40, "bf16"
     rng = np.random.default_rng(9)
