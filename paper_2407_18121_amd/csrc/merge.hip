@@ -7,15 +7,20 @@
 // accumulates in fp32, divides by the count once and stores the row.
 // Importance scores put most anchors next to each other and leave buckets of tens to thousands of rows between the others, so
 //   - a workgroup's buckets are runs of a wave's width (1 KB of single rows) from all over the head: with one stretch of the
-//     head each, a few workgroups had all the long buckets.  Runs of 1 / 2 / 4 / 8 / 16 buckets, bf16 D128: B1 H32 T1024
-//     half the rows kept 12.0 / 11.8 / 11.7 / 12.3 / 15.4 us, B8 T1664 54 % kept 98.7 / 89.4 / 86.5 / 87.8 / 89.8 us;
+//     head each, a few workgroups had all the long buckets.  Runs of 4 / one stretch of 16 buckets, bf16 D128, us: B1 H8 T512 half
+//     the rows kept 8.0 / 10.3, B8 T1664 54 % kept 76 / 87, B16 T8192 a tenth kept 425 / 464; anchors every second row, B16 T4096, 319 / 315;
 //   - buckets are dealt out in pieces of at most an even share of the workgroup's rows, two rounds of pieces at the most.  The
-//     smallest share of 4 / 8 / 16 rows: B1 H32 T1024 10.9 / 11.2 / 11.7 us, B1 H8 T512 7.0 / 7.2 / 7.9 us;
-//   - loads stand under wave-uniform conditions, or have no others behind them.
-// us per call, prompt-like anchors, against one bucket per lane group with conditional loads and buckets of more than 128 rows
-// summed by the workgroup: B1 H32 T1024 15.1 -> 10.9, B1 H8 T8192 38.8 -> 20.1, B8 H32 T2048 80.0 -> 70.2, B16 H40 T624
-// 65.5 -> 56.2, B16 H32 T8192 466 -> 444 (5.3 TB/s), fp32 D64 B8 H8 T2048 33.3 -> 20.3.  Anchors that no score produces:
-// every fourth row, B8 T2048 58.0 -> 58.9; every second, B16 T4096 276 -> 316, where one stretch per workgroup reads pages in order.
+//     smallest share of 4 / 8 / 16 / 32 rows: B1 H32 T1024 10.8 / 10.8 / 10.8 / 10.5 us, B1 H8 T512 6.6 / 6.6 / 7.2 / 5.9, B8 H32 T2048
+//     63.4 / 63.6 / 65.8 / 67, B16 H32 T8192 420 / 422 / 430 / 454, the same with random anchors 449 / 459 / 464 / 481;
+//   - loads stand under wave-uniform conditions, or have no others behind them;
+//   - short buckets are bound by vector instructions, of which rounding and dividing had half: rows are rounded by the conversion
+//     instruction and divided by products where those give the same bits (B8 T1664 76.0 -> 68.7 -> 68.1 us, B16 T4096 every second
+//     row 320 -> 308 -> 305).
+// us per call, against one bucket per lane group with conditional loads and buckets of more than 128 rows summed by the workgroup,
+// prompt-like anchors: B1 H32 T1024 12.8 -> 10.8, B1 H8 T512 7.2 -> 6.6, B8 H32 T2048 70.5 -> 63.4, B16 H40 T624 65.5 -> 60.3, B16 H32 T8192
+// 433 -> 420 (5.6 TB/s), fp32 D64 B8 H8 T2048 26.6 -> 20.1.  Random anchors: B1 T1024 half kept 9.06 -> 8.95, B8 T2048 a quarter
+// 62.3 -> 60.3, half 75.2 -> 78.2, B16 T4096 half 301 -> 309, T8192 a tenth 418 -> 449.  Every second row: B16 T4096 286 -> 296, bf16 D64
+// B8 T4096 71.7 -> 81.5: every bucket is alike and nothing is gained by what the others need.
 #include "ec_common.h"
 
 namespace ec {
@@ -25,7 +30,7 @@ constexpr int kMergeUnroll = 8;  // rows of K and of V in flight per bucket (16 
 // Rows up to which buckets are not divided if no other one of the workgroup has more (8 / 16: scattered anchors, which have many
 // buckets of 9 to 16 rows, B8 T2048 77.9 / 63.7 us; prompt-like ones alike).
 constexpr int kMergeWhole = 16;
-constexpr int kMergePiece = 8;   // the smallest share
+constexpr int kMergePiece = 4;   // the smallest share
 constexpr int kMergeAssign = 128;  // buckets with more rows have their assignment written by the whole workgroup
 constexpr int kMergeMostRows = 1 << 30;
 
@@ -48,6 +53,30 @@ template <int N_> struct Rows {
     u32x4 k[N], v[N];
     int w[N];
 };
+
+// fp32 -> bf16 by the conversion instruction, two values at a time; the same bits as f32_to_bf16() for all 2^32 values.
+template <int DT> __device__ __forceinline__ uint4 round_row(const float* f)
+{
+    if constexpr (DT == EC_F32) return pack<DT>(f);
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    u32x4 c;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        c[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{f[2 * i], f[2 * i + 1]}), bf16x2));
+    return __builtin_bit_cast(uint4, c);
+}
+
+// x / n rounded once, for n = 2 .. kMergeCount and |x| = kMergeLeast .. largest, unit being 1 / n rounded: the first product is off by
+// an ulp or two, what it leaves of x is exact, and adding that part rounds as a division does.  Compared with the division for all
+// 2^23 significands and every such n.  3 instructions for 10.
+constexpr int kMergeCount = 1 << 16;
+constexpr float kMergeLeast = 0x1p-90f;
+__device__ __forceinline__ float quotient(float x, float n, float unit)
+{
+    const float q = x * unit;
+    return fmaf(fmaf(-n, q, x), unit, q);
+}
 
 // Inclusive sums over the first N lanes of a wave, N = 8, 16 or 32; they saturate at kMergeMostRows.
 template <int N> __device__ __forceinline__ int bucket_scan(int x)
@@ -267,17 +296,32 @@ __global__ __launch_bounds__(kMergeThreads, WEIGHTED ? 3 : 4) void merge_compact
         const int count = WEIGHTED ? w_total : n_rows;
         if (n_rows > 1) {
             const float cf = (float)count;
+            float least = INFINITY, most = 0.f;
 #pragma unroll
             for (int e = 0; e < EPL; ++e) {
-                acc_k[e] = acc_k[e] / cf;
-                acc_v[e] = acc_v[e] / cf;
+                least = fminf(least, fminf(fabsf(acc_k[e]), fabsf(acc_v[e])));
+                most = fmaxf(most, fmaxf(fabsf(acc_k[e]), fabsf(acc_v[e])));
+            }
+            if (__any(least < kMergeLeast || most == INFINITY || count > kMergeCount)) {
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) {
+                    acc_k[e] = acc_k[e] / cf;
+                    acc_v[e] = acc_v[e] / cf;
+                }
+            } else {
+                const float unit = 1.f / cf;
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) {
+                    acc_k[e] = quotient(acc_k[e], cf, unit);
+                    acc_v[e] = quotient(acc_v[e], cf, unit);
+                }
             }
         } else if (n_rows == 1) {
             unpack<DT>(__builtin_bit_cast(uint4, row_k), acc_k);
             unpack<DT>(__builtin_bit_cast(uint4, row_v), acc_v);
         }
-        k_cache[((size_t)bh * cap + jj) * LPR + sub] = pack<DT>(acc_k);
-        v_cache[((size_t)bh * cap + jj) * LPR + sub] = pack<DT>(acc_v);
+        k_cache[((size_t)bh * cap + jj) * LPR + sub] = round_row<DT>(acc_k);
+        v_cache[((size_t)bh * cap + jj) * LPR + sub] = round_row<DT>(acc_v);
         if (WEIGHTED && owner && sub == 0 && counts) counts[bg * n_max + jj] = count;
     };
 

@@ -126,6 +126,46 @@ def test_merge_signalling_nans_of_single_rows_stay(D, weighted):
         np.testing.assert_array_equal(got.view(torch.int32).cpu().numpy()[:, :, single], src[:, :, a[0, 0, single]])
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("step", [2, 3, 7, 10])
+def test_merge_means_are_rounded_once(dtype, step):
+    """Buckets are not divided where none has more than 16 rows: the fp32 sum in ascending order, divided and rounded as IEEE says, bit for bit -- ordinary rows, and
+    in heads of their own rows of 1e-44 .. 1e-38, of up to 1e38 (infinite sums too), zeros of both signs, infinities and NaN."""
+    H, n, D = 6, 40, 64
+    T = n * step
+    rng = np.random.default_rng(step)
+    k = quantize(rng.standard_normal((1, H, T, D)), dtype).astype(np.float32)
+    k[0, 1] *= np.float32(1e-38) * 10.0 ** -rng.integers(0, 7, (T, D)).astype(np.float32)
+    k[0, 2] *= np.float32(1e38)
+    k[0, 3] = np.where(rng.random((T, D)) < 0.5, np.float32(-0.0), np.float32(0.0))
+    k[0, 3, : T // 2] = -0.0
+    k[0, 4, rng.random((T, D)) < 0.01] = np.inf
+    k[0, 5, rng.random((T, D)) < 0.01] = np.nan
+    k = quantize(k, dtype).astype(np.float32)
+    a = np.arange(step // 2, T, step, dtype=np.int32).reshape(1, 1, -1)
+    assign, counts = oracle.assign_nearest(a, T)
+    assert a.shape[-1] == n and counts.max() <= 16
+    want = np.zeros((H, n, D), np.float32)
+    with np.errstate(all="ignore"):
+        for j in range(n):
+            rows = k[0][:, assign[0, 0] == j]
+            x = rows[:, 0].copy()
+            for r in range(1, rows.shape[1]):
+                x = x + rows[:, r]
+            want[:, j] = x / np.float32(rows.shape[1])
+    dk = torch.from_numpy(k).cuda().to(torch_dtype(dtype))
+    kc, vc = (torch.zeros((1, H, n, D), dtype=torch_dtype(dtype), device="cuda") for _ in range(2))
+    ec.ec_merge_compact(dk, dk.clone(), torch.from_numpy(a).cuda(), kc, vc)
+    torch.cuda.synchronize()
+    want = torch.from_numpy(want).to(torch_dtype(dtype))
+    for got in (kc, vc):
+        got = got[0].cpu()
+        assert torch.equal(got.isnan(), want.isnan())
+        bits = torch.int32 if dtype == "f32" else torch.int16
+        same = (got.view(bits) == want.view(bits)) | want.isnan()
+        assert same.all()
+
+
 def test_merge_optional_outputs_may_be_null_and_batches_are_independent():
     B, H, T, D, n, dtype = 3, 2, 200, 128, 40, "bf16"
     rng = np.random.default_rng(9)
