@@ -262,7 +262,8 @@ int ec_decode_step(const void* q, const void* k_new, const void* v_new, void* k_
  *   unroll  16-byte loads of K and of V each lane keeps in flight per tile (0 = the library's choice;
  *           6 and 12 run as 8)
  *   splits  workgroups per (batch, head): 0 = the library's choice, 1 = one workgroup, n > 1 = n
- *           workgroups; ws must then hold 4 * B * H * n * (D + 2) bytes, else EC_EWORKSPACE
+ *           workgroups; ws must then hold 4 * B * H * n * (D + 2) bytes, else EC_EWORKSPACE (it
+ *           is not written; callers of earlier versions rely on the check)
  * Combinations the library has no kernel for return EC_EINVAL.  Everything else as ec_decode_step.
  */
 int ec_decode_step_shaped(const void* q, const void* k_new, const void* v_new, void* k_cache,

@@ -668,7 +668,8 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
 
     if (!moved_early) {
         // Rows behind the victim that left the registers long ago, through memory: slab by slab, each read completely before any
-        // of it is overwritten.  No other workgroup reads them any more.
+        // of it is overwritten.  No other workgroup's reads count any more: a helper that still has some going was given up on, cannot
+        // join, and drops its sums.
         const int total = (held - (evict_idx + 1)) * LPR;
         u32x4* kd = reinterpret_cast<u32x4*>(kc + (size_t)evict_idx * ROW);
         u32x4* vd = reinterpret_cast<u32x4*>(vc + (size_t)evict_idx * ROW);

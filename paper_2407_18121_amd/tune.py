@@ -1,6 +1,6 @@
 """Timing of single entry points over launch shapes and input structure, through the ctypes binding.
 
-    python -m paper_2407_18121_amd.tune decode   # ec_decode_step_shaped: fused launch against every split shape
+    python -m paper_2407_18121_amd.tune decode   # ec_decode_step_shaped: the library's choice, one workgroup per head, heads divided
     python -m paper_2407_18121_amd.tune merge    # ec_merge_compact on three anchor distributions
     python -m paper_2407_18121_amd.tune select   # ec_select_anchors
     python -m paper_2407_18121_amd.tune score    # ec_prefill_score
@@ -74,11 +74,11 @@ DECODE_SHAPES = {  # name: (B, H, D, cached rows in the middle of the generation
 def tune_decode():
     for name, (B, H, D, N) in DECODE_SHAPES.items():
         sets = 16 if name == "C5" else 32
-        us, gbps = time_decode(B, H, D, N, 0, 0, 1, sets)
-        print(f"decode {name} B{B} H{H} rows {N}: one launch (library's choice) {us:7.2f} us {gbps:7.0f} GB/s", flush=True)
-        for waves, unroll in ((2, 4), (2, 8), (4, 4), (4, 6), (4, 8), (4, 12), (8, 4), (8, 8), (16, 4)):
+        us, gbps = time_decode(B, H, D, N, 0, 0, 0, sets)
+        print(f"decode {name} B{B} H{H} rows {N}: library's choice {us:7.2f} us {gbps:7.0f} GB/s", flush=True)
+        for waves, unroll in ((2, 4), (2, 8), (4, 4), (4, 8), (8, 4), (8, 8)):  # the others that are accepted run as these
             us, gbps = time_decode(B, H, D, N, waves, unroll, 1, sets)
-            print(f"decode {name}:   one launch, {waves:2d} waves x {unroll:2d} loads in flight {us:7.2f} us {gbps:7.0f} GB/s", flush=True)
+            print(f"decode {name}:   one workgroup each, {waves:2d} waves x {unroll:2d} loads in flight {us:7.2f} us {gbps:7.0f} GB/s", flush=True)
         best = None
         for splits in (2, 3, 4, 6, 8, 12, 16):
             if B * H * splits > 4096 or N // splits < 32:
@@ -88,7 +88,7 @@ def tune_decode():
                 if best is None or us < best[0]:
                     best = (us, gbps, splits, waves, unroll)
         if best:
-            print(f"decode {name}: best split + merging launch: {best[0]:7.2f} us {best[1]:7.0f} GB/s "
+            print(f"decode {name}: best division: {best[0]:7.2f} us {best[1]:7.0f} GB/s "
                   f"(splits {best[2]}, waves {best[3]}, unroll {best[4]})", flush=True)
 
 

@@ -81,7 +81,8 @@ def test_decode_step_workgroup_widths(waves):
 
 @pytest.mark.parametrize("waves,unroll", [(2, 4), (2, 8), (4, 6), (4, 8), (4, 12), (8, 8), (8, 12), (16, 6)])
 def test_decode_step_loads_in_flight(waves, unroll):
-    """Every (width, loads in flight) pair the fused kernel is built for, victim inside and outside the last tile."""
+    """(width, loads in flight) pairs that the call accepts (6 and 12 loads run as 8, 16 waves as 8), victim inside and
+    outside the last tile."""
     shape = (waves, unroll, 1)
     _case("bf16", 128, 2, 3, 1, 900, 777, 777 - 25, seed=10 * waves + unroll, shape=shape)
     _case("f32", 128, 1, 2, 1, 900, 512, 512 - 25, seed=10 * waves + unroll + 1, shape=shape)
@@ -91,8 +92,8 @@ def test_decode_step_loads_in_flight(waves, unroll):
 @pytest.mark.parametrize("splits", [2, 3, 8, 16])
 @pytest.mark.parametrize("waves,unroll", [(4, 4), (8, 4), (2, 8)])
 def test_decode_step_split_over_workgroups(splits, waves, unroll):
-    """The rows of one (batch, head) divided over several workgroups + the merging launch: same outputs, and
-    the append / elimination through memory moves rows bit for bit, wherever the victim lies."""
+    """The rows of one (batch, head) divided over several workgroups of the launch: same outputs, and the append /
+    elimination through memory moves rows bit for bit, wherever the victim lies."""
     shape = (waves, unroll, splits)
     _case("bf16", 128, 2, 3, 1, 900, 777, 777 - 25, seed=splits, shape=shape)
     _case("bf16", 128, 1, 2, 2, 900, 640, -1, seed=splits + 50, shape=shape)      # append only
