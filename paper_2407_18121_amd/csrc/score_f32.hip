@@ -13,8 +13,8 @@
 // longest workgroups end alone, and there everything between the matrix instructions adds up: 6.9 thousand clocks a tile
 // with the compiler's order, of which 4.1 matrix time.  Operands requested ahead at constant addresses, loads among the matrix
 // instructions and the bare exponential instruction took that down.  Measured (graph replay), vector ALU -> matrix
-// instructions -> now: whole call at B1 H32 T1024 D128 694 -> 148 -> 129 us (100 TFLOP/s; a workgroup loops over up to 32 tiles
-// while the mean is 16), T2048 496 -> 450, T512 58.5 -> 51.7, H8 T1024 81 -> 69.5, B1 H32 T1024 D64 88 -> 74.5.
+// instructions -> now: whole call at B1 H32 T1024 D128 694 -> 148 -> 128 us (100 TFLOP/s; a workgroup loops over up to 32 tiles
+// while the mean is 16), T2048 496 -> 450, T512 58.5 -> 51.7, H8 T1024 81 -> 69.5, B1 H32 T1024 D64 88 -> 76.
 // Eight waves on 64 queries, two on the keys of each 16: 168 us at T1024 (81 at D64), all of them in step.
 // Error of out against 64 bits at T1024 6.3e-7 (vector ALU) -> 2.8e-7, of the scores 1.3e-7 -> 1.1e-7, no change by the order.
 // Operands are read from LDS 16 bytes at a time, each read feeding four instructions: both operands of a contraction
