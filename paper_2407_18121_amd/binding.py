@@ -1,4 +1,5 @@
-"""ctypes binding over libelastic_cache.so: same names as the C ABI, argument marshalling only.
+"""Binding over libelastic_cache.so: same names as the C ABI, argument marshalling only.  The usual calls go through a native
+module (csrc/fastcall.cpp), all others through ctypes, which is also where wrong arguments are put into words.
 
 Tensors are torch CUDA tensors (device memory + the current stream come from
 PyTorch); every computation happens in the library's HIP kernels.  There is no
@@ -29,6 +30,9 @@ SYMBOLS = ("ec_status_string", "ec_workspace_bytes", "ec_prefill_score", "ec_chu
            "ec_decode_score_step_static")
 
 _lib = None
+_fast = None  # the usual calls in native code (csrc/fastcall.cpp); None in an answer of theirs: not a usual call
+_FAST = ("prefill_score", "prefill_score_varlen", "chunk_score", "select_anchors", "merge_compact", "remerge_compact",
+         "decode_step", "decode_step_varlen", "decode_score_step", "evict_min")  # in the order of its table
 
 
 class EcError(RuntimeError):
@@ -39,12 +43,12 @@ class EcError(RuntimeError):
 
 def load():
     """Load the in-tree library (build it first with `python -m paper_2407_18121_amd.build`)."""
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise FileNotFoundError(
-            f"{LIB_PATH} not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
+    for path in (LIB_PATH, os.path.join(_HERE, "_fastcall.so")):
+        if not os.path.exists(path):
+            raise FileNotFoundError(f"{path} not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
     lib = ctypes.CDLL(LIB_PATH)
     c_int, c_vp, c_sz, c_f = ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_float
     lib.ec_status_string.argtypes = [c_int]
@@ -87,6 +91,10 @@ def load():
     lib.ec_importance_mean.restype = c_int
     lib.ec_retention_step_varlen.argtypes = [c_vp] * 5 + [c_int] * 10 + [c_vp]
     lib.ec_retention_step_varlen.restype = c_int
+    if _raw_stream is not None and _device is not None:
+        from . import _fastcall
+        _fastcall.bind(_raw_stream, _device, tuple(ctypes.cast(getattr(lib, "ec_" + n), c_vp).value for n in _FAST))
+        _fast = _fastcall
     _lib = lib
     return lib
 
@@ -147,6 +155,12 @@ def _call(fn, *args):
         return fn(*[a() if callable(a) else a for a in ptrs])
 
 
+def _status(fn, rc, check):
+    if check and rc != EC_OK:
+        raise EcError(fn, rc)
+    return rc
+
+
 def _ws(ws):
     """(pointer, bytes) of an optional workspace tensor."""
     if ws is None:
@@ -190,6 +204,10 @@ def new_workspace(fn: int, B: int, H: int, T: int, D: int, dt: int, device="cuda
 
 def ec_prefill_score(q, k, v, out, lse, score, scale: float, ws, check=True) -> int:
     """q,k,v [B,H,T,D]; out [B,H,T,D] or None; lse [B,H,T] f32 or None; score [B,G,T] f32."""
+    if _fast is not None:
+        rc = _fast.prefill_score(q, k, v, out, lse, score, scale, ws)
+        if rc is not None:
+            return _status("ec_prefill_score", rc, check)
     if q.dim() != 4 or score.dim() != 3:
         raise ValueError("ec_prefill_score: q must be [B,H,T,D] and score [B,G,T]")
     B, H, T, D = q.shape
@@ -207,6 +225,10 @@ def ec_prefill_score(q, k, v, out, lse, score, scale: float, ws, check=True) -> 
 
 def ec_chunk_score(q, k, v, P: int, out, lse, score, scale: float, ws, check=True) -> int:
     """q [B,H,T_new,D]; k,v [B,H,kv_rows,D] holding P cached rows then the chunk's rows; score [B,G,P+T_new]."""
+    if _fast is not None:
+        rc = _fast.chunk_score(q, k, v, P, out, lse, score, scale, ws)
+        if rc is not None:
+            return _status("ec_chunk_score", rc, check)
     if q.dim() != 4 or k.dim() != 4 or score.dim() != 3:
         raise ValueError("ec_chunk_score: q, k must be 4-D and score 3-D")
     B, H, T_new, D = q.shape
@@ -226,6 +248,10 @@ def ec_chunk_score(q, k, v, P: int, out, lse, score, scale: float, ws, check=Tru
 
 def ec_select_anchors(score, n_anchor: int, protect_first: int, protect_last: int, anchor_idx, check=True) -> int:
     """score [B,G,T] f32 -> anchor_idx [B,G,n_anchor] int32 ascending."""
+    if _fast is not None:
+        rc = _fast.select_anchors(score, n_anchor, protect_first, protect_last, anchor_idx)
+        if rc is not None:
+            return _status("ec_select_anchors", rc, check)
     if score.dim() != 3:
         raise ValueError("ec_select_anchors: score must be [B,G,T]")
     B, G, T = score.shape
@@ -240,6 +266,10 @@ def ec_select_anchors(score, n_anchor: int, protect_first: int, protect_last: in
 def ec_merge_compact(k, v, anchor_idx, k_cache, v_cache, counts=None, assign=None, pos=None,
                      merge_mode: int = EC_MERGE_MEAN, check=True) -> int:
     """k,v [B,H,T,D]; anchor_idx [B,G,n]; k_cache,v_cache [B,H,cap,D]."""
+    if _fast is not None:
+        rc = _fast.merge_compact(k, v, anchor_idx, k_cache, v_cache, counts, assign, pos, merge_mode)
+        if rc is not None:
+            return _status("ec_merge_compact", rc, check)
     if k.dim() != 4 or anchor_idx.dim() != 3 or k_cache.dim() != 4:
         raise ValueError("ec_merge_compact: k, k_cache must be 4-D and anchor_idx 3-D")
     B, H, T, D = k.shape
@@ -261,6 +291,10 @@ def ec_merge_compact(k, v, anchor_idx, k_cache, v_cache, counts=None, assign=Non
 def ec_remerge_compact(k, v, L: int, anchor_idx, k_cache, v_cache, weights=None, src_pos=None, counts=None,
                        assign=None, pos=None, merge_mode: int = EC_MERGE_MEAN, check=True) -> int:
     """k,v [B,H,src_rows,D] of which rows 0..L-1 are merged; weights, src_pos [B,G,L] int32 or None."""
+    if _fast is not None:
+        rc = _fast.remerge_compact(k, v, L, anchor_idx, k_cache, v_cache, weights, src_pos, counts, assign, pos, merge_mode)
+        if rc is not None:
+            return _status("ec_remerge_compact", rc, check)
     if k.dim() != 4 or anchor_idx.dim() != 3 or k_cache.dim() != 4:
         raise ValueError("ec_remerge_compact: k, k_cache must be 4-D and anchor_idx 3-D")
     B, H, src_rows, D = k.shape
@@ -309,6 +343,10 @@ def _decode_args(q, k_new, v_new, k_cache, v_cache, pos, out, G, what):
 def ec_decode_step(q, k_new, v_new, k_cache, v_cache, pos, cache_len: int, evict_idx: int, new_pos: int,
                    scale: float, out, ws, G: int | None = None, check=True) -> int:
     """q,k_new,v_new,out [B,H,D]; k_cache,v_cache [B,H,cap,D]; pos [B,G,cap] int32 or None."""
+    if _fast is not None:
+        rc = _fast.decode_step(q, k_new, v_new, k_cache, v_cache, pos, cache_len, evict_idx, new_pos, scale, out, ws, G)
+        if rc is not None:
+            return _status("ec_decode_step", rc, check)
     ptrs, po, (B, H, G, D, cap) = _decode_args(q, k_new, v_new, k_cache, v_cache, pos, out, G, "ec_decode_step")
     wp, wb = _ws(ws)
     rc = _call(load().ec_decode_step, *ptrs, B, H, G, D, cap, cache_len, evict_idx, new_pos, scale, dtype_code(k_cache), po,
@@ -334,6 +372,10 @@ def ec_decode_step_shaped(q, k_new, v_new, k_cache, v_cache, pos, cache_len: int
 def ec_decode_score_step(q, k_new, v_new, k_cache, v_cache, pos, freq, cache_len: int, new_pos: int, scale: float,
                          out, ws, check=True) -> int:
     """Frequency policy: append + attend + add the attention row to freq [B,G,cap] f32 (no removal)."""
+    if _fast is not None:
+        rc = _fast.decode_score_step(q, k_new, v_new, k_cache, v_cache, pos, freq, cache_len, new_pos, scale, out, ws)
+        if rc is not None:
+            return _status("ec_decode_score_step", rc, check)
     if freq.dim() != 3:
         raise ValueError("ec_decode_score_step: freq must be [B,G,cap]")
     ptrs, po, (B, H, G, D, cap) = _decode_args(q, k_new, v_new, k_cache, v_cache, pos, out, freq.shape[1],
@@ -363,6 +405,10 @@ def ec_decode_score_step_static(q, k_new, v_new, k_cache, v_cache, pos, freq, ca
 def ec_evict_min(k_cache, v_cache, pos, freq, length: int, protect_first: int, protect_recent: int, victim,
                  check=True) -> int:
     """Frequency policy: remove the least-mass row of every (b,g); victim [B,G] int32 receives the index."""
+    if _fast is not None:
+        rc = _fast.evict_min(k_cache, v_cache, pos, freq, length, protect_first, protect_recent, victim)
+        if rc is not None:
+            return _status("ec_evict_min", rc, check)
     if k_cache.dim() != 4 or freq.dim() != 3:
         raise ValueError("ec_evict_min: k_cache must be [B,H,cap,D] and freq [B,G,cap]")
     B, H, cap, D = k_cache.shape
@@ -389,6 +435,10 @@ def _i32(t, name, n, optional=False):
 
 def ec_prefill_score_varlen(q, k, v, out, lse, score, seq_len, scale: float, ws, check=True) -> int:
     """Ragged batch: q,k,v [B,H,T_max,D], seq_len int32 [B] on the device."""
+    if _fast is not None:
+        rc = _fast.prefill_score_varlen(q, k, v, out, lse, score, seq_len, scale, ws)
+        if rc is not None:
+            return _status("ec_prefill_score_varlen", rc, check)
     if q.dim() != 4 or score.dim() != 3:
         raise ValueError("ec_prefill_score_varlen: q must be [B,H,T,D] and score [B,G,T]")
     B, H, T, D = q.shape
@@ -446,6 +496,10 @@ def ec_merge_compact_varlen(k, v, anchor_idx, seq_len, n_anchor_b, k_cache, v_ca
 def ec_decode_step_varlen(q, k_new, v_new, k_cache, v_cache, pos, cache_len_b, evict_idx_b, new_pos_b, scale: float,
                           out, G: int | None = None, ws=None, check=True) -> int:
     """Ragged batch: per-sequence cache length, victim and position as int32 [B] device tensors."""
+    if _fast is not None:
+        rc = _fast.decode_step_varlen(q, k_new, v_new, k_cache, v_cache, pos, cache_len_b, evict_idx_b, new_pos_b, scale, out, G, ws)
+        if rc is not None:
+            return _status("ec_decode_step_varlen", rc, check)
     ptrs, po, (B, H, G, D, cap) = _decode_args(q, k_new, v_new, k_cache, v_cache, pos, out, G, "ec_decode_step_varlen")
     wp, wb = _ws(ws)
     rc = _call(load().ec_decode_step_varlen, *ptrs, _i32(cache_len_b, "cache_len_b", B),

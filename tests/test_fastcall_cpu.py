@@ -1,0 +1,31 @@
+"""The binding's native half answers None to every call that the Python half has to look at (host tensors: nothing is launched)."""
+import pytest
+import torch
+
+from paper_2407_18121_amd import binding as ec
+
+
+class Sub(torch.Tensor):
+    pass
+
+
+def _steps():
+    B, H, cap, D = 2, 4, 12, 64
+    x, kc = torch.zeros((B, H, D)), torch.zeros((B, H, cap, D))
+    good = dict(q=x, k_new=x, v_new=x, k_cache=kc, v_cache=kc, pos=None, cache_len=3, evict_idx=-1, new_pos=0, scale=0.1, out=x, ws=None, G=1)
+    yield good  # on the host
+    for name, value in (("q", None), ("q", 3), ("q", x.as_subclass(Sub)), ("k_cache", x), ("v_new", x.bfloat16()), ("out", x.to("meta")),
+                        ("k_cache", kc.transpose(2, 3)), ("cache_len", 3.0), ("cache_len", 1 << 40), ("scale", 1), ("G", 3), ("pos", x)):
+        yield dict(good, **{name: value})
+
+
+@pytest.mark.parametrize("i", range(13))
+def test_unusual_calls_are_left_to_python(i):
+    ec.load()
+    assert ec._fast.decode_step(*list(_steps())[i].values()) is None
+
+
+def test_number_of_arguments():
+    ec.load()
+    for name in ec._FAST:
+        assert getattr(ec._fast, name)() is None
