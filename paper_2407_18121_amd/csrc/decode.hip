@@ -45,29 +45,42 @@ template <int DT, int D, int WAVES, int UNROLL> struct DecodeShape {
 // joined by the time it is needed, forms that share itself, with the same instructions in the same order; a helper that finds its
 // line not open leaves without a trace.  Once a helper has joined it is running and waits for nothing, so the owner's wait for
 // its data ends; that wait is bounded all the same, and a line that exceeded it is never given back.
-// The data words carry their own validity (upper half not 0), as relaxed device-scope atomics: no fence, no cache write-back.
+// The data words carry their own validity (upper half not 0): no fence, no cache write-back.
+//
+// All workgroups of one (batch, head) are launched on one XCD (their linear ids are equal modulo eight), every XCD has lines of its
+// own, and a workgroup looks at those of the XCD that it finds itself on: one that was placed elsewhere merely never meets its owner.
+// So the atomics only have to reach the L2 of the XCD.  A helper joins when it starts, not when it is done; the owner takes words and
+// empties them in one access, so that it gives its lines back as soon as it has everything and not when the launch has been
+// written out; and each wave weighs the shares with a lane for each.  What the exchange adds to a launch was 3.3 us with atomics in
+// device memory, a join at the end and a separate clearing, and is 2.6: B*H 32, 640 rows of bf16 D128 8.46 -> 7.82 us, B*H 8, 4096 rows (16
+// shares) 11.9 -> 10.3.  Of the latter 2.6 the helpers' words take 0.5 to arrive and each access of the owner 0.5.  Looking first
+// by plain loads is slower (the owner has everything 0.7 us later).
 constexpr int kMaxShares = 64;
-constexpr int kLines = 2048;
+constexpr int kLines = 256;      // of every XCD
 constexpr int kLineWords = 136;  // D + 2, padded to whole 64 bytes
-constexpr int kJoinTries = 4;    // of a helper that finds its line not open yet, 0.7 us each
-constexpr int kPatience = 8;     // looks of the owner at missing data before it asks whether the helper has joined
+constexpr int kJoinTries = 4;    // of a helper that finds its line not open yet
+constexpr int kPatience = 24;    // looks of the owner at missing data before it asks whether the helper has joined
 constexpr int kStuck = 1 << 20;  // looks after that
 constexpr unsigned long long kOpen = 1, kJoined = 2;
-static __device__ unsigned long long line_state[kLines];
-static __device__ unsigned long long line_data[kLines][kLineWords];
+__device__ __align__(128) static unsigned long long line_state[kXcds * kLines];
+__device__ __align__(128) static unsigned long long line_data[kXcds * kLines][kLineWords];
 
-__device__ __forceinline__ unsigned long long device_load(const unsigned long long* p)
+// An XCD's lines are touched by its own workgroups alone, so the L2 that they share is where its atomics have to be carried out
+// and no further: an exchange takes what it finds and leaves the word empty.
+__device__ __forceinline__ unsigned long long line_swap(unsigned long long* p, unsigned long long x)
 {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_exchange(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-__device__ __forceinline__ void device_store(unsigned long long* p, unsigned long long x)
+__device__ __forceinline__ unsigned long long line_cas(unsigned long long* p, unsigned long long from, unsigned long long to)
 {
-    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long device_cas(unsigned long long* p, unsigned long long from, unsigned long long to)
-{
-    __hip_atomic_compare_exchange_strong(p, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_compare_exchange_strong(p, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     return from;  // what was there
+}
+__device__ __forceinline__ unsigned xcd_id()
+{
+    unsigned x;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(x));
+    return x % kXcds;
 }
 
 // The rows of one (batch, head) as shares: share s is the s-th run of `chunk` rows from the END of the cache, so that share
@@ -166,6 +179,15 @@ template <int DT> __device__ __forceinline__ float chunk_dot(const u32x4& k, con
     return d;
 }
 
+// Maximum over the lane's row of 16.
+__device__ __forceinline__ float row_max(float x)
+{
+    x = fmaxf(x, dpp_mov<kDppQuadXor1>(x));
+    x = fmaxf(x, dpp_mov<kDppQuadXor2>(x));
+    x = fmaxf(x, dpp_mov<kDppRowHalfMirror>(x));
+    return fmaxf(x, dpp_mov<kDppRowMirror>(x));
+}
+
 // x[i] <- 2^x[i].  The exponential instruction gives zero where the result is subnormal; exp2f, which is six times as long, does not,
 // and is taken only where there is one (-149.. < x < -126; what lies below is zero either way, lanes without rows included).
 template <int N> __device__ __forceinline__ void exp2_all(float (&x)[N])
@@ -202,6 +224,9 @@ __device__ __forceinline__ Pair lane_pair(float x, int off)
     return {low ? x : other, low ? other : x};
 }
 
+// Workgroups of a divided launch per share: workgroups are handed to the XCDs in turn, and those of one (batch, head) have to meet.
+__host__ __device__ constexpr int split_stride(int BH) { return (BH + kXcds - 1) / kXcds * kXcds; }
+
 // EMIT (frequency discard policy): the kernel also stores every row's scaled score (base-2 units) into
 // raw [B,H,cap] and the head's softmax maximum and denominator into stats [B,H,2], from which
 // freq_accumulate_kernel forms this step's probabilities.
@@ -215,8 +240,10 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
     const int32_t* __restrict__ new_pos_b, int splits, int least)
 {
     using S = DecodeShape<DT, D, WAVES, UNROLL>;
-    const int own_share = SPLIT ? blockIdx.x / BH : 0;
-    const int bh = SPLIT ? blockIdx.x - own_share * BH : blockIdx.x;
+    const int stride = SPLIT ? split_stride(BH) : BH;
+    const int own_share = SPLIT ? blockIdx.x / stride : 0;
+    const int bh = SPLIT ? blockIdx.x - own_share * stride : blockIdx.x;
+    if (SPLIT && bh >= BH) return;
     if (len_b) {  // ragged batch: every batch element has its own cache length, victim and position
         const int b = bh / H;
         cache_len = min(max(len_b[b], 0), cap - 1);
@@ -241,11 +268,14 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
     // lines of this (batch, head): neighbouring output rows use neighbouring lines
     const unsigned long long row_key = (unsigned long long)(uintptr_t)kc << 8;
     const unsigned line0 = (unsigned)(((uintptr_t)out + (unsigned long long)bh * ROW) / ROW) * (unsigned)(splits - 1);
-    auto line_of = [&](int s) { return (line0 + (unsigned)(s - 1)) % kLines; };
+    const unsigned xcd_lines = SPLIT ? xcd_id() * kLines : 0;
+    auto line_of = [&](int s) { return xcd_lines + (line0 + (unsigned)(s - 1)) % kLines; };
     auto key_of = [&](int s) { return row_key | (unsigned long long)s << 2; };
     bool claimed = false;  // owner, lane s of wave 0: the line of share s is this launch's
     if (SPLIT && own_share == 0 && wave == 0 && lane >= 1 && lane < shares.count)
-        claimed = device_cas(&line_state[line_of(lane)], 0, key_of(lane) | kOpen) == 0;
+        claimed = line_cas(&line_state[line_of(lane)], 0, key_of(lane) | kOpen) == 0;
+    unsigned long long seen = 0;  // helper: what its line held
+    if (SPLIT && own_share > 0 && tid == 0) seen = line_cas(&line_state[line_of(own_share)], key_of(own_share) | kOpen, key_of(own_share) | kJoined);
 
     // positions of the rows behind the victim, fetched early (stored after the barrier)
     const bool owns_pos = own_share == 0 && pos != nullptr && (G == H || (bh % H) == 0);
@@ -318,7 +348,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    __shared__ float sh_acc[WAVES][D];
+    __shared__ __align__(16) float sh_acc[WAVES][D];
     __shared__ float sh_m[WAVES];
     __shared__ float sh_l[WAVES];
     __shared__ float part[SPLIT ? kMaxShares : 1][D + 2];  // of every share: weighted V, maximum, sum of weights
@@ -457,10 +487,6 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
         }
         // ta holds the last tile: of share 0, the newest rows
 
-        unsigned long long seen = 0;  // helper: what its line held; asked for here, looked at behind the merging
-        if (SPLIT && own_share > 0 && tid == 0)
-            seen = device_cas(&line_state[line_of(s)], key_of(s) | kOpen, key_of(s) | kJoined);
-
         // ---- merge the lanes of each wave that hold the same features: the maximum first, then plain sums ----
         {
             float m_wave = m_run;
@@ -489,7 +515,8 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
         // ---- merge the waves through LDS ----
         if (lane < LPR) {
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) sh_acc[wave][sub * EPL + e] = acc[e];
+            for (int e = 0; e < EPL; e += 4)
+                *reinterpret_cast<float4*>(&sh_acc[wave][sub * EPL + e]) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
             if (sub == 0) {
                 sh_m[wave] = m_run;
                 sh_l[wave] = l_run;
@@ -497,7 +524,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
         }
         if (SPLIT && own_share > 0 && tid == 0) {
             for (int i = 0; seen == 0 && i < kJoinTries; ++i)
-                seen = device_cas(&line_state[line_of(s)], key_of(s) | kOpen, key_of(s) | kJoined);
+                seen = line_cas(&line_state[line_of(s)], key_of(s) | kOpen, key_of(s) | kJoined);
             sh_joined = seen == (key_of(s) | kOpen);
         }
         if (SPLIT && own_share == 0 && s == 0 && wave == 0) {
@@ -544,8 +571,8 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
                 if (sh_joined && tid < D) {
                     unsigned long long* line = line_data[line_of(s)];
                     const unsigned long long valid = 1ull << 32;
-                    device_store(line + tid, valid | __float_as_uint(o_d));
-                    if (tid < 2) device_store(line + D + tid, valid | __float_as_uint(tid == 0 ? M : L));
+                    line_swap(line + tid, valid | __float_as_uint(o_d));
+                    if (tid < 2) line_swap(line + D + tid, valid | __float_as_uint(tid == 0 ? M : L));
                 }
                 return;
             }
@@ -563,18 +590,17 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
                 auto look = [&](int patience) {
                     for (int i0 = 0; i0 * THREADS + tid < total; i0 += kBatch)
                         for (int n = 0; (pending >> i0 & ((1ull << kBatch) - 1)) && n < patience; ++n) {
-                            unsigned long long x[kBatch];
+                            unsigned long long x[kBatch] = {};
 #pragma unroll
                             for (int u = 0; u < kBatch; ++u) {
-                                const int j = min((i0 + u) * THREADS + tid, total - 1);
-                                x[u] = device_load(&line_data[line_of(1 + j / (D + 2))][j % (D + 2)]);
+                                const int j = (i0 + u) * THREADS + tid;
+                                if (pending >> (i0 + u) & 1) x[u] = line_swap(&line_data[line_of(1 + j / (D + 2))][j % (D + 2)], 0);
                             }
 #pragma unroll
                             for (int u = 0; u < kBatch; ++u)
-                                if ((pending >> (i0 + u) & 1) && x[u] >> 32) {
+                                if (x[u] >> 32) {
                                     const int j = (i0 + u) * THREADS + tid;
                                     part[1 + j / (D + 2)][j % (D + 2)] = __uint_as_float((uint32_t)x[u]);
-                                    device_store(&line_data[line_of(1 + j / (D + 2))][j % (D + 2)], 0);
                                     pending &= ~(1ull << (i0 + u));
                                 }
                         }
@@ -591,7 +617,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
                 if (const unsigned long long late = missing(0)) {  // uniform
                     if (wave == 0) {
                         const unsigned long long open = key_of(lane) | kOpen;
-                        const bool lost = (late >> lane & 1) && device_cas(&line_state[line_of(lane)], open, 0) == open;
+                        const bool lost = (late >> lane & 1) && line_cas(&line_state[line_of(lane)], open, 0) == open;
                         const unsigned long long l = __ballot(lost);
                         if (tid == 0) sh_lost = l;
                     }
@@ -603,7 +629,9 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
                     given_up |= missing(1);
                 }
                 todo = all & (~sh_claimed | given_up);
-                if (wave == 0) claimed = claimed && !(given_up >> lane & 1);  // lines to give back
+                // Every word of the lines that were joined has been taken (all threads have passed missing()): whoever claims one
+                // next finds it empty.
+                if (wave == 0 && claimed && !(given_up >> lane & 1)) line_swap(&line_state[line_of(lane)], 0);
             } else {
                 todo &= ~(1ull << s);
                 __syncthreads();  // sh_acc is written again
@@ -617,37 +645,27 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // arrived before any wave overwrites them
                 __syncthreads();
             }
-            M = kLowest, L = 0.f, o_d = 0.f;
+            // Every wave weighs the shares, a lane each, and adds their rows up in ascending order (a thread that weighs all of
+            // them itself takes twice as long, 0.9 us).
+            const bool has = lane < shares.count;
+            const int of = has ? lane : 0;
+            const float m_share = has ? part[of][D] : kLowest, l_share = has ? part[of][D + 1] : 0.f;
+            auto first = [](float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); };
+            M = first(shares.count > 16 ? wave_max(m_share) : row_max(m_share));
+            float wt[1] = {m_share - M};
+            exp2_all(wt);
+            L = first(shares.count > 16 ? group_sum<kWave>(l_share * wt[0]) : group_sum<16>(l_share * wt[0]));
+            o_d = 0.f;
             if (tid < D) {
-                // shares in ascending order, eight at a time so that their reads overlap
-                constexpr int N = 8;
+                constexpr int N = 8;  // reads that overlap
                 for (int i0 = 0; i0 < shares.count; i0 += N) {
-                    float m[N], l[N], x[N];
-                    float m_new = M;
+                    float x[N];
 #pragma unroll
-                    for (int i = 0; i < N; ++i) {
-                        const bool in = i0 + i < shares.count;
-                        const int at = in ? i0 + i : 0;
-                        m[i] = in ? part[at][D] : kLowest;
-                        l[i] = in ? part[at][D + 1] : 0.f;
-                        x[i] = in ? part[at][tid] : 0.f;
-                    }
-                    arrived(m), arrived(l), arrived(x);
+                    for (int i = 0; i < N; ++i) x[i] = i0 + i < shares.count ? part[i0 + i][tid] : 0.f;
+                    arrived(x);
 #pragma unroll
-                    for (int i = 0; i < N; ++i) m_new = fmaxf(m_new, m[i]);
-                    float wt[N + 1];
-#pragma unroll
-                    for (int i = 0; i < N; ++i) wt[i] = m[i] - m_new;
-                    wt[N] = M - m_new;
-                    exp2_all(wt);
-                    M = m_new;
-                    L *= wt[N];
-                    o_d *= wt[N];
-#pragma unroll
-                    for (int i = 0; i < N; ++i) {
-                        L = fmaf(l[i], wt[i], L);
-                        o_d = fmaf(x[i], wt[i], o_d);
-                    }
+                    for (int i = 0; i < N; ++i)  // lanes behind the last share: x is 0
+                        o_d = fmaf(x[i], __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wt[0]), i0 + i)), o_d);
                 }
             }
         }
@@ -689,11 +707,6 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
         __syncthreads();
         move_held();
     }
-    if (SPLIT) {  // the lines are empty: whoever claims one next finds no word of this launch
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (wave == 0 && claimed) device_store(&line_state[line_of(lane)], 0);
-    }
 }
 
 template <int DT, int D, int WAVES, int UNROLL, bool DEEP, bool EMIT, bool SPLIT>
@@ -704,7 +717,7 @@ static int launch_decode_w(const void* q, const void* k_new, const void* v_new, 
                            hipStream_t stream)
 {
     using S = DecodeShape<DT, D, WAVES, UNROLL>;
-    hipLaunchKernelGGL((decode_step_kernel<DT, D, WAVES, UNROLL, DEEP, EMIT, SPLIT>), dim3(B * H * splits),
+    hipLaunchKernelGGL((decode_step_kernel<DT, D, WAVES, UNROLL, DEEP, EMIT, SPLIT>), dim3(SPLIT ? split_stride(B * H) * splits : B * H),
                        dim3(S::kThreads), 0, stream, (const uint4*)q, (const uint4*)k_new, (const uint4*)v_new,
                        (uint4*)k_cache, (uint4*)v_cache, pos, (uint4*)out, B * H, H, G, cap, cache_len, evict_idx, new_pos,
                        score_scale(scale, DT), raw, stats, len_b, evict_b, new_pos_b, splits, least);
@@ -712,22 +725,22 @@ static int launch_decode_w(const void* q, const void* k_new, const void* v_new, 
 }
 
 // Workgroups that one (batch, head) is divided over when the caller leaves the choice to the library: as many as the chip has
-// compute units for, where that saves more than the exchange costs (3.3 us against 1 us per 54 KB of one (batch, head)'s rows).
+// compute units for, where that saves more than the exchange costs (2.6 us against 1 us per 54 KB of one (batch, head)'s rows).
 // Measured, us per launch (graph replay, D128, one workgroup / divided; crossover):
-//   bf16, B*H =  8:  550 rows 7.5 / 7.6    1200 13.0 / 8.4   4096 38.1 / 11.6     f32  250 rows 6.9 / 7.4   350  8.5 / 7.2   4096 73.3 / 14.3
-//   bf16, B*H = 32:  550 rows 7.9 / 8.2    1200 13.8 / 9.9   4096 40.3 / 16.5     f32  250 rows 7.4 / 8.1   350  9.3 / 8.5   4096 76.8 / 25.9
-//   bf16, B*H = 64:  700 rows 9.8 / 10.3   1200 14.8 / 12.1  4096 42.3 / 25.1     f32  350 rows 10.0 / 10.5   450 12.0 / 11.2   4096 82.1 / 44.5
-//   bf16, B*H = 96:  800 rows 11.5 / 12.3  1200 15.6 / 14.8  4096 50.7 / 35.8     f32  550 rows 14.8 / 14.6   4096 86.8 / 62.1
-//   bf16, B*H = 128: 1600 rows 20.7 / 21.0  2400 30.7 / 29.9  4096 49.2 / 43.9    f32 1000 rows 25.4 / 25.0   4096 92.2 / 82.3
+//   bf16, B*H =  8:  450 rows 7.1 / 7.1     550 8.0 / 7.6   4096 39.3 / 10.7     f32  220 rows 6.7 / 6.7   260  7.7 / 7.1   4096 75.0 / 13.0
+//   bf16, B*H = 32:  500 rows 7.7 / 7.8     640 9.2 / 8.1   4096 40.6 / 15.9     f32  230 rows 7.4 / 7.3   260  8.0 / 7.7   4096 77.8 / 25.1
+//   bf16, B*H = 64:  600 rows 9.1 / 9.4     700 10.0 / 9.8  4096 42.7 / 25.2     f32  250 rows 8.3 / 8.8   300  9.8 / 9.3
+//   bf16, B*H = 96:  800 rows 11.6 / 12.2  1200 16.0 / 14.9 4096 51.0 / 35.3     f32  550 rows 14.8 / 14.6
+//   bf16, B*H = 128: 1600 rows 22.9 / 22.4 2400 33.1 / 31.2 4096 51.0 / 46.8     f32 1000 rows 28.0 / 26.5
 // More workgroups than compute units lose everywhere (B*H = 160, two each: 19.8 / 30.1 at 1200 rows).  Sixteen shares instead of
-// eight pay from 2 MB on (B*H = 8, f32 4096 rows: 17.4 / 14.3; 1200 rows: 9.7 / 10.2).
+// eight: B*H = 8, bf16 1200 rows 8.3 / 8.8, 4096 rows (2 MB) 11.7 / 10.7, f32 4096 rows 16.5 / 13.0.
 constexpr int kComputeUnits = 256;
 constexpr int kLeastShareBytes = 48 << 10;  // of K and V
 int decode_auto_splits(int BH, int n_rows, int row_bytes)
 {
     const long long bytes = 2LL * n_rows * row_bytes;
-    const int splits = std::min(kComputeUnits / BH, bytes >= 2 << 20 ? 16 : 8);
-    const int pays = splits >= 5 ? 288 << 10 : splits >= 3 ? 352 << 10 : BH <= 96 ? 512 << 10 : 960 << 10;
+    const int splits = std::min(kComputeUnits / BH, bytes >= 3 << 19 ? 16 : 8);
+    const int pays = splits >= 5 ? 240 << 10 : splits >= 3 ? 320 << 10 : BH <= 96 ? 512 << 10 : 960 << 10;
     return splits >= 2 && bytes >= pays ? splits : 1;
 }
 

@@ -13,7 +13,6 @@ typedef u32x4 __attribute__((aligned(2))) u32x4_any;  // at any element of a 16-
 // eight times.  Heads go to the XCDs in turn: a ragged batch, whose long sequences are neighbouring heads, then loads
 // them alike (B16 H40, 312..624 rows: the slowest XCD ended at 141 us, the fastest at 105, with contiguous ranges).  A
 // head count that eight does not divide is cut into equal contiguous ranges of items.
-constexpr int kXcds = 8;
 inline int xcd_grid(int total) { return (total + kXcds - 1) / kXcds * kXcds; }
 struct XcdItem {
     int bh, tile;  // bh < 0: nothing to do
