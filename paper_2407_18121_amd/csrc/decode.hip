@@ -874,6 +874,7 @@ int decode_dispatch(const void* q, const void* k_new, const void* v_new, void* k
 // scheduling.
 constexpr int kFreqRows = 64;
 constexpr int kFreqParts = 4;
+constexpr int kFreqHeads = 8;
 __global__ __launch_bounds__(kFreqRows * kFreqParts) void freq_accumulate_kernel(const float* __restrict__ raw,
                                                                                 const float* __restrict__ stats,
                                                                                 float* __restrict__ freq, int H, int G,
@@ -888,11 +889,30 @@ __global__ __launch_bounds__(kFreqRows * kFreqParts) void freq_accumulate_kernel
     const int per = (h_count + kFreqParts - 1) / kFreqParts;
     const int h0 = h_first + grp * per, h1 = min(h0 + per, h_first + h_count);
     float acc = 0.f;
-    if (j < n)
-        for (int h = h0; h < h1; ++h) {
-            const size_t bh = (size_t)b * H + h;
-            acc += exp2f(raw[bh * cap + j] - stats[bh * 2]) / stats[bh * 2 + 1];
+    auto mass = [&](float x, float m, float l) { return exp2f(x - m) / l; };
+    if (per < kFreqHeads / 2) {  // head-wise counts, few heads
+        if (j < n)
+            for (int h = h0; h < h1; ++h) {
+                const size_t bh = (size_t)b * H + h;
+                acc += mass(raw[bh * cap + j], stats[bh * 2], stats[bh * 2 + 1]);
+            }
+    } else {
+        // Eight heads at a time, all their reads in flight together (the last one again where there are fewer).  A trip to memory
+        // per head, one after the other, made a whole step (decode, masses, removal) 27.2 us at B8 H32 640 rows, now 25.8, and 15.4
+        // at B1 300 rows, now 13.9; below four heads a thread the reads for nothing cost more (H8: 16.1, 16.4).
+        for (int h = h0; h < h1; h += kFreqHeads) {
+            float x[kFreqHeads], m[kFreqHeads], l[kFreqHeads];
+#pragma unroll
+            for (int i = 0; i < kFreqHeads; ++i) {
+                const size_t bh = (size_t)b * H + min(h + i, h1 - 1);
+                x[i] = raw[bh * cap + min(j, n - 1)], m[i] = stats[bh * 2], l[i] = stats[bh * 2 + 1];
+            }
+            arrived(x);
+#pragma unroll
+            for (int i = 0; i < kFreqHeads; ++i)
+                if (h + i < h1) acc += mass(x[i], m[i], l[i]);
         }
+    }
     part[grp][r] = acc;
     __syncthreads();
     if (grp == 0 && j < n) {
