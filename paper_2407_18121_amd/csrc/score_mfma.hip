@@ -481,7 +481,15 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
     constexpr int BN = KW * KEYS_W;     // keys per workgroup
     constexpr int SPT = QT / 32 / QG;  // steps of one wave per tile
     constexpr int kNoStep = 0x3fffff00;  // "first query" of a block that holds no step: behind every sequence
-    __shared__ __align__(16) uint16_t qs[2 * QT * D];  // two tiles
+    // The keys of a wave, a row per lane, are read from LDS: straight from memory each of a load's 64 rows would be a request of its
+    // own, 64 clocks of the compute unit's cache instead of 16.  They come in where the second query tile goes afterwards (one
+    // wave group) or have a place of their own (two).  64 keys per wave would need twice the place, which is not there.  us of the
+    // whole call before / now: B1 H32 D128 T1000 36.9 / 35.7, T300 18.8 / 18.1, B16 H40 T512 136.9 / 134.5, B4 H32 T1100 98.1 /
+    // 98.1, D64 B2 H40 T700 28.4 / 27.9; two groups at D 64, whose rows are half as long: B1 H32 T1000 28.4 / 28.8, so not there.
+    constexpr bool STAGED = NB == 1 && DIRECT && (D == 128 || QG == 1);
+    constexpr int kKeysAt = QG == 1 ? QT * D : 2 * QT * D;  // element
+    static_assert(!STAGED || !PAIR, "one key tile");
+    __shared__ __align__(16) uint16_t qs[STAGED ? kKeysAt + BN * D : 2 * QT * D];  // two tiles
     __shared__ __align__(16) float ls[2 * QT];
     __shared__ __align__(16) float red[WAVES][4][KEYS_W / 2];  // [wave][half-wave, 16-lane row][16 sums per 32 keys]
 
@@ -514,16 +522,20 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
         if (wave < QT / kWave)
             load_lds_4(l_rsrc, ls_at + (buf * QT + wave * kWave) * 4, (m + wave * kWave + anew(lane)) * 4);
     };
-    {
+    auto first_tile = [&](int t) __attribute__((always_inline)) {
         const Mover mover(q_rsrc, wave, anew(lane));
+        const int m = PAIR ? max(m_last - t * QT, 0) : first_seen(ktile) + t * QT;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int m = PAIR ? max(m_last - t * QT, 0) : first_seen(ktile) + t * QT;
+        for (int j = 0; j < Mover::NI; ++j) mover.issue(qs_at + t * QT * D * 2, m, j);
+        fetch_lse(t, m);
+    };
+    if constexpr (STAGED) {
+        const TileToLds<D, BN, WAVES, SwizzleRows<D>> k_move(tile_rsrc(kh, (uint32_t)L * (D * 2)), wave, anew(lane));
 #pragma unroll
-            for (int j = 0; j < Mover::NI; ++j) mover.issue(qs_at + t * QT * D * 2, m, j);
-            fetch_lse(t, m);
-        }
+        for (int j = 0; j < k_move.NI; ++j) k_move.issue(qs_at + kKeysAt * 2, ktile * BN, j);
     }
+    first_tile(0);
+    if (!STAGED || QG == 2) first_tile(1);
     bf16x8 kf[NB][KB];
     auto load_keys = [&](int tile) __attribute__((always_inline)) {
         const int lk = anew(lane);
@@ -535,7 +547,7 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
                 kf[nb][kb] = *reinterpret_cast<const bf16x8_any*>(kh + (size_t)n * D + kb * 16 + lk / 32 * 8);
         }
     };
-    load_keys(ktile);
+    if constexpr (!STAGED) load_keys(ktile);
 
     for (;;) {  // one key tile after the other
         const int n0 = ktile * BN;
@@ -686,6 +698,17 @@ __global__ __launch_bounds__(KW * QG * kWave, 2) void colsum_mfma_kernel(
             }
         };
         tile_barrier();
+        if constexpr (STAGED) {
+            const int row = kw * 32 + lq % 32;
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+                kf[0][kb] = *(lds_bf16x8*)(uintptr_t)(qs_at + kKeysAt * 2 + row * (D * 2) + ((2 * kb + lq / 32) ^ swz) * 16);
+            if constexpr (QG == 1) {
+                wait_lds();
+                meet();  // the keys have been read: their place is free
+                first_tile(1);
+            }
+        }
         // The compiler learns here that the keys have arrived: the waits it would otherwise put before their uses inside the
         // loop would be waits for the tiles in flight (4.13 -> 3.86 ms at T8192, 56 -> 53 us with 32 keys per wave).  The few
         // steps of a two-group launch are 0.6 us slower without them (B1 T1024 13.5 / 14.1 us).
