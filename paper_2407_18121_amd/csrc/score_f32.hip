@@ -16,6 +16,8 @@
 // instructions -> now: whole call at B1 H32 T1024 D128 694 -> 148 -> 128 us (100 TFLOP/s; a workgroup loops over up to 32 tiles
 // while the mean is 16), T2048 496 -> 450, T512 58.5 -> 51.7, H8 T1024 81 -> 69.5, B1 H32 T1024 D64 88 -> 76.
 // Eight waves on 64 queries, two on the keys of each 16: 168 us at T1024 (81 at D64), all of them in step.
+// The operands that stay in registers come through LDS (whole call, graph replay, straight from memory / now): B1 H32 D128 T1024
+// 126.9 / 126.1, T512 49.3 / 47.2, H4 T100 14.7 / 13.5, B8 T130 51.1 / 48.8, B4 D64 T300 39.5 / 37.4, H4 D64 T256 14.2 / 13.5.
 // Error of out against 64 bits at T1024 6.3e-7 (vector ALU) -> 2.8e-7, of the scores 1.3e-7 -> 1.1e-7, no change by the order.
 // Operands are read from LDS 16 bytes at a time, each read feeding four instructions: both operands of a contraction
 // enumerate it in the same permuted order.
@@ -122,12 +124,18 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
     const int n_tiles = (n_end + TN - 1) / TN;
     fetch(0, 0, LOADS);
 
-    f32x4 qf[KB];  // B operand: element e of block kb is feature 16 kb + 4 h + e of this lane's query
+    // The queries, a row per lane, are read from LDS, where they come in at the places of the odd tiles: straight from memory each of a
+    // load's 64 lanes would be a request of its own, 64 clocks of the compute unit's cache instead of 16.
     {
-        const float* qrow = q + ((size_t)bh * geo.q_rows + min(m, Tq - 1)) * D;  // rows beyond Tq are not stored
+        const Mover q_move(tile_rsrc(q + (size_t)bh * geo.q_rows * D, (uint32_t)Tq * (D * 4)), wave, lane);
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) qf[kb] = *reinterpret_cast<const f32x4*>(qrow + kb * 16 + h * 4);
+        for (int half = 0; half < (BM + TN - 1) / TN; ++half)
+            if (q_move.w0 < BM) {
+#pragma unroll
+                for (int j = 0; j < Mover::NI; ++j) q_move.issue(base + (half == 0 ? 1 : 3) * TILE, m0 + half * TN, j);
+            }
     }
+    f32x4 qf[KB];  // B operand: element e of block kb is feature 16 kb + 4 h + e of this lane's query
     f32x4 o[DB];  // O^T: register r of block db is feature 64 (db / 4) + 4 (4h + r) + db % 4
 #pragma unroll
     for (int db = 0; db < DB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -135,11 +143,13 @@ __global__ __launch_bounds__(kF32Waves * kWave, KS == 1 ? 2 : 1) void attn_fwd_f
     // where a scaled maximum would leave the rounding of its product.  l_run: this lane's share of the row sum.
     float m_run = kLowest, l_run = 0.f;
 
-    // The compiler learns here that the operand has arrived: the waits it would otherwise put before its uses inside the loop
-    // would be waits for the tile in flight.
     wait_loads();
+    meet();
+    {
+        const uint32_t row = base + (BM > TN && qw * 16 >= TN ? 3 : 1) * TILE + (qw * 16 % TN + r16) * (D * 4);
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(qf[kb]));
+        for (int kb = 0; kb < KB; ++kb) qf[kb] = lds_read(row + ((4 * kb + h) ^ r16) * 16);
+    }
     // Byte addresses of this lane's operands in the even tiles.  K: contraction block kb of key r16 of the wave's first block.
     // V: 4 features (of every 64) of key 4h + j there.
     constexpr int VC = D / 64;
@@ -356,16 +366,21 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void colsum_f32_kernel(
     };
     fetch(0);
 
-    f32x4 kf[KB];  // A operand: element e of block kb is feature 16 kb + 4 h + e of key nw + r16
+    // the keys come in where the odd tiles go, as the queries of the forward pass do
     {
-        const float* krow = k + ((size_t)bh * geo.kv_rows + min(nw + r16, L - 1)) * D;  // keys beyond L are not stored
+        const Mover k_move(tile_rsrc(k + (size_t)bh * geo.kv_rows * D, (uint32_t)L * (D * 4)), wave, lane);
+        if (k_move.w0 < BN) {
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) kf[kb] = *reinterpret_cast<const f32x4*>(krow + kb * 16 + h * 4);
+            for (int j = 0; j < Mover::NI; ++j) k_move.issue(base + TILE, n0, j);
+        }
     }
+    f32x4 kf[KB];  // A operand: element e of block kb is feature 16 kb + 4 h + e of key nw + r16
     f32x4 col = f32x4{0.f, 0.f, 0.f, 0.f};  // keys nw + 4 h + r
-    wait_loads();  // as in the forward pass: no wait for the operand inside the loop
+    static_assert(BN <= TQ, "an odd tile holds the keys");
+    wait_loads();
+    meet();
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(kf[kb]));
+    for (int kb = 0; kb < KB; ++kb) kf[kb] = lds_read(base + TILE + (kw * 16 + r16) * (D * 4) + ((4 * kb + h) ^ r16) * 16);
     uint32_t q_at[KB];  // byte address of this lane's operand of contraction block kb in the even tiles
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) q_at[kb] = one_register(base + (qg * 16 + r16) * (D * 4) + ((4 * kb + h) ^ r16) * 16);
