@@ -249,8 +249,9 @@ __global__ __launch_bounds__(64) void head_mean_kernel(const float* __restrict__
     const int b = blockIdx.y;
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= T) return;
-    // A chain of load latencies: loads are issued 32 at a time, then 8 (B1 H32 T1024: 3.8 us with 8 at a time, 3.4 us); the
-    // additions keep ascending head order.
+    // A chain of load latencies: loads are issued 32 at a time, then 8 (B1 H32 T1024: 3.8 us with 8 at a time, 3.4 us), 4, 2 and 1 (whole
+    // fp32 call with the last up to seven one by one / so: H4 T256 13.2 / 12.9, H7 T400 18.6 / 17.9); the additions keep ascending
+    // head order.
     float acc = 0.f;
     int h = 0;
     auto batch = [&](auto n_loads) __attribute__((always_inline)) {
@@ -264,7 +265,9 @@ __global__ __launch_bounds__(64) void head_mean_kernel(const float* __restrict__
     };
     while (h + 32 <= H) batch(std::integral_constant<int, 32>{});
     while (h + 8 <= H) batch(std::integral_constant<int, 8>{});
-    for (; h < H; ++h) acc += head_imp[((size_t)b * H + h) * T + n];
+    if (h + 4 <= H) batch(std::integral_constant<int, 4>{});
+    if (h + 2 <= H) batch(std::integral_constant<int, 2>{});
+    if (h < H) batch(std::integral_constant<int, 1>{});
     score[(size_t)b * T + n] = acc / (float)H;
 }
 
