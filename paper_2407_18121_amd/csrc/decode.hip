@@ -53,8 +53,8 @@ template <int DT, int D, int WAVES, int UNROLL> struct DecodeShape {
 // empties them in one access, so that it gives its lines back as soon as it has everything and not when the launch has been
 // written out; and each wave weighs the shares with a lane for each.  What the exchange adds to a launch was 3.3 us with atomics in
 // device memory, a join at the end and a separate clearing, and is 2.6: B*H 32, 640 rows of bf16 D128 8.46 -> 7.82 us, B*H 8, 4096 rows (16
-// shares) 11.9 -> 10.3.  Of the latter 2.6 the helpers' words take 0.5 to arrive and each access of the owner 0.5.  Looking first
-// by plain loads is slower (the owner has everything 0.7 us later).
+// shares) 11.9 -> 10.3.  Stamps at B*H 32, 640 rows, us after the first workgroup's start: rows streamed 3.6, waves brought together 4.0,
+// helpers' words sent 4.3, all of them taken 5.9, written out 6.7.  Looking first by plain loads is slower (all taken 6.6).
 constexpr int kMaxShares = 64;
 constexpr int kLines = 256;      // of every XCD
 constexpr int kLineWords = 136;  // D + 2, padded to whole 64 bytes
@@ -645,8 +645,8 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // arrived before any wave overwrites them
                 __syncthreads();
             }
-            // Every wave weighs the shares, a lane each, and adds their rows up in ascending order (a thread that weighs all of
-            // them itself takes twice as long, 0.9 us).
+            // Every wave weighs the shares, a lane each, and adds their rows up in ascending order (every thread all of them: 16 shares
+            // 10.8 us, so 10.3).
             const bool has = lane < shares.count;
             const int of = has ? lane : 0;
             const float m_share = has ? part[of][D] : kLowest, l_share = has ? part[of][D + 1] : 0.f;
