@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -46,9 +47,9 @@ def load():
     global _lib, _fast
     if _lib is not None:
         return _lib
-    for path in (LIB_PATH, os.path.join(_HERE, "_fastcall.so")):
-        if not os.path.exists(path):
-            raise FileNotFoundError(f"{path} not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
+    if not os.path.exists(LIB_PATH):
+        raise FileNotFoundError(
+            f"{LIB_PATH} not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
     lib = ctypes.CDLL(LIB_PATH)
     c_int, c_vp, c_sz, c_f = ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_float
     lib.ec_status_string.argtypes = [c_int]
@@ -91,12 +92,30 @@ def load():
     lib.ec_importance_mean.restype = c_int
     lib.ec_retention_step_varlen.argtypes = [c_vp] * 5 + [c_int] * 10 + [c_vp]
     lib.ec_retention_step_varlen.restype = c_int
-    if _raw_stream is not None and _device is not None:
-        from . import _fastcall
-        _fastcall.bind(_raw_stream, _device, tuple(ctypes.cast(getattr(lib, "ec_" + n), c_vp).value for n in _FAST))
-        _fast = _fastcall
+    _fast = _load_fast(lib)
     _lib = lib
     return lib
+
+
+def _load_fast(lib):
+    """The native half, bound to the library's functions, or None, and every call then goes through ctypes: where this torch does
+    not say which stream is current, and where the module is missing or was built for another Python (its file's name says
+    so) or another torch (its headers' types are not this torch's)."""
+    if _raw_stream is None or _device is None:
+        return None
+    try:
+        from . import _fastcall
+    except ImportError as e:
+        why = str(e)
+    else:
+        built_for = getattr(_fastcall, "built_for", "an unknown version")
+        if built_for == str(torch.__version__):
+            _fastcall.bind(_raw_stream, _device,
+                           tuple(ctypes.cast(getattr(lib, "ec_" + n), ctypes.c_void_p).value for n in _FAST))
+            return _fastcall
+        why = f"it was built for torch {built_for}"
+    warnings.warn(f"the native half of the binding is not used, calls take 4 to 10 us longer: {why}", RuntimeWarning, stacklevel=3)
+    return None
 
 
 def status_string(status: int) -> str:

@@ -338,4 +338,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fastcall() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__fastcall()
+{
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", EC_TORCH_VERSION) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -1,7 +1,10 @@
 """The binding's native half answers None to every call that the Python half has to look at (host tensors: nothing is launched)."""
+import sys
+
 import pytest
 import torch
 
+import paper_2407_18121_amd
 from paper_2407_18121_amd import binding as ec
 
 
@@ -29,3 +32,21 @@ def test_number_of_arguments():
     ec.load()
     for name in ec._FAST:
         assert getattr(ec._fast, name)() is None
+
+
+@pytest.mark.parametrize("why", ["missing", "another torch"])
+def test_library_without_a_native_half(monkeypatch, why):
+    """The library alone is enough: every call goes through ctypes then."""
+    ec.load()
+    if why == "missing":  # importing it fails
+        monkeypatch.setitem(sys.modules, "paper_2407_18121_amd._fastcall", None)
+        monkeypatch.delattr(paper_2407_18121_amd, "_fastcall")
+    else:
+        monkeypatch.setattr(sys.modules["paper_2407_18121_amd._fastcall"], "built_for", "1.0")
+    monkeypatch.setattr(ec, "_lib", None)
+    monkeypatch.setattr(ec, "_fast", ec._fast)
+    with pytest.warns(RuntimeWarning, match="native half"):
+        lib = ec.load()
+    assert ec._fast is None and lib.ec_evict_index(10, 6, 1, 2, 0, 0, 0, 25, 0, 1) == ec.ec_evict_index(10, 6, 1, 2)
+    with pytest.raises(ValueError, match="device memory"):  # through ctypes, up to the device check
+        ec.ec_select_anchors(torch.zeros(1, 1, 8), 2, 1, 1, torch.zeros(1, 1, 2, dtype=torch.int32), check=False)
