@@ -1,5 +1,5 @@
 // The usual calls of binding.py without its way through Python and ctypes: the same checks of every tensor, one call each.
-// Whatever is not usual -- a tensor subclass, a wrong type, shape, device or layout, a number that is no plain int or float --
+// Whatever is not usual -- a tensor subclass, a wrong type, shape, device or layout, a number that is neither int nor float --
 // makes a function return None, and binding.py, which knows what to say about it, goes its own way.  Nothing is kept from call to
 // call but the addresses of the library's functions.
 //
@@ -79,7 +79,7 @@ int type_code(const at::Tensor& t)
 }
 int integer(PyObject* o)
 {
-    if (!PyLong_CheckExact(o)) throw Unusual{};
+    if (!PyLong_Check(o)) throw Unusual{};
     int overflow = 0;
     const long x = PyLong_AsLongAndOverflow(o, &overflow);
     if (overflow || x != static_cast<int>(x)) throw Unusual{};
@@ -87,8 +87,10 @@ int integer(PyObject* o)
 }
 float number(PyObject* o)
 {
-    if (!PyFloat_CheckExact(o)) throw Unusual{};
-    return static_cast<float>(PyFloat_AS_DOUBLE(o));
+    if (!PyFloat_Check(o) && !PyLong_Check(o)) throw Unusual{};  // numpy's float64 is a float
+    const double x = PyFloat_AsDouble(o);
+    if (x == -1.0 && PyErr_Occurred()) throw Unusual{};
+    return static_cast<float>(x);
 }
 int size(int64_t n)
 {

@@ -1,4 +1,5 @@
-"""The binding's native half answers None to every call that the Python half has to look at (host tensors: nothing is launched)."""
+"""The binding's native half without a device: tensors on the host make it answer None whatever else is right or wrong with a call
+(each argument by itself, on device tensors: test_gpu_fastcall.py), and so does a wrong number of arguments; the binding without it."""
 import sys
 
 import pytest
@@ -24,6 +25,7 @@ def _steps():
 
 @pytest.mark.parametrize("i", range(13))
 def test_unusual_calls_are_left_to_python(i):
+    """Nothing but None, and no exception, for whatever comes in the place of an argument."""
     ec.load()
     assert ec._fast.decode_step(*list(_steps())[i].values()) is None
 
