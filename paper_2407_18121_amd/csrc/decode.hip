@@ -49,10 +49,11 @@ template <int DT, int D, int WAVES, int UNROLL> struct DecodeShape {
 //
 // All workgroups of one (batch, head) are launched on one XCD (their linear ids are equal modulo eight), every XCD has lines of its
 // own, and a workgroup looks at those of the XCD that it finds itself on: one that was placed elsewhere merely never meets its owner.
-// So the atomics only have to reach the L2 of the XCD.  A helper joins when it starts, not when it is done; the owner takes words and
+// Exchanges and compare-exchanges are carried out by the L2 that they arrive at, and lines that one XCD alone touches stay in its L2
+// (loads and stores of device scope, by which words were passed before, go past it).  A helper joins when it starts, not when it is done; the owner takes words and
 // empties them in one access, so that it gives its lines back as soon as it has everything and not when the launch has been
-// written out; and each wave weighs the shares with a lane for each.  What the exchange adds to a launch was 3.3 us with atomics in
-// device memory, a join at the end and a separate clearing, and is 2.6: B*H 32, 640 rows of bf16 D128 8.46 -> 7.82 us, B*H 8, 4096 rows (16
+// written out; and each wave weighs the shares with a lane for each.  What the exchange adds to a launch was 3.3 us with loads and
+// stores past the L2, a join at the end and a separate clearing, and is 2.6: B*H 32, 640 rows of bf16 D128 8.46 -> 7.82 us, B*H 8, 4096 rows (16
 // shares) 11.9 -> 10.3.  Stamps at B*H 32, 640 rows, us after the first workgroup's start: rows streamed 3.6, waves brought together 4.0,
 // helpers' words sent 4.3, all of them taken 5.9, written out 6.7.  Looking first by plain loads is slower (all taken 6.6).
 constexpr int kMaxShares = 64;
@@ -65,15 +66,15 @@ constexpr unsigned long long kOpen = 1, kJoined = 2;
 __device__ __align__(128) static unsigned long long line_state[kXcds * kLines];
 __device__ __align__(128) static unsigned long long line_data[kXcds * kLines][kLineWords];
 
-// An XCD's lines are touched by its own workgroups alone, so the L2 that they share is where its atomics have to be carried out
-// and no further: an exchange takes what it finds and leaves the word empty.
+// An exchange takes what it finds and leaves the word empty.  Device scope, as the two sides are different workgroups; for these two
+// operations the instructions are those of workgroup scope.
 __device__ __forceinline__ unsigned long long line_swap(unsigned long long* p, unsigned long long x)
 {
-    return __hip_atomic_exchange(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return __hip_atomic_exchange(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ unsigned long long line_cas(unsigned long long* p, unsigned long long from, unsigned long long to)
 {
-    __hip_atomic_compare_exchange_strong(p, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_compare_exchange_strong(p, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return from;  // what was there
 }
 __device__ __forceinline__ unsigned xcd_id()
