@@ -17,6 +17,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "decode_split.h"
 #include "ec_common.h"
 
 namespace ec {
@@ -224,9 +225,6 @@ __device__ __forceinline__ Pair lane_pair(float x, int off)
     const bool low = threadIdx.x % 16 < 8;
     return {low ? x : other, low ? other : x};
 }
-
-// Workgroups of a divided launch per share: workgroups are handed to the XCDs in turn, and those of one (batch, head) have to meet.
-__host__ __device__ constexpr int split_stride(int BH) { return (BH + kXcds - 1) / kXcds * kXcds; }
 
 // EMIT (frequency discard policy): the kernel also stores every row's scaled score (base-2 units) into
 // raw [B,H,cap] and the head's softmax maximum and denominator into stats [B,H,2], from which
@@ -725,25 +723,7 @@ static int launch_decode_w(const void* q, const void* k_new, const void* v_new, 
     return status_from_hip(hipGetLastError());
 }
 
-// Workgroups that one (batch, head) is divided over when the caller leaves the choice to the library: as many as the chip has
-// compute units for, where that saves more than the exchange costs (2.6 us against 1 us per 54 KB of one (batch, head)'s rows).
-// Measured, us per launch (graph replay, D128, one workgroup / divided; crossover):
-//   bf16, B*H =  8:  450 rows 7.1 / 7.1     550 8.0 / 7.6   4096 39.3 / 10.7     f32  220 rows 6.7 / 6.7   260  7.7 / 7.1   4096 75.0 / 13.0
-//   bf16, B*H = 32:  500 rows 7.7 / 7.8     640 9.2 / 8.1   4096 40.6 / 15.9     f32  230 rows 7.4 / 7.3   260  8.0 / 7.7   4096 77.8 / 25.1
-//   bf16, B*H = 64:  600 rows 9.1 / 9.4     700 10.0 / 9.8  4096 42.7 / 25.2     f32  250 rows 8.3 / 8.8   300  9.8 / 9.3
-//   bf16, B*H = 96:  800 rows 11.6 / 12.2  1200 16.0 / 14.9 4096 51.0 / 35.3     f32  550 rows 14.8 / 14.6
-//   bf16, B*H = 128: 1600 rows 22.9 / 22.4 2400 33.1 / 31.2 4096 51.0 / 46.8     f32 1000 rows 28.0 / 26.5
-// More workgroups than compute units lose everywhere (B*H = 160, two each: 19.8 / 30.1 at 1200 rows).  Sixteen shares instead of
-// eight: B*H = 8, bf16 1200 rows 8.3 / 8.8, 4096 rows (2 MB) 11.7 / 10.7, f32 4096 rows 16.5 / 13.0.
-constexpr int kComputeUnits = 256;
 constexpr int kLeastShareBytes = 48 << 10;  // of K and V
-int decode_auto_splits(int BH, int n_rows, int row_bytes)
-{
-    const long long bytes = 2LL * n_rows * row_bytes;
-    const int splits = std::min(kComputeUnits / BH, bytes >= 3 << 19 ? 16 : 8);
-    const int pays = splits >= 5 ? 240 << 10 : splits >= 3 ? 320 << 10 : BH <= 96 ? 512 << 10 : 960 << 10;
-    return splits >= 2 && bytes >= pays ? splits : 1;
-}
 
 // Shape of a workgroup when the caller leaves it to the library: waves, loads of K and of V per lane and tile, and whether the next
 // tile travels while one is used (deep).  Up to one workgroup per compute unit wants as much in flight as it can have.  Beyond

@@ -6,11 +6,11 @@
 #include <stdint.h>
 
 #include "../../include/ec.h"
+#include "chip.h"
 
 namespace ec {
 
 constexpr int kWave = 64;
-constexpr int kXcds = 8;  // each with an L2 of its own; workgroups are handed to them round-robin by linear id
 
 // 16 bytes in registers.  Arrays of it stay there, where an array of uint4 (a class with a union inside) that is filled
 // under a condition goes to scratch memory.
