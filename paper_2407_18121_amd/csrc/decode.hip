@@ -787,7 +787,7 @@ static int launch_decode(const void* q, const void* k_new, const void* v_new, vo
     if (strict && splits > 1 && part_floats < (size_t)B * H * splits * (D + 2)) return EC_EWORKSPACE;
     const bool choose = forced_waves <= 0 && forced_unroll <= 0 && splits <= 0;
     if (splits <= 0) {  // with a width or a depth given, one workgroup takes everything
-        splits = choose ? decode_auto_splits(B * H, n_rows, kRow) : 1;
+        splits = choose ? decode_auto_splits(B * H, n_rows, kRow, DT == EC_BF16) : 1;
         least = kLeastShareBytes / (2 * kRow);
     }
 #define EC_DECODE_W(W_, U_, DEEP_, SPLIT_)                                                                                 \
@@ -913,7 +913,7 @@ static int launch_decode_score(const void* q, const void* k_new, const void* v_n
                                hipStream_t stream)
 {
     constexpr int kRow = D * Elem<DT>::kBytes;
-    const int n = cache_len + 1, splits = decode_auto_splits(B * H, n, kRow), least = kLeastShareBytes / (2 * kRow);
+    const int n = cache_len + 1, splits = decode_auto_splits(B * H, n, kRow, DT == EC_BF16), least = kLeastShareBytes / (2 * kRow);
 #define EC_DSCORE(W_, U_, DEEP_, SPLIT_)                                                                                       \
     rc = launch_decode_w<DT, D, W_, U_, DEEP_, true, SPLIT_>(q, k_new, v_new, k_cache, v_cache, pos, B, H, G, cap, cache_len, -1, \
                                                              new_pos, scale, out, raw, stats, nullptr, nullptr, nullptr, splits, \

@@ -11,11 +11,11 @@ PROGRAM = r"""
 #include <stdio.h>
 #include <stdlib.h>
 #include "decode_split.h"
-int main(int argc, char** argv)  // B * H, rows, bytes of a row
+int main(int argc, char** argv)  // B * H, rows, bytes of a row, bf16
 {
-    for (int i = 1; i + 2 < argc; i += 3) {
+    for (int i = 1; i + 3 < argc; i += 4) {
         const int BH = atoi(argv[i]);
-        printf("%d %d\n", ec::decode_auto_splits(BH, atoi(argv[i + 1]), atoi(argv[i + 2])), ec::split_stride(BH));
+        printf("%d %d\n", ec::decode_auto_splits(BH, atoi(argv[i + 1]), atoi(argv[i + 2]), atoi(argv[i + 3])), ec::split_stride(BH));
     }
 }
 """
@@ -23,7 +23,7 @@ int main(int argc, char** argv)  // B * H, rows, bytes of a row
 
 @pytest.fixture(scope="module")
 def divided(tmp_path_factory):
-    """(shares of a pair, workgroups per share) of calls (B * H, rows, bytes of a row)."""
+    """(shares of a pair, workgroups per share) of calls (B * H, rows, bytes of a row, bf16)."""
     at = tmp_path_factory.mktemp("split")
     source, binary = at / "split.cpp", at / "split"
     source.write_text(PROGRAM)
@@ -40,15 +40,24 @@ def test_no_xcd_gets_more_workgroups_than_it_has_compute_units(divided):
     """A pair's workgroups are on one XCD: its pairs, the most that any of the eight has, share 32 compute units."""
     for rows in (300, 640, 1030, 3100, 4400, 100000):
         pairs = range(1, 400)
-        for BH, (splits, stride) in zip(pairs, divided([(BH, rows, 256) for BH in pairs])):
+        for BH, (splits, stride) in zip(pairs, divided([(BH, rows, 256, 1) for BH in pairs])):
             assert stride % 8 == 0 and BH <= stride < BH + 8
             assert splits == 1 or stride // 8 * splits <= 32, (BH, rows, splits)
 
 
 def test_long_caches_are_divided_as_far_as_an_xcd_has_room(divided):
-    calls = [(8, 8192, 256), (16, 8192, 256), (8, 2000, 256), (24, 8192, 256), (32, 640, 256), (33, 8192, 256), (48, 8192, 256),
-             (64, 8192, 256), (80, 8192, 256), (96, 8192, 256), (128, 8192, 256), (129, 8192, 256)]
-    assert [s for s, _ in divided(calls)] == [16, 16, 8, 8, 8, 6, 5, 4, 3, 2, 2, 1]
+    calls = [(8, 8192), (16, 8192), (8, 2000), (24, 8192), (32, 640), (33, 8192), (48, 8192), (64, 8192), (80, 8192), (96, 8192), (128, 8192), (129, 8192)]
+    assert [s for s, _ in divided([(*c, 256, 1) for c in calls])] == [16, 16, 8, 8, 8, 6, 5, 4, 3, 2, 2, 1]
+
+
+def test_short_caches_are_left_alone(divided):
+    """On both sides of the size from which dividing a pair is measured to be faster (KB of K and V)."""
+    bf16_d128 = ((1, 256, 8), (40, 268, 6), (48, 292, 5), (49, 320, 4), (64, 340, 4), (65, 343, 3), (80, 388, 3), (81, 423, 2), (96, 468, 2), (97, 960, 2))
+    others = ((1, 240, 8), (40, 252, 6), (48, 276, 5), (49, 320, 4), (64, 324, 4), (65, 327, 3), (80, 372, 3), (81, 407, 2), (96, 452, 2), (97, 960, 2))
+    for row, half, table in ((256, 1, bf16_d128), (256, 0, others), (512, 0, others), (128, 1, others)):
+        for BH, kb, shares in table:
+            rows = kb * 512 // row
+            assert [s for s, _ in divided([(BH, rows - 1, row, half), (BH, rows, row, half)])] == [1, shares]
 
 
 def test_workgroups_exchange_at_device_scope():

@@ -22,9 +22,12 @@ def _step(dtype, D, B, H, rows, victim, seed=0, **shape):
     return out, kc, vc, pos
 
 
-# on both sides of the size from which a pair is divided (288 KB, 352 KB with fewer than five shares each), and every place
+# on both sides of the size from which a pair is divided (256 KB in bf16 D128, else 240; 340 for 64 pairs), and every place
 # the victim can have: in the owner's registers, in its share, in a helper's share, the first row, the new row, none
-@pytest.mark.parametrize("dtype,D,B,H,rows", [("bf16", 128, 1, 8, 574), ("bf16", 128, 1, 8, 575), ("bf16", 64, 2, 8, 1151),
+@pytest.mark.parametrize("dtype,D,B,H,rows", [("bf16", 128, 1, 8, 510), ("bf16", 128, 1, 8, 511), ("bf16", 64, 2, 8, 958),
+                                              ("bf16", 64, 2, 8, 959), ("f32", 128, 1, 8, 238), ("f32", 128, 1, 8, 239),
+                                              ("bf16", 128, 2, 32, 678), ("bf16", 128, 2, 32, 679),
+                                              ("bf16", 128, 1, 8, 574), ("bf16", 128, 1, 8, 575), ("bf16", 64, 2, 8, 1151),
                                               ("f32", 128, 1, 8, 287), ("f32", 64, 1, 5, 2100), ("bf16", 128, 2, 32, 703)])
 def test_divided_step(dtype, D, B, H, rows):
     for victim in (-1, rows - 25, rows - 90, rows // 2, 0, rows):
@@ -62,7 +65,7 @@ def test_lines_that_are_taken(dtype):
     taken, or its helper not there yet, forms the share itself, with the same result bit for bit."""
     D, rows = 64, 900
     want = _step(dtype, D, 1, 8, rows, rows // 3, waves=4, splits=16)
-    many = _step(dtype, D, 16, 24, 200, 40, waves=2, splits=64)  # 24192 shares, 2048 lines
+    many = _step(dtype, D, 16, 24, 200, 40, waves=2, splits=64)  # 24192 shares, 256 lines of each XCD
     again = _step(dtype, D, 16, 24, 200, 40, waves=2, splits=64)
     plain = _step(dtype, D, 16, 24, 200, 40, waves=2, splits=1)
     for a, b, c in zip(many, again, plain):
