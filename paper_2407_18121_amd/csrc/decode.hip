@@ -58,7 +58,6 @@ template <int DT, int D, int WAVES, int UNROLL> struct DecodeShape {
 // shares) 11.9 -> 10.3.  Stamps at B*H 32, 640 rows, us after the first workgroup's start: rows streamed 3.6, waves brought together 4.0,
 // helpers' words sent 4.3, all of them taken 5.9, written out 6.7.  Looking first by plain loads is slower (all taken 6.6).
 constexpr int kMaxShares = 64;
-constexpr int kLines = 256;      // of every XCD
 constexpr int kLineWords = 136;  // D + 2, padded to whole 64 bytes
 constexpr int kJoinTries = 4;    // of a helper that finds its line not open yet
 constexpr int kPatience = 24;    // looks of the owner at missing data before it asks whether the helper has joined
@@ -264,9 +263,8 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
     const char* kn = reinterpret_cast<const char*>(k_new) + (size_t)bh * ROW;
     const char* vn = reinterpret_cast<const char*>(v_new) + (size_t)bh * ROW;
 
-    // lines of this (batch, head): neighbouring output rows use neighbouring lines
     const unsigned long long row_key = (unsigned long long)(uintptr_t)kc << 8;
-    const unsigned line0 = (unsigned)(((uintptr_t)out + (unsigned long long)bh * ROW) / ROW) * (unsigned)(splits - 1);
+    const unsigned line0 = first_line((uintptr_t)out / ROW + bh, splits);
     const unsigned xcd_lines = SPLIT ? xcd_id() * kLines : 0;
     auto line_of = [&](int s) { return xcd_lines + (line0 + (unsigned)(s - 1)) % kLines; };
     auto key_of = [&](int s) { return row_key | (unsigned long long)s << 2; };

@@ -10,6 +10,11 @@ namespace ec {
 // Workgroups of a divided launch per share: workgroups are handed to the XCDs in turn, and those of one pair have to meet.
 constexpr int split_stride(int BH) { return (BH + kXcds - 1) / kXcds * kXcds; }
 
+// Lines of a pair: its XCD's from first_line(row) on, one for each share but the owner's; row: number of the pair's output row, counted over
+// all of memory.  The pairs of a launch that meet on one XCD have numbers eight apart, and their lines follow each other.
+constexpr int kLines = 256;  // of every XCD
+constexpr unsigned first_line(unsigned long long row, int splits) { return (unsigned)(row / kXcds) * (unsigned)(splits - 1) % kLines; }
+
 // Workgroups that one (batch, head) is divided over when the caller leaves the choice to the library: as many as its XCD has
 // compute units for, where that saves more than the exchange costs (2.6 us against 1 us per 54 KB of one (batch, head)'s rows).
 // Measured, divided against one workgroup, % of the time, at KB of K and V of one pair (graph replay; bf16 D128, f32 D128, bf16 D64, f32 D64):

@@ -11,8 +11,12 @@ PROGRAM = r"""
 #include <stdio.h>
 #include <stdlib.h>
 #include "decode_split.h"
-int main(int argc, char** argv)  // B * H, rows, bytes of a row, bf16
+int main(int argc, char** argv)  // B * H, rows, bytes of a row, bf16; or "lines", shares of a pair, number of the first output row, pairs
 {
+    if (argc > 4 && argv[1][0] == 'l') {
+        for (int bh = 0; bh < atoi(argv[4]); ++bh) printf("%d %u\n", bh % ec::kXcds, ec::first_line(atoll(argv[3]) + bh, atoi(argv[2])));
+        return 0;
+    }
     for (int i = 1; i + 3 < argc; i += 4) {
         const int BH = atoi(argv[i]);
         printf("%d %d\n", ec::decode_auto_splits(BH, atoi(argv[i + 1]), atoi(argv[i + 2]), atoi(argv[i + 3])), ec::split_stride(BH));
@@ -58,6 +62,19 @@ def test_short_caches_are_left_alone(divided):
         for BH, kb, shares in table:
             rows = kb * 512 // row
             assert [s for s, _ in divided([(BH, rows - 1, row, half), (BH, rows, row, half)])] == [1, shares]
+
+
+def test_pairs_that_meet_on_an_xcd_have_lines_of_their_own(divided):
+    """As long as 256 lines are enough for the shares of an XCD's pairs, wherever the output lies."""
+    for splits in (2, 3, 8, 9, 16, 17, 32, 33, 64):
+        pairs = 8 * (256 // (splits - 1))
+        for row in (0, 5, 123456789, (1 << 47) // 256):
+            lines = {}
+            for xcd, first in divided([("lines", splits, row, pairs)]):
+                lines.setdefault(xcd, []).extend((first + s) % 256 for s in range(splits - 1))
+            assert len(lines) == 8
+            for used in lines.values():
+                assert len(set(used)) == len(used) <= 256, (splits, row)
 
 
 def test_workgroups_exchange_at_device_scope():

@@ -1,7 +1,10 @@
 """Divided generation steps at the sizes from which a (batch, head) is divided, and with numbers of pairs that the XCDs do not share
 out evenly (the launch is padded to eight)."""
 import pytest
+import torch
 
+from paper_2407_18121_amd import binding as ec
+from paper_2407_18121_amd.tune import graph_time_ms
 from test_gpu_decode import _case
 
 pytestmark = pytest.mark.gpu
@@ -21,3 +24,19 @@ pytestmark = pytest.mark.gpu
 def test_divided_launch_sizes(dtype, D, B, H, rows):
     for victim in (rows - 25, 0):
         _case(dtype, D, B, H, 1, rows + 2, rows, victim, seed=rows + victim)
+
+
+@pytest.mark.parametrize("H,splits", [(8, 8), (8, 16), (16, 16), (16, 33), (32, 8), (32, 33), (24, 64)])
+def test_shares_come_from_their_helpers(H, splits):
+    """Owners that never met a helper would form every share themselves, with the same bits, in the time of one workgroup or more: a
+    divided launch has to be faster than that.  Measured 11 to 24 us against 40 to 43; with 33 and 64 shares, where pairs of an XCD that
+    wanted the same lines took 99 to 153, most of an XCD's lines are in use."""
+    rows, D = 4400, 128
+    t = lambda *s: torch.randn(*s, device="cuda").bfloat16()
+    q, kn, vn, kc, vc = t(1, H, D), t(1, H, D), t(1, H, D), t(1, H, rows + 2, D), t(1, H, rows + 2, D)
+    out, ws = torch.empty_like(q), torch.zeros(4 * H * 64 * (D + 2), dtype=torch.uint8, device="cuda")
+
+    def us(splits):
+        step = lambda: ec.ec_decode_step_shaped(q, kn, vn, kc, vc, None, rows, rows - 25, 7, 0.1, out, ws, waves=4, unroll=4, splits=splits, G=1)
+        return min(graph_time_ms(lambda: [step() for _ in range(16)]) for _ in range(3)) / 16 * 1e3
+    assert us(splits) < 0.8 * us(1)
