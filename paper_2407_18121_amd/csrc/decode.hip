@@ -60,7 +60,12 @@ template <int DT, int D, int WAVES, int UNROLL> struct DecodeShape {
 constexpr int kMaxShares = 64;
 constexpr int kLineWords = 136;  // D + 2, padded to whole 64 bytes
 constexpr int kJoinTries = 4;    // of a helper that finds its line not open yet
-constexpr int kPatience = 24;    // looks of the owner at missing data before it asks whether the helper has joined
+// Looks of the owner at missing data before it asks whether the helper has joined.  Where owners alone do not fill the chip helpers are
+// there or about to be: 4 to 24 looks are alike in launches of one workgroup a compute unit, and in larger ones, which only the shaped entry
+// point makes, 24 are better than 8 (160 pairs of 640 rows in 2 shares 16.2 / 18.8 us, 48 of 4400 in 24 28.1 / 35.5).  Where
+// they do, and all workgroups have no room at once, helpers wait until owners have left: 24 looks / 1, 256 pairs in 16 shares 68.4 / 62.2, 512
+// pairs in 2 39.1 / 28.2, 1536 in 2 95 / 61.
+__device__ __forceinline__ int patience(int BH) { return BH >= kComputeUnits && gridDim.x > 3 * kComputeUnits ? 1 : 24; }
 constexpr int kStuck = 1 << 20;  // looks after that
 constexpr unsigned long long kOpen = 1, kJoined = 2;
 __device__ __align__(128) static unsigned long long line_state[kXcds * kLines];
@@ -608,7 +613,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_step_kernel(
                     __syncthreads();
                     return sh_missing[round];
                 };
-                look(kPatience);
+                look(patience(BH));
                 const unsigned long long all = (shares.count < 64 ? 1ull << shares.count : 0ull) - 2;
                 unsigned long long given_up = 0;
                 if (const unsigned long long late = missing(0)) {  // uniform
