@@ -6,7 +6,7 @@
     python -m paper_2407_18121_amd.tune score    # ec_prefill_score
 
 Every measurement replays one HIP graph that walks several distinct sets of buffers (so that nothing is served
-from a cache a real layer loop would not have), 20 ms of it before anything is timed, and reports microseconds per call by HIP
+from a cache a real layer loop would not have), 100 ms of it before anything is timed, and reports microseconds per call by HIP
 events on the launch stream, the median of five runs.  Inputs are seeded random numbers: this tool times kernels, it checks nothing.
 """
 from __future__ import annotations
@@ -33,8 +33,8 @@ def graph_time_ms(fn, iters: int = 5) -> float:
             fn()
     torch.cuda.current_stream().wait_stream(s)
     torch.cuda.synchronize()
-    # the clock has to rise again after new buffers have been filled: with one replay before it, the first shape of a table was timed 7 % high
-    end = time.perf_counter() + 0.02
+    # the clock has to rise again after new buffers have been filled: with one replay before it, the first shape of a table was timed 7 % high, with 20 ms 3 %
+    end = time.perf_counter() + 0.1
     while time.perf_counter() < end:
         g.replay()
         torch.cuda.synchronize()
@@ -54,23 +54,26 @@ def _randn(*shape):
     return torch.randn(*shape, device="cuda").to(BF16)
 
 
-def time_decode(B, H, D, N, waves, unroll, splits, sets=32):
-    """(us per launch, algorithmic GB/s) of one generation step over N cached rows with an eviction."""
+def decode_timer(B, H, D, N, sets=32):
+    """time(waves, unroll, splits) -> (us per launch, algorithmic GB/s) of one generation step over N cached rows with an eviction; every
+    shape on the same buffers."""
     cap = N + 2
     kc = [_randn(B, H, cap, D) for _ in range(sets)]
     vc = [_randn(B, H, cap, D) for _ in range(sets)]
     q, kn, vn = (_randn(B, H, D) for _ in range(3))
     out = torch.empty(B, H, D, device="cuda", dtype=BF16)
     pos = torch.zeros(B, 1, cap, dtype=torch.int32, device="cuda")
-    ws = torch.zeros(4 * B * H * max(splits, 1) * (D + 2) + 256, dtype=torch.uint8, device="cuda")
+    ws = torch.zeros(4 * B * H * 16 * (D + 2) + 256, dtype=torch.uint8, device="cuda")
 
-    def fn():
-        for l in range(sets):
-            ec.ec_decode_step_shaped(q, kn, vn, kc[l], vc[l], pos, N, N - 25, 5, 0.088, out, ws,
-                                     waves=waves, unroll=unroll, splits=splits)
+    def timed(waves, unroll, splits):
+        def fn():
+            for l in range(sets):
+                ec.ec_decode_step_shaped(q, kn, vn, kc[l], vc[l], pos, N, N - 25, 5, 0.088, out, ws,
+                                         waves=waves, unroll=unroll, splits=splits)
 
-    ms = graph_time_ms(fn) / sets
-    return ms * 1e3, 2 * B * H * (N + 1) * D * 2 / (ms * 1e-3) / 1e9
+        ms = graph_time_ms(fn) / sets
+        return ms * 1e3, 2 * B * H * (N + 1) * D * 2 / (ms * 1e-3) / 1e9
+    return timed
 
 
 DECODE_SHAPES = {  # name: (B, H, D, cached rows in the middle of the generation)
@@ -80,17 +83,17 @@ DECODE_SHAPES = {  # name: (B, H, D, cached rows in the middle of the generation
 
 def tune_decode():
     for name, (B, H, D, N) in DECODE_SHAPES.items():
-        sets = 16 if name == "C5" else 32
-        us, gbps = time_decode(B, H, D, N, 0, 0, 0, sets)
+        timed = decode_timer(B, H, D, N, 16 if name == "C5" else 32)
+        us, gbps = timed(0, 0, 0)
         print(f"decode {name} B{B} H{H} rows {N}: library's choice {us:7.2f} us {gbps:7.0f} GB/s", flush=True)
         for waves, unroll in ((2, 4), (2, 8), (4, 4), (4, 8), (8, 4), (8, 8)):  # the others that are accepted run as these
-            us, gbps = time_decode(B, H, D, N, waves, unroll, 1, sets)
+            us, gbps = timed(waves, unroll, 1)
             print(f"decode {name}:   one workgroup each, {waves:2d} waves x {unroll:2d} loads in flight {us:7.2f} us {gbps:7.0f} GB/s", flush=True)
         for splits in (2, 3, 4, 6, 8, 12, 16):
             if B * H * splits > 4096 or N // splits < 32:
                 continue
             for waves, unroll in ((4, 4), (8, 4), (4, 8), (2, 8)):
-                us, gbps = time_decode(B, H, D, N, waves, unroll, splits, sets)
+                us, gbps = timed(waves, unroll, splits)
                 print(f"decode {name}:   {splits:2d} workgroups each, {waves:2d} waves x {unroll:2d} loads in flight {us:7.2f} us {gbps:7.0f} GB/s", flush=True)
 
 
